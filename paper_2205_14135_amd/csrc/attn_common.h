@@ -101,36 +101,39 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// acc + the sum of the eight 16-bit values of v, each widened exactly (four two-element dot products
-// with ones: half an instruction per element)
-__device__ __forceinline__ float sum8(bf16x8 v, float acc) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 one = {(__bf16)1.f, (__bf16)1.f};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const bf16x2 pr = {v[2 * k], v[2 * k + 1]};
-    acc = __builtin_amdgcn_fdot2_f32_bf16(pr, one, acc, false);
-  }
-  return acc;
+__device__ __forceinline__ f32x4 mfma16(f16x8 a, f16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ float sum8(f16x8 v, float acc) {
-  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-  const f16x2 one = {(_Float16)1.f, (_Float16)1.f};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const f16x2 pr = {v[2 * k], v[2 * k + 1]};
-    acc = __builtin_amdgcn_fdot2(pr, one, acc, false);
-  }
-  return acc;
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Online softmax, when the reference of a row is moved: only when the maximum of a new tile
-// exceeds the reference by more than this (base-2 exponent units; the first tile always does).
-// Probabilities then reach 2^kLazyRescale at most, exactly representable scalings in both 16-bit
-// types.  What makes a lagging reference as accurate as the exact running maximum is that O is
-// normalised by the sum of the ROUNDED 16-bit probabilities, the very weights the second product
-// used: O stays a convex combination of V rows whatever the reference is.
-constexpr float kLazyRescale = 8.0f;
+// Row sums of 16-bit probabilities on the matrix cores, "lane = query" layout.  A fragment of P^T is
+// the B operand of a 32x32x16 MFMA: lane (r, g) holds eight keys of query r.  Read as the B operand of
+// a 16x16x32 MFMA the same registers are column lane % 16, k group lane / 16, so the two lanes of a
+// query are the two k groups of one parity, that of bit 4 of r.  With A[i][k] = 1 where the parity
+// of k's group equals bit 2 of i, and 0 elsewhere, row i = 4 (lane / 16) + j of the result is the
+// sum over both lanes of this lane's own query, the same in all four registers.  One such MFMA
+// (16 clocks of the matrix pipe) adds a 16-key fragment of 32 queries.  The vector ALU's two-element
+// dot products that did it before (four per fragment) do not run beside an MFMA: 64 of them next to 16
+// 32x32x16 MFMAs take 405 ns on a SIMD with two wavefronts against 235 to 250 ns for 64 adds,
+// multiplies, conversions or comparisons (219 ns for the MFMAs alone).
+template <typename T> __device__ __forceinline__ typename Vec<T>::x8 row_sum_ones() {
+  const int lane = threadIdx.x & 63;
+  const T one = (((lane >> 4) ^ (lane >> 2)) & 1) ? (T)0.f : (T)1.f;   // k group lane / 16, row lane % 16
+  typename Vec<T>::x8 v;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = one;
+  return v;
+}
+
+// Online softmax, when the reference of a row is moved: only when a lane's sum of the 32 probabilities it
+// holds of a new 64-key tile, against the reference so far, exceeds this (the first tile always does).
+// Probabilities are then at most this, exactly representable scalings in both 16-bit types.  What
+// makes a lagging reference as accurate as the exact running maximum is that O is normalised by
+// the sum of the ROUNDED 16-bit probabilities, the very weights the second product used: O
+// stays a convex combination of V rows whatever the reference is.
+constexpr float kLazySum = 1024.0f;
 
 // Philox-4x32-10 (Salmon et al., SC'11): counter (c0..c3), key (k0,k1) -> 4 words.
 __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
@@ -324,12 +327,16 @@ __device__ __forceinline__ uint32_t keep_mask_lane_key(uint32_t word, int bit) {
 // 16-key B-operand fragments of O^T += V^T P^T, with dropout applied.  Masks keys beyond `last`
 // on tiles that cross the causal diagonal or the end of the sequence, moves the running reference
 // m_run (and rescales o, l_run, lr_run) only when a row of the wavefront outgrew it by more than
-// kLazyRescale, and keeps two row sums per lane: l_run of the exact probabilities (for the saved
-// statistic) and lr_run of the rounded ones (the normaliser of O), both before dropout.
+// kLazyRescale, and keeps two row sums, both before dropout: l_run, this lane's share, of the exact
+// probabilities (for the saved statistic), and lr_run, complete, of the rounded ones (the normaliser of O).
+// The vector ALU bounds the forward at d <= 64 (65 % of the issue slots at N = 2048): a logit costs an
+// fma, an exp, an add and half a conversion, and no comparison: the maximum of a tile is only
+// looked for when the sum of its probabilities asks for it (170 -> 138 vector instructions per tile;
+// B H = 128, N = 2048, d = 64: 166.8 -> 154.2 us; d = 32, N = 4096: 227 -> 209 us; d = 128, N = 4096: 495 -> 487 us).
 template <typename T, int DB, bool CAUSAL, bool DROPOUT>
 __device__ __forceinline__ void softmax_tile_lane_query(const KArgs& a, f32x16 (&s)[2], f32x16 (&o)[DB],
                                                         typename Vec<T>::x8 (&pf)[4], float& m_run, float& l_run,
-                                                        float& lr_run, float c, int k0, int q0, int qi, int len, int g,
+                                                        f32x4& lr_run, const typename Vec<T>::x8& ones, float c, int k0, int q0, int qi, int len, int g,
                                                         int bh) {
   if ((CAUSAL && k0 + 63 > q0) || k0 + 64 > len) {   // diagonal tiles, and the padded last tile
     const int last = CAUSAL ? min(qi, len - 1) : len - 1;   // last visible key of this row
@@ -341,44 +348,48 @@ __device__ __forceinline__ void softmax_tile_lane_query(const KArgs& a, f32x16 (
         if (key > last) s[kb][i] = -INFINITY;
       }
   }
-  float mx = s[0][0];
+  // Probabilities against the reference the row has, with no look at the tile's maximum: their sum
+  // says whether the reference still serves.  (A row without one has m_run = -inf: its sum is inf or NaN.)
+  float neg_m = -m_run;
+  float psum;
+  auto probabilities = [&]() __attribute__((always_inline)) {
+    float part[2] = {0.f, 0.f};
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
-  mx = fmaxf(mx, xchg32(mx)) * c;
-  if (__builtin_amdgcn_ballot_w64(mx > m_run + kLazyRescale) != 0) {   // wavefront-uniform: rare after the first tiles
+      for (int i = 0; i < 16; ++i) {
+        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], c, neg_m));
+        part[i & 1] += p;
+        // P^T fragments: 16-key chunk cc = 2 kb + i / 8
+        pf[2 * kb + (i >> 3)][i & 7] = (T)p;
+      }
+    psum = part[0] + part[1];
+  };
+  probabilities();
+  if (__builtin_amdgcn_ballot_w64(!(psum <= kLazySum)) != 0) {   // wavefront-uniform: rare after the first tile
+    float mx = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
+    mx = fmaxf(mx, xchg32(mx)) * c;
     const float m_new = fmaxf(m_run, mx);
     const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
     m_run = m_new;
     l_run *= alpha;
-    lr_run *= alpha;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lr_run[i] *= alpha;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+    neg_m = -m_safe;
+    probabilities();
   }
-  const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
-  float psum = 0.f;
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], c, -m_use));
-      s[kb][i] = p;
-      psum += p;
-    }
   l_run += psum;
-  // P^T fragments: 16-key chunk cc = 2 kb + half
 #pragma unroll
-  for (int cc = 0; cc < 4; ++cc)
-#pragma unroll
-    for (int t = 0; t < 8; ++t) pf[cc][t] = (T)s[cc >> 1][8 * (cc & 1) + t];
-  float part[4];
-#pragma unroll
-  for (int cc = 0; cc < 4; ++cc) part[cc] = sum8(pf[cc], 0.f);
-  lr_run += (part[0] + part[1]) + (part[2] + part[3]);
+  for (int cc = 0; cc < 4; ++cc) lr_run = mfma16(ones, pf[cc], lr_run);
   if constexpr (DROPOUT) {   // element t of chunk cc has field t % 4 of word 2 (cc & 1) + t / 4 of its block
     const KeepLQ kq = keep_tile_lane_query(k0, qi, bh, g, a.offset_lo, a.seed_lo, a.seed_hi);
 #pragma unroll

@@ -9,9 +9,10 @@
 // on every pass).  K/V tiles of 64 keys are staged in LDS.
 //
 // Online softmax, two departures from the printed recurrence that leave the result the same up
-// to rounding.  (1) The reference m of a row is moved (and O, l rescaled) only when a tile's
-// maximum exceeds it by more than 2^kLazyRescale: any reference gives the same softmax in exact
-// arithmetic, and most tiles then skip the rescaling of the whole O accumulator.  (2) O is divided
+// to rounding.  (1) The reference m of a row is moved (and O, l rescaled) only when the sum of a
+// tile's probabilities in a lane exceeds kLazySum: any reference gives the same softmax in exact
+// arithmetic, and most tiles then skip both the rescaling of the whole O accumulator and the search
+// for the tile's maximum.  (2) O is divided
 // by the sum of the probabilities AS ROUNDED to 16 bits for the second product, not by l: O is
 // then a convex combination of V rows with exactly the weights that were used, which is what
 // keeps a lagging reference accurate (with the exact l a peaked row would see the rounding of its
@@ -93,9 +94,10 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
   float m_run = -INFINITY;  // reference of the row's probabilities, base-2 domain: lags the running
-                            // maximum of the scaled logits by at most kLazyRescale
+                            // maximum of the scaled logits by at most log2(kLazySum)
   float l_run = 0.f;        // this lane's share of the exact running row sum (for the saved statistic)
-  float lr_run = 0.f;       // its share of the sum of the rounded probabilities (normalises O)
+  f32x4 lr_run = {0.f, 0.f, 0.f, 0.f};   // the sum of the rounded probabilities (normalises O), four times the same
+  const T8 ones = row_sum_ones<T>();
 
   // key-padding mask: keys >= len are masked, rows >= len produce O = 0, LSE = -inf
   const int len = a.klen ? min(max(a.klen[b], 0), a.N) : a.N;
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
       }
       // ---- masks, online softmax, dropout; P^T fragments (B operand) for the second product
       T8 pf[4];
-      softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT>(a, s, o, pf, m_run, l_run, lr_run, c, k0, q0, qi, len, g, bh);
+      softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT>(a, s, o, pf, m_run, l_run, lr_run, ones, c, k0, q0, qi, len, g, bh);
       // ---- O^T += V^T P^T
       {
         auto v_frag = [&](int f) {   // f = DB cc + db: consecutive MFMAs hit different accumulators
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
 
   // ---- epilogue: normalise, apply the dropout scale, write O and L once
   const float l_sum = l_run + xchg32(l_run);
-  const float lr_sum = lr_run + xchg32(lr_run);
+  const float lr_sum = lr_run[0];
   const float l_tot = qi < len ? l_sum : 0.f;   // padding rows: O = 0, LSE = -inf
   const float inv = (l_tot > 0.f && lr_sum > 0.f) ? (DROPOUT ? a.keep_scale : 1.f) / lr_sum : 0.f;
   if (g == 0 && row_ok) {

@@ -65,9 +65,11 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
   // m_run: reference of the row's probabilities (base 2; lags the running maximum by at most
-  // kLazyRescale); l_run: this lane's share of the exact row sum (for the saved statistic);
-  // lr_run: its share of the sum of the rounded probabilities (normalises O)
-  float m_run = -INFINITY, l_run = 0.f, lr_run = 0.f;
+  // log2(kLazySum)); l_run: this lane's share of the exact row sum (for the saved statistic);
+  // lr_run: the sum of the rounded probabilities (normalises O), four times the same
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4 lr_run = {0.f, 0.f, 0.f, 0.f};
+  const T8 ones = row_sum_ones<T>();
 
   // key-padding mask: keys >= len are masked, rows >= len produce O = 0, LSE = -inf
   const int len = a.klen ? min(max(a.klen[b], 0), a.N) : a.N;
@@ -149,7 +151,7 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
   };
 
   auto do_softmax = [&](int j) {
-    softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT>(a, s, o, pf, m_run, l_run, lr_run, c, j * BC, q0, qi, len, g, bh);
+    softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT>(a, s, o, pf, m_run, l_run, lr_run, ones, c, j * BC, q0, qi, len, g, bh);
   };
 
   // ring slot of a tile in this group's ring
@@ -188,7 +190,7 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
 
   if (!valid) return;
   const float l_sum = l_run + xchg32(l_run);
-  const float lr_sum = lr_run + xchg32(lr_run);
+  const float lr_sum = lr_run[0];
   const float l_tot = qi < len ? l_sum : 0.f;   // padding rows: O = 0, LSE = -inf
   const float inv = (l_tot > 0.f && lr_sum > 0.f) ? (DROPOUT ? a.keep_scale : 1.f) / lr_sum : 0.f;
   if (g == 0 && row_ok) {
