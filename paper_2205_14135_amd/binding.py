@@ -1,8 +1,10 @@
-"""ctypes binding for libattn_gfx950.so: same entry points as include/attn.h.
+"""Binding for libattn_gfx950.so: same entry points as include/attn.h.
 
 Argument marshalling only: torch supplies device memory and the current
-stream, every step of the computation runs inside the HIP library.  There is
-no fallback: if the library has not been built, loading raises.
+stream, every step of the computation runs inside the HIP library.  The
+forward and backward calls go through a native extension (csrc/attn_marshal.cpp),
+the measurement and test entry points through ctypes.  There is no
+fallback: if the library has not been built, loading raises.
 """
 from __future__ import annotations
 
@@ -14,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libattn_gfx950.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 
 ATTN_FP16, ATTN_BF16 = 0, 1
 
@@ -46,6 +49,22 @@ class AttnError(RuntimeError):
 
 
 _lib = None
+_marshal = None
+
+
+def _attach(lib: ctypes.CDLL) -> None:
+    """Points the native marshalling at the entry points of a loaded library."""
+    global _marshal
+    if _marshal is None:
+        if not os.path.exists(MARSHAL_PATH):
+            raise FileNotFoundError(
+                f"{MARSHAL_PATH} is missing: build it with `python -m paper_2205_14135_amd.build`; "
+                "there is no fallback path")
+        from . import _marshal as native
+        _marshal = native
+    _marshal.attach(AttnError, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in (
+        "attn_fwd", "attn_bwd", "attn_bwd_workspace_bytes", "attn_blocksparse_fwd", "attn_blocksparse_bwd",
+        "attn_blocksparse_bwd_workspace_bytes")))
 
 
 def load() -> ctypes.CDLL:
@@ -88,6 +107,7 @@ def load() -> ctypes.CDLL:
     lib.attn_strerror.restype = ctypes.c_char_p
     lib.attn_version.argtypes = []
     lib.attn_version.restype = ctypes.c_int
+    _attach(lib)
     _lib = lib
     return lib
 
@@ -163,16 +183,9 @@ def _mask_args(block_mask: torch.Tensor, H: int):
 def attn_fwd(Q, K, V, *, softmax_scale, causal=False, dropout_p=0.0, seed=0, offset=0,
              o_fp32=False, out=None, lse=None, stream=None, key_lengths=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """O, LSE = attention forward.  Outputs are allocated with torch unless given."""
-    _same_layout(Q, K, V)
-    p = make_params(Q, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths)
-    B, H, N, d = Q.shape
-    if out is None:
-        out = torch.empty_strided(Q.shape, Q.stride(), dtype=torch.float32 if o_fp32 else Q.dtype,
-                                  device=Q.device)
-    if lse is None:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
-    _check(load().attn_fwd(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(out), _ptr(lse)), "attn_fwd")
-    return out, lse
+    if _lib is None:
+        load()
+    return _marshal.fwd(Q, K, V, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths, out, lse)
 
 
 def attn_bwd_workspace_bytes(p: AttnParams) -> int:
@@ -193,16 +206,11 @@ def _workspace(p: AttnParams, device, workspace, sparse=False):
 def attn_bwd(Q, K, V, O, dO, LSE, *, softmax_scale, causal=False, dropout_p=0.0, seed=0, offset=0,
              o_fp32=False, workspace=None, grads=None, stream=None, key_lengths=None):
     """dQ, dK, dV = attention backward (O, LSE from attn_fwd with the same options)."""
-    _same_layout(Q, K, V, dO)
-    p = make_params(Q, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths)
-    if grads is None:
-        grads = tuple(torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
-                      for _ in range(3))
-    dQ, dK, dV = grads
-    workspace, nbytes = _workspace(p, Q.device, workspace)
-    _check(load().attn_bwd(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE),
-                           _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(workspace), nbytes), "attn_bwd")
-    return dQ, dK, dV
+    if _lib is None:
+        load()
+    dQ, dK, dV = (None, None, None) if grads is None else grads
+    return _marshal.bwd(Q, K, V, O, dO, LSE, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths,
+                        workspace, dQ, dK, dV)
 
 
 STATIC_SCRATCH_BYTES = 8 << 20
@@ -222,37 +230,20 @@ def attn_bwd_static(Q, K, V, O, dO, LSE, grads, *, softmax_scale, causal=False, 
 def attn_blocksparse_fwd(Q, K, V, block_mask, *, softmax_scale, mask_block=128, causal=False,
                          dropout_p=0.0, seed=0, offset=0, o_fp32=False, out=None, lse=None, stream=None,
                          key_lengths=None):
-    _same_layout(Q, K, V)
-    p = make_params(Q, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths)
-    B, H, N, d = Q.shape
-    msh = _mask_args(block_mask, H)
-    if out is None:
-        out = torch.empty_strided(Q.shape, Q.stride(), dtype=torch.float32 if o_fp32 else Q.dtype,
-                                  device=Q.device)
-    if lse is None:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
-    _check(load().attn_blocksparse_fwd(ctypes.byref(p), _ptr(block_mask), int(mask_block), int(msh),
-                                       _ptr(Q), _ptr(K), _ptr(V), _ptr(out), _ptr(lse)),
-           "attn_blocksparse_fwd")
-    return out, lse
+    if _lib is None:
+        load()
+    return _marshal.blocksparse_fwd(Q, K, V, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths,
+                                    out, lse, block_mask, mask_block)
 
 
 def attn_blocksparse_bwd(Q, K, V, O, dO, LSE, block_mask, *, softmax_scale, mask_block=128, causal=False,
                          dropout_p=0.0, seed=0, offset=0, o_fp32=False, workspace=None, grads=None,
                          stream=None, key_lengths=None):
-    _same_layout(Q, K, V, dO)
-    p = make_params(Q, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths)
-    msh = _mask_args(block_mask, Q.shape[1])
-    if grads is None:
-        grads = tuple(torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device)
-                      for _ in range(3))
-    dQ, dK, dV = grads
-    workspace, nbytes = _workspace(p, Q.device, workspace, sparse=True)
-    _check(load().attn_blocksparse_bwd(ctypes.byref(p), _ptr(block_mask), int(mask_block), int(msh),
-                                       _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE),
-                                       _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(workspace), nbytes),
-           "attn_blocksparse_bwd")
-    return dQ, dK, dV
+    if _lib is None:
+        load()
+    dQ, dK, dV = (None, None, None) if grads is None else grads
+    return _marshal.blocksparse_bwd(Q, K, V, O, dO, LSE, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream,
+                                    key_lengths, workspace, dQ, dK, dV, block_mask, mask_block)
 
 
 def attn_bwd_timed(Q, K, V, O, dO, LSE, events, *, softmax_scale, block_mask=None, mask_block=128,

@@ -1,4 +1,5 @@
-"""Builds the HIP library in-tree: csrc/*.hip + csrc/attn_api.cpp -> libattn_gfx950.so.
+"""Builds the HIP library in-tree: csrc/*.hip + csrc/attn_api.cpp -> libattn_gfx950.so, and the binding's
+native argument marshalling: csrc/attn_marshal.cpp -> _marshal.so.
 
 hipcc cross-compiles for gfx950 without a GPU.  Usage: python -m paper_2205_14135_amd.build
 """
@@ -14,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libattn_gfx950.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")   # the binding's native argument marshalling (host code only)
 SOURCES = ["attn_fwd.hip", "attn_fwd_pp.hip", "attn_bwd.hip", "attn_bwd_dkv.hip", "attn_bwd_dkv_fr.hip", "attn_bwd_dkv_fr128.hip",
            "attn_bwd_dkv_w64.hip", "attn_probe.hip", "attn_api.cpp"]
 # Kernels that keep their accumulators in accumulation registers addressed by name in raw MFMA
@@ -99,10 +101,26 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    dirs = [*cpp_extension.include_paths("cuda"), sysconfig.get_path("include")]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f"-isystem{d}" for d in dirs],
+           os.path.join(CSRC, "attn_marshal.cpp"), "-o", MARSHAL,
+           "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on attn_marshal.cpp:\n{r.stdout}\n{r.stderr}")
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=4) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
+        marshal.result()
     cmd = [_hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

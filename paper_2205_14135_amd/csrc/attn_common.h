@@ -326,8 +326,8 @@ __device__ __forceinline__ uint32_t keep_mask_lane_key(uint32_t word, int bit) {
 // and is left holding the unnormalised probabilities; pf receives them rounded to T as the four
 // 16-key B-operand fragments of O^T += V^T P^T, with dropout applied.  Masks keys beyond `last`
 // on tiles that cross the causal diagonal or the end of the sequence, moves the running reference
-// m_run (and rescales o, l_run, lr_run) only when a row of the wavefront outgrew it by more than
-// kLazyRescale, and keeps two row sums, both before dropout: l_run, this lane's share, of the exact
+// m_run (and rescales o, l_run, lr_run) only when a lane of the wavefront outgrew it by kLazySum,
+// and keeps two row sums, both before dropout: l_run, this lane's share, of the exact
 // probabilities (for the saved statistic), and lr_run, complete, of the rounded ones (the normaliser of O).
 // The vector ALU bounds the forward at d <= 64 (65 % of the issue slots at N = 2048): a logit costs an
 // fma, an exp, an add and half a conversion, and no comparison: the maximum of a tile is only
