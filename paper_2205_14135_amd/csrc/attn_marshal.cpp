@@ -2,8 +2,9 @@
 // as a CPython extension: tensor checks, output allocation, parameter block and the library call in
 // one native call.  The same steps in Python and ctypes took 9 us of a forward call with its
 // buffers given, and 30 + 46 us of a training step through autograd, whose backward runs on the engine's own
-// thread with cold caches; a small problem's kernels take 5 to 10 us each.  Here: 3 us of a forward call, and a
-training step of 96 heads of 197 tokens went from 157 to 69 us, one forward call of one head from 9.2 to 4.8 us.
+// thread with cold caches; a small problem's kernels take 5 to 10 us each.  Here
+// a forward call takes 3 us of host time; a training step of 96 heads of 197 tokens went from 157 to 69 us, one
+// forward call of one head from 9.2 to 4.8 us.
 // The functions take positional arguments only (binding.py holds the public signatures and
 // defaults) and raise what the Python code raised: ValueError, TypeError, AttnError.
 #define PY_SSIZE_T_CLEAN
