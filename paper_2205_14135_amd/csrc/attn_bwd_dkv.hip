@@ -221,12 +221,14 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
       keep_row_store(Kw[p2][pair], draw_keep(i0));
       kw = keep_row_load_all(Kw[p2][pair]);
     }
-    if (kw0 + 32 > len) {   // this wavefront holds padded keys: their logits become -inf, hence P = 0
+    // hidden entries get the logit -inf, hence P = 0: above the causal diagonal (tiles that cross it only) or padded keys
+    if ((CAUSAL && i0 < kw0 + 31) || kw0 + 32 > len) {
+      const int first_query = kj < len ? (CAUSAL ? kj : 0) : 0x7fffffff;   // that sees this lane's key
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (kj >= len) sd[qb][i] = -INFINITY;
+          if (i0 + 32 * qb + 8 * (i >> 2) + 4 * g + (i & 3) < first_query) sd[qb][i] = -INFINITY;
     }
     T8 pf[4], pfull[4];
     f16x8 ph[4];
@@ -238,8 +240,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int i = 4 * i4 + e;
-          float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sd[qb][i], c, -l4[e]));
-          if (CAUSAL && kj > i0 + 32 * qb + 8 * i4 + 4 * g + e) p = 0.f;
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sd[qb][i], c, -l4[e]));
           const int cc = 2 * qb + (i4 >> 1), t = 4 * (i4 & 1) + e;
           pfull[cc][t] = (T)p;
           ph[cc][t] = (_Float16)p;

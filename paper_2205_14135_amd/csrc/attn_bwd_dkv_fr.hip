@@ -242,12 +242,16 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
       uint32_t* const kslot = Kb[ROW_LDS ? (threadIdx.x >> 6) : 0];
       if constexpr (DROPOUT) drawn = draw_keep(i0);
       if constexpr (ROW_LDS) keep_row_store(kslot, drawn);
-      if (kw0 + 32 > len) {   // this wavefront holds padded keys: their logits become -inf, hence P = 0
+      // hidden entries get the logit -inf, hence P = 0: above the causal diagonal (tiles that cross it
+      // only: a comparison and a select per element on every tile were a third of the vector instructions;
+      // B H = 128, N = 2048: 173 -> 158 us) or padded keys
+      if ((CAUSAL && i0 < kw0 + 31) || kw0 + 32 > len) {
+        const int first_query = kj < len ? (CAUSAL ? kj : 0) : 0x7fffffff;   // that sees this lane's key
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
           for (int i = 0; i < 16; ++i)
-            if (kj >= len) s[qb][i] = -INFINITY;
+            if (i0 + 32 * qb + 8 * (i >> 2) + 4 * g + (i & 3) < first_query) s[qb][i] = -INFINITY;
       }
       // P = exp(S - L), kept in fp32 in s[] for dS; the 16-bit (dropped) copy feeds dV
       T8 pf[4];
@@ -262,8 +266,7 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int i = 4 * i4 + e;
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qb][i], c, -l4[e]));
-            if (CAUSAL && kj > i0 + 32 * qb + 8 * i4 + 4 * g + e) p = 0.f;
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qb][i], c, -l4[e]));
             s[qb][i] = p;
             const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
             if constexpr (DROPOUT) {

@@ -119,10 +119,8 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
     constexpr int buf = decltype(buf_c)::value;
     if (t + 1 < limit) fetch_tile(t + 1, buf ^ 1);
     // causal: of the four tiles on the diagonal of the key block, wavefront w joins from the w-th
-    // on, and masks inside that one: query 8 i4 + 4 g + e of the tile sees this lane's key iff
-    // that number is >= kj - first query of the tile
+    // on, and masks inside that one
     const int i0 = t * QT;
-    const int hidden_below = CAUSAL && i0 == kw0 ? r - 4 * g : -(1 << 30);
     if (!CAUSAL || i0 >= kw0) {
       const T* Qt = Qs0 + buf * QT * D;
       const T* Gt = Gs0 + buf * QT * D;
@@ -156,10 +154,12 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      if (kw0 + 32 > len) {
+      // hidden entries get the logit -inf, hence P = 0: above the diagonal (one tile per wavefront) or padded keys
+      if ((CAUSAL && i0 == kw0) || kw0 + 32 > len) {
+        const int first_query = kj < len ? (CAUSAL ? kj : 0) : 0x7fffffff;   // that sees this lane's key
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (kj >= len) s[i] = -INFINITY;
+          if (i0 + 8 * (i >> 2) + 4 * g + (i & 3) < first_query) s[i] = -INFINITY;
       }
       // dropout: this lane draws the tile's query 8 (u / 4) + 4 g + u % 4 (u = r % 16) for the 16 keys
       // of its row; bit u' of the word of lane u is key u' of that query
@@ -183,8 +183,7 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int i = 4 * i4 + e;
-          float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c, -l4[e]));
-          if (CAUSAL && 8 * i4 + e < hidden_below) p = 0.f;
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c, -l4[e]));
           if constexpr (DROPOUT) {
             const uint32_t mask = keep_mask_lane_key(kw.w[e], r & 15);
             pf[i4 >> 1][4 * (i4 & 1) + e] = (T)keep_or_zero(p, mask);
