@@ -47,6 +47,11 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
   __shared__ __attribute__((aligned(16))) f16x8 Px[2][4][4][64];
   __shared__ __attribute__((aligned(16))) uint32_t Kw[2][4][64];                                // dropout keep words [buf][pair][lane]
 
+  // dropout flags in this layout: see KeepLK in attn_common.h (role A draws)
+  __shared__ __attribute__((aligned(16))) uint32_t keep_table[DROPOUT ? KeepLK::kTable : 4];
+  KeepLK keep;
+  if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
+
   const int n_kt = a.T;   // ceil(N / 128): the last key block may be ragged
   // Work assignment.  Dense: one key block per workgroup; under the causal mask key block k is
   // visited by N/64 - 2k query tiles, so a workgroup takes the pair (k, n_kt - 1 - k), one per
@@ -205,21 +210,13 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // Dropout bits in this layout: see draw_keep_lane_key() / keep_words_lane_key() in attn_common.h.
-  const int kbit = r & 15;   // position of this lane's key in the 16-key group of a draw
-  auto draw_keep = [&](int i0) {
-    return draw_keep_lane_key(i0, kj, r, g, bh, a.offset_lo, a.seed_lo, a.seed_hi, a.drop_thr);
-  };
-
   // ---- role A, tile with first query i0, buffers (q3, p2)
   auto role_a = [&](int i0, int q4, int g3, int p2) {
     row_product(Qs[q4], false, nullptr);                         // S = Q K^T
-    KeepLK kw = {};
-    if constexpr (DROPOUT) {
-      // the drawn bits go to LDS: the lanes of a 16-lane row read each other's words there, and
-      // role B regenerates nothing, it reads them too
-      keep_row_store(Kw[p2][pair], draw_keep(i0));
-      kw = keep_row_load_all(Kw[p2][pair]);
+    uint32_t kept = 0;
+    if constexpr (DROPOUT) {   // role B regenerates nothing: it reads the flags of the same lane from LDS
+      kept = keep.draw<2>(i0, kw0, bh, a.offset_lo, a.seed_lo, a.seed_hi);
+      Kw[p2][pair][lane] = kept;
     }
     // hidden entries get the logit -inf, hence P = 0: above the causal diagonal (tiles that cross it only) or padded keys
     if ((CAUSAL && i0 < kw0 + 31) || kw0 + 32 > len) {
@@ -245,7 +242,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
           pfull[cc][t] = (T)p;
           ph[cc][t] = (_Float16)p;
           if constexpr (DROPOUT) {
-            pf[cc][t] = (T)keep_or_zero(p, keep_mask_lane_key(kw.w[i4][e], kbit + 16 * qb));
+            pf[cc][t] = (T)keep_or_zero(p, KeepLK::mask(kept, qb, i4, e));
           }
         }
       }
@@ -256,8 +253,8 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
   };
   // ---- role B, second half for the previous tile: dS from sd (= dP) and A's P, then dK
   auto role_b_ds_dk = [&](int q4, int p2) {
-    KeepLK kw = {};
-    if constexpr (DROPOUT) kw = keep_row_load_all(Kw[p2][pair]);
+    uint32_t kept = 0;
+    if constexpr (DROPOUT) kept = Kw[p2][pair][lane];
     f16x8 pin[4];
     T8 dsf[4];
 #pragma unroll
@@ -274,7 +271,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
           const int cc = 2 * qb + (i4 >> 1), t = 4 * (i4 & 1) + e;
           float dpv = sd[qb][i];   // without dropout: already dP - D
           if constexpr (DROPOUT) {
-            dpv = dropped_dp_minus_d(dpv, a.keep_scale, keep_mask_lane_key(kw.w[i4][e], kbit + 16 * qb), d4[e]);
+            dpv = dropped_dp_minus_d(dpv, a.keep_scale, KeepLK::mask(kept, qb, i4, e), d4[e]);
           }
           // (an fma with an fp16 operand is one v_fma_mix_f32: the half is widened inside the instruction)
           dsf[cc][t] = (T)__builtin_fmaf((float)pin[cc][t], dpv, 0.f);

@@ -49,11 +49,10 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
     __shared__ __attribute__((aligned(16))) float Ds[2 * TILE];
     Qs0 = Qs; Gs0 = Gs; Ls0 = Ls; Ds0 = Ds;
   }
-  // dropout: the keep bits are exchanged along 16-lane rows either through one 64-word LDS slot per
-  // wavefront (four 16-byte reads per pass) or by row broadcasts (sixteen per pass, no memory); the
-  // forms that are short of registers keep the broadcasts, whose results need no aligned quadruples
-  constexpr bool ROW_LDS = DROPOUT && !CAUSAL && !SPARSE;
-  __shared__ __attribute__((aligned(16))) uint32_t Kb[ROW_LDS ? NT / 64 : 1][64];
+  // dropout flags in this layout: see KeepLK in attn_common.h
+  __shared__ __attribute__((aligned(16))) uint32_t keep_table[DROPOUT ? KeepLK::kTable : 4];
+  KeepLK keep;
+  if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
 
   const int n_kt = a.T;   // ceil(N / 128): the last key block may be ragged
   // Work assignment.  Dense: one key block per workgroup; under the causal mask key block k is
@@ -215,12 +214,6 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // Dropout bits in this layout: see draw_keep_lane_key() / keep_words_lane_key() in attn_common.h.
-  const int kbit = r & 15;   // position of this lane's key in the 16-key group of a draw
-  auto draw_keep = [&](int i0) {
-    return draw_keep_lane_key(i0, kj, r, g, bh, a.offset_lo, a.seed_lo, a.seed_hi, a.drop_thr);
-  };
-
   // ---- pipeline over the query tiles of this key block: tile t + 1 streams in while t is used
   int buf_rt = 0;
   int t = it.next();
@@ -237,11 +230,8 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
     if (!CAUSAL || i0 + TILE - 1 >= kw0) {
       f32x16 s[2], dp[2];
       row_product(Qs0 + buf * TILE * D, kf, false, nullptr, s);                // S = Q K^T
-      // this lane's packed keep bits; the words of a row group are fetched where they are used
-      uint32_t drawn = 0;
-      uint32_t* const kslot = Kb[ROW_LDS ? (threadIdx.x >> 6) : 0];
-      if constexpr (DROPOUT) drawn = draw_keep(i0);
-      if constexpr (ROW_LDS) keep_row_store(kslot, drawn);
+      uint32_t kept = 0;   // the keep flags of this lane's key for the tile's 64 queries it holds
+      if constexpr (DROPOUT) kept = keep.draw<2>(i0, kw0, bh, a.offset_lo, a.seed_lo, a.seed_hi);
       // hidden entries get the logit -inf, hence P = 0: above the causal diagonal (tiles that cross it
       // only: a comparison and a select per element on every tile were a third of the vector instructions;
       // B H = 128, N = 2048: 173 -> 158 us) or padded keys
@@ -257,9 +247,9 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
       T8 pf[4];
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
-        KeepLK4 kw = {};
-        if constexpr (ROW_LDS) kw = keep_row_load(kslot, i4);
-        else if constexpr (DROPOUT) kw = keep_words_lane_key(drawn, i4);
+        // (keeps the bit extracts where they are used: hoisted, they make the forms short of registers spill; the
+        // plain form is faster without)
+        if constexpr (DROPOUT && (CAUSAL || SPARSE)) asm volatile("" : "+v"(kept));
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
           const f32x4 l4 = *(const f32x4*)(Ls0 + buf * TILE + 32 * qb + 8 * i4 + 4 * g);
@@ -270,7 +260,7 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
             s[qb][i] = p;
             const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
             if constexpr (DROPOUT) {
-              pf[cc][tt] = (T)keep_or_zero(p, keep_mask_lane_key(kw.w[e], kbit + 16 * qb));
+              pf[cc][tt] = (T)keep_or_zero(p, KeepLK::mask(kept, qb, i4, e));
             } else {
               pf[cc][tt] = (T)p;
             }
@@ -281,15 +271,8 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
       // dP = dO V^T; without dropout it starts from -D, so the result is dP - D
       row_product(Gs0 + buf * TILE * D, vf, !DROPOUT, Ds0 + buf * TILE, dp);
       T8 dsf[4];
-      // (the keep words are fetched again here rather than kept from the P pass: sixteen registers
-      // held across the dP product would spill; the empty statement keeps the compiler from merging
-      // the two sets of broadcasts)
-      if constexpr (DROPOUT && !ROW_LDS) asm volatile("" : "+v"(drawn));
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
-        KeepLK4 kw = {};
-        if constexpr (ROW_LDS) kw = keep_row_load(kslot, i4);
-        else if constexpr (DROPOUT) kw = keep_words_lane_key(drawn, i4);
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
           f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
@@ -300,7 +283,7 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
             const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
             float dpv = dp[qb][i];
             if constexpr (DROPOUT) {
-              dpv = dropped_dp_minus_d(dpv, a.keep_scale, keep_mask_lane_key(kw.w[e], kbit + 16 * qb), d4[e]);
+              dpv = dropped_dp_minus_d(dpv, a.keep_scale, KeepLK::mask(kept, qb, i4, e), d4[e]);
             }
             dsf[cc][tt] = (T)(s[qb][i] * dpv);
           }

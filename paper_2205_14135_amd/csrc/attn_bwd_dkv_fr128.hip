@@ -14,9 +14,8 @@
 // mask a workgroup takes one key block (not a pair: the loop over a pair costs registers this
 // kernel does not have) and the blocks are dealt out heaviest first.  Dropout: a call of the
 // generator decides 16 consecutive keys of a query, i.e. the 16 lanes of one row of the wavefront,
-// which need the draws of the tile's 16 queries 8 i4 + 4 g + e: every lane draws one of them, packs
-// the keep bits and the row exchanges them (draw_keep_lane_key / keep_words_lane_key in
-// attn_common.h, here with 32-query tiles: one call per lane and tile).
+// which need the draws of the tile's 16 queries 8 i4 + 4 g + e: every lane draws one of them and the
+// row transposes the flags (KeepLK in attn_common.h, here with 32-query tiles: one call per lane and tile).
 #include <type_traits>
 
 #include "attn_common.h"
@@ -42,6 +41,11 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
   T* const Qs0 = (T*)(smem + kVecBytes);           // Q tiles:  Qs0 + buf QT D
   T* const Gs0 = Qs0 + 2 * QT * D;                 // dO tiles: Gs0 + buf QT D
   T* const Vb = Qs0 + 4 * QT * D;                  // V rows of this key block
+
+  // dropout flags in this layout: see KeepLK in attn_common.h
+  __shared__ __attribute__((aligned(16))) uint32_t keep_table[DROPOUT ? KeepLK::kTable : 4];
+  KeepLK keep;
+  if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
 
   const int n_kt = a.T;   // ceil(N / 128): the last key block may be ragged
   const int item = xcd_item(a.n_items, a.chunk);
@@ -161,23 +165,14 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
         for (int i = 0; i < 16; ++i)
           if (i0 + 8 * (i >> 2) + 4 * g + (i & 3) < first_query) s[i] = -INFINITY;
       }
-      // dropout: this lane draws the tile's query 8 (u / 4) + 4 g + u % 4 (u = r % 16) for the 16 keys
-      // of its row; bit u' of the word of lane u is key u' of that query
-      uint32_t drawn = 0;
-      if constexpr (DROPOUT) {
-        const int u = r & 15;
-        const u32x4 w = philox_draw16((uint32_t)kj >> 4, (uint32_t)(i0 + 8 * (u >> 2) + 4 * g + (u & 3)), (uint32_t)bh,
-                                      a.offset_lo, a.seed_lo, a.seed_hi);
-        drawn = keep_bits16(w, dropout_carry2(a.drop_thr));
-      }
+      uint32_t kept = 0;   // dropout: the keep flags of this lane's key for the tile's queries it holds
+      if constexpr (DROPOUT) kept = keep.draw<1>(i0, kw0, bh, a.offset_lo, a.seed_lo, a.seed_hi);
       T8 pf[2], dsf[2];
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
         const f32x4 l4 = *(const f32x4*)(Ls0 + 64 * buf + 8 * i4 + 4 * g);
-        KeepLK4 kw = {};
         f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
         if constexpr (DROPOUT) {
-          kw = keep_words_lane_key(drawn, i4);
           d4 = *(const f32x4*)(Ds0 + 64 * buf + 8 * i4 + 4 * g);   // -D_i
         }
 #pragma unroll
@@ -185,7 +180,7 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
           const int i = 4 * i4 + e;
           const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c, -l4[e]));
           if constexpr (DROPOUT) {
-            const uint32_t mask = keep_mask_lane_key(kw.w[e], r & 15);
+            const uint32_t mask = KeepLK::mask(kept, 1, i4, e);
             pf[i4 >> 1][4 * (i4 & 1) + e] = (T)keep_or_zero(p, mask);
             dsf[i4 >> 1][4 * (i4 & 1) + e] = (T)(p * dropped_dp_minus_d(dp[i], a.keep_scale, mask, d4[e]));
           } else {

@@ -5,17 +5,6 @@
 
 namespace attn {
 
-// Lane index read by an instruction the compiler will not move: address arithmetic of a rarely
-// taken path that starts from it stays inside that path instead of being hoisted out of the tile
-// loop, where it would occupy registers for the whole kernel.
-__device__ __forceinline__ int lane_id_here() {
-  int lane = 0;
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
-#endif
-  return lane;
-}
-
 // Asynchronous copy of a [64][D] tile from global memory straight into swizzled LDS (no register
 // staging, no LDS store instructions): each global_load_lds_dwordx4 moves 64 lanes x 16 bytes to
 // 1 KB of consecutive LDS, so lane l of copy q lands on row q*(64/CPR) + l/CPR, physical chunk
