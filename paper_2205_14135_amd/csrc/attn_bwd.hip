@@ -83,7 +83,8 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const KArgs a) {
   const T* __restrict__ Kg = (const T*)a.K + head_off;
   const T* __restrict__ Vg = (const T*)a.V + head_off;
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register: addresses and branches on it are scalar
   const int r = lane & 31, g = lane >> 5;
   const int q0 = qt * 128 + wave * 32;
   // lanes beyond a ragged end work on a copy of the last row with P = 0 and store nothing
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const KArgs a) {
   TrOffsets<D> tro;
   tro.init();
   TileAsync<T, D, NT / 64> dma;
-  dma.init(a.sn, threadIdx.x >> 6, D == 32 ? a.dvalid : D);
+  dma.init(a.sn, wave, D == 32 ? a.dvalid : D);
   if (D == 32 && a.dvalid < D) {   // the copies leave columns >= 16 of the tile buffers untouched
     zero_tiles(Ks0, 2 * TILE * D);
     zero_tiles(Vs0, 2 * TILE * D);

@@ -72,7 +72,8 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
   const float* __restrict__ Lg = a.L2vec + (int64_t)bh * a.Nr;
   const float* __restrict__ Dg = a.Dvec + (int64_t)bh * a.Nr;
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register: addresses and branches on it are scalar
   const int r = lane & 31, g = lane >> 5;
   const int kw0 = kt * 128 + wave * 32;
   const int kj = kw0 + r;

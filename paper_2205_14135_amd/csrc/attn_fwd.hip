@@ -69,7 +69,8 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
   const T* __restrict__ Vg = (const T*)a.V + head_off;
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register: addresses and branches on it are scalar
   const int r = lane & 31, g = lane >> 5;
   const int q0 = qt * BR + wave * 32;  // first query row of this wavefront
   // this lane's query row; lanes beyond a ragged end work on a copy of the last row and store nothing
@@ -129,13 +130,22 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
   }
   wait_async_copies();
   __syncthreads();   // tile 0 has landed, and so have the Q fragments
+  // the scalar loads of the kernel arguments that the loop uses have completed: one in flight makes the first
+  // operand wait of the loop a wait for every LDS read issued so far (scalar loads return out of order)
+  asm volatile("" :: "s"(c));
+  // byte offsets of this lane's K fragments in a tile, kept whole (derived again on every tile otherwise)
+  uint32_t k_off[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    k_off[kk] = lds_addr(&Ks[0][0]) + (uint32_t)(lds_off<D>(r, 2 * kk + g) * sizeof(T));
+    asm volatile("" : "+v"(k_off[kk]));
+  }
   while (jt >= 0) {
     const int jn = it.next();
     if (jn >= 0) {   // the next tile streams into the other buffer while this one is used
       dma.copy_rows(Kg, a.sn, jn * BC, a.N, Ks[buf ^ 1]);
       dma.copy_rows(Vg, a.sn, jn * BC, a.N, Vs[buf ^ 1]);
     }
-    const T* Kt = Ks[buf];
     const T* Vt = Vs[buf];
 
     const int k0 = jt * BC;
@@ -151,7 +161,8 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
         for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
       {
         auto k_frag = [&](int f) {   // f = 2 kk + kb
-          return *(const T8*)(Kt + lds_off<D>(32 * (f & 1) + r, 2 * (f >> 1) + g));
+          const auto* p = (const __attribute__((address_space(3))) T8*)(k_off[f >> 1] + (uint32_t)(buf * BC * D * sizeof(T)));
+          return p[32 * (f & 1) * D / 8];
         };
         T8 ring[PF];
 #pragma unroll

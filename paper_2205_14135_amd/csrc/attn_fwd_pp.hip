@@ -45,7 +45,8 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
   const T* __restrict__ Vg = (const T*)a.V + head_off;
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register: addresses and branches on it are scalar
   const bool group_b = wave >= 4;
   const int r = lane & 31, g = lane >> 5;
   const int q0 = qt * BRW + wave * 32;
