@@ -14,13 +14,13 @@
 // is read in slots 2t, 2t+1 and V(t) in slots 2t+2, 2t+3.  Tiles arrive by asynchronous
 // global-to-LDS copies that the compiler does not track; group A copies the K tiles and group B
 // the V tiles.  Issuing a tile's copy instructions blocks a wavefront for hundreds of clocks (the
-// vector memory path takes 64 bytes per clock), so a wavefront issues tile j + 1 at the END of its
-// matrix block M(j), the shorter of the two blocks, where it would otherwise wait at the barrier
-// for the other group's vector block, and waits for the copy only at the end of its own X(j): the
-// copy has a whole block to land and its latency never shows.  (Measured against issuing at the
-// start or at the end of the vector block, or half and half: this placement is the fastest.)  The
-// third V buffer is what allows it: when a group B wavefront leaves M(j), its neighbours may still
-// be reading V(j-1).
+// vector memory path takes 64 bytes per clock), so they stand in the shorter of the two blocks: the
+// vector block, since the softmax no longer looks for each tile's maximum.  Tile j + 2 is issued at the
+// START of X(j), two tiles ahead, into the buffer of tile j - 1 (for group A in slot 2j + 1: K(j-1) was last read in
+// slot 2j - 1; for group B in slot 2j + 2: V(j-1) was last read in slot 2j + 1), and the end of X(j) waits for tile
+// j + 1 only, issued a whole tile earlier.  Measured against issuing tile j + 1 at the end of M(j), where the copies stood
+// while M was the shorter block: B H = 64, d = 128, N = 4096 491 -> 484 us, causal 272 -> 266 us, N = 16384 1895 -> 1868 us;
+// issuing at the end of X(j) instead: 538 us.
 #include "attn_common.h"
 #include "attn_tiles.h"
 
@@ -157,10 +157,11 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
 
   // ring slot of a tile in this group's ring
   auto ring = [&](int slot) -> T* { return group_b ? Vs[slot] : Ks[slot]; };
-  // ---- prologue: tile 0 of this group's tensor.  Group B starts one block later (an extra
+  // ---- prologue: tiles 0 and 1 of this group's tensor.  Group B starts one block later (an extra
   // barrier).  The wait also covers the Q fragment loads issued before.
   dma.copy_rows(Tg, a.sn, 0, a.N, ring(0));
   wait_async_copies();
+  if (J > 1) dma.copy_rows(Tg, a.sn, BC, a.N, ring(1));   // lands during M(0) and X(0)
   __syncthreads();
   if (group_b) {
     __builtin_amdgcn_sched_barrier(0);
@@ -170,16 +171,18 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
   int cur = 0;   // ring slot of tile j: j % 3
   for (int j = 0; j < J; ++j) {
     const int nxt = cur == 2 ? 0 : cur + 1, prv = cur == 0 ? 2 : cur - 1;   // slots of tiles j + 1, j - 1
-    // ---- M(j): matrix work, then the copy of this group's tile j + 1 (its slot held tile j - 2)
+    // ---- M(j): matrix work
     do_M(j > 0 && active(j - 1), Vs[prv], active(j), Ks[cur]);
     __builtin_amdgcn_sched_barrier(0);
-    if (j + 1 < J) dma.copy_rows(Tg, a.sn, (j + 1) * BC, a.N, ring(nxt));
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
-    // ---- X(j): the online softmax; then tile j + 1 must have landed
+    // ---- X(j): the copy of this group's tile j + 2 (its slot held tile j - 1) and the online softmax;
+    // then tile j + 1 must have landed
+    const bool more = j + 2 < J;
+    if (more) dma.copy_rows(Tg, a.sn, (j + 2) * BC, a.N, ring(prv));
     if (active(j)) do_softmax(j);
     __builtin_amdgcn_sched_barrier(0);
-    wait_async_copies();
+    if (more) wait_async_copies_but<Dma::PER_WAVE>(); else wait_async_copies();
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
     cur = nxt;
