@@ -27,6 +27,8 @@
 #include "attn_common.h"
 #include "attn_tiles.h"
 
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 namespace attn {
@@ -288,26 +290,48 @@ __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
 
 }  // namespace
 
+// Which dense d = 128 problems take the two-group kernel (attn_fwd_pp.hip): an estimate of either kernel's time,
+// in units of one 64-key tile of the two-group kernel (256 rows on a whole compute unit, 1.89 us without
+// dropout).  Per tile it is the faster one, but it has one workgroup per compute unit: its work items (pairs of row blocks
+// under the causal mask) run in whole rounds over the chip, and nothing covers an item's prologue and epilogue.
+// This file's kernel has two workgroups of 128 rows on a compute unit, dealt out as they finish (unpaired and
+// therefore less evenly under the causal mask).  The constants are fits to these times (us, two-group | this file's):
+//   causal     N = 512 78 | 76, 640 116 | 71, 768 110 | 78, 1024 97 | 105, 1400 150 | 124, 2048 150 | 170, 4096 265 | 299
+//   no mask    N = 512 91 | 79, 768 117 | 108, 1024 144 | 139, 1400 212 | 201, 2048 259 | 261, 4096 484 | 516
+//   causal with dropout  N = 512 84 | 85, 1024 110 | 127, 2048 175 | 208, 4096 310 | 362; 64 heads of 1024: 49 | 41
+// (16384 tokens, 16 heads).  Without a mask, dropout (plain vector ALU work) evens the two out: 572 | 599 at
+// N = 4096, 172 | 166 at 1024; this file's kernel keeps those.
+static bool two_group_is_faster(const KArgs& a, bool causal, bool dropout) {
+  if (dropout && !causal) return false;
+  const double heads = (double)a.B * a.H;
+  const double tiles = (a.N + BC - 1) / BC;              // 64-key tiles of a row without a mask
+  const double tile_pp = dropout ? 1.13 : 1.0, tile_base = dropout ? 1.32 : 1.08;
+  const double extra_pp = causal ? 7.2 : 4.0, extra_base = causal ? 4.1 : 1.8;   // per work item, per workgroup
+  const double blocks256 = (a.N + 255) / 256, blocks128 = a.T;
+  const double items = heads * (causal ? std::floor((blocks256 + 1) / 2) : blocks256);
+  const double item_tiles = causal && blocks256 > 1 ? tiles + 4 : tiles;
+  const double pp = std::ceil(items / kComputeUnits) * (item_tiles * tile_pp + extra_pp);
+  const double groups = heads * blocks128;
+  const double head_tiles = causal ? std::min(blocks128 * (blocks128 + 1), blocks128 * tiles) : blocks128 * tiles;
+  // A compute unit that has only one workgroup of this file's kernel left (few workgroups, or the long ones under a
+  // causal mask, whose neighbours have ended) gets through a tile in 0.65 of the time: 8 heads of 8192 with dropout,
+  // 203 us here, 247 in the two-group kernel.
+  const bool alone = causal || groups <= kComputeUnits;
+  const double longest = tiles * (alone ? 0.65 : 1.0) * tile_base + extra_base;
+  const double base = std::max((heads * head_tiles * tile_base + groups * extra_base) / (2 * kComputeUnits), longest);
+  return pp < base;
+}
+
 int choose_fwd(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
   const int variant = fwd_variant();
-  const int n_qt256 = (a.N + 255) / 256;
-  const int64_t pp_items = (int64_t)a.B * a.H * (causal ? (n_qt256 + 1) / 2 : n_qt256);
-  bool use_pp = d == 128 && pp_items >= kComputeUnits &&
-                (dropout ? causal : (a.N >= 1024 || (causal && a.N >= 512)));
+  bool use_pp = d == 128 && two_group_is_faster(a, causal, dropout);
   if (variant == 1) use_pp = false;
   if (variant == 2 && d != 32) use_pp = true;
-  return !sparse && use_pp ? kFwdTwoGroup : kFwdFreeRunning;   // (the reasons: see launch_fwd)
+  return !sparse && use_pp ? kFwdTwoGroup : kFwdFreeRunning;
 }
 
 int launch_fwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s) {
-  // Which dense d = 128 problems take the two-group ping-pong kernel (attn_fwd_pp.hip), by
-  // measurement against this file's kernel (two free-running 4-wave workgroups per compute unit):
-  //   no dropout: from N = 1024 on (4-6 % faster from 2048, equal at 1024, 6 % slower at 512), under
-  //     the causal mask from N = 512 (its paired work items balance better);
-  //   dropout: only under the causal mask (the pairing again: 10-15 % faster); without a mask the
-  //     free-running kernel is ~3 % faster at every N (the generator is plain vector ALU work);
-  //   and only if its 256-row work items (pairs of them under the causal mask) are at least as
-  //     many as the compute units: a problem with few heads would leave half of the chip idle.
+  // Dense d = 128 problems: see two_group_is_faster above.
   // At d <= 64 the vector ALU work dominates and this file's kernel measured faster at every N;
   // block-sparse problems always take it.  attn_debug_set_variant overrides the choice
   // (comparisons and tests).
