@@ -378,16 +378,23 @@ __device__ __forceinline__ void softmax_tile_lane_query(const KArgs& a, f32x16 (
   // says whether the reference still serves.  (A row without one has m_run = -inf: its sum is inf or NaN.)
   float neg_m = -m_run;
   float psum;
+  uint32_t pw[16];   // P^T fragments, two probabilities to a word: word i / 2 of 32-key block kb (whole words, so that
+                     // the two passes below meet in 16 registers and not in 32 halves that are packed again)
   auto probabilities = [&]() __attribute__((always_inline)) {
+    typedef T T2 __attribute__((ext_vector_type(2)));
     float part[2] = {0.f, 0.f};
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], c, neg_m));
-        part[i & 1] += p;
-        // P^T fragments: 16-key chunk cc = 2 kb + i / 8
-        pf[2 * kb + (i >> 3)][i & 7] = (T)p;
+      for (int i = 0; i < 16; i += 2) {
+        T2 pair;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i + e], c, neg_m));
+          part[e] += p;
+          pair[e] = (T)p;
+        }
+        pw[8 * kb + i / 2] = __builtin_bit_cast(uint32_t, pair);
       }
     psum = part[0] + part[1];
   };
@@ -412,8 +419,19 @@ __device__ __forceinline__ void softmax_tile_lane_query(const KArgs& a, f32x16 (
       for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
     neg_m = -m_safe;
     probabilities();
+    // A row with a logit that is not a number (an input that is not finite, or a product beyond float32) must not
+    // reach the sum of row r +- 16, which shares its column of the MFMA below and is separated from it by factors 0:
+    // its probabilities become zeros, and l_run, which is NaN from here on, makes its O NaN in the epilogue.
+    const uint32_t number = psum == psum ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) pw[w] &= number;
   }
   l_run += psum;
+#pragma unroll
+  for (int cc = 0; cc < 4; ++cc) {   // 16-key chunk cc
+    const u32x4 chunk = {pw[4 * cc], pw[4 * cc + 1], pw[4 * cc + 2], pw[4 * cc + 3]};
+    pf[cc] = __builtin_bit_cast(typename Vec<T>::x8, chunk);
+  }
 #pragma unroll
   for (int cc = 0; cc < 4; ++cc) lr_run = mfma16(ones, pf[cc], lr_run);
   if constexpr (DROPOUT) {   // element t of chunk cc has field t % 4 of word 2 (cc & 1) + t / 4 of its block

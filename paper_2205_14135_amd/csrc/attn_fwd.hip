@@ -210,7 +210,8 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
   const float l_sum = l_run + xchg32(l_run);
   const float lr_sum = lr_run[0];
   const float l_tot = qi < len ? l_sum : 0.f;   // padding rows: O = 0, LSE = -inf
-  const float inv = (l_tot > 0.f && lr_sum > 0.f) ? (DROPOUT ? a.keep_scale : 1.f) / lr_sum : 0.f;
+  const float inv = (l_tot > 0.f && lr_sum > 0.f) ? (DROPOUT ? a.keep_scale : 1.f) / lr_sum
+                                                  : (l_tot == l_tot ? 0.f : l_tot);   // (a row of NaN stays one)
   if (g == 0 && row_ok) {
     const float lse = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
     a.LSE[(int64_t)bh * a.N + qi] = lse;
