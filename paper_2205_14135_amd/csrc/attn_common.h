@@ -127,14 +127,18 @@ template <typename T> __device__ __forceinline__ typename Vec<T>::x8 row_sum_one
   return v;
 }
 
-// Online softmax, when the reference of a row is moved: only when a lane's sum of the 32 probabilities it holds of a new 64-key
-// tile, against the reference so far, exceeds this (the first tile always does).  What makes a lagging reference as accurate as
+// Online softmax, when the reference of a row is moved: when a lane's sum of the 32 probabilities it holds of a new 64-key
+// tile, against the reference so far, exceeds kLazySum, or where the tile's maximum is looked for first, when that
+// exceeds the reference by more than kLazyRise (base-2 exponent units).  What makes a lagging reference as accurate as
 // the running maximum is that O is normalised by the sum of the ROUNDED 16-bit probabilities, the very weights
 // the second product used: O stays a convex combination of V rows whatever the reference is.  It still matters how far it
 // lags where a few keys dominate a row: at the reference itself a probability is exactly 1, away from it the largest is rounded as well.
-// Error of O against 64 bits (bf16, d = 64, N = 2048; logits of standard deviation 4 and 8, in units of e): 8.54e-4 and
-// 4.79e-4 with this bar, 8.97e-4 and 5.37e-4 with 2^10, 8.58e-4 and 5.06e-4 if the maximum of a tile may exceed the reference by 8 (base 2).
-constexpr float kLazySum = 256.0f;
+// Error of O against 64 bits (bf16, d = 64, N = 2048; logits of standard deviation 4 and 8, in units of e): 8.58e-4 and
+// 5.06e-4 here, 8.97e-4 and 5.37e-4 with a bar of 2^10 for the sum, 9.27e-4 and 5.54e-4 with 2^15.
+constexpr float kLazySum = 256.0f, kLazyRise = 8.0f;
+// How many tiles after a move another one still counts as restless, and how many quiet tiles end that (see
+// softmax_tile_lane_query); the state before a row's first tile.
+constexpr int kRestless = 8, kFirstTile = -kRestless - 1;
 
 // Philox-4x32-10 (Salmon et al., SC'11): counter (c0..c3), key (k0,k1) -> 4 words.
 __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
@@ -350,7 +354,7 @@ __device__ __forceinline__ float dropped_dp_minus_d(float dp, float keep_scale, 
 // Online softmax of one 64-key tile in the "lane = query" layout of the forward kernels (Algorithm 2
 // of the paper's follow-up formulation of Algorithm 1's inner loop, base 2): s holds the raw logits
 // S^T (two 32-key blocks; lane (r, g) has query row q0 + r and keys 32 kb + 8 (i / 4) + 4 g + i % 4)
-// and is left holding the unnormalised probabilities; pf receives them rounded to T as the four
+// (masked ones set to -inf); pf receives the unnormalised probabilities rounded to T as the four
 // 16-key B-operand fragments of O^T += V^T P^T, with dropout applied.  Masks keys beyond `last`
 // on tiles that cross the causal diagonal or the end of the sequence, moves the running reference
 // m_run (and rescales o, l_run, lr_run) only when a lane of the wavefront outgrew it by kLazySum,
@@ -360,10 +364,20 @@ __device__ __forceinline__ float dropped_dp_minus_d(float dp, float keep_scale, 
 // fma, an exp, an add and half a conversion, and no comparison: the maximum of a tile is only
 // looked for when the sum of its probabilities asks for it (170 -> 138 vector instructions per tile;
 // B H = 128, N = 2048, d = 64: 166.8 -> 154.2 us; d = 32, N = 4096: 227 -> 209 us; d = 128, N = 4096: 495 -> 487 us).
-template <typename T, int DB, bool CAUSAL, bool DROPOUT>
+// `calm` (the same in all lanes) keeps tiles that are likely to move the reference from forming their probabilities twice.
+// Above 0 it counts the tiles since the last move, and the next tile is tried as it is.  From 0 down the tile looks for its maximum
+// first and moves the reference by that: the first tile, and after two moves within kRestless tiles every one until
+// kRestless in a row have moved nothing (peaked rows, logits that rise along the keys).  us, with the trial on every tile | this | a maximum
+// on every tile: logits that rise by 0.1 per key (in units of e), B H = 128, N = 2048, d = 64 205 | 170 | 173, d = 32, N = 700
+// 27.8 | 22.2 | 21.6, B H = 64, d = 128, N = 4096 596 | 531 | 514; Gaussian logits of standard deviation 8: 178 | 172 | 173,
+// 25.6 | 22.2 | 21.4, 539 | 540 | 525; standard deviation 1, N = 512 causal 38.1 | 36.1, GPT-2 shape 39.8 | 38.1 | 41.8.
+// PACK_LATE: probabilities are rounded after the two passes have met, not inside each.  The exps then have more room between
+// them, for 13 registers more (d = 128, B H = 64, N = 1024 causal with dropout 40.8 -> 39.4 us; BERT-large shape 34.6 -> 34.1);
+// the causal d = 64 forms spill with it (N = 512 38.2 -> 46 us).
+template <typename T, int DB, bool CAUSAL, bool DROPOUT, bool PACK_LATE>
 __device__ __forceinline__ void softmax_tile_lane_query(const KArgs& a, f32x16 (&s)[2], f32x16 (&o)[DB],
                                                         typename Vec<T>::x8 (&pf)[4], float& m_run, float& l_run,
-                                                        f32x4& lr_run, const typename Vec<T>::x8& ones, float c, int k0, int q0, int qi, int len, int g,
+                                                        f32x4& lr_run, int& calm, const typename Vec<T>::x8& ones, float c, int k0, int q0, int qi, int len, int g,
                                                         int bh) {
   if ((CAUSAL && k0 + 63 > q0) || k0 + 64 > len) {   // diagonal tiles, and the padded last tile
     const int last = CAUSAL ? min(qi, len - 1) : len - 1;   // last visible key of this row
@@ -376,11 +390,12 @@ __device__ __forceinline__ void softmax_tile_lane_query(const KArgs& a, f32x16 (
       }
   }
   // Probabilities against the reference the row has, with no look at the tile's maximum: their sum
-  // says whether the reference still serves.  (A row without one has m_run = -inf: its sum is inf or NaN.)
+  // says whether the reference still serves.  (A row that has seen no key has m_run = -inf: its sum is inf or NaN.)
   float neg_m = -m_run;
   float psum;
-  uint32_t pw[16];   // P^T fragments, two probabilities to a word: word i / 2 of 32-key block kb (whole words, so that
-                     // the two passes below meet in 16 registers and not in 32 halves that are packed again)
+  f32x16 pr[2];      // PACK_LATE: the probabilities
+  uint32_t pw[16];   // else: the P^T fragments, in whole words, so that the two passes meet in 16 registers and not in 32
+                     // halves that are packed again (5 % of the forms with dropout)
   auto probabilities = [&]() __attribute__((always_inline)) {
     typedef T T2 __attribute__((ext_vector_type(2)));
     float part[2] = {0.f, 0.f};
@@ -393,45 +408,67 @@ __device__ __forceinline__ void softmax_tile_lane_query(const KArgs& a, f32x16 (
         for (int e = 0; e < 2; ++e) {
           const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i + e], c, neg_m));
           part[e] += p;
-          pair[e] = (T)p;
+          if constexpr (PACK_LATE) pr[kb][i + e] = p;
+          else pair[e] = (T)p;
         }
-        pw[8 * kb + i / 2] = __builtin_bit_cast(uint32_t, pair);
+        if constexpr (!PACK_LATE) pw[8 * kb + i / 2] = __builtin_bit_cast(uint32_t, pair);
       }
     psum = part[0] + part[1];
   };
-  probabilities();
-  if (__builtin_amdgcn_ballot_w64(!(psum <= kLazySum)) != 0) {   // wavefront-uniform: rare after the first tile
+  bool search = calm <= 0, move = false;
+  if (__builtin_expect(!search, 1)) {
+    probabilities();
+    search = move = __builtin_amdgcn_ballot_w64(!(psum <= kLazySum)) != 0;
+    ++calm;
+  }
+  if (__builtin_expect(search, 0)) {
     float mx = s[0][0];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
     mx = fmaxf(mx, xchg32(mx)) * c;
-    const float m_new = fmaxf(m_run, mx);
-    const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
-    m_run = m_new;
-    l_run *= alpha;
+    if (move) calm = calm <= kRestless ? -kRestless : 1;
+    else if ((move = __builtin_amdgcn_ballot_w64(mx > m_run + kLazyRise) != 0)) calm = calm < -kRestless ? 1 : -kRestless;
+    else ++calm;
+    if (move) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) lr_run[i] *= alpha;
+      for (int i = 0; i < 4; ++i) lr_run[i] *= alpha;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
-    neg_m = -m_safe;
+        for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+    }
+    neg_m = m_run == -INFINITY ? 0.f : -m_run;
     probabilities();
     // A row with a logit that is not a number (an input that is not finite, or a product beyond float32) must not
     // reach the sum of row r +- 16, which shares its column of the MFMA below and is separated from it by factors 0:
     // its probabilities become zeros, and l_run, which is NaN from here on, makes its O NaN in the epilogue.
-    const uint32_t number = psum == psum ? 0xFFFFFFFFu : 0u;
+    if (__builtin_amdgcn_ballot_w64(psum != psum) != 0) {
+      const bool number = psum == psum;
+      if constexpr (PACK_LATE) {
 #pragma unroll
-    for (int w = 0; w < 16; ++w) pw[w] &= number;
+        for (int i = 0; i < 32; ++i) pr[i >> 4][i & 15] = number ? pr[i >> 4][i & 15] : 0.f;
+      } else {
+#pragma unroll
+        for (int w = 0; w < 16; ++w) pw[w] = number ? pw[w] : 0u;
+      }
+    }
   }
   l_run += psum;
 #pragma unroll
   for (int cc = 0; cc < 4; ++cc) {   // 16-key chunk cc
-    const u32x4 chunk = {pw[4 * cc], pw[4 * cc + 1], pw[4 * cc + 2], pw[4 * cc + 3]};
-    pf[cc] = __builtin_bit_cast(typename Vec<T>::x8, chunk);
+    if constexpr (PACK_LATE) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) pf[cc][t] = (T)pr[cc >> 1][8 * (cc & 1) + t];
+    } else {
+      const u32x4 chunk = {pw[4 * cc], pw[4 * cc + 1], pw[4 * cc + 2], pw[4 * cc + 3]};
+      pf[cc] = __builtin_bit_cast(typename Vec<T>::x8, chunk);
+    }
   }
 #pragma unroll
   for (int cc = 0; cc < 4; ++cc) lr_run = mfma16(ones, pf[cc], lr_run);

@@ -100,6 +100,7 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
                             // maximum of the scaled logits by at most log2(kLazySum)
   float l_run = 0.f;        // this lane's share of the exact running row sum (for the saved statistic)
   f32x4 lr_run = {0.f, 0.f, 0.f, 0.f};   // the sum of the rounded probabilities (normalises O), four times the same
+  int calm = kFirstTile;   // whether the next tile starts with its maximum: see softmax_tile_lane_query
   const T8 ones = row_sum_ones<T>();
 
   // key-padding mask: keys >= len are masked, rows >= len produce O = 0, LSE = -inf
@@ -178,9 +179,10 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+      constexpr bool PACK_LATE = D == 128 || (D == 64 && DROPOUT && !CAUSAL);
       // ---- masks, online softmax, dropout; P^T fragments (B operand) for the second product
       T8 pf[4];
-      softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT>(a, s, o, pf, m_run, l_run, lr_run, ones, c, k0, q0, qi, len, g, bh);
+      softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT, PACK_LATE>(a, s, o, pf, m_run, l_run, lr_run, calm, ones, c, k0, q0, qi, len, g, bh);
       // ---- O^T += V^T P^T
       {
         auto v_frag = [&](int f) {   // f = DB cc + db: consecutive MFMAs hit different accumulators

@@ -70,6 +70,7 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
   // lr_run: the sum of the rounded probabilities (normalises O), four times the same
   float m_run = -INFINITY, l_run = 0.f;
   f32x4 lr_run = {0.f, 0.f, 0.f, 0.f};
+  int calm = kFirstTile;   // whether the next tile starts with its maximum: see softmax_tile_lane_query
   const T8 ones = row_sum_ones<T>();
 
   // key-padding mask: keys >= len are masked, rows >= len produce O = 0, LSE = -inf
@@ -152,7 +153,7 @@ __device__ __forceinline__ void fwd_pp_rows(const KArgs& a, const int bh, const 
   };
 
   auto do_softmax = [&](int j) {
-    softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT>(a, s, o, pf, m_run, l_run, lr_run, ones, c, j * BC, q0, qi, len, g, bh);
+    softmax_tile_lane_query<T, DB, CAUSAL, DROPOUT, !CAUSAL>(a, s, o, pf, m_run, l_run, lr_run, calm, ones, c, j * BC, q0, qi, len, g, bh);
   };
 
   // ring slot of a tile in this group's ring
