@@ -210,7 +210,7 @@ def attn_bwd(Q, K, V, O, dO, LSE, *, softmax_scale, causal=False, dropout_p=0.0,
         load()
     dQ, dK, dV = (None, None, None) if grads is None else grads
     return _marshal.bwd(Q, K, V, O, dO, LSE, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream, key_lengths,
-                        workspace, dQ, dK, dV)
+                        workspace, grads is None, dQ, dK, dV)
 
 
 STATIC_SCRATCH_BYTES = 8 << 20
@@ -243,7 +243,7 @@ def attn_blocksparse_bwd(Q, K, V, O, dO, LSE, block_mask, *, softmax_scale, mask
         load()
     dQ, dK, dV = (None, None, None) if grads is None else grads
     return _marshal.blocksparse_bwd(Q, K, V, O, dO, LSE, softmax_scale, causal, dropout_p, seed, offset, o_fp32, stream,
-                                    key_lengths, workspace, dQ, dK, dV, block_mask, mask_block)
+                                    key_lengths, workspace, grads is None, dQ, dK, dV, block_mask, mask_block)
 
 
 def attn_bwd_timed(Q, K, V, O, dO, LSE, events, *, softmax_scale, block_mask=None, mask_block=128,

@@ -2,11 +2,11 @@
 // as a CPython extension: tensor checks, output allocation, parameter block and the library call in
 // one native call.  The same steps in Python and ctypes took 9 us of a forward call with its
 // buffers given, and 30 + 46 us of a training step through autograd, whose backward runs on the engine's own
-// thread with cold caches; a small problem's kernels take 5 to 10 us each.  Here
-// a forward call takes 3 us of host time; a training step of 96 heads of 197 tokens went from 157 to 69 us, one
-// forward call of one head from 9.2 to 4.8 us.
+// thread with cold caches; a small problem's kernels take 5 to 10 us each.  A pass with the one binding and with the other, over
+// the same library, in turn: one forward call of one head of 128 tokens 9.5 -> 4.6 us, a training step of 96 heads of 197 tokens
+// 149 -> 85 us (4 % between runs), of a padded batch of 128 heads of up to 700 tokens 147 -> 86 us (6 %).
 // The functions take positional arguments only (binding.py holds the public signatures and
-// defaults) and raise what the Python code raised: ValueError, TypeError, AttnError.
+// defaults) and raise what the Python marshalling of the measurement entry points raises: ValueError, TypeError, AttnError.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -16,6 +16,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
+#include <initializer_list>
 
 #include "../../include/attn.h"
 
@@ -54,9 +55,19 @@ const at::Tensor& tensor(PyObject* o) {
   if (!THPVariable_Check(o)) raise(PyExc_TypeError, "expected a torch.Tensor");
   return THPVariable_Unpack(o);
 }
-double number(PyObject* o) {
-  const double v = PyFloat_AsDouble(o);
-  if (v == -1.0 && PyErr_Occurred()) throw Raised();
+void* data(PyObject* o) {   // of a buffer the library checks for: None is its NULL
+  return o == Py_None ? nullptr : tensor(o).data_ptr();
+}
+PyObject* wrap(const at::Tensor& t) {
+  PyObject* o = THPVariable_Wrap(t);
+  if (o == nullptr) throw Raised();
+  return o;
+}
+double number(PyObject* o) {   // float(o)
+  PyObject* f = PyNumber_Float(o);
+  if (f == nullptr) throw Raised();
+  const double v = PyFloat_AS_DOUBLE(f);
+  Py_DECREF(f);
   return v;
 }
 bool truth(PyObject* o) {
@@ -85,13 +96,20 @@ struct Options {
 Options options(PyObject* const* a) { return {a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7]}; }
 constexpr Py_ssize_t kOptions = 8;
 
-attn_params make_params(const at::Tensor& q, const Options& o) {
+attn_params make_params(PyObject* q_object, const Options& o) {
+  const at::Tensor& q = tensor(q_object);
   if (q.dim() != 4 || q.stride(3) != 1) raise(PyExc_ValueError, "expected a [B,H,N,d] tensor with contiguous last axis");
   attn_params p = {};
   p.B = (int32_t)q.size(0); p.H = (int32_t)q.size(1); p.N = (int32_t)q.size(2); p.d = (int32_t)q.size(3);
   if (q.scalar_type() == at::kHalf) p.dtype = ATTN_FP16;
   else if (q.scalar_type() == at::kBFloat16) p.dtype = ATTN_BF16;
-  else raise(PyExc_TypeError, "Q/K/V must be float16 or bfloat16");
+  else {
+    PyObject* dtype = PyObject_GetAttrString(q_object, "dtype");
+    if (dtype == nullptr) throw Raised();
+    PyErr_Format(PyExc_TypeError, "Q/K/V must be float16 or bfloat16, got %S", dtype);
+    Py_DECREF(dtype);
+    throw Raised();
+  }
   p.stride_b = q.stride(0); p.stride_h = q.stride(1); p.stride_n = q.stride(2);
   p.softmax_scale = (float)number(o.softmax_scale);
   p.causal = truth(o.causal);
@@ -149,6 +167,14 @@ template <typename F> PyObject* guarded(F&& f) {
   END_HANDLE_TH_ERRORS
 }
 
+PyObject* tuple(std::initializer_list<PyObject*> items) {   // takes the references over
+  PyObject* t = PyTuple_New((Py_ssize_t)items.size());
+  if (t == nullptr) throw Raised();
+  Py_ssize_t i = 0;
+  for (PyObject* o : items) PyTuple_SET_ITEM(t, i++, o);
+  return t;
+}
+
 // fwd(Q, K, V, <options>, out, lse[, block_mask, mask_block]) -> (O, LSE)
 PyObject* forward(PyObject* const* a, Py_ssize_t n, bool sparse) {
   return guarded([&]() -> PyObject* {
@@ -156,7 +182,7 @@ PyObject* forward(PyObject* const* a, Py_ssize_t n, bool sparse) {
     const at::Tensor &q = tensor(a[0]), &k = tensor(a[1]), &v = tensor(a[2]);
     same_layout(q, k);
     same_layout(q, v);
-    const attn_params p = make_params(q, options(a + 3));
+    const attn_params p = make_params(a[0], options(a + 3));
     PyObject* const* r = a + 3 + kOptions;
     Mask m = {};
     if (sparse) m = mask_args(r[2], r[3], q.size(1));
@@ -168,29 +194,30 @@ PyObject* forward(PyObject* const* a, Py_ssize_t n, bool sparse) {
     check_status(without_gil([&] {
       return sparse ? lib.sparse_fwd(&p, m.ptr, m.block, m.stride_h, qp, kp, vp, op, lp) : lib.fwd(&p, qp, kp, vp, op, lp);
     }), sparse ? "attn_blocksparse_fwd" : "attn_fwd");
-    PyObject* t = PyTuple_New(2);
-    if (t == nullptr) throw Raised();
-    PyTuple_SET_ITEM(t, 0, r[0] != Py_None ? Py_NewRef(r[0]) : THPVariable_Wrap(out));
-    PyTuple_SET_ITEM(t, 1, r[1] != Py_None ? Py_NewRef(r[1]) : THPVariable_Wrap(lse));
-    return t;
+    return tuple({r[0] != Py_None ? Py_NewRef(r[0]) : wrap(out), r[1] != Py_None ? Py_NewRef(r[1]) : wrap(lse)});
   });
 }
 
-// bwd(Q, K, V, O, dO, LSE, <options>, workspace, dQ, dK, dV[, block_mask, mask_block]) -> (dQ, dK, dV);
-// dQ, dK and dV are all None or all given
+// bwd(Q, K, V, O, dO, LSE, <options>, workspace, allocate, dQ, dK, dV[, block_mask, mask_block]) -> (dQ, dK, dV);
+// allocate: dQ, dK and dV are made here, else they are the caller's
 PyObject* backward(PyObject* const* a, Py_ssize_t n, bool sparse) {
   return guarded([&]() -> PyObject* {
-    expect_args(n, 6 + kOptions + 4 + (sparse ? 2 : 0));
-    const at::Tensor &q = tensor(a[0]), &k = tensor(a[1]), &v = tensor(a[2]), &o = tensor(a[3]), &go = tensor(a[4]), &lse = tensor(a[5]);
+    expect_args(n, 6 + kOptions + 5 + (sparse ? 2 : 0));
+    const at::Tensor &q = tensor(a[0]), &k = tensor(a[1]), &v = tensor(a[2]), &go = tensor(a[4]);
     same_layout(q, k);
     same_layout(q, v);
     same_layout(q, go);
-    const attn_params p = make_params(q, options(a + 6));
+    const attn_params p = make_params(a[0], options(a + 6));
     PyObject* const* r = a + 6 + kOptions;
     Mask m = {};
-    if (sparse) m = mask_args(r[4], r[5], q.size(1));
+    if (sparse) m = mask_args(r[5], r[6], q.size(1));
+    const bool allocate = truth(r[1]);
     at::Tensor g[3];
-    for (int i = 0; i < 3; ++i) g[i] = r[1 + i] != Py_None ? tensor(r[1 + i]) : like(q, q.scalar_type());
+    void* gp[3];
+    for (int i = 0; i < 3; ++i) {
+      if (allocate) g[i] = like(q, q.scalar_type());
+      gp[i] = allocate ? g[i].data_ptr() : data(r[2 + i]);
+    }
     at::Tensor ws;
     if (r[0] != Py_None) {
       ws = tensor(r[0]);
@@ -199,17 +226,16 @@ PyObject* backward(PyObject* const* a, Py_ssize_t n, bool sparse) {
       ws = at::empty({(int64_t)std::max<size_t>(need, 256)}, q.options().dtype(at::kByte));
     }
     const size_t ws_bytes = (size_t)ws.numel() * ws.element_size();
-    const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr(), *op = o.data_ptr(), *gp = go.data_ptr();
-    const float* lp = (const float*)lse.data_ptr();
-    void *dq = g[0].data_ptr(), *dk = g[1].data_ptr(), *dv = g[2].data_ptr(), *wp = ws.data_ptr();
+    const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr(), *op = data(a[3]), *gop = go.data_ptr();
+    const float* lp = (const float*)data(a[5]);
+    void* wp = ws.data_ptr();
     check_status(without_gil([&] {
-      return sparse ? lib.sparse_bwd(&p, m.ptr, m.block, m.stride_h, qp, kp, vp, op, gp, lp, dq, dk, dv, wp, ws_bytes)
-                    : lib.bwd(&p, qp, kp, vp, op, gp, lp, dq, dk, dv, wp, ws_bytes);
+      return sparse ? lib.sparse_bwd(&p, m.ptr, m.block, m.stride_h, qp, kp, vp, op, gop, lp, gp[0], gp[1], gp[2], wp, ws_bytes)
+                    : lib.bwd(&p, qp, kp, vp, op, gop, lp, gp[0], gp[1], gp[2], wp, ws_bytes);
     }), sparse ? "attn_blocksparse_bwd" : "attn_bwd");
-    PyObject* t = PyTuple_New(3);
-    if (t == nullptr) throw Raised();
-    for (int i = 0; i < 3; ++i) PyTuple_SET_ITEM(t, i, r[1 + i] != Py_None ? Py_NewRef(r[1 + i]) : THPVariable_Wrap(g[i]));
-    return t;
+    PyObject* t[3];
+    for (int i = 0; i < 3; ++i) t[i] = allocate ? wrap(g[i]) : Py_NewRef(r[2 + i]);
+    return tuple({t[0], t[1], t[2]});
   });
 }
 
