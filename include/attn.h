@@ -214,7 +214,7 @@ int attn_bwd_timed(const attn_params* p, const uint8_t* block_mask, int32_t mask
                    void* const* events);
 
 /*
- * Test hook: writes the dropout keep mask the kernels use, keep[b][h][i][j] in
+ * Test hook: writes the dropout keep mask of the rule above, keep[b][h][i][j] in
  * {0, 1}, as a packed device uint8 [B,H,N,N] array (N*N bytes per head: only
  * for small problems).  Uses B, H, N, dropout_p, seed, offset, stream of p.
  */

@@ -268,7 +268,7 @@ def attn_bwd_timed(Q, K, V, O, dO, LSE, events, *, softmax_scale, block_mask=Non
 
 
 def attn_debug_dropout_mask(B, H, N, dropout_p, seed, offset, device="cuda") -> torch.Tensor:
-    """uint8 [B,H,N,N] keep mask as the kernels generate it (small problems only)."""
+    """uint8 [B,H,N,N] keep mask of the written rule, from the kernels' generator (small problems only)."""
     dummy = torch.empty((B, H, N, 64), dtype=torch.float16, device=device)
     p = make_params(dummy, 1.0, False, dropout_p, seed, offset)
     keep = torch.empty((B, H, N, N), dtype=torch.uint8, device=device)

@@ -164,17 +164,6 @@ __device__ __forceinline__ u32x4 philox_draw16(uint32_t g16, uint32_t i, uint32_
                                                uint32_t seed_lo, uint32_t seed_hi) {
   return philox4x32_10(g16, i, bh, offset_lo, seed_lo, seed_hi);
 }
-// The threshold test of the four 8-bit fields of a word, two at a time: field >= T iff
-// field + (256 - T) carries out of its eight bits, and in 16-bit lanes the carry of fields 0 / 2
-// (even) or 1 / 3 (odd) lands in bit 8 / bit 24, alone in its byte.  carry2 = (256 - T) * 0x00010001.
-struct Keep4 { uint32_t even, odd; };
-__device__ __forceinline__ uint32_t dropout_carry2(uint32_t thr8) { return (256u - thr8) * 0x00010001u; }
-__device__ __forceinline__ Keep4 keep4(uint32_t w, uint32_t carry2) {
-  Keep4 k;
-  k.even = (w & 0x00FF00FFu) + carry2;
-  k.odd = __builtin_amdgcn_perm(0u, w, 0x0C030C01u) + carry2;   // (w >> 8) & 0x00FF00FF in one instruction
-  return k;
-}
 __device__ __forceinline__ float keep_or_zero(float x, uint32_t mask) {
   return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & mask);
 }
@@ -209,20 +198,6 @@ __device__ __forceinline__ void drop_fragment8(T8& frag, uint32_t w_lo, uint32_t
   const u32x4 q = {p0, p1, p2, p3};
   frag = __builtin_bit_cast(T8, q);
 }
-// the sixteen keep bits of a call: bit f set iff key 16 g16 + f is kept
-__device__ __forceinline__ uint32_t keep_bits16(const u32x4& w, uint32_t carry2) {
-  uint32_t bits = 0;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const Keep4 k = keep4(w[t], carry2);
-    // the four flag bytes (0 or 1) of the word side by side: fields 0, 1, 2, 3
-    const uint32_t flags = __builtin_amdgcn_perm(k.odd, k.even, 0x07030501u);
-    const uint32_t nib = (flags | (flags >> 7) | (flags >> 14) | (flags >> 21)) & 0xFu;
-    bits |= nib << (4 * t);
-  }
-  return bits;
-}
-
 // value of the lane 32 positions away (wave64)
 __device__ __forceinline__ float xchg32(float x) {
   const uint32_t u = __builtin_bit_cast(uint32_t, x);

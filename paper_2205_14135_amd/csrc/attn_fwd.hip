@@ -265,7 +265,9 @@ int launch_fwd_td(const KArgs& a_in, bool causal, bool dropout, bool sparse, hip
   return (int)hipErrorInvalidValue;
 }
 
-// keep[bh][i][j] for the test hook: one thread per group of sixteen consecutive keys
+// keep[bh][i][j] for the test hook: one thread per group of sixteen consecutive keys, with the generator of the product kernels and
+// the test of dQ.  (The forward and the dK/dV kernels test packed fields in ways of their own; the tests read the masks
+// that those apply back from their outputs.)
 __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
   const int64_t ngrp = ((int64_t)a.N + 15) / 16;
   const int64_t total = (int64_t)a.B * a.H * a.N * ngrp;
@@ -275,8 +277,9 @@ __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
     const uint32_t i = (uint32_t)((idx / ngrp) % a.N);
     const uint32_t bh = (uint32_t)(idx / (ngrp * a.N));
     const u32x4 w = philox_draw16(g16, i, bh, a.offset_lo, a.seed_lo, a.seed_hi);
-    // (when dropout rounds down to nothing the kernels do not draw at all: everything is kept)
-    const uint32_t m = a.drop_thr == 0 ? 0xFFFFu : keep_bits16(w, dropout_carry2(a.drop_thr));
+    uint32_t m = 0;   // bit f: key 16 g16 + f is kept (with a threshold of 0, where the kernels do not draw at all, every one)
+#pragma unroll
+    for (int f = 0; f < 16; ++f) m |= dropped(w[f >> 2], f & 3, a.drop_thr) ? 0u : 1u << f;
     uint8_t* dst = keep + ((int64_t)bh * a.N + i) * a.N + 16 * (int64_t)g16;
     const int n = min(16, a.N - 16 * (int)g16);
     if (n == 16 && a.N % 4 == 0) {
