@@ -501,9 +501,10 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
   // d = 128, dense: the one-wavefront kernel with the V block in LDS (attn_bwd_dkv_fr128.hip)
   // (without dropout, with 64 keys per wavefront where a head has at least two blocks of 256 keys
   // and whole 32-query tiles: attn_bwd_dkv_w64.hip)
-  // (dropout under the causal mask keeps the role-split kernel: measured 15 % faster than the
-  // one-wavefront kernel at B H = 64, N = 1024 and equal at N = 4096; without a mask the
-  // one-wavefront kernel is 1-6 % faster with dropout as well)
+  // (dropout under the causal mask keeps the role-split kernel, which was 15 % faster than the one-wavefront kernel at
+  // B H = 64, N = 1024 and equal at N = 4096 while that one spilled.  It no longer does, and the line now loses except for few heads of
+  // long sequences; us, role-split | one wavefront: B H = 64, N = 256 29 | 19, 512 40 | 30, 1024 64 | 56, 2048 200 | 163, 4096 714 | 569;
+  // B H = 128, N = 1024 126 | 92; B H = 48, N = 1400 137 | 77; B H = 8, N = 2048 91 | 87, 4096 158 | 164, 8192 322 | 382)
   if (!sparse && d == 128 && !force_role_split() && !(dropout && causal && dkv_variant() == 0)) {
     // measured against the 32-key kernel: 1 % faster at N = 2048, 5 % at 4096, 7 % at 16384; slower below,
     // and slower under the causal mask at every length (its 256-key work items balance worse)

@@ -10,9 +10,9 @@
 //
 // Online softmax, two departures from the printed recurrence that leave the result the same up
 // to rounding.  (1) The reference m of a row is moved (and O, l rescaled) only when the sum of a
-// tile's probabilities in a lane exceeds kLazySum: any reference gives the same softmax in exact
-// arithmetic, and most tiles then skip both the rescaling of the whole O accumulator and the search
-// for the tile's maximum.  (2) O is divided
+// tile's probabilities in a lane exceeds kLazySum (or, on tiles that look for it, the maximum exceeds m by kLazyRise):
+// any reference gives the same softmax in exact arithmetic, and most tiles then skip both the rescaling of
+// the whole O accumulator and the search for the tile's maximum.  (2) O is divided
 // by the sum of the probabilities AS ROUNDED to 16 bits for the second product, not by l: O is
 // then a convex combination of V rows with exactly the weights that were used, which is what
 // keeps a lagging reference accurate (with the exact l a peaked row would see the rounding of its
@@ -20,8 +20,9 @@
 //
 // Register layout trick: the kernel computes S^T = K Q^T with 32x32x16 MFMA, so that a lane
 // holds 16 keys of ONE query (accumulator register i of key block kb is key
-// 32 kb + 8 (i/4) + 4 (lane/32) + i%4, query lane%32).  Row max / row sum are then in-lane
-// reductions plus one exchange with lane^32, the rescale factor is a per-lane scalar, and the
+// 32 kb + 8 (i/4) + 4 (lane/32) + i%4, query lane%32).  The exact row sum and, where it is looked
+// for, the row maximum are then in-lane reductions plus one exchange with lane^32, the sum of the rounded
+// probabilities is one small MFMA per fragment (row_sum_ones in attn_common.h), the rescale factor is a per-lane scalar, and the
 // probabilities are already in the B-operand layout of the second product O^T = V^T P^T.
 // V^T fragments come from the row-major V tile in LDS through the gfx950 transposing LDS read.
 #include "attn_common.h"
@@ -297,16 +298,21 @@ __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
 }  // namespace
 
 // Which dense d = 128 problems take the two-group kernel (attn_fwd_pp.hip): an estimate of either kernel's time,
-// in units of one 64-key tile of the two-group kernel (256 rows on a whole compute unit, 1.89 us without
+// in units of one 64-key tile of the two-group kernel (256 rows on a whole compute unit, 1.78 us without
 // dropout).  Per tile it is the faster one, but it has one workgroup per compute unit: its work items (pairs of row blocks
 // under the causal mask) run in whole rounds over the chip, and nothing covers an item's prologue and epilogue.
 // This file's kernel has two workgroups of 128 rows on a compute unit, dealt out as they finish (unpaired and
-// therefore less evenly under the causal mask).  The constants are fits to these times (us, two-group | this file's):
-//   causal     N = 512 78 | 76, 640 116 | 71, 768 110 | 78, 1024 97 | 105, 1400 150 | 124, 2048 150 | 170, 4096 265 | 299
-//   no mask    N = 512 91 | 79, 768 117 | 108, 1024 144 | 139, 1400 212 | 201, 2048 259 | 261, 4096 484 | 516
-//   causal with dropout  N = 512 84 | 85, 1024 110 | 127, 2048 175 | 208, 4096 310 | 362; 64 heads of 1024: 49 | 41
-// (16384 tokens, 16 heads).  Without a mask, dropout (plain vector ALU work) evens the two out: 572 | 599 at
-// N = 4096, 172 | 166 at 1024; this file's kernel keeps those.
+// therefore less evenly under the causal mask).  us, two-group | this file's (16384 tokens, 16 heads):
+//   causal     N = 512 76 | 74, 640 111 | 70, 768 111 | 81, 1024 97 | 107, 1400 138 | 116, 2048 151 | 174, 4096 268 | 309
+//   no mask    N = 512 89 | 83, 640 110 | 97, 768 115 | 111, 1024 142 | 143, 1400 205 | 184, 2048 253 | 267, 4096 485 | 517
+//   causal with dropout  N = 512 85 | 84, 1024 114 | 125, 2048 182 | 206, 4096 326 | 369; 64 heads of 1024: 51 | 40
+//   few heads  12 of 4096 102 | 118, 24 of 2001 55 | 62; causal with dropout, 8 of 8192 267 | 209
+// The estimate is the faster kernel in all of these but for less than 1 % (no mask, 1024; causal with dropout, 512).  It is
+// no better than that: for the two-group kernel it is within 4 % of the time from N = 1024 on where the rounds are full, 6-13 % short
+// with dropout, and up to 36 % long where the last round is part-filled or the odd block of a head stands alone, charged
+// as a pair (causal 640: 151; no mask 1400: 231); for this file's kernel within 10 %, but for 64 heads of 1024 (32).
+// Dropout without a mask is plain vector ALU work, which evens the two out in favour of this file's: N = 512
+// 112 | 94, 1024 180 | 165, 2048 322 | 313, 4096 626 | 610, 8192 1215 | 1203.
 static bool two_group_is_faster(const KArgs& a, bool causal, bool dropout) {
   if (dropout && !causal) return false;
   const double heads = (double)a.B * a.H;
@@ -320,8 +326,7 @@ static bool two_group_is_faster(const KArgs& a, bool causal, bool dropout) {
   const double groups = heads * blocks128;
   const double head_tiles = causal ? std::min(blocks128 * (blocks128 + 1), blocks128 * tiles) : blocks128 * tiles;
   // A compute unit that has only one workgroup of this file's kernel left (few workgroups, or the long ones under a
-  // causal mask, whose neighbours have ended) gets through a tile in 0.65 of the time: 8 heads of 8192 with dropout,
-  // 203 us here, 247 in the two-group kernel.
+  // causal mask, whose neighbours have ended) gets through a tile in 0.65 of the time.
   const bool alone = causal || groups <= kComputeUnits;
   const double longest = tiles * (alone ? 0.65 : 1.0) * tile_base + extra_base;
   const double base = std::max((heads * head_tiles * tile_base + groups * extra_base) / (2 * kComputeUnits), longest);
