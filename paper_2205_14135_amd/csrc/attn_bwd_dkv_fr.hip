@@ -107,7 +107,8 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
 
   const int lane = threadIdx.x & 63;
   // The wavefront number in a scalar register, so that addresses and branches on it are scalar: 1-4 % faster at
-  // d = 64; causal with dropout, and d = 32 on short sequences, measured 2 % slower that way.
+  // d = 64 (B H = 128, N = 2048 266 -> 260 us, block-sparse N = 16384 122 -> 117); causal with dropout (GPT-2 shape 64.2 -> 65.9)
+  // and d = 32 (B H = 128, N = 700 36.4 -> 37.3) lose 2.5 % that way.
   constexpr bool SCALAR_WAVE = D == 64 && !(CAUSAL && DROPOUT);
   const int wave = SCALAR_WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)threadIdx.x >> 6;
   const int r = lane & 31, g = lane >> 5;
