@@ -252,6 +252,8 @@ int attn_debug_kernel_choice(const attn_params* p, int32_t sparse, int32_t* fwd_
  * forward kernel (where both exist).  dkv_variant: 0 = by measurement, 1 = role-split dK/dV kernel
  * wherever it exists, 2 = one-wavefront dK/dV kernels with 32 keys per wavefront only, 3 = the
  * 64-keys-per-wavefront dK/dV kernel wherever it exists (d = 128, no dropout, N >= 512, N % 32 == 0).
+ * While dkv_variant is not 0, no kernel divides the sweep of a work item over groups of wavefronts (which
+ * they do where there are few work items).
  * -1 leaves a setting unchanged.  Process-wide and thread-safe; affects calls issued afterwards.
  */
 int attn_debug_set_variant(int32_t fwd_variant, int32_t dkv_variant);

@@ -23,7 +23,6 @@
 namespace attn {
 namespace {
 
-constexpr int NT = 256;
 constexpr int TILE = 64;  // keys of the streamed tile
 
 // ---------------------------------------------------------------------------------------------
@@ -35,8 +34,10 @@ constexpr int TILE = 64;  // keys of the streamed tile
 // three by themselves at d = 32; at d = 64 three cost more in spills or half tiles (B H = 128, N = 2048 210 -> 211, N = 128 54 -> 62).
 constexpr bool three_waves(int d, bool causal, bool dropout) { return d == 32 && !causal && !dropout; }
 
-template <typename T, int D, bool CAUSAL, bool DROPOUT, bool SPARSE>
-__global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void dq_kernel(const KArgs a) {
+// RW wavefronts of 32 query rows, times KG groups of them that each take every KG-th tile (as in the forward kernel): the groups'
+// dQ are summed through LDS at the end.
+template <typename T, int D, bool CAUSAL, bool DROPOUT, bool SPARSE, int RW, int KG>
+__global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void dq_kernel(const KArgs a) {
   typedef typename Vec<T>::x8 T8;
   constexpr int KK = D / 16, DB = D / 32;
   // K and V tiles, double buffered, filled by async copies.  Without the causal mask they form one
@@ -44,22 +45,27 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
   // is a per-lane register plus an immediate offset once the buffer index is a compile-time
   // constant (see tile_step below); the causal kernels, which cannot afford that unrolling, keep
   // two arrays (the form that the register allocator handles without spilling).
+  constexpr int BR = 32 * RW;
   T* Ks0;
   T* Vs0;
-  if constexpr (!CAUSAL) {
-    __shared__ __attribute__((aligned(16))) T smem[4 * TILE * D];
-    Ks0 = smem;
-    Vs0 = smem + 2 * TILE * D;
+  T* all;   // the LDS of all groups, one block (KG > 1)
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / RW;
+  if constexpr (!CAUSAL || KG > 1) {
+    __shared__ __attribute__((aligned(16))) T smem[KG * 4 * TILE * D];
+    all = smem;
+    Ks0 = smem + group * 4 * TILE * D;
+    Vs0 = Ks0 + 2 * TILE * D;
   } else {
     __shared__ __attribute__((aligned(16))) T Ks[2 * TILE * D];
     __shared__ __attribute__((aligned(16))) T Vs[2 * TILE * D];
     Ks0 = Ks;
     Vs0 = Vs;
+    all = Ks;
   }
 
   const int item = xcd_item(a.n_items, a.chunk);
   if (item < 0) return;
-  const int n_qt = a.T;   // ceil(N / 128): the last block may be ragged
+  const int n_qt = a.T * (4 / RW);   // blocks of BR rows, to the end of the last 128-row block: the scratch vectors are written whole
   // Work item = (head, row block).  Under the causal mask row block q sweeps 2 (q + 1) key tiles;
   // for dense d = 64 problems an item is the pair (n_qt - 1 - q, q), one per pass, so that every
   // workgroup does the same amount of work (at d = 128 the loop costs registers the kernel does
@@ -91,9 +97,9 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
   const T* __restrict__ Vg = (const T*)a.V + head_off;
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register: addresses and branches on it are scalar
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - RW * group;   // in a scalar register: addresses and branches on it are scalar
   const int r = lane & 31, g = lane >> 5;
-  const int q0 = qt * 128 + wave * 32;
+  const int q0 = qt * BR + wave * 32;
   // lanes beyond a ragged end work on a copy of the last row with P = 0 and store nothing
   const bool row_ok = q0 + r < a.N;
   const int qi = min(q0 + r, a.N - 1);
@@ -128,9 +134,9 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
   const float l2 = (lse == -INFINITY || !row_ok) ? INFINITY : lse * 1.4426950408889634f;
   const float neg_d = row_ok ? -(d_part + xchg32(d_part)) : 0.f;   // -D_i
   // The dK/dV kernel reads both per 64-row tile from the scratch vectors (padded to whole blocks
-  // of 128 rows per head: this workgroup writes all 128 of its block).  The tile kernels start
+  // of 128 rows per head: this workgroup writes all of its block).  The tile kernels start
   // their dP accumulators from -D, so that dP - D needs no instruction of its own.
-  if (g == 0) {
+  if (g == 0 && (KG == 1 || group == 0)) {
     a.Dvec[(int64_t)bh * a.Nr + q0 + r] = neg_d;
     a.L2vec[(int64_t)bh * a.Nr + q0 + r] = l2;
   }
@@ -150,23 +156,30 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
   TileIter<SPARSE> it;
   {
     int lim;
-    if constexpr (SPARSE) lim = min(CAUSAL ? qt + 1 : a.T, (len + 127) / 128);
-    else lim = CAUSAL ? min(2 * qt + 2, (len + TILE - 1) / TILE) : (len + TILE - 1) / TILE;   // len <= N
-    if (qt * 128 >= len) lim = 0;
-    it.init(SPARSE ? a.mask + (int64_t)h * a.mask_sh + (int64_t)qt * a.T : nullptr, 1, 0, lim);
+    const int mask_row = qt * BR / 128;
+    if constexpr (SPARSE) lim = min(CAUSAL ? mask_row + 1 : a.T, (len + 127) / 128);
+    else lim = CAUSAL ? min((qt + 1) * BR / TILE, (len + TILE - 1) / TILE) : (len + TILE - 1) / TILE;   // len <= N
+    if (qt * BR >= len) lim = 0;
+    it.init(SPARSE ? a.mask + (int64_t)h * a.mask_sh + (int64_t)mask_row * a.T : nullptr, 1, 0, lim);
   }
   TrOffsets<D> tro;
   tro.init();
-  TileAsync<T, D, NT / 64> dma;
+  TileAsync<T, D, RW> dma;
   dma.init(a.sn, wave, D == 32 ? a.dvalid : D);
   if (D == 32 && a.dvalid < D) {   // the copies leave columns >= 16 of the tile buffers untouched
-    zero_tiles(Ks0, 2 * TILE * D);
-    zero_tiles(Vs0, 2 * TILE * D);
+    if constexpr (KG > 1) {
+      zero_tiles(all, KG * 4 * TILE * D);
+    } else {
+      zero_tiles(Ks0, 2 * TILE * D);
+      zero_tiles(Vs0, 2 * TILE * D);
+    }
     __syncthreads();
   }
 
   const float c = a.scale_log2;
-  int jt = it.next();
+  // jt: this group's tile, -1 if there is none; more: some group (then the first) has one
+  int jt;
+  bool more = it.template next_of<KG>(group, jt);
   if (jt >= 0) {
     dma.copy_rows(Kg, a.sn, jt * TILE, a.N, Ks0);
     dma.copy_rows(Vg, a.sn, jt * TILE, a.N, Vs0);
@@ -177,11 +190,12 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
   // constant in each copy of its body; the causal kernels have no registers for two copies.
   constexpr int UNROLL = CAUSAL ? 1 : 2;
   int buf_rt = 0;
-  while (jt >= 0) {
+  while (KG == 1 ? jt >= 0 : more) {
 #pragma unroll
   for (int u = 0; u < UNROLL; ++u) {
     const int buf = UNROLL == 2 ? u : buf_rt;
-    const int jn = it.next();
+    int jn;
+    const bool more_next = it.template next_of<KG>(group, jn);
     if (jn >= 0) {   // next tile streams into the other buffer while this one is used
       dma.copy_rows(Kg, a.sn, jn * TILE, a.N, Ks0 + (buf ^ 1) * TILE * D);
       dma.copy_rows(Vg, a.sn, jn * TILE, a.N, Vs0 + (buf ^ 1) * TILE * D);
@@ -190,7 +204,7 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
     const T* Vt = Vs0 + buf * TILE * D;
 
     const int k0 = jt * TILE;
-    if (!CAUSAL || k0 <= q0 + 31) {
+    if ((KG == 1 || jt >= 0) && (!CAUSAL || k0 <= q0 + 31)) {
       f32x16 s[2], dp[2];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -278,9 +292,40 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
     wait_async_copies();
     __syncthreads();   // next tile has landed, and everyone is done with this buffer
     jt = jn;
+    more = more_next;
     buf_rt ^= 1;
-    if (jt < 0) break;
+    if (KG == 1 ? jt < 0 : !more) break;
   }
+  }
+  if constexpr (KG > 1) {
+    // the loop ended on a barrier (or never touched LDS): the groups but the first leave their dQ in the tile buffers
+    constexpr int kLanes = 64 * RW;
+    static_assert((KG - 1) * DB * 16 * kLanes * 4 <= KG * 4 * TILE * D * (int)sizeof(T), "LDS holds the groups' dQ");
+    f32x4* const part = (f32x4*)all + wave * 64 + lane;
+    if (group > 0) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 v = {dq[db][4 * i4], dq[db][4 * i4 + 1], dq[db][4 * i4 + 2], dq[db][4 * i4 + 3]};
+          part[((group - 1) * 4 * DB + 4 * db + i4) * kLanes] = v;
+        }
+    }
+    __syncthreads();
+    if (group == 0) {
+#pragma unroll
+      for (int k = 0; k < KG - 1; ++k)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) {
+            const f32x4 v = part[(k * 4 * DB + 4 * db + i4) * kLanes];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dq[db][4 * i4 + e] += v[e];
+          }
+    }
+    __syncthreads();   // the buffers stage the output rows
+    if (group > 0) continue;
   }
   // the loop ends on a barrier (or never touched LDS): the tile buffers stage the output rows
   T* stage = (wave < 2 ? Ks0 + wave * 32 * D : Vs0 + (wave - 2) * 32 * D);
@@ -289,47 +334,82 @@ __global__ __launch_bounds__(NT, three_waves(D, CAUSAL, DROPOUT) ? 3 : 2) void d
   }  // for pass
 }
 
+template <typename T, int D, int RW, int KG>
+int launch_dq(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
+  const int blocks = a.T * (4 / RW);
+  a.n_items = a.B * a.H * (causal && !sparse && D == 64 ? (blocks + 1) / 2 : blocks);   // (pairs of row blocks)
+  a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  {
+    const int64_t kv_bytes = 2 * (int64_t)a.N * D * (int64_t)sizeof(T);
+    const int64_t fit = ((int64_t)8 << 20) / kv_bytes;
+    a.group = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
+  }
+  const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
+#define ATTN_DQ_CASE(C, P, S)                                                          \
+  if (causal == C && dropout == P && sparse == S) {                                    \
+    hipLaunchKernelGGL((dq_kernel<T, D, C, P, S, RW, KG>), grid, block, 0, s, a);      \
+    return (int)hipGetLastError();                                                     \
+  }
+  ATTN_DQ_CASE(false, false, false)
+  ATTN_DQ_CASE(true, false, false)
+  ATTN_DQ_CASE(false, true, false)
+  ATTN_DQ_CASE(true, true, false)
+  ATTN_DQ_CASE(false, false, true)
+  ATTN_DQ_CASE(true, false, true)
+  ATTN_DQ_CASE(false, true, true)
+  ATTN_DQ_CASE(true, true, true)
+#undef ATTN_DQ_CASE
+  return (int)hipErrorInvalidValue;
+}
+
 template <typename T> constexpr int kDtype = 0;
 template <> constexpr int kDtype<__bf16> = 1;
+
+// us of the backward pass with {4, 1}, and the difference with {4, 2} | {2, 2} | {2, 4} (wavefronts of rows, groups) in this kernel
+// alone; heads x N:
+//   d = 64   1 x 128 12.3 +1.2 -0.3 +1.3; 16 x 197 17.7 +0.6 -1.3 +0.1; 4 x 512 25.0 -0.3 -2.8 -1.9; 16 x 1024 41.0 -2.0 -5.2 -5.1; 8 x 2048 72.2 -5.3 -10.2 -11.6;
+//            1 x 8192 263 -28 -48 -61; 60 x 512 26.5 -0.1 +0.5 +6.2; 24 x 1024 42.0 -2.0 -1.2 +4.5; 8 x 4096 140 -8.7 -5.5 -0.8;
+//            10 x 4096 186 +10.1 -1.3 +2.6, dropout 271 +9.5 -15.9 -7.3; 24 x 2001 110 +6.1 -2.1 +4.9; 40 x 1024 57.1 +5.8 +0.9 +8.1; 32 x 2048 116 +3.6 +4.8 +16.8
+//   d = 64 causal (pairs of row blocks)  1 x 128 13.1 +1.0 +2.8 +6.2; 16 x 197 26.9 +1.0 -1.9 +1.2; 16 x 1024 51.6 -0.6 -5.9 -4.4;
+//            8 x 4096 146 -8.2 -20.5 -24.4; 40 x 1024 53.2 -0.5 -1.3 +11.4; 10 x 4096 148 -8.8 -8.8 +5.8; 32 x 2048 85.8 -2.6 -2.3 +9.6; 128 x 512 39.5 +0.8 -0.4 +12.2
+//   d = 32   1 x 128 10.0 -0.4 -0.4 +0.1; 16 x 640 22.6 -1.0 -2.6 -2.6; 8 x 2048 56.2 -3.8 -8.0 -10.0; 60 x 512 20.1 -0.7 -0.7 +2.1; 8 x 4096 107 -8.3 -8.1 -4.9;
+//            10 x 4096 138 +8.1 -12.7 -2.7; 24 x 2001 81.7 +5.3 -5.1 +1.9; 64 x 1024 43.1 +3.1 +0.9 +8.8
+//   d = 128  1 x 128 17.4 +2.5 +0.2; 16 x 640 42.5 +0.9 -2.4; 8 x 2048 130 -3.5 -9.1; 1 x 8192 474 -26 -45; 60 x 512 41.5 +2.5 +9.7;
+//            16 x 2048 136 -1.5 +18.3; 8 x 4096 253 -5.1 +28.4, causal 213 -6.0 +23.5, dropout 272 -8.3 +30.0; 40 x 1024 93.6 +10.1 +18.4
+//   block-sparse (butterfly mask of T x T blocks, heads x T)  d = 64  4 x 8 48.2 -1.5 -4.2 -4.0; 4 x 32 65.7 -1.8 -4.4 -4.4; 4 x 64 76.0 -2.0 -1.4 +7.0;
+//            8 x 64 112 +5.8 +6.2 +24.1; d = 128  4 x 32 89.9 -0.3 -4.4; 4 x 64 132 +0.3 +17.4
+WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse) {
+  if (!may_divide()) return {4, 1};
+  const bool pairs = causal && !sparse && d == 64;
+  const WorkItems w(a, sparse, pairs);
+  if (w.of64 <= kComputeUnits && w.tiles >= 4) return d <= 64 && w.tiles >= (d == 64 ? 24 : 12) && !sparse ? WaveGroups{2, 4} : WaveGroups{2, 2};
+  if (d == 32) return w.of64 <= 3 * kComputeUnits && w.tiles >= 4 ? WaveGroups{2, 2} : WaveGroups{4, 1};   // (three workgroups fit)
+  if (w.of128 <= kComputeUnits && w.tiles >= (d == 64 ? 16 : 24)) return {4, 2};
+  if (d == 64 && !pairs && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
+  return {4, 1};
+}
+
+template <typename T, int D>
+int launch_dq_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStream_t s) {
+  const WaveGroups w = dq_groups(a, D, causal, sparse);
+  if constexpr (D <= 64)
+    if (w.waves == 2 && w.groups == 4) return launch_dq<T, D, 2, 4>(a, causal, dropout, sparse, s);
+  if (w.waves == 2) return launch_dq<T, D, 2, 2>(a, causal, dropout, sparse, s);
+  if constexpr (D >= 64)
+    if (w.groups == 2) return launch_dq<T, D, 4, 2>(a, causal, dropout, sparse, s);
+  return launch_dq<T, D, 4, 1>(a, causal, dropout, sparse, s);
+}
 
 template <typename T, int D>
 int launch_bwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStream_t s, hipEvent_t* ev) {
   if (ev) (void)hipEventRecord(ev[0], s);
-  int e = 0;
   if (ev) (void)hipEventRecord(ev[1], s);   // (there is no separate preparation launch any more)
-  const dim3 block(NT);
-  // dense causal d = 64 dQ items are pairs of row blocks
-  KArgs aq = a;
-  if (causal && !sparse && D == 64) {
-    aq.n_items = a.B * a.H * ((a.T + 1) / 2);
-    aq.chunk = (aq.n_items + kXcds - 1) / kXcds;
-  }
-  {
-    const int64_t kv_bytes = 2 * (int64_t)a.N * D * (int64_t)sizeof(T);
-    const int64_t fit = ((int64_t)8 << 20) / kv_bytes;
-    aq.group = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
-  }
-  const dim3 grid_q(kXcds * aq.chunk);
-#define ATTN_BWD_CASE(C, P, S)                                                   \
-  if (causal == C && dropout == P && sparse == S) {                              \
-    hipLaunchKernelGGL((dq_kernel<T, D, C, P, S>), grid_q, block, 0, s, aq);     \
-    e = (int)hipGetLastError();                                                  \
-    if (e != 0) return e;                                                        \
-    if (ev) (void)hipEventRecord(ev[2], s);                                      \
-    e = launch_dkv_rs(a, kDtype<T>, D, C, P, S, s);                              \
-    if (ev) (void)hipEventRecord(ev[3], s);                                      \
-    return e;                                                                    \
-  }
-  ATTN_BWD_CASE(false, false, false)
-  ATTN_BWD_CASE(true, false, false)
-  ATTN_BWD_CASE(false, true, false)
-  ATTN_BWD_CASE(true, true, false)
-  ATTN_BWD_CASE(false, false, true)
-  ATTN_BWD_CASE(true, false, true)
-  ATTN_BWD_CASE(false, true, true)
-  ATTN_BWD_CASE(true, true, true)
-#undef ATTN_BWD_CASE
-  return (int)hipErrorInvalidValue;
+  int e = launch_dq_td<T, D>(a, causal, dropout, sparse, s);
+  if (e != 0) return e;
+  if (ev) (void)hipEventRecord(ev[2], s);
+  e = launch_dkv_rs(a, kDtype<T>, D, causal, dropout, sparse, s);
+  if (ev) (void)hipEventRecord(ev[3], s);
+  return e;
 }
 
 }  // namespace

@@ -501,14 +501,18 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
   // d = 128, dense: the one-wavefront kernel with the V block in LDS (attn_bwd_dkv_fr128.hip)
   // (without dropout, with 64 keys per wavefront where a head has at least two blocks of 256 keys
   // and whole 32-query tiles: attn_bwd_dkv_w64.hip)
-  // (dropout under the causal mask keeps the role-split kernel, which was 15 % faster than the one-wavefront kernel at
-  // B H = 64, N = 1024 and equal at N = 4096 while that one spilled.  It no longer does, and the line now loses except for few heads of
-  // long sequences; us, role-split | one wavefront: B H = 64, N = 256 29 | 19, 512 40 | 30, 1024 64 | 56, 2048 200 | 163, 4096 714 | 569;
-  // B H = 128, N = 1024 126 | 92; B H = 48, N = 1400 137 | 77; B H = 8, N = 2048 91 | 87, 4096 158 | 164, 8192 322 | 382)
-  if (!sparse && d == 128 && !force_role_split() && !(dropout && causal && dkv_variant() == 0)) {
+  // (dropout under the causal mask: the role-split kernel pairs a long and a short key block in one workgroup of eight wavefronts and
+  // is ahead where those make one full round over the compute units.  us, role-split | one wavefront: B H = 10, N = 4096 289 | 311,
+  // B H = 32, N = 2048 185 | 193, B H = 8, N = 8192 322 | 382, 40 heads of 1024 99 | 96, 64 102 | 95, 128 of 512 77 | 71.  With fewer blocks the one-wavefront kernel
+  // splits their sweep (B H = 8, N = 4096 265 | 236; B H = 16, N = 1024 86 | 63), with more its workgroups even out by themselves: B H = 64, N = 2048
+  // 200 | 163, 4096 714 | 569; B H = 128, N = 1024 126 | 92; B H = 48, N = 1400 137 | 77)
+  const int64_t blocks = (int64_t)a.B * a.H * a.T;
+  const bool one_round_of_pairs = blocks > kComputeUnits && blocks <= 2 * kComputeUnits && a.N >= 1024;
+  if (!sparse && d == 128 && !force_role_split() && !(dropout && causal && dkv_variant() == 0 && one_round_of_pairs)) {
     // measured against the 32-key kernel: 1 % faster at N = 2048, 5 % at 4096, 7 % at 16384; slower below,
-    // and slower under the causal mask at every length (its 256-key work items balance worse)
-    const bool w64 = dkv_variant() == 3 || (dkv_variant() == 0 && !causal && a.N >= 2048);
+    // slower under the causal mask at every length (its 256-key work items balance worse), and with no more key blocks than compute
+    // units, where the 32-key kernel can split a block's sweep: B H = 8, N = 2048 130 | 86 us of the backward pass, B H = 8, N = 4096 253 | 205
+    const bool w64 = dkv_variant() == 3 || (dkv_variant() == 0 && !causal && a.N >= 2048 && blocks > kComputeUnits);
     return w64 && !dropout && a.N >= 512 && a.N % 32 == 0 ? kDkvOneWave64 : kDkvOneWave128;
   }
   return kDkvRoleSplit;

@@ -19,11 +19,12 @@
 namespace attn {
 namespace {
 
-constexpr int NT = 256;
 constexpr int TILE = 64;
 
-template <typename T, int D, bool CAUSAL, bool DROPOUT, bool SPARSE>
-__global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
+// RW wavefronts of 32 keys, times KG groups of them that each take every KG-th query tile, into buffers of their own; the groups'
+// gradients are summed through LDS at the end.  (Block-sparse work is assigned by columns of 128 keys: RW = 4.)
+template <typename T, int D, bool CAUSAL, bool DROPOUT, bool SPARSE, int RW, int KG>
+__global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) {
   typedef typename Vec<T>::x8 T8;
   constexpr int KK = D / 16, DB = D / 32;
   static_assert(D <= 64, "the accumulators of both gradients must fit one wavefront");
@@ -34,13 +35,18 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
   // immediate.  The other forms have no registers for two copies of the loop body and keep the
   // separate arrays (the form their register allocation is tuned to).
   constexpr int UNROLL = (!CAUSAL && !DROPOUT && !SPARSE) ? 2 : 1;
+  static_assert(!SPARSE || RW == 4, "mask columns are 128 keys wide");
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / RW;
+  constexpr int kGroupBytes = 4 * TILE * sizeof(float) + 4 * TILE * D * sizeof(T);
   T *Qs0, *Gs0;
   float *Ls0, *Ds0;
-  if constexpr (UNROLL == 2) {
-    __shared__ __attribute__((aligned(16))) unsigned char smem[4 * TILE * sizeof(float) + 4 * TILE * D * sizeof(T)];
-    Ls0 = (float*)smem;
+  unsigned char* all = nullptr;   // the LDS of all groups (KG > 1)
+  if constexpr (UNROLL == 2 || KG > 1) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[KG * kGroupBytes];
+    all = smem;
+    Ls0 = (float*)(smem + group * kGroupBytes);
     Ds0 = Ls0 + 2 * TILE;
-    Qs0 = (T*)(smem + 4 * TILE * sizeof(float));
+    Qs0 = (T*)(Ls0 + 4 * TILE);
     Gs0 = Qs0 + 2 * TILE * D;
   } else {
     __shared__ __attribute__((aligned(16))) T Qs[2 * TILE * D];
@@ -54,7 +60,8 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
   KeepLK keep;
   if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
 
-  const int n_kt = a.T;   // ceil(N / 128): the last key block may be ragged
+  constexpr int BR = 32 * RW;
+  const int n_kt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last key block may be ragged
   // Work assignment.  Dense: one key block per workgroup; under the causal mask key block k is
   // visited by N/64 - 2k query tiles, so a workgroup takes the pair (k, n_kt - 1 - k), one per
   // round.  Block-sparse (as in attn_bwd_dkv.hip): the first 8 * chunk workgroups take one mask
@@ -109,10 +116,10 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
   // The wavefront number in a scalar register, so that addresses and branches on it are scalar: 1-4 % faster at
   // d = 64 (B H = 128, N = 2048 266 -> 260 us, block-sparse N = 16384 122 -> 117); causal with dropout (GPT-2 shape 64.2 -> 65.9)
   // and d = 32 (B H = 128, N = 700 36.4 -> 37.3) lose 2.5 % that way.
-  constexpr bool SCALAR_WAVE = D == 64 && !(CAUSAL && DROPOUT);
-  const int wave = SCALAR_WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)threadIdx.x >> 6;
+  constexpr bool SCALAR_WAVE = KG > 1 || (D == 64 && !(CAUSAL && DROPOUT));
+  const int wave = SCALAR_WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - RW * group : (int)threadIdx.x >> 6;
   const int r = lane & 31, g = lane >> 5;
-  const int kw0 = kt * 128 + wave * 32;
+  const int kw0 = kt * BR + wave * 32;
   const int kj = kw0 + r;  // this lane's key (>= N beyond a ragged end: masked like a padded key, never stored)
 
   // loop-invariant B operands: the K and V fragments of this lane's key
@@ -147,22 +154,27 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
     it.init(a.mask + (int64_t)h * a.mask_sh + kt, a.T, CAUSAL ? kt : 0,
             kt * 128 >= len ? 0 : min(a.T, (len + 127) / 128), skip_blocks, take_blocks);
   else
-    it.init(nullptr, 0, CAUSAL ? 2 * kt : 0, kt * 128 >= len ? 0 : (len + TILE - 1) / TILE);   // len <= N
+    it.init(nullptr, 0, CAUSAL ? kt * BR / TILE : 0, kt * BR >= len ? 0 : (len + TILE - 1) / TILE);   // len <= N
 
   TrOffsets<D> tro;
   tro.init();
-  TileAsync<T, D, 4> dma;
+  TileAsync<T, D, RW> dma;
   dma.init(a.sn, wave, D == 32 ? a.dvalid : D);
   if (D == 32 && a.dvalid < D) {   // the copies leave columns >= 16 of the tile buffers untouched
-    zero_tiles(Qs0, 2 * TILE * D);   // (again in every round: the buffers staged output rows)
-    zero_tiles(Gs0, 2 * TILE * D);
+    // (again in every round: the buffers staged output rows)
+    if constexpr (KG > 1) {
+      zero_tiles((T*)all, KG * kGroupBytes / (int)sizeof(T));
+    } else {
+      zero_tiles(Qs0, 2 * TILE * D);
+      zero_tiles(Gs0, 2 * TILE * D);
+    }
     __syncthreads();
   }
   auto fetch_tile = [&](int t, int buf) {
     dma.copy_rows(Qg, a.sn, t * TILE, a.N, Qs0 + buf * TILE * D);
     dma.copy_rows(Gg, a.sn, t * TILE, a.N, Gs0 + buf * TILE * D);
-    if (wave == 1) async_copy_b32(Lg + t * TILE + lane, __builtin_amdgcn_readfirstlane(lds_addr(Ls0 + buf * TILE)));
-    if (wave == 2) async_copy_b32(Dg + t * TILE + lane, __builtin_amdgcn_readfirstlane(lds_addr(Ds0 + buf * TILE)));
+    if (wave == RW / 2 - 1) async_copy_b32(Lg + t * TILE + lane, __builtin_amdgcn_readfirstlane(lds_addr(Ls0 + buf * TILE)));
+    if (wave == RW / 2) async_copy_b32(Dg + t * TILE + lane, __builtin_amdgcn_readfirstlane(lds_addr(Ds0 + buf * TILE)));
   };
   const float c = a.scale_log2;
 
@@ -221,18 +233,21 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
   };
   // ---- pipeline over the query tiles of this key block: tile t + 1 streams in while t is used
   int buf_rt = 0;
-  int t = it.next();
+  // t: this group's tile, -1 if there is none; more: some group (then the first) has one
+  int t;
+  bool more = it.template next_of<KG>(group, t);
   if (t >= 0) fetch_tile(t, 0);
   wait_async_copies();
   __syncthreads();
-  while (t >= 0) {
+  while (KG == 1 ? t >= 0 : more) {
 #pragma unroll
   for (int u = 0; u < UNROLL; ++u) {
     const int buf = UNROLL == 2 ? u : buf_rt;
-    const int t_next = it.next();
+    int t_next;
+    const bool more_next = it.template next_of<KG>(group, t_next);
     if (t_next >= 0) fetch_tile(t_next, buf ^ 1);
     const int i0 = t * TILE;
-    if (!CAUSAL || i0 + TILE - 1 >= kw0) {
+    if ((KG == 1 || t >= 0) && (!CAUSAL || i0 + TILE - 1 >= kw0)) {
       f32x16 s[2], dp[2];
       row_product(Qs0 + buf * TILE * D, kf, false, nullptr, s);                // S = Q K^T
       uint32_t kept = 0;   // the keep flags of this lane's key for the tile's 64 queries it holds
@@ -300,11 +315,42 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
     __syncthreads();   // the next tile has landed, and everyone is done with this buffer
     buf_rt ^= 1;
     t = t_next;
-    if (t < 0) break;
+    more = more_next;
+    if (KG == 1 ? t < 0 : !more) break;
   }
   }
 
-  if (SPARSE && heavy) {
+  if constexpr (KG > 1) {
+    // the loop ended on a barrier (or never touched LDS): the groups but the first leave their gradients in the tile buffers
+    constexpr int kLanes = 64 * RW;
+    static_assert((KG - 1) * 2 * DB * 16 * kLanes * 4 <= KG * kGroupBytes, "LDS holds the groups' gradients");
+    f32x4* const part = (f32x4*)all + wave * 64 + lane;
+    if (group > 0) {
+#pragma unroll
+      for (int f = 0; f < 8 * DB; ++f) {   // dV^T, then dK^T
+        const f32x16& x = f < 4 * DB ? dv[f / 4 % DB] : dk[f / 4 % DB];
+        const int i = 4 * (f % 4);
+        const f32x4 v = {x[i], x[i + 1], x[i + 2], x[i + 3]};
+        part[((group - 1) * 8 * DB + f) * kLanes] = v;
+      }
+    }
+    __syncthreads();
+    if (group == 0) {
+#pragma unroll
+      for (int k = 0; k < KG - 1; ++k)
+#pragma unroll
+        for (int f = 0; f < 8 * DB; ++f) {
+          f32x16& x = f < 4 * DB ? dv[f / 4 % DB] : dk[f / 4 % DB];
+          const f32x4 v = part[(k * 8 * DB + f) * kLanes];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[4 * (f % 4) + e] += v[e];
+        }
+    }
+    __syncthreads();   // the buffers stage the output rows
+  }
+  if (KG > 1 && group > 0) {
+    // (merged)
+  } else if (SPARSE && heavy) {
     // one of several segments of this column: sum in fp32; sparse_finish_kernel converts.  The loop
     // ended on a barrier: the two Q buffers stage the rows of wavefronts 0 and 1, the two dO buffers
     // those of wavefronts 2 and 3 (32 x D floats each), first for dV, then for dK
@@ -326,18 +372,18 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr_kernel(const KArgs a) {
   }  // for round
 }
 
-template <typename T, int D>
-int launch_td(KArgs a, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
-  if (causal && !sparse) {   // items are pairs of key blocks
-    a.n_items = a.B * a.H * ((a.T + 1) / 2);
-    a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  }
-  const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(NT);
-#define ATTN_DKV_FR_CASE(C, P, S)                                                     \
-  if (causal == C && dropout == P && sparse == S) {                                   \
-    hipLaunchKernelGGL((dkv_fr_kernel<T, D, C, P, S>), grid, block, 0, s, a);         \
-    return (int)hipGetLastError();                                                    \
-  }
+template <typename T, int D, int RW, int KG>
+int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
+  const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
+  a.n_items = a.B * a.H * (causal && !sparse ? (blocks + 1) / 2 : blocks);   // (pairs of key blocks)
+  a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(64 * RW * KG);
+#define ATTN_DKV_FR_CASE(C, P, S)                                                           \
+  if constexpr (!S || RW == 4)                                                              \
+    if (causal == C && dropout == P && sparse == S) {                                       \
+      hipLaunchKernelGGL((dkv_fr_kernel<T, D, C, P, S, RW, KG>), grid, block, 0, s, a);     \
+      return (int)hipGetLastError();                                                        \
+    }
   ATTN_DKV_FR_CASE(false, false, false)
   ATTN_DKV_FR_CASE(true, false, false)
   ATTN_DKV_FR_CASE(false, true, false)
@@ -348,6 +394,39 @@ int launch_td(KArgs a, bool causal, bool dropout, bool sparse, int extra_groups,
   ATTN_DKV_FR_CASE(true, true, true)
 #undef ATTN_DKV_FR_CASE
   return (int)hipErrorInvalidValue;
+}
+
+// us of the backward pass with {4, 1}, and the difference with {4, 2} | {2, 2} | {2, 4} (wavefronts of keys, groups) in this kernel
+// alone; heads x N:
+//   d = 64   1 x 128 12.3 +1.0 -0.3 +1.4; 16 x 197 17.7 -0.4 -2.1 -0.9; 4 x 512 25.0 -1.3 -3.8 -3.4; 16 x 1024 41.0 -4.2 -7.5 -8.1; 8 x 2048 72.2 -10.2 -15.6 -18.5;
+//            1 x 8192 263 -47 -68 -89; 60 x 300 20.6 -0.2 +0.1 +7.0; 24 x 1024 42.0 -4.2 -3.2 +3.2; 8 x 4096 140 -16.6 -10.8 -5.6;
+//            10 x 4096 186 +9.3 -4.4 -0.2, dropout 271 +14.7 -19.0 -9.5; 24 x 2001 110 +2.6 -4.2 +3.1; 40 x 1024 57.1 +5.4 +0.4 +8.2; 32 x 2048 116 +2.3 +6.0 +19.2
+//   d = 64 causal (pairs of key blocks)  1 x 128 13.1 +0.8 +2.9 +6.6; 16 x 197 26.9 -0.1 -2.9 +0.3; 16 x 1024 51.6 -3.6 -9.4 -7.8;
+//            8 x 4096 146 -20 -34 -39; 40 x 1024 53.2 -3.7 -3.3 +10.4; 32 x 2048 85.8 -6.3 -4.5 +7.4; 128 x 512 39.5 -0.7 -1.5 +12.2
+//   d = 32   1 x 128 10.0 -0.3 -0.4 -0.1; 16 x 640 22.6 -2.2 -3.7 -4.5; 8 x 2048 56.2 -8.9 -12.2 -16.4; 60 x 512 20.1 -1.6 -1.5 +1.6;
+//            8 x 4096 107 -18.5 -16.4 -11.7; 10 x 4096 138 +6.0 -5.7 -4.1; 64 x 1024 43.1 +2.9 +3.1 +10.6
+//   d = 32 causal (pairs)  16 x 197 18.9 -2.0 -3.6 -2.9; 8 x 4096 121 -22 -33 -42; 10 x 4096 132 -23 -24 -16; 128 x 512 29.2 -2.9 -3.0 +3.3
+//   block-sparse (butterfly mask of T x T blocks, heads x T), {4, 2} only  d = 64  4 x 8 48.1 +0.2; 8 x 16 69.8 -5.7; 4 x 32 65.8 -4.7; 8 x 32 69.6 +6.9,
+//            causal 68.4 -3.8; 4 x 64 75.5 +9.2 (the workgroups of the segment list take whole compute units then)
+WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse) {
+  if (!may_divide()) return {4, 1};
+  const bool pairs = causal && !sparse;
+  const WorkItems w(a, sparse, pairs);
+  if (sparse) return w.of128 <= kComputeUnits / 2 ? WaveGroups{4, 2} : WaveGroups{4, 1};
+  if (w.of64 <= kComputeUnits && w.tiles >= 4) return w.tiles >= (d == 64 ? 24 : 12) ? WaveGroups{2, 4} : WaveGroups{2, 2};
+  if (d == 64 && w.of128 <= kComputeUnits && w.tiles >= 4) return {4, 2};
+  if (d == 32 && w.of64 <= 2 * kComputeUnits && w.tiles >= 4) return {2, 2};
+  if (!pairs && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
+  return {4, 1};
+}
+
+template <typename T, int D>
+int launch_td(const KArgs& a, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
+  const WaveGroups w = dkv_fr_groups(a, D, causal, sparse);
+  if (w.waves == 2 && w.groups == 4) return launch_groups<T, D, 2, 4>(a, causal, dropout, sparse, extra_groups, s);
+  if (w.waves == 2) return launch_groups<T, D, 2, 2>(a, causal, dropout, sparse, extra_groups, s);
+  if (w.groups == 2) return launch_groups<T, D, 4, 2>(a, causal, dropout, sparse, extra_groups, s);
+  return launch_groups<T, D, 4, 1>(a, causal, dropout, sparse, extra_groups, s);
 }
 
 }  // namespace

@@ -24,30 +24,34 @@
 namespace attn {
 namespace {
 
-constexpr int NT = 256;
 constexpr int QT = 32;    // queries per streamed tile
 constexpr int D = 128;
 
-template <typename T, bool CAUSAL, bool DROPOUT>
-__global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
+// RW wavefronts of 32 keys, times KG groups of them that each take every KG-th query tile, into buffers of their own (the V rows are
+// shared); the groups' gradients are summed through LDS at the end.
+template <typename T, bool CAUSAL, bool DROPOUT, int RW, int KG>
+__global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs a) {
   typedef typename Vec<T>::x8 T8;
   constexpr int KK = D / 16, DB = D / 32;
   // One LDS block, so that every address is a per-lane register plus a 16-bit immediate: the row
   // vectors first (1 KB), then the Q tiles, the dO tiles and the V rows of this key block.
-  constexpr int kVecBytes = 4 * 64 * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kVecBytes + (4 * QT * D + 128 * D) * sizeof(T)];
+  constexpr int BR = 32 * RW;
+  constexpr int kVecBytes = 4 * 64 * 4, kGroupBytes = kVecBytes + 4 * QT * D * (int)sizeof(T);
+  __shared__ __attribute__((aligned(16))) unsigned char all[KG * kGroupBytes + BR * D * sizeof(T)];
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / RW;
+  unsigned char* const smem = all + group * kGroupBytes;
   float* const Ls0 = (float*)smem;                 // base-2 row statistic: Ls0 + 64 buf (first QT entries used:
   float* const Ds0 = Ls0 + 2 * 64;                 // -D_i:                 Ds0 + 64 buf  a copy moves 64 floats)
   T* const Qs0 = (T*)(smem + kVecBytes);           // Q tiles:  Qs0 + buf QT D
   T* const Gs0 = Qs0 + 2 * QT * D;                 // dO tiles: Gs0 + buf QT D
-  T* const Vb = Qs0 + 4 * QT * D;                  // V rows of this key block
+  T* const Vb = (T*)(all + KG * kGroupBytes);      // V rows of this key block
 
   // dropout flags in this layout: see KeepLK in attn_common.h
   __shared__ __attribute__((aligned(16))) uint32_t keep_table[DROPOUT ? KeepLK::kTable : 4];
   KeepLK keep;
   if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
 
-  const int n_kt = a.T;   // ceil(N / 128): the last key block may be ragged
+  const int n_kt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last key block may be ragged
   const int item = xcd_item(a.n_items, a.chunk);
   if (item < 0) return;
   int bh = item / n_kt;
@@ -73,9 +77,9 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
   const float* __restrict__ Dg = a.Dvec + (int64_t)bh * a.Nr;
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register: addresses and branches on it are scalar
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - RW * group;   // in a scalar register: addresses and branches on it are scalar
   const int r = lane & 31, g = lane >> 5;
-  const int kw0 = kt * 128 + wave * 32;
+  const int kw0 = kt * BR + wave * 32;
   const int kj = kw0 + r;
 
   T8 kf[KK];
@@ -92,41 +96,46 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
     for (int i = 0; i < 16; ++i) { dv[db][i] = 0.f; dk[db][i] = 0.f; }
 
   const int len = a.klen ? min(max(a.klen[b], 0), a.N) : a.N;
-  const int first = CAUSAL ? kt * (128 / QT) : 0;   // causal: the tiles above the diagonal see none of these keys
-  const int limit = kt * 128 >= len ? 0 : (len + QT - 1) / QT;
+  const int first = CAUSAL ? kt * (BR / QT) : 0;   // causal: the tiles above the diagonal see none of these keys
+  const int limit = kt * BR >= len ? 0 : (len + QT - 1) / QT;
 
   TrOffsets<D> tro;
   tro.init();
-  TileAsync<T, D, 4, QT> dma;      // 32-row tiles: two copy instructions per wavefront
+  TileAsync<T, D, RW, QT> dma;     // 32-row tiles: 8 / RW copy instructions per wavefront
   dma.init(a.sn, wave);
-  TileAsync<T, D, 4, 64> dma64;    // the V block: two 64-row pieces
+  TileAsync<T, D, RW, 64> dma64;   // the V block: 64-row pieces, copied by the first group
   dma64.init(a.sn, wave);
   auto fetch_tile = [&](int t, int buf) {
     dma.copy_rows(Qg, a.sn, t * QT, a.N, Qs0 + buf * QT * D);
     dma.copy_rows(Gg, a.sn, t * QT, a.N, Gs0 + buf * QT * D);
     const int row = min(t * QT + lane, a.Nr - 1);   // whole-wavefront copies: 64 floats, clamped to the head
-    if (wave == 1) async_copy_b32(Lg + row, __builtin_amdgcn_readfirstlane(lds_addr(Ls0 + 64 * buf)));
-    if (wave == 2) async_copy_b32(Dg + row, __builtin_amdgcn_readfirstlane(lds_addr(Ds0 + 64 * buf)));
+    if (wave == RW / 2 - 1) async_copy_b32(Lg + row, __builtin_amdgcn_readfirstlane(lds_addr(Ls0 + 64 * buf)));
+    if (wave == RW / 2) async_copy_b32(Dg + row, __builtin_amdgcn_readfirstlane(lds_addr(Ds0 + 64 * buf)));
   };
   const float c = a.scale_log2;
   constexpr int PF = 4;
 
   // V rows of this key block (rows >= N repeat the last one; their keys are masked)
-  if (kt * 128 < a.N) dma64.copy_rows(Vg, a.sn, kt * 128, a.N, Vb);
-  if (kt * 128 + 64 < a.N) dma64.copy_rows(Vg, a.sn, kt * 128 + 64, a.N, Vb + 64 * D);
-  else if (kt * 128 < a.N) dma64.copy_rows(Vg, a.sn, kt * 128, a.N, Vb + 64 * D);   // all of these keys are masked
-  if (first < limit) fetch_tile(first, 0);
+  if (KG == 1 || group == 0) {
+    if (kt * BR < a.N) dma64.copy_rows(Vg, a.sn, kt * BR, a.N, Vb);
+    if (RW == 4) {
+      if (kt * BR + 64 < a.N) dma64.copy_rows(Vg, a.sn, kt * BR + 64, a.N, Vb + 64 * D);
+      else if (kt * BR < a.N) dma64.copy_rows(Vg, a.sn, kt * BR, a.N, Vb + 64 * D);   // all of these keys are masked
+    }
+  }
+  const int mine = first + group;   // this group's first tile
+  if (mine < limit) fetch_tile(mine, 0);
   wait_async_copies();
   __syncthreads();
   // One query tile.  The buffer index is a compile-time constant (the loop below is unrolled by
   // two), so that every LDS address is a per-lane register plus an immediate offset.
   auto tile_step = [&](int t, auto buf_c) {
     constexpr int buf = decltype(buf_c)::value;
-    if (t + 1 < limit) fetch_tile(t + 1, buf ^ 1);
+    if (t + KG < limit) fetch_tile(t + KG, buf ^ 1);
     // causal: of the four tiles on the diagonal of the key block, wavefront w joins from the w-th
     // on, and masks inside that one
     const int i0 = t * QT;
-    if (!CAUSAL || i0 >= kw0) {
+    if ((KG == 1 || t < limit) && (!CAUSAL || i0 >= kw0)) {
       const T* Qt = Qs0 + buf * QT * D;
       const T* Gt = Gs0 + buf * QT * D;
       // ---- S = Q K^T and dP = dO V^T (32 queries x 32 keys each) as one stream of alternating
@@ -218,9 +227,41 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
     wait_async_copies();
     __syncthreads();
   };
-  for (int t = first; t < limit; t += 2) {
-    tile_step(t, std::integral_constant<int, 0>());
-    if (t + 1 < limit) tile_step(t + 1, std::integral_constant<int, 1>());
+  for (int t = first; t < limit; t += 2 * KG) {   // (the same number of steps in every group)
+    tile_step(t + group, std::integral_constant<int, 0>());
+    if (t + KG < limit) tile_step(t + KG + group, std::integral_constant<int, 1>());
+  }
+  if constexpr (KG > 1) {
+    // the loop ended on a barrier (or never touched LDS): the groups but the first leave dV, then dK in the buffers
+    constexpr int kLanes = 64 * RW;
+    static_assert((KG - 1) * DB * 16 * kLanes * 4 <= (int)sizeof(all), "LDS holds one gradient of the groups");
+    f32x4* const part = (f32x4*)all + wave * 64 + lane;
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+      f32x16 (&x)[DB] = which == 0 ? dv : dk;
+      if (which == 0) wait_async_copies();   // (the V rows, where the loop did not run)
+      __syncthreads();
+      if (group > 0) {
+#pragma unroll
+        for (int f = 0; f < 4 * DB; ++f) {
+          const int i = 4 * (f % 4);
+          const f32x4 v = {x[f / 4][i], x[f / 4][i + 1], x[f / 4][i + 2], x[f / 4][i + 3]};
+          part[((group - 1) * 4 * DB + f) * kLanes] = v;
+        }
+      }
+      __syncthreads();
+      if (group == 0) {
+#pragma unroll
+        for (int k = 0; k < KG - 1; ++k)
+#pragma unroll
+          for (int f = 0; f < 4 * DB; ++f) {
+            const f32x4 v = part[(k * 4 * DB + f) * kLanes];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[f / 4][4 * (f % 4) + e] += v[e];
+          }
+      }
+    }
+    if (group > 0) return;
   }
   {
     // 4 wavefronts x 32 rows x 128 = 32 KB per gradient: the V block, then the four tile buffers
@@ -232,7 +273,7 @@ __global__ __launch_bounds__(NT, 2) void dkv_fr128_kernel(const KArgs a) {
   }
 }
 
-template <typename T>
+template <typename T, int RW, int KG>
 int launch_t(const KArgs& a_in, bool causal, bool dropout, hipStream_t s) {
   KArgs a = a_in;
   {
@@ -240,18 +281,39 @@ int launch_t(const KArgs& a_in, bool causal, bool dropout, hipStream_t s) {
     const int64_t fit = ((int64_t)8 << 20) / tile_bytes;
     a.group = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
   }
-  const dim3 grid(kXcds * a.chunk), block(NT);
-  if (causal && dropout) hipLaunchKernelGGL((dkv_fr128_kernel<T, true, true>), grid, block, 0, s, a);
-  else if (causal) hipLaunchKernelGGL((dkv_fr128_kernel<T, true, false>), grid, block, 0, s, a);
-  else if (dropout) hipLaunchKernelGGL((dkv_fr128_kernel<T, false, true>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((dkv_fr128_kernel<T, false, false>), grid, block, 0, s, a);
+  const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
+  a.n_items = a.B * a.H * blocks;
+  a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
+  if (causal && dropout) hipLaunchKernelGGL((dkv_fr128_kernel<T, true, true, RW, KG>), grid, block, 0, s, a);
+  else if (causal) hipLaunchKernelGGL((dkv_fr128_kernel<T, true, false, RW, KG>), grid, block, 0, s, a);
+  else if (dropout) hipLaunchKernelGGL((dkv_fr128_kernel<T, false, true, RW, KG>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((dkv_fr128_kernel<T, false, false, RW, KG>), grid, block, 0, s, a);
   return (int)hipGetLastError();
 }
 
 }  // namespace
 
+// us of the backward pass with {4, 1}, and the difference with {4, 2} | {2, 2} | {2, 4} (wavefronts of keys, groups) in this kernel
+// alone; heads x N:
+//   no mask  1 x 128 17.4 +1.1 +0.3 +3.2; 16 x 197 23.8 +0.3 -1.0 +1.5; 4 x 512 36.5 -2.4 -4.8 -3.7; 16 x 1024 60.8 -5.4 -9.6 -7.4; 8 x 2048 109 -14 -23 -23;
+//            1 x 8192 399 -72 -101 -136; 96 x 197 26.0 +0.4 +7.6 +17.1; 60 x 300 30.2 -0.7 +7.7 +15.9; 24 x 1024 62.5 -4.5 +10.2 +13.1; 8 x 4096 220 -15 +20 +9;
+//            40 x 1024 93.6 +7.3 +16.3 +21.6
+//   causal   16 x 1024 62.4 -5.5 -9.1 -7.6; 8 x 2048 110 -15 -21 -22; 8 x 4096 213 -23 +6 -9; 40 x 1024 78.3 -2.8 +11.3 +19.4; 10 x 4096 254 +8 +42 +16
+//   dropout  8 x 2048 137 -19 -31 -35; 8 x 4096 272 -30 +16 -5; 60 x 512 48.2 -2.7 +8.2 +16.5; 10 x 4096 372 +23 +46 +5
+static WaveGroups fr128_groups(const KArgs& a) {
+  if (!may_divide()) return {4, 1};
+  const WorkItems w(a, false, false);
+  if (w.of64 <= kComputeUnits && w.tiles >= 4) return w.tiles >= 32 ? WaveGroups{2, 4} : WaveGroups{2, 2};
+  return w.of128 <= kComputeUnits && w.tiles >= 5 ? WaveGroups{4, 2} : WaveGroups{4, 1};
+}
+
 int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, hipStream_t s) {
-  return dtype == 0 ? launch_t<_Float16>(a, causal, dropout, s) : launch_t<__bf16>(a, causal, dropout, s);
+  const WaveGroups w = fr128_groups(a);
+  if (w.waves == 2 && w.groups == 4) return dtype == 0 ? launch_t<_Float16, 2, 4>(a, causal, dropout, s) : launch_t<__bf16, 2, 4>(a, causal, dropout, s);
+  if (w.waves == 2) return dtype == 0 ? launch_t<_Float16, 2, 2>(a, causal, dropout, s) : launch_t<__bf16, 2, 2>(a, causal, dropout, s);
+  if (w.groups == 2) return dtype == 0 ? launch_t<_Float16, 4, 2>(a, causal, dropout, s) : launch_t<__bf16, 4, 2>(a, causal, dropout, s);
+  return dtype == 0 ? launch_t<_Float16, 4, 1>(a, causal, dropout, s) : launch_t<__bf16, 4, 1>(a, causal, dropout, s);
 }
 
 }  // namespace attn

@@ -68,6 +68,27 @@ enum { kDkvRoleSplit = 0, kDkvOneWave = 1, kDkvOneWave128 = 2, kDkvOneWave64 = 3
 int choose_fwd(const KArgs& a, int d, bool causal, bool dropout, bool sparse);
 int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse);
 
+// How a tile kernel divides its work: `waves` wavefronts of 32 rows (dK/dV: keys) each share the streamed tiles of a workgroup,
+// and `groups` groups of that many wavefronts work on the same rows, group k on every groups-th tile; what the groups
+// accumulated is added up through LDS at the end, in a fixed order.  With few work items the chip holds one wavefront per SIMD or
+// fewer, and a row's sweep over the tiles is what a launch takes: half the rows make twice the items, and two or four groups
+// sweep a half or a quarter of the tiles each.  With more items than fit at once neither helps, {4, 1} has least overhead.
+// A dK/dV override (comparisons and tests) keeps every kernel at {4, 1}.
+struct WaveGroups { int waves, groups; };
+inline bool may_divide() { return dkv_variant() == 0; }
+// The problem as these choices see it: work items with 64 and with 128 rows (pairs of row blocks where the kernel takes pairs),
+// 64-wide tiles that a row sweeps (block-sparse: a guess, the masks are on the GPU; a row of the butterfly mask keeps 5 to 10 blocks).
+struct WorkItems {
+  int64_t of64, of128;
+  int tiles;
+  WorkItems(const KArgs& a, bool sparse, bool pairs) {
+    const int64_t heads = (int64_t)a.B * a.H, blocks64 = ((int64_t)a.N + 63) / 64, blocks128 = a.T;
+    of64 = heads * (pairs ? (blocks64 + 1) / 2 : blocks64);
+    of128 = heads * (pairs ? (blocks128 + 1) / 2 : blocks128);
+    tiles = sparse ? 16 : (int)blocks64;
+  }
+};
+
 // Launchers (defined in the .hip files).  dtype: 0 fp16, 1 bf16.  Return hipError_t as int.
 int launch_fwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s);
 // ev: nullptr, or four events: two recorded before the first launch, one after the dQ kernel, one after dK/dV.
@@ -486,6 +507,17 @@ template <bool SPARSE> struct TileIter {
                                        int skip_blocks = 0, int take_blocks = 0x7fffffff) {
     mask = m; stride = st; limit = lim; pos = first; bits = 0; base = 0; half = -1;
     skip = skip_blocks; take = take_blocks;
+  }
+  // The next GROUPS tiles, one for each group of wavefronts; own: that of `group`, -1 past the end.  False once there is none for any.
+  template <int GROUPS> __device__ __forceinline__ bool next_of(int group, int& own) {
+    own = next();
+    const bool any = own >= 0;
+#pragma unroll
+    for (int k = 1; k < GROUPS; ++k) {
+      const int t = next();
+      if (group == k) own = t;
+    }
+    return any;
   }
   __device__ __forceinline__ int next() {
     if constexpr (!SPARSE) {

@@ -35,24 +35,35 @@
 namespace attn {
 namespace {
 
-constexpr int BR = 128;  // query rows per workgroup
 constexpr int BC = 64;   // keys per K/V tile
-constexpr int NT = 256;  // threads
 
-template <typename T, int D, bool CAUSAL, bool DROPOUT, bool SPARSE>
-__global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a) {
+// RW wavefronts of 32 query rows each share the K/V tiles of a workgroup.  KG groups of RW wavefronts work on the same rows: group
+// k takes every KG-th tile, into buffers of its own, and the groups' (m, l, O) are merged through LDS at the end.
+template <typename T, int D, bool CAUSAL, bool DROPOUT, bool SPARSE, int RW, int KG>
+__global__ __launch_bounds__(64 * RW * KG, KG == 1 ? (D <= 64 ? 3 : 2) : (RW * KG > 8 ? RW * KG / 4 : 2)) void fwd_kernel(const KArgs a) {
   typedef typename Vec<T>::x8 T8;
   typedef typename Vec<T>::x4 T4;
   constexpr int KK = D / 16;        // MFMA k-steps over the head dimension
   constexpr int DB = D / 32;        // 32-row blocks of O^T
 
   // double buffered, unpadded XOR-swizzled tiles, filled by asynchronous global-to-LDS copies
-  __shared__ __attribute__((aligned(16))) T Ks[2][BC * D];
-  __shared__ __attribute__((aligned(16))) T Vs[2][BC * D];
+  constexpr int BR = 32 * RW;       // query rows of the workgroup
+  // (two arrays, the form that the register allocation of the ungrouped kernels is tuned to, or one block that the merge can use whole)
+  typedef T Tile[BC * D];
+  Tile *Ks, *Vs;   // buffers 2 k and 2 k + 1: key group k's
+  if constexpr (KG == 1) {
+    __shared__ __attribute__((aligned(16))) Tile k_bufs[2], v_bufs[2];
+    Ks = k_bufs;
+    Vs = v_bufs;
+  } else {
+    __shared__ __attribute__((aligned(16))) Tile bufs[4 * KG];
+    Ks = bufs;
+    Vs = bufs + 2 * KG;
+  }
 
   const int item = xcd_item(a.n_items, a.chunk);
   if (item < 0) return;
-  const int n_qt = a.T;   // ceil(N / BR): the last block may be ragged
+  const int n_qt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last block may be ragged
   // Work item = (head, row block), heavy (late) blocks first under a causal mask.  For dense
   // causal d = 64 problems an item is the pair (n_qt - 1 - q, q), one block per pass, so that
   // every workgroup does the same amount of work.
@@ -73,7 +84,8 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // in a scalar register: addresses and branches on it are scalar
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / RW;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - RW * group;   // in a scalar register: addresses and branches on it are scalar
   const int r = lane & 31, g = lane >> 5;
   const int q0 = qt * BR + wave * 32;  // first query row of this wavefront
   // this lane's query row; lanes beyond a ragged end work on a copy of the last row and store nothing
@@ -109,28 +121,31 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
   TileIter<SPARSE> it;
   {
     int lim;
-    if constexpr (SPARSE) lim = min(CAUSAL ? qt + 1 : a.T, (len + 127) / 128);
-    else lim = CAUSAL ? min(2 * qt + 2, (len + BC - 1) / BC) : (len + BC - 1) / BC;   // len <= N
+    const int mask_row = qt * BR / 128;
+    if constexpr (SPARSE) lim = min(CAUSAL ? mask_row + 1 : a.T, (len + 127) / 128);
+    else lim = CAUSAL ? min((qt + 1) * BR / BC, (len + BC - 1) / BC) : (len + BC - 1) / BC;   // len <= N
     if (qt * BR >= len) lim = 0;
-    it.init(SPARSE ? a.mask + (int64_t)h * a.mask_sh + (int64_t)qt * a.T : nullptr, 1, 0, lim);
+    it.init(SPARSE ? a.mask + (int64_t)h * a.mask_sh + (int64_t)mask_row * a.T : nullptr, 1, 0, lim);
   }
 
   TrOffsets<D> tro;
   tro.init();
-  TileAsync<T, D, NT / 64> dma;
+  TileAsync<T, D, RW> dma;
   dma.init(a.sn, wave, D == 32 ? a.dvalid : D);
   if (D == 32 && a.dvalid < D) {   // the copies leave columns >= 16 of the tile buffers untouched
-    zero_tiles(&Ks[0][0], 2 * BC * D);
-    zero_tiles(&Vs[0][0], 2 * BC * D);
+    zero_tiles(&Ks[0][0], 2 * KG * BC * D);
+    zero_tiles(&Vs[0][0], 2 * KG * BC * D);
     __syncthreads();
   }
 
   const float c = a.scale_log2;
-  int jt = it.next();
+  // jt: this group's tile, -1 if there is none; more: some group (then the first) has one
+  int jt;
+  bool more = it.template next_of<KG>(group, jt);
   int buf = 0;
   if (jt >= 0) {
-    dma.copy_rows(Kg, a.sn, jt * BC, a.N, Ks[0]);
-    dma.copy_rows(Vg, a.sn, jt * BC, a.N, Vs[0]);
+    dma.copy_rows(Kg, a.sn, jt * BC, a.N, Ks[2 * group]);
+    dma.copy_rows(Vg, a.sn, jt * BC, a.N, Vs[2 * group]);
   }
   wait_async_copies();
   __syncthreads();   // tile 0 has landed, and so have the Q fragments
@@ -141,19 +156,20 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
   uint32_t k_off[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
-    k_off[kk] = lds_addr(&Ks[0][0]) + (uint32_t)(lds_off<D>(r, 2 * kk + g) * sizeof(T));
+    k_off[kk] = lds_addr(&Ks[2 * group][0]) + (uint32_t)(lds_off<D>(r, 2 * kk + g) * sizeof(T));
     asm volatile("" : "+v"(k_off[kk]));
   }
-  while (jt >= 0) {
-    const int jn = it.next();
+  while (KG == 1 ? jt >= 0 : more) {
+    int jn;
+    const bool more_next = it.template next_of<KG>(group, jn);
     if (jn >= 0) {   // the next tile streams into the other buffer while this one is used
-      dma.copy_rows(Kg, a.sn, jn * BC, a.N, Ks[buf ^ 1]);
-      dma.copy_rows(Vg, a.sn, jn * BC, a.N, Vs[buf ^ 1]);
+      dma.copy_rows(Kg, a.sn, jn * BC, a.N, Ks[2 * group + (buf ^ 1)]);
+      dma.copy_rows(Vg, a.sn, jn * BC, a.N, Vs[2 * group + (buf ^ 1)]);
     }
-    const T* Vt = Vs[buf];
+    const T* Vt = Vs[2 * group + buf];
 
     const int k0 = jt * BC;
-    const bool wave_active = !CAUSAL || k0 <= q0 + 31;
+    const bool wave_active = (KG == 1 || jt >= 0) && (!CAUSAL || k0 <= q0 + 31);
     if (wave_active) {
       // ---- S^T = K Q^T  (64 keys x 32 queries per wavefront); operand reads run PF fragments
       // ahead of their MFMA (the scheduling barriers keep that distance)
@@ -206,7 +222,50 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
     wait_async_copies();
     __syncthreads();   // the next tile has landed, and everyone is done with this buffer
     jt = jn;
+    more = more_next;
     buf ^= 1;
+  }
+
+  if constexpr (KG > 1) {
+    // The loop ended on a barrier (or never touched LDS).  The groups but the first leave O in the tile buffers from the first one
+    // on; the last two take the output rows.
+    constexpr int kLanes = 64 * RW;
+    static_assert((KG - 1) * RW + 2 <= 4 * KG && RW <= 4 && sizeof(Tile) == 4 * D * 32, "LDS holds the groups' O and the output rows");
+    __shared__ float sums[(KG - 1) * 3 * kLanes];   // references and row sums
+    f32x4* const o_part = (f32x4*)Ks + (group - 1) * (4 * DB * kLanes) + wave * 64 + lane;
+    float* const s_part = sums + (group - 1) * 3 * kLanes + wave * 64 + lane;
+    if (group > 0) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 v = {o[db][4 * i4], o[db][4 * i4 + 1], o[db][4 * i4 + 2], o[db][4 * i4 + 3]};
+          o_part[(4 * db + i4) * kLanes] = v;
+        }
+      s_part[0] = m_run;
+      s_part[kLanes] = l_run;
+      s_part[2 * kLanes] = lr_run[0];
+    }
+    __syncthreads();
+    if (group > 0) continue;
+#pragma unroll
+    for (int k = 1; k < KG; ++k) {
+      const float* const sp = s_part + k * 3 * kLanes;
+      const f32x4* const op = o_part + k * (4 * DB * kLanes);
+      const float mk = sp[0], m = fmaxf(m_run, mk), ref = m == -INFINITY ? 0.f : m;
+      const float w0 = __builtin_amdgcn_exp2f(m_run - ref), w1 = __builtin_amdgcn_exp2f(mk - ref);
+      m_run = m;
+      l_run = l_run * w0 + sp[kLanes] * w1;
+      lr_run[0] = lr_run[0] * w0 + sp[2 * kLanes] * w1;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 v = op[(4 * db + i4) * kLanes];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[db][4 * i4 + e] = o[db][4 * i4 + e] * w0 + v[e] * w1;
+        }
+    }
   }
 
   // ---- epilogue: normalise, apply the dropout scale, write O and L once
@@ -234,25 +293,24 @@ __global__ __launch_bounds__(NT, D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a)
     }
   } else {
     // coalesced row stores through the (now idle) tile buffers: two wavefronts per buffer
-    T* stage = (wave < 2 ? &Ks[0][0] + wave * 32 * D : &Vs[0][0] + (wave - 2) * 32 * D);
+    // (of several groups: two that hold nothing of the merge, which other wavefronts may still read)
+    T* stage = KG > 1 ? &Vs[2 * KG - 2][0] + wave * 32 * D : (wave < 2 ? &Ks[0][0] + wave * 32 * D : &Vs[0][0] + (wave - 2) * 32 * D);
     store_rows_coalesced<T, D>(stage, (T*)a.O + head_off + (int64_t)q0 * a.sn, a.sn, o, inv, a.N - q0,
                                D == 32 ? a.dvalid : D);
   }
   }  // for pass
 }
 
-template <typename T, int D>
-int launch_fwd_td(const KArgs& a_in, bool causal, bool dropout, bool sparse, hipStream_t s) {
-  KArgs a = a_in;
-  if (causal && !sparse && D == 64) {   // items are pairs of row blocks
-    a.n_items = a.B * a.H * ((a.T + 1) / 2);
-    a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  }
-  const dim3 grid(kXcds * a.chunk), block(NT);
-#define ATTN_FWD_CASE(C, P, S)                                                         \
-  if (causal == C && dropout == P && sparse == S) {                                    \
-    hipLaunchKernelGGL((fwd_kernel<T, D, C, P, S>), grid, block, 0, s, a);             \
-    return (int)hipGetLastError();                                                     \
+template <typename T, int D, int RW, int KG>
+int launch_fwd_groups(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
+  const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
+  a.n_items = a.B * a.H * (causal && !sparse && D == 64 ? (blocks + 1) / 2 : blocks);   // (pairs of row blocks)
+  a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
+#define ATTN_FWD_CASE(C, P, S)                                                              \
+  if (causal == C && dropout == P && sparse == S) {                                         \
+    hipLaunchKernelGGL((fwd_kernel<T, D, C, P, S, RW, KG>), grid, block, 0, s, a);          \
+    return (int)hipGetLastError();                                                          \
   }
   ATTN_FWD_CASE(false, false, false)
   ATTN_FWD_CASE(true, false, false)
@@ -264,6 +322,55 @@ int launch_fwd_td(const KArgs& a_in, bool causal, bool dropout, bool sparse, hip
   ATTN_FWD_CASE(true, true, true)
 #undef ATTN_FWD_CASE
   return (int)hipErrorInvalidValue;
+}
+
+// us, forward alone, {4, 1} | {4, 2} | {2, 2} | {2, 4} (wavefronts of rows, groups; heads x N):
+//   d = 64   4 x 117 5.5 5.7 5.3 6.3; 16 x 256 6.9 7.1 6.2 6.8; 16 x 640 11.1 10.3 8.5 9.1; 16 x 1024 16.0 13.7 12.9 11.0;
+//            8 x 2048 27.5 22.5 21.9 16.5; 1 x 8192 99.2 76.2 73.2 46.5; 24 x 1024 16.0 13.7 16.7 19.7; 16 x 2048 28.4 24.2 29.7 30.6;
+//            8 x 4096 52.4 43.0 54.4 51.2; 60 x 512 9.9 9.6 10.7 14.7; 20 x 2048 38.5 44.2 44.9 43.9; 128 x 512 14.1 17.1 19.6 27.6
+//   d = 64 causal (pairs of row blocks)  60 x 400 14.1 13.7 11.1 12.3; 16 x 1024 20.3 18.3 16.8 15.2; 8 x 4096 57.1 45.4 43.4 31.8;
+//            20 x 2048 32.7 27.7 33.2 38.8; 10 x 4096 57.3 45.6 56.7 59.0; 64 x 1024 21.1 19.2 - 28.7; 48 x 1400 33.0 41.7 - 47.0
+//   d = 32   4 x 117 4.7 5.0 5.1 5.0; 16 x 640 9.7 8.9 7.1 7.1; 16 x 1024 13.5 11.6 10.3 8.4; 60 x 512 8.5 7.9 8.6 8.5; 8 x 4096 45.1 35.5 39.8 32.8;
+//            10 x 4096 60.7 55.3 52.9 47.6; 32 x 2048 32.9 31.3 38.5 35.1, causal 34.0 30.0 29.2 26.9; 128 x 512 11.1 11.4 13.9 14.7
+//   d = 128  4 x 117 6.6 7.8 7.2; 64 x 189 8.5 - 9.7; 40 x 359 11.7 - 11.0; 16 x 1024 22.1 19.9 18.8; 1 x 8192 140 107 107; 60 x 512 14.4 14.5 23.1; 24 x 1024 22.4 20.5 35.3;
+//            8 x 4096 78.3 69.9 112, causal 75.9 58.4 62.8; 40 x 1024 32.8 39.8 51.8; causal 10 x 4096 104 71.5 116, 8 x 8192 170 141 230,
+//            48 x 693 20.1 22.2 -, 24 x 2001 56.4 45.1 66.5, 40 x 1024 32.0 32.1 36.5, 48 x 1400 42.9 44.0 62.3, 64 x 1024 34.0 38.9 56.4
+//   block-sparse (butterfly mask of T x T blocks, heads x T)  d = 64  4 x 16 15.5 13.1 10.8 11.0; 4 x 64 20.0 17.0 17.4 24.3; 8 x 64 27.7 31.0 31.5 46.5;
+//            d = 128  4 x 16 20.4 18.3 17.4; 4 x 64 28.4 26.9 43.1; 8 x 64 43.8 51.7 85.0
+WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
+  if (!may_divide()) return {4, 1};
+  const WorkItems w(a, sparse, causal && !sparse && d == 64);
+  // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise)
+  const int64_t fit24 = d == 64 ? kComputeUnits : (causal && w.tiles >= 24 ? 4 * kComputeUnits : 5 * kComputeUnits / 2);
+  if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
+  if (w.of64 <= kComputeUnits && w.tiles >= (d == 128 ? 6 : 3)) return {2, 2};
+  if (d <= 64) return w.of128 <= (d == 32 ? 2 : 1) * kComputeUnits && w.tiles >= 10 ? WaveGroups{4, 2} : WaveGroups{4, 1};
+  // d = 128: {4, 2} has one workgroup on a compute unit, {4, 1} two, which together get through a tile hardly faster than one
+  // of them alone.  Estimates in us: the tiles of all items over the compute units, and under the causal mask the longest sweep.
+  // (From 512 items on {4, 2} would gain for few heads of long causal sequences only, 8 x 8192 above, where the results are held to the
+  // last bit to those of the two-group kernel, whose references a row's undivided sweep shares; the line stays below.)
+  if (w.of128 > 3 * kComputeUnits / 2 || (w.of128 > kComputeUnits && w.tiles < 16)) return {4, 1};
+  const double heads = (double)a.B * a.H, per_unit = 1.0 / kComputeUnits;
+  double one, two;
+  if (causal && !sparse) {
+    const double tiles = heads * std::min<double>((double)a.T * (a.T + 1), (double)a.T * w.tiles);
+    one = std::max(1.12 * tiles * per_unit, 1.25 * w.tiles) + 3.0;
+    two = std::max(1.08 * tiles * per_unit + 4.5 * (double)w.of128 * per_unit, 0.9 * w.tiles + 4.5);
+  } else {
+    one = std::max(1.12 * (double)w.of128 * per_unit, 1.25) * w.tiles + 3.0;
+    two = std::ceil((double)w.of128 * per_unit) * (1.08 * w.tiles + 4.5);
+  }
+  return two < one ? WaveGroups{4, 2} : WaveGroups{4, 1};
+}
+
+template <typename T, int D>
+int launch_fwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStream_t s) {
+  const WaveGroups w = fwd_groups(a, D, causal, dropout, sparse);
+  if constexpr (D <= 64)
+    if (w.waves == 2 && w.groups == 4) return launch_fwd_groups<T, D, 2, 4>(a, causal, dropout, sparse, s);
+  if (w.waves == 2) return launch_fwd_groups<T, D, 2, 2>(a, causal, dropout, sparse, s);
+  if (w.groups == 2) return launch_fwd_groups<T, D, 4, 2>(a, causal, dropout, sparse, s);
+  return launch_fwd_groups<T, D, 4, 1>(a, causal, dropout, sparse, s);
 }
 
 // keep[bh][i][j] for the test hook: one thread per group of sixteen consecutive keys, with the generator of the product kernels and
