@@ -205,7 +205,8 @@ int attn_blocksparse_bwd(const attn_params* p, const uint8_t* block_mask, int32_
  * addition records the caller's four hipEvent_t handles on p->stream: events[0] and events[1]
  * before the first launch (two handles for one instant: an earlier version had a preparation
  * launch between them; D = rowsum(dO o O) is now computed inside the dQ kernel), events[2] after
- * the dQ kernel, events[3] after the dK/dV kernel.  The events stay owned by the caller.
+ * the dQ kernel, events[3] after the dK/dV kernel (where one launch does both, both after it).  The
+ * events stay owned by the caller.
  */
 int attn_bwd_timed(const attn_params* p, const uint8_t* block_mask, int32_t mask_block,
                    int64_t mask_stride_h, const void* Q, const void* K, const void* V,
@@ -242,7 +243,8 @@ int attn_debug_mfma_rate(int32_t dtype, int32_t iters, int32_t operand_sets, flo
  * *fwd_kernel: 0 = free-running forward kernel, 1 = two-group forward kernel.
  * *dkv_kernel: 0 = role-split dK/dV kernel, 1 = one-wavefront kernel (d <= 64),
  * 2 = one-wavefront kernel for d = 128 (32 keys per wavefront), 3 = the same with 64 keys
- * per wavefront.  (The dQ kernel is the same for every problem.)
+ * per wavefront, 4 = short heads at d <= 64, dQ included (one launch).  (The dQ kernel is the same
+ * for every other problem.)
  */
 int attn_debug_kernel_choice(const attn_params* p, int32_t sparse, int32_t* fwd_kernel, int32_t* dkv_kernel);
 
@@ -252,7 +254,7 @@ int attn_debug_kernel_choice(const attn_params* p, int32_t sparse, int32_t* fwd_
  * forward kernel (where both exist).  dkv_variant: 0 = by measurement, 1 = role-split dK/dV kernel
  * wherever it exists, 2 = one-wavefront dK/dV kernels with 32 keys per wavefront only, 3 = the
  * 64-keys-per-wavefront dK/dV kernel wherever it exists (d = 128, no dropout, N >= 512, N % 32 == 0).
- * While dkv_variant is not 0, no kernel divides the sweep of a work item over groups of wavefronts (which
+ * While dkv_variant is not 0, short heads take the two launches too, and no kernel divides the sweep of a work item over groups of wavefronts (which
  * they do where there are few work items).
  * -1 leaves a setting unchanged.  Process-wide and thread-safe; affects calls issued afterwards.
  */

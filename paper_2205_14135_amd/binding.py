@@ -277,7 +277,7 @@ def attn_debug_dropout_mask(B, H, N, dropout_p, seed, offset, device="cuda") -> 
 
 
 FWD_KERNELS = ("fwd_kernel", "fwd_pp_kernel")
-DKV_KERNELS = ("dkv_rs_kernel", "dkv_fr_kernel", "dkv_fr128_kernel", "dkv_w64_kernel")
+DKV_KERNELS = ("dkv_rs_kernel", "dkv_fr_kernel", "dkv_fr128_kernel", "dkv_w64_kernel", "bwd_short_kernel")
 
 
 def attn_debug_kernel_choice(p: AttnParams, sparse: bool = False) -> Tuple[str, str]:

@@ -17,7 +17,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libattn_gfx950.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")   # the binding's native argument marshalling (host code only)
 SOURCES = ["attn_fwd.hip", "attn_fwd_pp.hip", "attn_bwd.hip", "attn_bwd_dkv.hip", "attn_bwd_dkv_fr.hip", "attn_bwd_dkv_fr128.hip",
-           "attn_bwd_dkv_w64.hip", "attn_probe.hip", "attn_api.cpp"]
+           "attn_bwd_dkv_w64.hip", "attn_bwd_short.hip", "attn_probe.hip", "attn_api.cpp"]
 # Kernels that keep their accumulators in accumulation registers addressed by name in raw MFMA
 # statements: builtin MFMA results must then stay in architectural registers (this option), and the
 # generated code is checked (check_pinned_agprs below).

@@ -404,7 +404,14 @@ template <typename T, int D>
 int launch_bwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStream_t s, hipEvent_t* ev) {
   if (ev) (void)hipEventRecord(ev[0], s);
   if (ev) (void)hipEventRecord(ev[1], s);   // (there is no separate preparation launch any more)
-  int e = launch_dq_td<T, D>(a, causal, dropout, sparse, s);
+  int e;
+  if (choose_dkv(a, D, causal, dropout, sparse) == kBwdShort) {
+    e = launch_bwd_short(a, kDtype<T>, D, causal, dropout, s);
+    if (ev) (void)hipEventRecord(ev[2], s);
+    if (ev) (void)hipEventRecord(ev[3], s);
+    return e;
+  }
+  e = launch_dq_td<T, D>(a, causal, dropout, sparse, s);
   if (e != 0) return e;
   if (ev) (void)hipEventRecord(ev[2], s);
   e = launch_dkv_rs(a, kDtype<T>, D, causal, dropout, sparse, s);

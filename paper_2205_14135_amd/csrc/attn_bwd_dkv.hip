@@ -493,6 +493,8 @@ int launch_td(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
 }  // namespace
 
 int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
+  // short heads: one workgroup has all of a head's keys, and both launches become one
+  if (!sparse && dkv_variant() == 0 && bwd_short_is_faster(a, d, causal)) return kBwdShort;
   // Problems with d <= 64 take the kernel in which one wavefront does all four products
   // (attn_bwd_dkv_fr.hip; the block-sparse ones from inside launch_td, between the column
   // planning and the finish kernel).

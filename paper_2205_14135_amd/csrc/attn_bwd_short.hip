@@ -1,0 +1,336 @@
+// Backward pass of short sequences at d <= 64 (dense, N <= 256): one workgroup takes a whole head, and one launch
+// does all five tile products.
+//
+// Arithmetic: Algorithm 4 of the paper with a single key block,
+//     S = Q K^T, P = exp(S - L), dV = (P o Z)^T dO, dP = (dO V^T) o Z, dS = P o (dP - D), dK = tau dS^T Q, dQ = tau dS K,
+// D = rowsum(dO o O).  The longer sequences take two launches (attn_bwd.hip), because a key block's share of dQ
+// would have to be added up in memory; here the only key block is the whole sequence, so dQ needs no other workgroup's share.  S, P,
+// dP and the dropout draw are done once instead of twice, Q, K, V and dO are read once, and nothing goes
+// through the scratch vectors.
+// A wavefront owns 32 keys (layout "lane = key", as in attn_bwd_dkv_fr.hip) for dK and dV, and then 32 queries for dQ: dS
+// changes owner through LDS, [key][query] rows written four queries at a time and read with the transposing read, so
+// that dQ^T = K^T dS^T takes both operands from LDS in the layout the other kernels read V^T and K^T in.
+// What bounds it: at N = 128 memory (2048 heads, d = 64: 268 MB in 66.6 us, 4.0 TB/s; the two launches moved 402 MB in 83.9);
+// with few heads the latency of one head (96 heads of 128: 13.2 -> 8.6 us); at N > 128 a compute unit holds one workgroup, and
+// nothing covers its loads and stores from the second head on (256 heads of 197 27.0 -> 22.3 us, 1024 of 256 102 -> 107, not taken).
+#include "attn_common.h"
+#include "attn_tiles.h"
+
+namespace attn {
+namespace {
+
+constexpr int TILE = 64;
+
+// KW wavefronts: heads of up to 32 KW tokens (KW = 4 or 8)
+template <typename T, int D, bool CAUSAL, bool DROPOUT, int KW>
+__global__ __launch_bounds__(64 * KW, 2) void bwd_short_kernel(const KArgs a) {
+  typedef typename Vec<T>::x8 T8;
+  typedef typename Vec<T>::x4 T4;
+  constexpr int KK = D / 16, DB = D / 32;
+  // One LDS block.  Two Q tiles and two dO tiles of 64 queries (Q, dO, Q, dO; KW = 4: all there are, KW = 8: a double buffer), the
+  // K rows, dS of two tiles ([32 KW keys][64 queries], swizzled like a tile; KW = 8: one is read while the next is written), the
+  // row vectors, and (KW = 8) room for dQ rows on their way out.  KW = 4 at d = 64: dS of the second tile takes the place
+  // of the first tile's Q and dO, so that two workgroups fit on a compute unit.
+  constexpr int kQ = TILE * D, kS = 32 * KW * 64;   // elements
+  constexpr bool OVERLAY = KW == 4 && 2 * kQ >= kS;
+  constexpr int kElems = 4 * kQ + 32 * KW * D + (OVERLAY ? kS : 2 * kS) + (KW == 8 ? KW * 32 * 32 : 0);
+  __shared__ __attribute__((aligned(16))) unsigned char smem[kElems * sizeof(T) + 2 * 32 * KW * sizeof(float)];
+  T* const Q0 = (T*)smem;
+  T* const Kl = Q0 + 4 * kQ;
+  T* const S0 = Kl + 32 * KW * D;
+  T* const S1 = OVERLAY ? Q0 : S0 + kS;
+  float* const Lv = (float*)(smem + kElems * sizeof(T));   // base-2 row statistic
+  float* const Dv = Lv + 32 * KW;                          // -D_i
+  // dropout flags in this layout: see KeepLK in attn_common.h
+  __shared__ __attribute__((aligned(16))) uint32_t keep_table[DROPOUT ? KeepLK::kTable : 4];
+  KeepLK keep;
+  if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
+
+  const int bh = xcd_item(a.n_items, a.chunk);
+  if (bh < 0) return;
+  const int b = bh / a.H, h = bh % a.H;
+  const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, g = lane >> 5;
+  const int w0 = wave * 32;            // the wavefront's first key, and its first query
+  const int row = w0 + r;
+  const bool row_ok = row < a.N;
+  const int64_t row_off = head_off + (int64_t)min(row, a.N - 1) * a.sn;
+  const int len = a.klen ? min(max(a.klen[b], 0), a.N) : a.N;
+  const int n_tiles = (len + TILE - 1) / TILE;   // query tiles with a row that sees anything
+  const int dvalid = D == 32 ? a.dvalid : D;
+
+  TileAsync<T, D, 4> dma;   // four wavefronts copy a tile; of eight, the second four copy another one
+  const int half = KW == 8 ? wave >> 2 : 0;
+  dma.init(a.sn, wave & 3, dvalid);
+  if (D == 32 && a.dvalid < D) {   // the copies leave columns >= 16 of the tiles untouched
+    zero_tiles(Q0, 4 * kQ + 32 * KW * D);
+    __syncthreads();
+  }
+  const T* const Qg = (const T*)a.Q + head_off;
+  const T* const Gg = (const T*)a.dO + head_off;
+  const T* const Kg = (const T*)a.K + head_off;
+  auto fetch_tile = [&](int t, T* Qt) __attribute__((always_inline)) {
+    if (KW == 4 || half == 0) dma.copy_rows(Qg, a.sn, t * TILE, a.N, Qt);
+    if (KW == 4 || half == 1) dma.copy_rows(Gg, a.sn, t * TILE, a.N, Qt + kQ);
+  };
+  if (len > 0) fetch_tile(0, Q0);
+  if (KW == 4 && len > TILE) fetch_tile(1, Q0 + 2 * kQ);
+#pragma unroll
+  for (int t = 0; t < KW / 2; ++t)
+    if (t * TILE < len && (KW == 4 || half == (t & 1))) dma.copy_rows(Kg, a.sn, t * TILE, a.N, Kl + t * kQ);
+  // this lane's key (K and V fragments, B operands) and this lane's query (row statistic, -D from half of the row)
+  T8 kf[KK], vf[KK];
+  float d_part = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    const int64_t off = row_off + 16 * kk + 8 * g;
+    if (D == 32 && 16 * kk + 8 * g >= a.dvalid) {   // head dimension 16: the upper columns are zeros
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { kf[kk][e] = (T)0.f; vf[kk][e] = (T)0.f; }
+      continue;
+    }
+    kf[kk] = *(const T8*)((const T*)a.K + off);
+    vf[kk] = *(const T8*)((const T*)a.V + off);
+    const T8 go = *(const T8*)((const T*)a.dO + off);
+    if (a.o_fp32) {
+      const f32x4 o0 = *(const f32x4*)((const float*)a.O + off);
+      const f32x4 o1 = *(const f32x4*)((const float*)a.O + off + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d_part += (float)go[e] * o0[e] + (float)go[4 + e] * o1[e];
+    } else {
+      const T8 o = *(const T8*)((const T*)a.O + off);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d_part += (float)go[e] * (float)o[e];
+    }
+  }
+  const float lse = a.LSE[(int64_t)bh * a.N + min(row, a.N - 1)];
+  // a row that saw no key (or lies beyond a ragged end) has P = 0 everywhere
+  const float l2 = (lse == -INFINITY || !row_ok) ? INFINITY : lse * 1.4426950408889634f;
+  const float neg_d = row_ok ? -(d_part + xchg32(d_part)) : 0.f;
+  if (g == 0) {
+    Lv[row] = l2;
+    Dv[row] = neg_d;
+  }
+
+  f32x16 dv[DB], dk[DB];   // dV^T, dK^T (rows d, column = this lane's key)
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { dv[db][i] = 0.f; dk[db][i] = 0.f; }
+  TrOffsets<D> tro;
+  tro.init();
+  const float c = a.scale_log2;
+  wait_async_copies();
+  __syncthreads();
+
+  // LDS operand reads run PF fragments ahead of the MFMA that consumes them
+  constexpr int PF = 4;
+  // out[qb] = Tile[32 qb .. +31][:] . frags, starting from out
+  auto row_product = [&](const T* tile, const T8 (&bfrag)[KK], f32x16 (&out)[2]) {
+    auto frag = [&](int f) { return *(const T8*)(tile + lds_off<D>(32 * (f & 1) + r, 2 * (f >> 1) + g)); };  // f = 2 kk + qb
+    T8 ring[PF];
+#pragma unroll
+    for (int f = 0; f < PF; ++f) ring[f] = frag(f);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int f = 0; f < 2 * KK; ++f) {
+      const T8 cur = ring[f % PF];
+      out[f & 1] = mfma32(cur, bfrag[f >> 1], out[f & 1]);
+      if (f + PF < 2 * KK) ring[f % PF] = frag(f + PF);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // acc^T += Tile^T . frag   (contraction over the 64 queries of the tile)
+  auto col_product = [&](const T* tile, const T8 (&bfrag)[4], f32x16 (&acc)[DB]) {
+    auto frag = [&](int f) {   // f = DB cc + db: consecutive MFMAs hit different accumulators
+      const T* base = tile + 16 * (f / DB) * D;
+      return tr_frag<T8>(base + tro.off[f % DB][0], base + tro.off[f % DB][1]);
+    };
+    T8 ring[PF];
+#pragma unroll
+    for (int f = 0; f < PF; ++f) ring[f] = frag(f);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int f = 0; f < 4 * DB; ++f) {
+      const T8 cur = ring[f % PF];
+      acc[f % DB] = mfma32(cur, bfrag[f / DB], acc[f % DB]);
+      if (f + PF < 4 * DB) ring[f % PF] = frag(f + PF);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  auto tile_step = [&](const int i0, const T* const Qt, T* const St) __attribute__((always_inline)) {
+    const T* const Gt = Qt + kQ;
+    // hidden from the whole tile: keys beyond the length, or beyond the tile's last query
+    if (w0 >= len || (CAUSAL && i0 + TILE - 1 < w0)) return;
+    f32x16 s[2], dp[2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[qb][i] = 0.f;
+    row_product(Qt, kf, s);                // S = Q K^T
+    uint32_t kept = 0;   // the keep flags of this lane's key for the tile's 64 queries it holds
+    if constexpr (DROPOUT) kept = keep.draw<2>(i0, w0, bh, a.offset_lo, a.seed_lo, a.seed_hi);
+    // hidden entries get the logit -inf, hence P = 0: above the causal diagonal, or padded keys
+    if ((CAUSAL && i0 < w0 + 31) || w0 + 32 > len) {
+      const int first_query = row < len ? (CAUSAL ? row : 0) : 0x7fffffff;   // that sees this lane's key
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (i0 + 32 * qb + 8 * (i >> 2) + 4 * g + (i & 3) < first_query) s[qb][i] = -INFINITY;
+    }
+    T8 pf[4];
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4)
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        const f32x4 l4 = *(const f32x4*)(Lv + i0 + 32 * qb + 8 * i4 + 4 * g);
+        f32x4 d4 = {0.f, 0.f, 0.f, 0.f};   // without dropout dP starts from -D
+        if constexpr (!DROPOUT) d4 = *(const f32x4*)(Dv + i0 + 32 * qb + 8 * i4 + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * i4 + e;
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qb][i], c, -l4[e]));
+          s[qb][i] = p;
+          dp[qb][i] = d4[e];
+          const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
+          pf[cc][tt] = DROPOUT ? (T)keep_or_zero(p, KeepLK::mask(kept, qb, i4, e)) : (T)p;
+        }
+      }
+    col_product(Gt, pf, dv);               // dV^T += dO^T P_dropped
+    row_product(Gt, vf, dp);               // dP = dO V^T
+    T8 dsf[4];
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4)
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (DROPOUT) d4 = *(const f32x4*)(Dv + i0 + 32 * qb + 8 * i4 + 4 * g);   // -D_i
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * i4 + e;
+          const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
+          float dpv = dp[qb][i];
+          if constexpr (DROPOUT) dpv = dropped_dp_minus_d(dpv, a.keep_scale, KeepLK::mask(kept, qb, i4, e), d4[e]);
+          dsf[cc][tt] = (T)(s[qb][i] * dpv);
+        }
+      }
+    // dS for the wavefronts that own the queries: four queries 8 i4 + 4 g .. of this lane's key at a time
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        T4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = dsf[cc][4 * hb + e];
+        *(T4*)(St + lds_off<64>(row, 2 * cc + hb) + 4 * g) = v;
+      }
+    col_product(Qt, dsf, dk);              // dK^T += Q^T dS
+  };
+  TrOffsets<64> trs;
+  trs.init();
+  // dq[db] = (K^T dS^T)[d block DB0 + db] of the 32 queries from q0 on, block qb of the tile whose dS is St, over the
+  // 16-key chunks that any of them sees
+  auto dq_product = [&](const int q0, const int qb, const T* const St, const int db0, auto& dq) __attribute__((always_inline)) {
+    constexpr int NB = sizeof(dq) / sizeof(f32x16);
+#pragma unroll
+    for (int db = 0; db < NB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
+    const int n_keys = q0 < n_tiles * TILE ? (CAUSAL ? min(len, q0 + 32) : len) : 0;
+    const int s_lo = qb ? trs.off[1][0] : trs.off[0][0], s_hi = qb ? trs.off[1][1] : trs.off[0][1];
+#pragma unroll
+    for (int cc = 0; cc < 2 * KW; ++cc) {
+      if (16 * cc >= n_keys) break;
+      const T8 ds = tr_frag<T8>(St + 16 * cc * 64 + s_lo, St + 16 * cc * 64 + s_hi);
+      const T* const base = Kl + 16 * cc * D;
+#pragma unroll
+      for (int db = 0; db < NB; ++db) {
+        const int k_lo = NB == DB || db0 == 0 ? tro.off[db][0] : tro.off[DB - 1][0], k_hi = NB == DB || db0 == 0 ? tro.off[db][1] : tro.off[DB - 1][1];
+        dq[db] = mfma32(tr_frag<T8>(base + k_lo, base + k_hi), ds, dq[db]);
+      }
+    }
+  };
+  const int64_t out_row0 = head_off + (int64_t)w0 * a.sn;
+  if constexpr (KW == 4) {
+    if (n_tiles > 0) tile_step(0, Q0, S0);
+    __syncthreads();   // everyone is done with the first Q and dO
+    if (n_tiles > 1) tile_step(TILE, Q0 + 2 * kQ, S1);
+    __syncthreads();   // dS is complete, the second Q and dO are free: they stage the output rows
+  } else {
+    // dQ of tile j - 1 beside tile j: a tile's 2 DB blocks of 32 x 32 are the work of as many wavefronts, which take turns
+    constexpr int TURNS = KW / (2 * DB);
+    const int turn = wave / (2 * DB), qb = wave & 1, db = DB == 2 ? (wave >> 1) & 1 : 0;
+    T* const stage = S1 + kS + wave * 32 * 32;
+    for (int j = 0; j <= n_tiles; ++j) {
+      if (j + 1 < n_tiles) fetch_tile(j + 1, Q0 + 2 * ((j + 1) & 1) * kQ);
+      if (j < n_tiles) tile_step(j * TILE, Q0 + 2 * (j & 1) * kQ, j & 1 ? S1 : S0);
+      if (j > 0 && turn == (j - 1) % TURNS) {
+        const int q0 = (j - 1) * TILE + 32 * qb;
+        f32x16 dq[1];
+        dq_product(q0, qb, j & 1 ? S0 : S1, db, dq);
+        store_rows_coalesced<T, 32>(stage, (T*)a.dQ + head_off + (int64_t)q0 * a.sn + 32 * db, a.sn, dq, a.tau, a.N - q0, dvalid);
+      }
+      wait_async_copies();
+      __syncthreads();
+    }
+  }
+  T* const stage = KW == 4 ? Q0 + 2 * kQ + wave * 32 * D : Q0 + wave * 32 * D;
+  store_rows_coalesced<T, D>(stage, (T*)a.dV + out_row0, a.sn, dv, DROPOUT ? a.keep_scale : 1.f, a.N - w0, dvalid);
+  __builtin_amdgcn_wave_barrier();
+  store_rows_coalesced<T, D>(stage, (T*)a.dK + out_row0, a.sn, dk, a.tau, a.N - w0, dvalid);
+  __builtin_amdgcn_wave_barrier();
+  if (KW == 4 || w0 >= n_tiles * TILE) {   // KW = 8: rows of tiles that see nothing
+    f32x16 dq[DB];
+    dq_product(w0, wave & 1, wave < 2 ? S0 : S1, 0, dq);
+    store_rows_coalesced<T, D>(stage, (T*)a.dQ + out_row0, a.sn, dq, a.tau, a.N - w0, dvalid);
+  }
+}
+
+template <typename T, int D, int KW>
+int launch_kw(const KArgs& a, bool causal, bool dropout, hipStream_t s) {
+  const dim3 grid(kXcds * a.chunk), block(64 * KW);
+  if (causal && dropout) hipLaunchKernelGGL((bwd_short_kernel<T, D, true, true, KW>), grid, block, 0, s, a);
+  else if (causal) hipLaunchKernelGGL((bwd_short_kernel<T, D, true, false, KW>), grid, block, 0, s, a);
+  else if (dropout) hipLaunchKernelGGL((bwd_short_kernel<T, D, false, true, KW>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((bwd_short_kernel<T, D, false, false, KW>), grid, block, 0, s, a);
+  return (int)hipGetLastError();
+}
+
+template <typename T, int D>
+int launch_td(const KArgs& a, bool causal, bool dropout, hipStream_t s) {
+  return a.N <= 128 ? launch_kw<T, D, 4>(a, causal, dropout, s) : launch_kw<T, D, 8>(a, causal, dropout, s);
+}
+
+}  // namespace
+
+// us of the backward pass, two launches (divided over wavefront groups where there are few heads) | this kernel; heads x N, d = 64:
+//   N <= 128  1 x 128 12.1 | 7.9, 96 x 128 13.2 | 8.6, 2048 x 128 83.9 | 66.6, causal with dropout 91.7 | 70.5; 4032 x 65 116 | 85; 96 x 1 10.4 | 6.0
+//   three tiles  16 x 150 15.3 | 14.1, causal 23.1 | 13.2; 256 x 150 22.9 | 17.2; 1024 x 150 75.4 | 67.3, causal with dropout 80.2 | 80.7; 1600 x 129 110 | 102
+//   four tiles  16 x 197 14.3 | 17.6, causal 23.0 | 16.5; 96 x 197 18.9 | 18.7, dropout 21.7 | 22.9; 96 x 256 19.0 | 20.7, causal 25.0 | 19.5;
+//     200 x 256 26.8 | 26.0, causal 32.7 | 23.9; 256 x 197 27.0 | 22.3; 400 x 197 47.3 | 41.3, causal with dropout 49.0 | 47.7; 1024 x 197 92.5 | 88.1,
+//     causal with dropout 95.9 | 99.9; 400 x 256 50.2 | 52.2; 1024 x 256 102 | 107
+//   d = 32  16 x 150 12.9 | 11.6; 96 x 197 13.8 | 15.2, causal 15.3 | 13.2; 200 x 197 18.3 | 15.7; 200 x 256 18.8 | 18.2; 400 x 197 31.2 | 29.5; 400 x 256 33.6 | 37.8
+bool bwd_short_is_faster(const KArgs& a, int d, bool causal) {
+  if (d > 64 || a.N > 256) return false;
+  if (a.N <= 3 * TILE) return true;
+  const int64_t heads = (int64_t)a.B * a.H;
+  if (heads > kComputeUnits) return a.N <= 208 && heads <= 2 * kComputeUnits;
+  return causal || heads >= (d == 64 && a.N <= 208 ? 80 : 160);   // fewer: the two launches' divided blocks fill more of the chip
+}
+
+int launch_bwd_short(const KArgs& a_in, int dtype, int d, bool causal, bool dropout, hipStream_t s) {
+  KArgs a = a_in;
+  a.n_items = a.B * a.H;   // a workgroup per head
+  a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  if (dtype == 0 && d == 32) return launch_td<_Float16, 32>(a, causal, dropout, s);
+  if (dtype == 1 && d == 32) return launch_td<__bf16, 32>(a, causal, dropout, s);
+  if (dtype == 0 && d == 64) return launch_td<_Float16, 64>(a, causal, dropout, s);
+  if (dtype == 1 && d == 64) return launch_td<__bf16, 64>(a, causal, dropout, s);
+  return (int)hipErrorInvalidValue;
+}
+
+}  // namespace attn

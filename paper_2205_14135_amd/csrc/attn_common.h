@@ -64,7 +64,7 @@ int dkv_variant();
 
 // Which kernel serves a problem (the launchers use these; attn_debug_kernel_choice reports them).
 enum { kFwdFreeRunning = 0, kFwdTwoGroup = 1 };
-enum { kDkvRoleSplit = 0, kDkvOneWave = 1, kDkvOneWave128 = 2, kDkvOneWave64 = 3 };
+enum { kDkvRoleSplit = 0, kDkvOneWave = 1, kDkvOneWave128 = 2, kDkvOneWave64 = 3, kBwdShort = 4 };
 int choose_fwd(const KArgs& a, int d, bool causal, bool dropout, bool sparse);
 int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse);
 
@@ -104,6 +104,9 @@ int launch_dkv_fr(const KArgs& a, int dtype, int d, bool causal, bool dropout, b
 int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, hipStream_t s);
 // the same with 64 keys per wavefront and the accumulators in the accumulation registers (attn_bwd_dkv_w64.hip)
 int launch_dkv_w64(const KArgs& a, int dtype, bool causal, hipStream_t s);
+// the whole backward pass of short dense heads at d <= 64, one launch (attn_bwd_short.hip), and which heads take it
+bool bwd_short_is_faster(const KArgs& a, int d, bool causal);
+int launch_bwd_short(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);
 // dense forward with two wavefront groups in ping-pong (attn_fwd_pp.hip); sets its own work items
 int launch_fwd_pp(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);
 // MFMA-only kernel for measuring the sustained matrix rate (attn_probe.hip); *flops = FLOPs launched
