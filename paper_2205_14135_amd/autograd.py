@@ -12,6 +12,7 @@ import math
 from typing import Optional
 
 import torch
+from torch.autograd import forward_ad
 
 from . import binding
 
@@ -61,5 +62,13 @@ def flash_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, softma
         softmax_scale = 1.0 / math.sqrt(q.shape[-1])
     if dropout_p > 0.0 and seed is None:
         seed = int(torch.randint(0, 2 ** 62, (), dtype=torch.int64).item())
-    return _FlashAttention.apply(q, k, v, float(softmax_scale), bool(causal), float(dropout_p),
-                                 int(seed or 0), int(offset), key_lengths, block_mask)
+    if binding._lib is None:
+        binding.load()
+    # The node in Python stays for what has rules of its own for functions written in Python: functorch's transforms, forward-mode
+    # differentiation, tracing and compilation.
+    if (torch.compiler.is_compiling() or torch._C._are_functorch_transforms_active() or forward_ad._current_level >= 0
+            or torch.jit.is_tracing()):
+        apply = _FlashAttention.apply
+    else:
+        apply = binding._marshal.attention
+    return apply(q, k, v, float(softmax_scale), bool(causal), float(dropout_p), int(seed or 0), int(offset), key_lengths, block_mask)

@@ -5,6 +5,10 @@
 // thread with cold caches; a small problem's kernels take 5 to 10 us each.  A pass with the one binding and with the other, over
 // the same library, in turn: one forward call of one head of 128 tokens 9.5 -> 4.6 us, a training step of 96 heads of 197 tokens
 // 149 -> 85 us (4 % between runs), of a padded batch of 128 heads of up to 700 tokens 147 -> 86 us (6 %).
+// The autograd node of flash_attention (paper_2205_14135_amd/autograd.py) is here too: the engine runs backwards on a thread
+// of its own, and a node in Python waits there for the interpreter lock, twice, with cold caches.  Host time of a training step of 96
+// heads of 197 tokens, node in Python | here: 82 | 64 us, or 39 | 34 where the machine happens to run both threads close together (33 us
+// and more of either are the engine's own change of threads: so much takes the backward of a single product).
 // The functions take positional arguments only (binding.py holds the public signatures and
 // defaults) and raise what the Python marshalling of the measurement entry points raises: ValueError, TypeError, AttnError.
 #define PY_SSIZE_T_CLEAN
@@ -13,6 +17,7 @@
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
@@ -175,6 +180,123 @@ PyObject* tuple(std::initializer_list<PyObject*> items) {   // takes the referen
   return t;
 }
 
+// ---- autograd: the forward call keeps what the backward one needs (the O(N) state: O, the row statistic and the generator state)
+
+// What a backward call takes from its forward call beside the saved tensors.
+struct Attention {
+  attn_params p;            // pointers (stream, key lengths) are set again for each call
+  at::Tensor key_lengths, block_mask;
+};
+
+attn_params on_current_stream(const Attention& a, const at::Tensor& q) {
+  attn_params p = a.p;
+  p.stride_b = q.stride(0); p.stride_h = q.stride(1); p.stride_n = q.stride(2);
+  p.stream = (void*)c10::hip::getCurrentHIPStream(q.device().index()).stream();
+  p.key_lengths = a.key_lengths.defined() ? (const int32_t*)a.key_lengths.data_ptr() : nullptr;
+  return p;
+}
+int64_t mask_stride(const at::Tensor& mask) { return mask.dim() == 3 ? mask.stride(0) : 0; }
+
+// A refusal of the library on the engine's thread: AttnError, carried to the caller of backward().
+[[noreturn]] void refused_in_backward(int status, const char* where) {
+  const PyGILState_STATE gil = PyGILState_Ensure();
+  python_error e;
+  try {
+    check_status(status, where);
+  } catch (const Raised&) {
+    e.persist();
+  }
+  PyGILState_Release(gil);
+  throw e;
+}
+
+using torch::autograd::AutogradContext;
+using torch::autograd::variable_list;
+
+struct FlashAttention : torch::autograd::Function<FlashAttention> {
+  static at::Tensor forward(AutogradContext* ctx, const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const Attention& a) {
+    const bool sparse = a.block_mask.defined();
+    const attn_params p = on_current_stream(a, q);
+    const at::Tensor out = like(q, q.scalar_type()), lse = at::empty(q.sizes().slice(0, 3), q.options().dtype(at::kFloat));
+    const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr();
+    void* op = out.data_ptr();
+    float* lp = (float*)lse.data_ptr();
+    check_status(without_gil([&] {
+      return sparse ? lib.sparse_fwd(&p, (const uint8_t*)a.block_mask.data_ptr(), 128, mask_stride(a.block_mask), qp, kp, vp, op, lp)
+                    : lib.fwd(&p, qp, kp, vp, op, lp);
+    }), sparse ? "attn_blocksparse_fwd" : "attn_fwd");
+    ctx->save_for_backward({q, k, v, out, lse});
+    auto& data = ctx->saved_data;
+    data["softmax_scale"] = (double)a.p.softmax_scale;
+    data["causal"] = a.p.causal != 0;
+    data["dropout_p"] = (double)a.p.dropout_p;
+    data["seed"] = (int64_t)a.p.seed;
+    data["offset"] = (int64_t)a.p.offset;
+    if (a.key_lengths.defined()) data["key_lengths"] = a.key_lengths;
+    if (sparse) data["block_mask"] = a.block_mask;
+    return out;
+  }
+
+  static variable_list backward(AutogradContext* ctx, const variable_list& d_outs) {
+    const variable_list saved = ctx->get_saved_variables();
+    const at::Tensor &q = saved[0], &k = saved[1], &v = saved[2], &out = saved[3], &lse = saved[4];
+    at::Tensor d_out = d_outs[0];
+    if (d_out.sizes() != q.sizes() || d_out.strides() != q.strides())   // the library addresses dO with the strides of q
+      d_out = like(q, q.scalar_type()).copy_(d_out);
+    auto& data = ctx->saved_data;
+    Attention a = {};
+    a.p.B = (int32_t)q.size(0); a.p.H = (int32_t)q.size(1); a.p.N = (int32_t)q.size(2); a.p.d = (int32_t)q.size(3);
+    a.p.dtype = q.scalar_type() == at::kHalf ? ATTN_FP16 : ATTN_BF16;
+    a.p.softmax_scale = (float)data["softmax_scale"].toDouble();
+    a.p.causal = data["causal"].toBool();
+    a.p.dropout_p = (float)data["dropout_p"].toDouble();
+    a.p.seed = (uint64_t)data["seed"].toInt();
+    a.p.offset = (uint64_t)data["offset"].toInt();
+    if (data.count("key_lengths")) a.key_lengths = data["key_lengths"].toTensor();
+    if (data.count("block_mask")) a.block_mask = data["block_mask"].toTensor();
+    const bool sparse = a.block_mask.defined();
+    const attn_params p = on_current_stream(a, q);
+    at::Tensor g[3];
+    for (at::Tensor& t : g) t = like(q, q.scalar_type());
+    const size_t need = sparse ? lib.sparse_workspace_bytes(&p) : lib.workspace_bytes(&p);
+    const at::Tensor ws = at::empty({(int64_t)std::max<size_t>(need, 256)}, q.options().dtype(at::kByte));
+    const float* lp = (const float*)lse.data_ptr();
+    const int status =
+        sparse ? lib.sparse_bwd(&p, (const uint8_t*)a.block_mask.data_ptr(), 128, mask_stride(a.block_mask), q.data_ptr(), k.data_ptr(), v.data_ptr(),
+                                out.data_ptr(), d_out.data_ptr(), lp, g[0].data_ptr(), g[1].data_ptr(), g[2].data_ptr(), ws.data_ptr(), ws.numel())
+               : lib.bwd(&p, q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), d_out.data_ptr(), lp, g[0].data_ptr(), g[1].data_ptr(),
+                         g[2].data_ptr(), ws.data_ptr(), ws.numel());
+    if (status != ATTN_OK) refused_in_backward(status, sparse ? "attn_blocksparse_bwd" : "attn_bwd");
+    return {g[0], g[1], g[2], at::Tensor()};
+  }
+};
+
+// attention(Q, K, V, softmax_scale, causal, dropout_p, seed, offset, key_lengths, block_mask) -> O, differentiable
+PyObject* py_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject* {
+    expect_args(n, 10);
+    const at::Tensor &q = tensor(a[0]), &k = tensor(a[1]), &v = tensor(a[2]);
+    same_layout(q, k);
+    same_layout(q, v);
+    Attention at = {};
+    at.p = make_params(a[0], {a[3], a[4], a[5], a[6], a[7], Py_False, Py_None, a[8]});
+    if (a[8] != Py_None) at.key_lengths = tensor(a[8]);
+    if (a[9] != Py_None) {
+      PyObject* block = PyLong_FromLong(128);
+      if (block == nullptr) throw Raised();
+      try {
+        mask_args(a[9], block, q.size(1));
+      } catch (...) {
+        Py_DECREF(block);
+        throw;
+      }
+      Py_DECREF(block);
+      at.block_mask = tensor(a[9]);
+    }
+    return wrap(FlashAttention::apply(q, k, v, at));
+  });
+}
+
 // fwd(Q, K, V, <options>, out, lse[, block_mask, mask_block]) -> (O, LSE)
 PyObject* forward(PyObject* const* a, Py_ssize_t n, bool sparse) {
   return guarded([&]() -> PyObject* {
@@ -265,6 +387,7 @@ PyObject* py_attach(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 PyMethodDef methods[] = {
     {"attach", (PyCFunction)(void*)py_attach, METH_FASTCALL, nullptr},
+    {"attention", (PyCFunction)(void*)py_attention, METH_FASTCALL, nullptr},
     {"fwd", (PyCFunction)(void*)py_fwd, METH_FASTCALL, nullptr},
     {"bwd", (PyCFunction)(void*)py_bwd, METH_FASTCALL, nullptr},
     {"blocksparse_fwd", (PyCFunction)(void*)py_sparse_fwd, METH_FASTCALL, nullptr},
