@@ -114,7 +114,7 @@ WsLayout ws_layout(const attn_params* p) {
   const size_t T = ((size_t)p->N + attn::kMaskBlock - 1) / attn::kMaskBlock;
   // two floats per row, rows padded to whole 128-blocks per head
   w.d_bytes = align_up(2 * (size_t)p->B * p->H * T * attn::kMaskBlock * sizeof(float), 256);
-  // column counts, then the segment list: one counter plus at most kMaxSegs entries per column
+  // column counts, tickets and segment counts (a third of this would do; the size is part of what callers see)
   w.cnt_bytes = align_up(((size_t)p->B * p->H * T * (1 + attn::kMaxSegs) + 64) * sizeof(int), 256);
   const size_t d_kernel = p->d == 16 ? 32 : p->d;   // the fp32 accumulators have the kernels' row length
   w.acc_bytes = align_up((size_t)p->B * p->H * p->N * d_kernel * sizeof(float), 256);
@@ -159,8 +159,11 @@ int bwd_common(const attn_params* p, const uint8_t* mask, int64_t mask_sh, bool 
   c.k.L2vec = c.k.Dvec + (size_t)p->B * p->H * c.k.Nr;
   if (sparse) {
     const WsLayout w = ws_layout(p);
-    c.k.seglist = (int*)((char*)ws + w.d_bytes);
-    c.k.colcnt = c.k.seglist + 64 + (size_t)p->B * p->H * (p->N / attn::kMaskBlock) * attn::kMaxSegs;
+    const size_t cols = (size_t)p->B * p->H * (p->N / attn::kMaskBlock);
+    c.k.colcnt = (int*)((char*)ws + w.d_bytes);
+    c.k.col_segs = c.k.colcnt + cols;
+    c.k.ticket = c.k.col_segs + cols;
+    c.k.group_segs = c.k.ticket + cols;
     c.k.dKacc = (float*)((char*)ws + w.d_bytes + w.cnt_bytes);
     c.k.dVacc = (float*)((char*)ws + w.d_bytes + w.cnt_bytes + w.acc_bytes);
   }

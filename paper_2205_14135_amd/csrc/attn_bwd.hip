@@ -16,6 +16,7 @@
 // S and dP are therefore recomputed in both launches (seven tile products per (i, j) instead of
 // five) in exchange for no atomics, no fp32 dQ round trip and bit-reproducible gradients.
 #include "attn_common.h"
+#include "attn_sparse.h"
 #include "attn_tiles.h"
 
 #include <cstdlib>
@@ -63,7 +64,14 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
     all = Ks;
   }
 
-  const int item = xcd_item(a.n_items, a.chunk);
+  if constexpr (SPARSE) {
+    // the first workgroups plan the dK/dV launch (a multiple of the XCD count of them)
+    if ((int)blockIdx.x < a.plan_groups) {
+      sparse_plan<D>(a, (int)blockIdx.x, CAUSAL, (int*)all);
+      return;
+    }
+  }
+  const int item = xcd_item(a.n_items, a.chunk, SPARSE ? (int)blockIdx.x - a.plan_groups : (int)blockIdx.x);
   if (item < 0) return;
   const int n_qt = a.T * (4 / RW);   // blocks of BR rows, to the end of the last 128-row block: the scratch vectors are written whole
   // Work item = (head, row block).  Under the causal mask row block q sweeps 2 (q + 1) key tiles;
@@ -139,10 +147,6 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
   if (g == 0 && (KG == 1 || group == 0)) {
     a.Dvec[(int64_t)bh * a.Nr + q0 + r] = neg_d;
     a.L2vec[(int64_t)bh * a.Nr + q0 + r] = l2;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && pass == 0 && a.seglist != nullptr) {
-    a.seglist[0] = 0;   // block-sparse: empty segment list, no blocks counted (the dK/dV planning
-    a.seglist[1] = 0;   // kernels run after this one)
   }
 
   f32x16 dq[DB];
@@ -344,7 +348,8 @@ int launch_dq(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
     const int64_t fit = ((int64_t)8 << 20) / kv_bytes;
     a.group = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
   }
-  const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
+  if (sparse) a.plan_groups = sparse_plan_groups(a);
+  const dim3 grid(kXcds * a.chunk + (sparse ? a.plan_groups : 0)), block(64 * RW * KG);
 #define ATTN_DQ_CASE(C, P, S)                                                          \
   if (causal == C && dropout == P && sparse == S) {                                    \
     hipLaunchKernelGGL((dq_kernel<T, D, C, P, S, RW, KG>), grid, block, 0, s, a);      \

@@ -21,6 +21,7 @@
 // LDS: Q and D x4 (tile j is read by A in iteration j and by B in iteration j+1, tile j+2 is
 // being written), dO and L x3, P exchange x2.
 #include "attn_common.h"
+#include "attn_sparse.h"
 #include "attn_tiles.h"
 
 #include <cstdlib>
@@ -57,8 +58,8 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
   // visited by N/64 - 2k query tiles, so a workgroup takes the pair (k, n_kt - 1 - k), one per
   // round, and all workgroups do the same amount of work.  Block-sparse: the first 8 * chunk
   // workgroups take one mask column each and leave the heavy ones (many kept blocks, e.g. a
-  // global-token column) alone; those were cut into segments by sparse_plan_kernel and the
-  // remaining workgroups walk that segment list.
+  // global-token column) alone; those are cut into segments (attn_sparse.h), which the
+  // remaining workgroups walk.
   const int n_col_groups = kXcds * a.chunk;
   // (the list workgroups come first in the grid, a multiple of the XCD count of them, so that the
   // long segments start with the launch instead of queueing behind every column)
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
     item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
     if (item < 0) return;
     if constexpr (SPARSE) {
-      if (a.colcnt[item] > a.seglist[2]) return;
+      if (n_list > 0 && a.col_segs[item] > 0) return;   // heavy
     }
     if constexpr (PAIRED) {
       const int q = item % n_pair;
@@ -81,16 +82,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
       item = (item / n_pair) * n_kt + (round == 0 ? q : n_kt - 1 - q);
     }
   } else {
-    const int idx = (int)blockIdx.x + round * n_list;
-    if (idx >= a.seglist[0]) return;
-    const int e = a.seglist[kSegHeader + idx];
-    item = e / kMaxSegs;
-    const int seg = e % kMaxSegs;
-    const int cnt = a.colcnt[item];
-    const int nseg = min((int)kMaxSegs, (cnt + kSegBlocks - 1) / kSegBlocks);
-    const int len = (cnt + nseg - 1) / nseg;
-    skip_blocks = seg * len;
-    take_blocks = len;
+    if (!sparse_segment((int)blockIdx.x + round * n_list, item, skip_blocks, take_blocks)) return;
     heavy = true;
   }
   const int bh = item / n_kt;
@@ -321,7 +313,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
 
   const float out_scale = role_b ? a.tau : (DROPOUT ? a.keep_scale : 1.f);
   if (SPARSE && heavy) {
-    // one of several segments of this column: sum in fp32; sparse_finish_kernel converts.  The four
+    // one of several segments of this column: sum in fp32; the last of them converts.  The four
     // Q buffers stage 32 x D floats for each of four wavefronts: role A's dV first, then role B's dK
     __syncthreads();   // role B has finished reading the tiles
     float* stage = (float*)&Qs[0][0] + pair * 32 * D;
@@ -335,109 +327,11 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
     store_rows_coalesced<T, D>(stage, (T*)(role_b ? a.dK : a.dV) + head_off + (int64_t)kw0 * a.sn, a.sn, acc,
                                out_scale, a.N - kw0);
   }
+  if constexpr (SPARSE)
+    if (heavy) sparse_finish<T, D>(item);
   if (!list_mode && last_round) return;
   __syncthreads();   // LDS is reused by the next segment / key block
   }  // for round
-}
-
-// Block-sparse preparation, step 1: kept blocks per mask column (rows >= column under a causal
-// mask) and their total.  One 1024-thread group per (bh, 64 consecutive columns): thread = (column,
-// one of 16 row groups), so that the 64 lanes of a wavefront read 64 consecutive mask bytes of one
-// row (a thread per column entry of one column reads one byte per 64-byte line).
-constexpr int kCountRowGroups = 16;
-__global__ __launch_bounds__(64 * kCountRowGroups) void sparse_count_kernel(const KArgs a) {
-  __shared__ int part[kCountRowGroups][64];
-  const int n_kt = a.T;
-  const int n_cg = (n_kt + 63) / 64;
-  const int bh = blockIdx.x / n_cg, cg = blockIdx.x % n_cg;
-  const int h = bh % a.H;
-  const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
-  const int kt = cg * 64 + c;
-  const int len = a.klen ? min(max(a.klen[bh / a.H], 0), a.N) : a.N;
-  int cnt = 0;
-  if (kt < n_kt) {
-    const uint8_t* col = a.mask + (int64_t)h * a.mask_sh + kt;
-    const int first = a.causal ? kt : 0;                                     // same row range as the
-    const int limit = kt * 128 >= len ? 0 : min(a.T, (len + 127) / 128);     // tile iterators of the dK/dV kernels
-    for (int blk = first + rg; blk < limit; blk += kCountRowGroups) cnt += col[(int64_t)blk * a.T] != 0;
-  }
-  part[rg][c] = cnt;
-  __syncthreads();
-  if (rg == 0) {   // one wavefront: the column totals, then their sum as ONE atomic per workgroup
-#pragma unroll
-    for (int g = 1; g < kCountRowGroups; ++g) cnt += part[g][c];
-    if (kt < n_kt) a.colcnt[bh * n_kt + kt] = cnt;
-    int sum = kt < n_kt ? cnt : 0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
-    if (c == 0 && sum > 0) atomicAdd(a.seglist + 1, sum);
-  }
-}
-
-// Step 2: the heavy threshold, the segment list of the heavy columns and zeroed fp32
-// accumulators for them.  One 256-thread group per kPlanCols consecutive columns (bh, kt): most
-// columns are light and need one comparison, so a group per column would be launch overhead only.
-constexpr int kPlanCols = 16;
-template <int D>
-__global__ __launch_bounds__(256) void sparse_plan_kernel(const KArgs a) {
-  __shared__ int heavy_col[kPlanCols];
-  const int n_kt = a.T;
-  const int n_cols = a.B * a.H * n_kt;
-  const int first = blockIdx.x * kPlanCols;
-  const int thr = max((int)kHeavyBlocks, a.seglist[1] / (2 * kComputeUnits));
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.seglist[2] = thr;
-  if (threadIdx.x < kPlanCols) {
-    const int item = first + (int)threadIdx.x;
-    const int cnt = item < n_cols ? a.colcnt[item] : 0;
-    heavy_col[threadIdx.x] = cnt > thr;
-    if (cnt > thr) {
-      const int nseg = min((int)kMaxSegs, (cnt + kSegBlocks - 1) / kSegBlocks);
-      const int at = atomicAdd(a.seglist, nseg);
-      for (int sgi = 0; sgi < nseg; ++sgi) a.seglist[kSegHeader + at + sgi] = item * kMaxSegs + sgi;
-    }
-  }
-  __syncthreads();
-  for (int cidx = 0; cidx < kPlanCols; ++cidx) {
-    if (!heavy_col[cidx]) continue;
-    const int item = first + cidx;
-    const int bh = item / n_kt, kt = item % n_kt;
-    const int64_t off = ((int64_t)bh * a.N + (int64_t)kt * 128) * D;
-    for (int i = threadIdx.x; i < 128 * D / 4; i += 256) {
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      *(f32x4*)(a.dKacc + off + 4 * i) = z;
-      *(f32x4*)(a.dVacc + off + 4 * i) = z;
-    }
-  }
-}
-
-// Block-sparse finish: dK, dV of the split columns, fp32 accumulators -> 16-bit outputs (same
-// grouping of columns as the plan kernel).
-template <typename T, int D>
-__global__ __launch_bounds__(256) void sparse_finish_kernel(const KArgs a) {
-  typedef typename Vec<T>::x4 T4;
-  const int n_kt = a.T;
-  const int n_cols = a.B * a.H * n_kt;
-  const int thr = a.seglist[2];
-  for (int cidx = 0; cidx < kPlanCols; ++cidx) {
-    const int item = blockIdx.x * kPlanCols + cidx;
-    if (item >= n_cols) return;
-    if (a.colcnt[item] <= thr) continue;
-    const int bh = item / n_kt, kt = item % n_kt;
-    const int64_t head_off = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-    const int64_t acc_off = ((int64_t)bh * a.N + (int64_t)kt * 128) * D;
-    for (int i = threadIdx.x; i < 128 * D / 4; i += 256) {
-      const int row = (4 * i) / D, colx = (4 * i) % D;
-      const f32x4 k4 = *(const f32x4*)(a.dKacc + acc_off + 4 * i);
-      const f32x4 v4 = *(const f32x4*)(a.dVacc + acc_off + 4 * i);
-      T4 ko, vo;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { ko[e] = (T)k4[e]; vo[e] = (T)v4[e]; }
-      const int64_t o = head_off + (int64_t)(kt * 128 + row) * a.sn + colx;
-      if (D == 32 && colx >= a.dvalid) continue;   // head dimension 16: the tensors' rows end there
-      *(T4*)((T*)a.dK + o) = ko;
-      *(T4*)((T*)a.dV + o) = vo;
-    }
-  }
 }
 
 // dK/dV override 1 keeps the role-split kernel at every head dimension (comparisons and tests)
@@ -445,38 +339,20 @@ bool force_role_split() { return dkv_variant() == 1; }
 
 template <typename T, int D>
 int launch_td(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
-  const int cols = a.B * a.H * a.T;
-  if (sparse) {
-    a.causal = causal;
-    hipLaunchKernelGGL(sparse_count_kernel, dim3(a.B * a.H * ((a.T + 63) / 64)), dim3(64 * kCountRowGroups), 0, s, a);
-    hipLaunchKernelGGL((sparse_plan_kernel<D>), dim3((cols + kPlanCols - 1) / kPlanCols), dim3(256), 0, s, a);
-    const int e = (int)hipGetLastError();
-    if (e != 0) return e;
-  }
-  // block-sparse: kListGroups extra workgroups walk the list of heavy-column segments
+  const int list_groups = sparse && sparse_plan_groups(a) > 0 ? kListGroups : 0;   // walk the segments of heavy columns
   if (causal && !sparse) {   // items are pairs of key blocks
     a.n_items = a.B * a.H * ((a.T + 1) / 2);
     a.chunk = (a.n_items + kXcds - 1) / kXcds;
   }
   if (sparse && choose_dkv(a, D, causal, dropout, sparse) == kDkvOneWave) {
     // d <= 64: the kernel in which one wavefront does all four products, same work assignment
-    int e = launch_dkv_fr(a, std::is_same<T, __bf16>::value ? 1 : 0, D, causal, dropout, true, kListGroups, s);
-    if (e == 0) {
-      hipLaunchKernelGGL((sparse_finish_kernel<T, D>), dim3((cols + kPlanCols - 1) / kPlanCols), dim3(256), 0, s, a);
-      e = (int)hipGetLastError();
-    }
-    return e;
+    return launch_dkv_fr(a, std::is_same<T, __bf16>::value ? 1 : 0, D, causal, dropout, true, list_groups, s);
   }
-  const dim3 grid(kXcds * a.chunk + (sparse ? kListGroups : 0)), block(NT);
+  const dim3 grid(kXcds * a.chunk + list_groups), block(NT);
 #define ATTN_DKV_CASE(C, P, S)                                                    \
   if (causal == C && dropout == P && sparse == S) {                               \
     hipLaunchKernelGGL((dkv_rs_kernel<T, D, C, P, S>), grid, block, 0, s, a);     \
-    int e = (int)hipGetLastError();                                               \
-    if (e == 0 && S) {                                                            \
-      hipLaunchKernelGGL((sparse_finish_kernel<T, D>), dim3((cols + kPlanCols - 1) / kPlanCols), dim3(256), 0, s, a); \
-      e = (int)hipGetLastError();                                                 \
-    }                                                                             \
-    return e;                                                                     \
+    return (int)hipGetLastError();                                                \
   }
   ATTN_DKV_CASE(false, false, false)
   ATTN_DKV_CASE(true, false, false)
@@ -496,8 +372,7 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
   // short heads: one workgroup has all of a head's keys, and both launches become one
   if (!sparse && dkv_variant() == 0 && bwd_short_is_faster(a, d, causal)) return kBwdShort;
   // Problems with d <= 64 take the kernel in which one wavefront does all four products
-  // (attn_bwd_dkv_fr.hip; the block-sparse ones from inside launch_td, between the column
-  // planning and the finish kernel).
+  // (attn_bwd_dkv_fr.hip; the block-sparse ones from inside launch_td).
   // (head dimension 16 exists in that kernel only)
   if (d <= 64 && (!force_role_split() || a.dvalid < d)) return kDkvOneWave;
   // d = 128, dense: the one-wavefront kernel with the V block in LDS (attn_bwd_dkv_fr128.hip)
@@ -517,6 +392,10 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
     const bool w64 = dkv_variant() == 3 || (dkv_variant() == 0 && !causal && a.N >= 2048 && blocks > kComputeUnits);
     return w64 && !dropout && a.N >= 512 && a.N % 32 == 0 ? kDkvOneWave64 : kDkvOneWave128;
   }
+  // d = 128, block-sparse: the one-wavefront kernel as well (us of the backward pass, role-split | one wavefront, butterfly mask of heads x T:
+  // 2 x 8 51 | 48, 4 x 16 78 | 71, 8 x 64 186 | 160, 8 x 128 351 | 287, causal 251 | 194, 4 x 200 312 | 246).  Above that, where no more than
+  // 64 heads of 32 blocks and 8 of 512 were looked at, the role-split kernel stays.
+  if (sparse && d == 128 && !force_role_split() && blocks < 8 * kComputeUnits) return kDkvOneWave128;
   return kDkvRoleSplit;
 }
 
@@ -524,7 +403,7 @@ int launch_dkv_rs(const KArgs& a, int dtype, int d, bool causal, bool dropout, b
   const int choice = choose_dkv(a, d, causal, dropout, sparse);
   if (!sparse && choice == kDkvOneWave) return launch_dkv_fr(a, dtype, d, causal, dropout, false, 0, s);
   if (choice == kDkvOneWave64) return launch_dkv_w64(a, dtype, causal, s);
-  if (choice == kDkvOneWave128) return launch_dkv_fr128(a, dtype, causal, dropout, s);
+  if (choice == kDkvOneWave128) return launch_dkv_fr128(a, dtype, causal, dropout, sparse, sparse && sparse_plan_groups(a) > 0 ? kListGroups : 0, s);
   if (dtype == 0 && d == 32) return launch_td<_Float16, 32>(a, causal, dropout, sparse, s);
   if (dtype == 1 && d == 32) return launch_td<__bf16, 32>(a, causal, dropout, sparse, s);
   if (dtype == 0 && d == 64) return launch_td<_Float16, 64>(a, causal, dropout, sparse, s);

@@ -14,6 +14,7 @@
 // Register layout "lane = key" (S = Q K^T: accumulator rows = queries of the tile, column = the
 // lane's key), as in attn_bwd_dkv.hip.
 #include "attn_common.h"
+#include "attn_sparse.h"
 #include "attn_tiles.h"
 
 namespace attn {
@@ -65,8 +66,8 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
   // Work assignment.  Dense: one key block per workgroup; under the causal mask key block k is
   // visited by N/64 - 2k query tiles, so a workgroup takes the pair (k, n_kt - 1 - k), one per
   // round.  Block-sparse (as in attn_bwd_dkv.hip): the first 8 * chunk workgroups take one mask
-  // column each and leave the heavy ones alone; those were cut into segments by
-  // sparse_plan_kernel and the remaining workgroups walk that segment list.
+  // column each and leave the heavy ones alone; those are cut into segments (attn_sparse.h),
+  // which the remaining workgroups walk.
   const int n_col_groups = kXcds * a.chunk;
   // (the list workgroups come first in the grid, a multiple of the XCD count of them, so that the
   // long segments start with the launch instead of queueing behind every column)
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
     item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
     if (item < 0) return;
     if constexpr (SPARSE) {
-      if (a.colcnt[item] > a.seglist[2]) return;
+      if (n_list > 0 && a.col_segs[item] > 0) return;   // heavy
     }
     if constexpr (PAIRED) {
       const int q = item % n_pair;
@@ -89,16 +90,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
       item = (item / n_pair) * n_kt + (round == 0 ? q : n_kt - 1 - q);
     }
   } else {
-    const int idx = (int)blockIdx.x + round * n_list;
-    if (idx >= a.seglist[0]) return;
-    const int e = a.seglist[kSegHeader + idx];
-    item = e / kMaxSegs;
-    const int seg = e % kMaxSegs;
-    const int cnt = a.colcnt[item];
-    const int nseg = min((int)kMaxSegs, (cnt + kSegBlocks - 1) / kSegBlocks);
-    const int seg_len = (cnt + nseg - 1) / nseg;
-    skip_blocks = seg * seg_len;
-    take_blocks = seg_len;
+    if (!sparse_segment((int)blockIdx.x + round * n_list, item, skip_blocks, take_blocks)) return;
     heavy = true;
   }
   const int bh = item / n_kt;
@@ -173,8 +165,13 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
   auto fetch_tile = [&](int t, int buf) {
     dma.copy_rows(Qg, a.sn, t * TILE, a.N, Qs0 + buf * TILE * D);
     dma.copy_rows(Gg, a.sn, t * TILE, a.N, Gs0 + buf * TILE * D);
-    if (wave == RW / 2 - 1) async_copy_b32(Lg + t * TILE + lane, __builtin_amdgcn_readfirstlane(lds_addr(Ls0 + buf * TILE)));
-    if (wave == RW / 2) async_copy_b32(Dg + t * TILE + lane, __builtin_amdgcn_readfirstlane(lds_addr(Ds0 + buf * TILE)));
+    // (addresses from the arrays themselves: from a pointer into them the compiler tests for null, with an instruction that it
+    // then finds to be illegal in the block-sparse forms)
+    const uint32_t at = (uint32_t)(buf * TILE * sizeof(float));
+    const uint32_t l_at = KG > 1 ? lds_addr(all) + (uint32_t)(group * kGroupBytes) : lds_addr(Ls0);
+    const uint32_t d_at = KG > 1 ? l_at + (uint32_t)(2 * TILE * sizeof(float)) : lds_addr(Ds0);
+    if (wave == RW / 2 - 1) async_copy_b32(Lg + t * TILE + lane, __builtin_amdgcn_readfirstlane(l_at + at));
+    if (wave == RW / 2) async_copy_b32(Dg + t * TILE + lane, __builtin_amdgcn_readfirstlane(d_at + at));
   };
   const float c = a.scale_log2;
 
@@ -324,7 +321,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
     // the loop ended on a barrier (or never touched LDS): the groups but the first leave their gradients in the tile buffers
     constexpr int kLanes = 64 * RW;
     static_assert((KG - 1) * 2 * DB * 16 * kLanes * 4 <= KG * kGroupBytes, "LDS holds the groups' gradients");
-    f32x4* const part = (f32x4*)all + wave * 64 + lane;
+    f32x4* const part = (f32x4*)all + wave * 64 + (SPARSE ? lane_id_here() : lane);
     if (group > 0) {
 #pragma unroll
       for (int f = 0; f < 8 * DB; ++f) {   // dV^T, then dK^T
@@ -351,7 +348,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
   if (KG > 1 && group > 0) {
     // (merged)
   } else if (SPARSE && heavy) {
-    // one of several segments of this column: sum in fp32; sparse_finish_kernel converts.  The loop
+    // one of several segments of this column: sum in fp32; the last of them converts.  The loop
     // ended on a barrier: the two Q buffers stage the rows of wavefronts 0 and 1, the two dO buffers
     // those of wavefronts 2 and 3 (32 x D floats each), first for dV, then for dK
     float* stage = (float*)(wave < 2 ? Qs0 : Gs0) + (wave & 1) * 32 * D;
@@ -362,11 +359,14 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
     // the loop ends on a barrier (or never touched LDS): the tile buffers stage the output rows
     T* stage_v = Qs0 + wave * 32 * D;   // 4 wavefronts x 32 rows = the two Q buffers
     T* stage_k = Gs0 + wave * 32 * D;
+    const int out_lane = SPARSE || PAIRED ? lane_id_here() : lane;
     store_rows_coalesced<T, D>(stage_v, (T*)a.dV + head_off + (int64_t)kw0 * a.sn, a.sn, dv,
-                               DROPOUT ? a.keep_scale : 1.f, a.N - kw0, D == 32 ? a.dvalid : D);
+                               DROPOUT ? a.keep_scale : 1.f, a.N - kw0, D == 32 ? a.dvalid : D, out_lane);
     store_rows_coalesced<T, D>(stage_k, (T*)a.dK + head_off + (int64_t)kw0 * a.sn, a.sn, dk, a.tau, a.N - kw0,
-                               D == 32 ? a.dvalid : D);
+                               D == 32 ? a.dvalid : D, out_lane);
   }
+  if constexpr (SPARSE)
+    if (heavy) sparse_finish<T, D>(item);
   if (!list_mode && last_round) return;
   __syncthreads();   // LDS is reused by the next key block
   }  // for round
@@ -431,8 +431,7 @@ int launch_td(const KArgs& a, bool causal, bool dropout, bool sparse, int extra_
 
 }  // namespace
 
-// sparse: the caller (attn_bwd_dkv.hip) has run the column count / plan kernels and runs the
-// finish kernel afterwards; extra_groups workgroups walk the list of heavy-column segments.
+// sparse: extra_groups workgroups walk the segments of heavy columns.
 int launch_dkv_fr(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int extra_groups,
                   hipStream_t s) {
   if (dtype == 0 && d == 32) return launch_td<_Float16, 32>(a, causal, dropout, sparse, extra_groups, s);

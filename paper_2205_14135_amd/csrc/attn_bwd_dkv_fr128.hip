@@ -1,6 +1,6 @@
-// dK / dV kernel for head dimension 128, dense problems, in which one wavefront
-// does all four tile products of its 32 keys (the arrangement of
-// attn_bwd_dkv_fr.hip carried to d = 128).
+// dK / dV kernel for head dimension 128, dense problems and the block-sparse ones
+// of fewer than 2048 mask columns, in which one wavefront does all four tile
+// products of its 32 keys (the arrangement of attn_bwd_dkv_fr.hip carried to d = 128).
 //
 // Arithmetic: Algorithm 4 of the paper for one block of 128 keys, swept over 32-query tiles:
 //     S = Q K^T, P = exp(S - L), dV += P^T dO, dP = dO V^T, dS = P o (dP - D), dK += tau dS^T Q.
@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "attn_common.h"
+#include "attn_sparse.h"
 #include "attn_tiles.h"
 
 namespace attn {
@@ -29,7 +30,7 @@ constexpr int D = 128;
 
 // RW wavefronts of 32 keys, times KG groups of them that each take every KG-th query tile, into buffers of their own (the V rows are
 // shared); the groups' gradients are summed through LDS at the end.
-template <typename T, bool CAUSAL, bool DROPOUT, int RW, int KG>
+template <typename T, bool CAUSAL, bool DROPOUT, bool SPARSE, int RW, int KG>
 __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs a) {
   typedef typename Vec<T>::x8 T8;
   constexpr int KK = D / 16, DB = D / 32;
@@ -52,11 +53,23 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
   if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
 
   const int n_kt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last key block may be ragged
-  const int item = xcd_item(a.n_items, a.chunk);
-  if (item < 0) return;
+  // Block-sparse: one workgroup per mask column, heavy ones in segments that the first workgroups walk (as in dkv_fr_kernel)
+  const int n_list = SPARSE ? (int)gridDim.x - kXcds * a.chunk : 0;
+  const bool list_mode = SPARSE && (int)blockIdx.x < n_list;
+  for (int round = 0;; ++round) {
+  int item, skip_blocks = 0, take_blocks = 0x7fffffff;
+  if (!list_mode) {
+    item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
+    if (item < 0) return;
+    if constexpr (SPARSE) {
+      if (n_list > 0 && a.col_segs[item] > 0) return;   // heavy
+    }
+  } else {
+    if (!sparse_segment((int)blockIdx.x + round * n_list, item, skip_blocks, take_blocks)) return;
+  }
   int bh = item / n_kt;
   int kt = item % n_kt;
-  if constexpr (CAUSAL) {
+  if constexpr (CAUSAL && !SPARSE) {
     // Key block k is visited by the query tiles from the diagonal on, so its work falls with k.
     // The key blocks of a.group consecutive heads are dealt out together, heaviest first, so that
     // the items a compute unit receives last are light ones (the host sizes the group so that the
@@ -123,19 +136,28 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
       else if (kt * BR < a.N) dma64.copy_rows(Vg, a.sn, kt * BR, a.N, Vb + 64 * D);   // all of these keys are masked
     }
   }
-  const int mine = first + group;   // this group's first tile
-  if (mine < limit) fetch_tile(mine, 0);
+  // this group's first tile; block-sparse: a 64-row tile of the iterator is two of this kernel's
+  TileIter<SPARSE> it;
+  int mine = first + group;
+  bool more = false;
+  if constexpr (SPARSE) {
+    it.init(a.mask + (int64_t)h * a.mask_sh + kt, a.T, CAUSAL ? kt : 0, kt * 128 >= len ? 0 : min(a.T, (len + 127) / 128), skip_blocks, take_blocks);
+    more = it.template next_of<KG>(group, mine);
+    if (mine >= 0) fetch_tile(2 * mine, 0);
+  } else {
+    if (mine < limit) fetch_tile(mine, 0);
+  }
   wait_async_copies();
   __syncthreads();
   // One query tile.  The buffer index is a compile-time constant (the loop below is unrolled by
   // two), so that every LDS address is a per-lane register plus an immediate offset.
-  auto tile_step = [&](int t, auto buf_c) {
+  auto tile_step = [&](int t, bool has_tile, int t_next, bool has_next, auto buf_c) __attribute__((always_inline)) {
     constexpr int buf = decltype(buf_c)::value;
-    if (t + KG < limit) fetch_tile(t + KG, buf ^ 1);
+    if (has_next) fetch_tile(t_next, buf ^ 1);
     // causal: of the four tiles on the diagonal of the key block, wavefront w joins from the w-th
     // on, and masks inside that one
     const int i0 = t * QT;
-    if ((KG == 1 || t < limit) && (!CAUSAL || i0 >= kw0)) {
+    if (has_tile && (!CAUSAL || i0 >= kw0)) {
       const T* Qt = Qs0 + buf * QT * D;
       const T* Gt = Gs0 + buf * QT * D;
       // ---- S = Q K^T and dP = dO V^T (32 queries x 32 keys each) as one stream of alternating
@@ -227,15 +249,28 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
     wait_async_copies();
     __syncthreads();
   };
-  for (int t = first; t < limit; t += 2 * KG) {   // (the same number of steps in every group)
-    tile_step(t + group, std::integral_constant<int, 0>());
-    if (t + KG < limit) tile_step(t + KG + group, std::integral_constant<int, 1>());
+  const std::integral_constant<int, 0> buf0;
+  const std::integral_constant<int, 1> buf1;
+  if constexpr (SPARSE) {
+    while (more) {
+      const int t = 2 * mine;
+      const bool has = KG == 1 || mine >= 0;
+      tile_step(t, has, t + 1, has, buf0);
+      more = it.template next_of<KG>(group, mine);
+      tile_step(t + 1, has, 2 * mine, mine >= 0, buf1);
+    }
+  } else {
+    for (int t0 = first; t0 < limit; t0 += 2 * KG) {   // (the same number of steps in every group)
+      const int t = t0 + group;
+      tile_step(t, KG == 1 || t < limit, t + KG, t + KG < limit, buf0);
+      if (t0 + KG < limit) tile_step(t + KG, KG == 1 || t + KG < limit, t + 2 * KG, t + 2 * KG < limit, buf1);
+    }
   }
   if constexpr (KG > 1) {
     // the loop ended on a barrier (or never touched LDS): the groups but the first leave dV, then dK in the buffers
     constexpr int kLanes = 64 * RW;
     static_assert((KG - 1) * DB * 16 * kLanes * 4 <= (int)sizeof(all), "LDS holds one gradient of the groups");
-    f32x4* const part = (f32x4*)all + wave * 64 + lane;
+    f32x4* const part = (f32x4*)all + wave * 64 + (SPARSE ? lane_id_here() : lane);
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
       f32x16 (&x)[DB] = which == 0 ? dv : dk;
@@ -261,20 +296,35 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
           }
       }
     }
-    if (group > 0) return;
+    if (!SPARSE && group > 0) return;
+    if (list_mode) __syncthreads();   // the sums are staged over what the groups left
   }
-  {
+  if (KG > 1 && group > 0) {
+    // (merged)
+  } else if (list_mode) {
+    // one of several segments of this column: sum in fp32; the last of them converts.  32 x 128 floats per wavefront
+    static_assert(!SPARSE || (RW == 4 && 4 * 32 * D * 4 <= (int)sizeof(all)), "LDS stages a gradient in fp32");
+    float* stage = (float*)all + wave * 32 * D;
+    const int64_t acc_row0 = ((int64_t)bh * a.N + kw0) * D;
+    atomic_add_rows_coalesced<D>(stage, a.dVacc + acc_row0, dv, DROPOUT ? a.keep_scale : 1.f);
+    atomic_add_rows_coalesced<D>(stage, a.dKacc + acc_row0, dk, a.tau);
+  } else {
     // 4 wavefronts x 32 rows x 128 = 32 KB per gradient: the V block, then the four tile buffers
     T* stage_v = Vb + wave * 32 * D;
+    const int out_lane = SPARSE ? lane_id_here() : (int)(threadIdx.x & 63);
     store_rows_coalesced<T, D>(stage_v, (T*)a.dV + head_off + (int64_t)kw0 * a.sn, a.sn, dv,
-                               DROPOUT ? a.keep_scale : 1.f, a.N - kw0);
+                               DROPOUT ? a.keep_scale : 1.f, a.N - kw0, D, out_lane);
     __builtin_amdgcn_wave_barrier();
-    store_rows_coalesced<T, D>(stage_v, (T*)a.dK + head_off + (int64_t)kw0 * a.sn, a.sn, dk, a.tau, a.N - kw0);
+    store_rows_coalesced<T, D>(stage_v, (T*)a.dK + head_off + (int64_t)kw0 * a.sn, a.sn, dk, a.tau, a.N - kw0, D, out_lane);
   }
+  if (!list_mode) return;
+  if constexpr (SPARSE) sparse_finish<T, D>(item);
+  __syncthreads();   // LDS is reused by the next segment
+  }  // for round
 }
 
 template <typename T, int RW, int KG>
-int launch_t(const KArgs& a_in, bool causal, bool dropout, hipStream_t s) {
+int launch_t(const KArgs& a_in, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
   KArgs a = a_in;
   {
     const int64_t tile_bytes = 2 * (int64_t)a.N * D * (int64_t)sizeof(T);   // Q and dO of one head
@@ -284,12 +334,31 @@ int launch_t(const KArgs& a_in, bool causal, bool dropout, hipStream_t s) {
   const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
-  if (causal && dropout) hipLaunchKernelGGL((dkv_fr128_kernel<T, true, true, RW, KG>), grid, block, 0, s, a);
-  else if (causal) hipLaunchKernelGGL((dkv_fr128_kernel<T, true, false, RW, KG>), grid, block, 0, s, a);
-  else if (dropout) hipLaunchKernelGGL((dkv_fr128_kernel<T, false, true, RW, KG>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((dkv_fr128_kernel<T, false, false, RW, KG>), grid, block, 0, s, a);
-  return (int)hipGetLastError();
+  const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(64 * RW * KG);
+#define ATTN_DKV_FR128_CASE(C, P, S)                                                            \
+  if constexpr (!S || RW == 4)                                                                  \
+    if (causal == C && dropout == P && sparse == S) {                                           \
+      hipLaunchKernelGGL((dkv_fr128_kernel<T, C, P, S, RW, KG>), grid, block, 0, s, a);         \
+      return (int)hipGetLastError();                                                            \
+    }
+  ATTN_DKV_FR128_CASE(false, false, false)
+  ATTN_DKV_FR128_CASE(true, false, false)
+  ATTN_DKV_FR128_CASE(false, true, false)
+  ATTN_DKV_FR128_CASE(true, true, false)
+  ATTN_DKV_FR128_CASE(false, false, true)
+  ATTN_DKV_FR128_CASE(true, false, true)
+  ATTN_DKV_FR128_CASE(false, true, true)
+  ATTN_DKV_FR128_CASE(true, true, true)
+#undef ATTN_DKV_FR128_CASE
+  return (int)hipErrorInvalidValue;
+}
+
+template <typename T>
+int launch_groups(const KArgs& a, const WaveGroups& w, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
+  if (w.waves == 2 && w.groups == 4) return launch_t<T, 2, 4>(a, causal, dropout, sparse, extra_groups, s);
+  if (w.waves == 2) return launch_t<T, 2, 2>(a, causal, dropout, sparse, extra_groups, s);
+  if (w.groups == 2) return launch_t<T, 4, 2>(a, causal, dropout, sparse, extra_groups, s);
+  return launch_t<T, 4, 1>(a, causal, dropout, sparse, extra_groups, s);
 }
 
 }  // namespace
@@ -301,19 +370,18 @@ int launch_t(const KArgs& a_in, bool causal, bool dropout, hipStream_t s) {
 //            40 x 1024 93.6 +7.3 +16.3 +21.6
 //   causal   16 x 1024 62.4 -5.5 -9.1 -7.6; 8 x 2048 110 -15 -21 -22; 8 x 4096 213 -23 +6 -9; 40 x 1024 78.3 -2.8 +11.3 +19.4; 10 x 4096 254 +8 +42 +16
 //   dropout  8 x 2048 137 -19 -31 -35; 8 x 4096 272 -30 +16 -5; 60 x 512 48.2 -2.7 +8.2 +16.5; 10 x 4096 372 +23 +46 +5
-static WaveGroups fr128_groups(const KArgs& a) {
+static WaveGroups fr128_groups(const KArgs& a, bool sparse) {
   if (!may_divide()) return {4, 1};
-  const WorkItems w(a, false, false);
+  const WorkItems w(a, sparse, false);
+  if (sparse) return w.of128 <= kComputeUnits / 2 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return w.tiles >= 32 ? WaveGroups{2, 4} : WaveGroups{2, 2};
   return w.of128 <= kComputeUnits && w.tiles >= 5 ? WaveGroups{4, 2} : WaveGroups{4, 1};
 }
 
-int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, hipStream_t s) {
-  const WaveGroups w = fr128_groups(a);
-  if (w.waves == 2 && w.groups == 4) return dtype == 0 ? launch_t<_Float16, 2, 4>(a, causal, dropout, s) : launch_t<__bf16, 2, 4>(a, causal, dropout, s);
-  if (w.waves == 2) return dtype == 0 ? launch_t<_Float16, 2, 2>(a, causal, dropout, s) : launch_t<__bf16, 2, 2>(a, causal, dropout, s);
-  if (w.groups == 2) return dtype == 0 ? launch_t<_Float16, 4, 2>(a, causal, dropout, s) : launch_t<__bf16, 4, 2>(a, causal, dropout, s);
-  return dtype == 0 ? launch_t<_Float16, 4, 1>(a, causal, dropout, s) : launch_t<__bf16, 4, 1>(a, causal, dropout, s);
+int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
+  const WaveGroups w = fr128_groups(a, sparse);
+  return dtype == 0 ? launch_groups<_Float16>(a, w, causal, dropout, sparse, extra_groups, s)
+                    : launch_groups<__bf16>(a, w, causal, dropout, sparse, extra_groups, s);
 }
 
 }  // namespace attn

@@ -25,8 +25,10 @@ struct KArgs {
   float* Dvec;             // bwd scratch: -D_i = -rowsum(dO_i o O_i)   [B,H,Nr], 0 for rows >= N
   float* L2vec;            // bwd scratch: L_i * log2(e), +inf where L_i = -inf and for rows >= N   [B,H,Nr]
   int* colcnt;             // block-sparse bwd scratch: kept blocks per mask column   [B*H, T]
-  int* seglist;            // block-sparse bwd scratch: [0] = number of entries, [1] = kept blocks in total,
-                           // [2] = heavy threshold, from [kSegHeader]: entries (column * kMaxSegs + segment)
+  int* col_segs;           // block-sparse bwd scratch: segments of a heavy column, 0 for the others   [B*H, T]
+  int* ticket;             // block-sparse bwd scratch: segments of a heavy column that have ended   [B*H, T]
+  int* group_segs;         // block-sparse bwd scratch: segments of the heavy columns among kPlanCols   [B*H, ceil(T / kPlanCols)]
+  int plan_groups;         // block-sparse bwd: planning workgroups at the head of the dQ launch (0: no column can be heavy)
   float* dKacc;            // block-sparse bwd scratch: fp32 dK / dV of the columns that are
   float* dVacc;            //   split over several workgroups                         [B,H,N,d]
   int causal;              // causal flag for the kernels that are not specialised on it
@@ -49,11 +51,14 @@ struct KArgs {
 };
 
 enum { kXcds = 8, kMaskBlock = 128 };
-// Block-sparse dK/dV: a mask column is "heavy" when it keeps more than kHeavyBlocks blocks AND
-// more than half of a compute unit's fair share of all kept blocks (so a mask whose columns are
-// all long, e.g. a dense one, is not split at all).  Heavy columns are cut into segments of about
-// kSegBlocks blocks (at most kMaxSegs), one workgroup each, summed with fp32 atomics.
-enum { kHeavyBlocks = 24, kSegBlocks = 12, kMaxSegs = 32, kSegHeader = 8, kComputeUnits = 256 };
+// Block-sparse dK/dV: a mask column is "heavy" when it keeps more than kLongBlocks blocks, or more than kHeavyBlocks and twice as
+// many as its neighbours on average, AND more than half of a compute unit's fair share of all kept blocks (so a mask whose columns are
+// all long, e.g. a dense one, is not split at all).  Heavy columns are cut into segments (at most kMaxSegs), one workgroup
+// each, summed with fp32 atomics: of about kSegBlocks blocks, or kShortSegBlocks where a single column stands out from its neighbours
+// and is not longer than kShortSegLimit.  us, backward with 24 and segments of 12 for all | this; heads x T, butterfly mask: d = 64
+// 8 x 24 83.5 | 54.3, 3 x 20 52.9 | 41.7, 4 x 32 50.2 | 45.6, 8 x 64 96.3 | 92.3; d = 128 8 x 24 126 | 87, 4 x 16 71.5 | 74.1, 8 x 64 165 | 156.  A dense mask
+// of 4 x 48: 182 | 207 with 14 and 8 for all columns, 8 x 128 at d = 128 292 | 294 with segments of 8 for the longest.
+enum { kLongBlocks = 24, kHeavyBlocks = 14, kSegBlocks = 12, kShortSegBlocks = 8, kShortSegLimit = 64, kMaxSegs = 32, kComputeUnits = 256 };
 
 // Kernel-choice overrides (attn_debug_set_variant; initial values from the environment, read once
 // when first needed).  fwd: 0 = by measurement, 1 = free-running kernel, 2 = two-group kernel;
@@ -89,6 +94,14 @@ struct WorkItems {
   }
 };
 
+// Planning workgroups of a block-sparse backward: one for kPlanCols mask columns of a head (what each clears takes no longer than the
+// launch it is part of), padded to whole rounds over the XCDs; none where the columns are too short for any to be heavy.
+constexpr int kPlanCols = 16;
+inline int sparse_plan_groups(const KArgs& a) {
+  if (a.T <= kHeavyBlocks) return 0;
+  return (a.B * a.H * ((a.T + kPlanCols - 1) / kPlanCols) + kXcds - 1) / kXcds * kXcds;
+}
+
 // Launchers (defined in the .hip files).  dtype: 0 fp16, 1 bf16.  Return hipError_t as int.
 int launch_fwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s);
 // ev: nullptr, or four events: two recorded before the first launch, one after the dQ kernel, one after dK/dV.
@@ -100,8 +113,8 @@ int launch_dkv_rs(const KArgs& a, int dtype, int d, bool causal, bool dropout, b
 // dense dK/dV kernel for d <= 64: one wavefront does all four tile products (attn_bwd_dkv_fr.hip)
 int launch_dkv_fr(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int extra_groups,
                   hipStream_t s);
-// the same at d = 128 for dense problems (attn_bwd_dkv_fr128.hip)
-int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, hipStream_t s);
+// the same at d = 128 (attn_bwd_dkv_fr128.hip)
+int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s);
 // the same with 64 keys per wavefront and the accumulators in the accumulation registers (attn_bwd_dkv_w64.hip)
 int launch_dkv_w64(const KArgs& a, int dtype, bool causal, hipStream_t s);
 // the whole backward pass of short dense heads at d <= 64, one launch (attn_bwd_short.hip), and which heads take it

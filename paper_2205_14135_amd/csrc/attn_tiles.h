@@ -188,15 +188,16 @@ __device__ __forceinline__ void store_rows(T* dst_row, const f32x16 (&acc)[D / 3
 // The area is unpadded; the 16-byte chunk index is XORed with the row to spread the banks.
 // dst_row0 points at the row of the wavefront's first token; only the first rows_valid of the 32
 // rows exist in the destination (fewer than 32 on the last block of a ragged tensor; may be <= 0).
+// lane: lane_id_here() where the call stands in a loop over work items, whose tile loop has no registers for addresses made for here.
 template <typename T, int D>
 __device__ __forceinline__ void store_rows_coalesced(T* stage, T* dst_row0, int64_t sn,
                                                      const f32x16 (&acc)[D / 32], float scale,
-                                                     int rows_valid = 32, int cols_valid = D) {
+                                                     int rows_valid = 32, int cols_valid = D, int lane = (int)(threadIdx.x & 63)) {
   typedef typename Vec<T>::x4 T4;
   typedef typename Vec<T>::x8 T8;
   constexpr int CPR = D / 8;         // 16-byte chunks per row
   constexpr int RPP = 64 / CPR;      // rows per pass of the read-back
-  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
+  const int r = lane & 31, g = lane >> 5;
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -226,7 +227,8 @@ template <int D>
 __device__ __forceinline__ void atomic_add_rows_coalesced(float* stage, float* dst_row0, const f32x16 (&acc)[D / 32],
                                                           float scale, int cols_valid = D) {
   constexpr int C4 = D / 4;   // 16-byte chunks per row
-  const int lane = threadIdx.x & 63, r = lane & 31, g = lane >> 5;
+  // (an address the compiler does not keep through the tile loops of the kernels that walk several segments)
+  const int lane = lane_id_here(), r = lane & 31, g = lane >> 5;
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
