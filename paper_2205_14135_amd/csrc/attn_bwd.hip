@@ -94,6 +94,7 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
     bh = grp0 + within % gsz;
     q_item = within / gsz;                                 // q_item-th heaviest block (see qt below)
   }
+  if constexpr (!SPARSE) bh = dealt_head(a, bh);
   const int n_pass = PAIRED && q_item != n_qt - 1 - q_item ? 2 : 1;
 #pragma clang loop unroll(disable)
   for (int pass = 0; pass < n_pass; ++pass) {

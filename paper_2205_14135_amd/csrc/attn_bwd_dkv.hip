@@ -85,7 +85,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
     if (!sparse_segment((int)blockIdx.x + round * n_list, item, skip_blocks, take_blocks)) return;
     heavy = true;
   }
-  const int bh = item / n_kt;
+  const int bh = SPARSE ? item / n_kt : dealt_head(a, item / n_kt);
   const int kt = item % n_kt;
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;

@@ -81,6 +81,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
     bh = grp0 + within % gsz;
     kt = within / gsz;
   }
+  if constexpr (!SPARSE) bh = dealt_head(a, bh);
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;

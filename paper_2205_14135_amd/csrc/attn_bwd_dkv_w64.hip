@@ -211,6 +211,7 @@ __global__ __launch_bounds__(NT, 1) void dkv_w64_kernel(const KArgs a) {
     bh = grp0 + within % gsz;
     kt = within / gsz;
   }
+  bh = dealt_head(a, bh);
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;

@@ -46,8 +46,9 @@ __global__ __launch_bounds__(64 * KW, 2) void bwd_short_kernel(const KArgs a) {
   KeepLK keep;
   if constexpr (DROPOUT) keep.init(keep_table, a.drop_thr);
 
-  const int bh = xcd_item(a.n_items, a.chunk);
-  if (bh < 0) return;
+  const int item = xcd_item(a.n_items, a.chunk);
+  if (item < 0) return;
+  const int bh = dealt_head(a, item);
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const int lane = threadIdx.x & 63;

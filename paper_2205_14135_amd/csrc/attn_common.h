@@ -498,6 +498,22 @@ __device__ __forceinline__ int xcd_item(int n_items, int chunk, int id = (int)bl
   const int item = (id % kXcds) * chunk + id / kXcds;
   return item < n_items && (id / kXcds) < chunk ? item : -1;
 }
+// The head that the dealt-out position `pos` of a dense problem stands for.  xcd_item gives each XCD a run of consecutive positions.  With a
+// key-padding mask the heads of a batch entry cost what its length says, and entries of like length tend to stand together
+// (batches sorted by length), so that one XCD would get the long ones: there the j-th head of XCD x is 8 j + (x + j) % 8.  (Not
+// 8 j + x: heads of 64 KB that are 512 KB apart fall on the same quarter of an L2: 16 x 16 heads of 512, causal, d = 64, backward 64 us.)  Every
+// XCD still has whole heads, whose K and V (or Q and dO) its L2 holds.  Without a mask all heads cost the same, and positions are heads; nor do heads of one
+// block of rows gain (64 x 12 of 128, d = 64: forward 11.5 | 12.0).  us, forward + backward, lengths from N to N / 2 in falling order, runs of
+// heads | dealt round: 16 x 8 of 700, d = 32 68.3 | 57.7, d = 64 101 | 86, d = 128 166 | 145; 16 x 16 of 512, dropout 127 | 109, causal 82 | 78; 5 x 12 of
+// 1000 88 | 72; 16 x 16 of 1024 316 | 246; 4 x 16 of 4096, d = 128 1958 | 1338; 8 x 16 of 1024 causal with dropout, d = 128 216 | 181; 32 x 12 of 197 46.4 | 44.9.
+__device__ __forceinline__ int dealt_head(const KArgs& a, int pos) {
+  if (!a.klen || a.T == 1) return pos;
+  const int n = a.B * a.H, whole = n / kXcds, rest = n % kXcds;   // XCDs below `rest` have one head more
+  const int in_long = rest * (whole + 1);
+  const int x = pos < in_long ? pos / (whole + 1) : rest + (pos - in_long) / (whole > 0 ? whole : 1);
+  const int j = pos - x * whole - (x < rest ? x : rest);
+  return j * kXcds + (j < whole ? (x + j) % kXcds : x);
+}
 // XOR swizzle of the 16-byte chunk index inside an unpadded [rows][D] LDS tile.  It makes both
 // access patterns used on the tiles conflict-free on a 64-bank LDS: 16 consecutive rows at one
 // chunk (row-wise 16-byte operand reads) and 4 consecutive rows x 64 bytes (transposing reads).

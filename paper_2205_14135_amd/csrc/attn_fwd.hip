@@ -69,7 +69,7 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 ? (D <= 64 ? 3 : 2) : (RW * K
   // every workgroup does the same amount of work.
   constexpr bool PAIRED = CAUSAL && !SPARSE && D == 64;
   const int n_per_head = PAIRED ? (n_qt + 1) / 2 : n_qt;
-  const int bh = item / n_per_head;
+  const int bh = SPARSE ? item / n_per_head : dealt_head(a, item / n_per_head);
   const int q_item = item % n_per_head;
   const int n_pass = PAIRED && q_item != n_qt - 1 - q_item ? 2 : 1;
 #pragma clang loop unroll(disable)

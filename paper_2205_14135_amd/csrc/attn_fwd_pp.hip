@@ -234,14 +234,14 @@ __global__ __launch_bounds__(NT) void fwd_pp_kernel(const KArgs a) {
   const int n_qt = (a.N + BRW - 1) / BRW;
   if constexpr (CAUSAL) {
     const int n_pair = (n_qt + 1) / 2;
-    const int bh = item / n_pair, q = item % n_pair;
+    const int bh = dealt_head(a, item / n_pair), q = item % n_pair;
     fwd_pp_rows<T, D, CAUSAL, DROPOUT>(a, bh, n_qt - 1 - q, Ks, Vs);
     if (q != n_qt - 1 - q) {
       __syncthreads();   // the tile buffers staged the first block's output rows
       fwd_pp_rows<T, D, CAUSAL, DROPOUT>(a, bh, q, Ks, Vs);
     }
   } else {
-    fwd_pp_rows<T, D, CAUSAL, DROPOUT>(a, item / n_qt, item % n_qt, Ks, Vs);
+    fwd_pp_rows<T, D, CAUSAL, DROPOUT>(a, dealt_head(a, item / n_qt), item % n_qt, Ks, Vs);
   }
 }
 
