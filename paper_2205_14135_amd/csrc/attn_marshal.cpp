@@ -89,9 +89,11 @@ uint64_t low64(PyObject* o) {   // int(o) & (2^64 - 1)
   return v;
 }
 
+bool alike(const at::Tensor& ref, const at::Tensor& t) {
+  return t.sizes() == ref.sizes() && t.strides() == ref.strides() && t.device() == ref.device();
+}
 void same_layout(const at::Tensor& ref, const at::Tensor& t) {
-  if (t.sizes() != ref.sizes() || t.strides() != ref.strides() || t.device() != ref.device())
-    raise(PyExc_ValueError, "all [B,H,N,d] tensors must share shape, strides and device");
+  if (!alike(ref, t)) raise(PyExc_ValueError, "all [B,H,N,d] tensors must share shape, strides and device");
 }
 
 // The arguments that every call has, in the order of the Python wrappers.
@@ -197,17 +199,29 @@ attn_params on_current_stream(const Attention& a, const at::Tensor& q) {
 }
 int64_t mask_stride(const at::Tensor& mask) { return mask.dim() == 3 ? mask.stride(0) : 0; }
 
-// A refusal of the library on the engine's thread: AttnError, carried to the caller of backward().
-[[noreturn]] void refused_in_backward(int status, const char* where) {
+// An error on the engine's thread, which runs without the interpreter lock: `set` raises it, and it is carried to the caller of backward().
+template <typename F> [[noreturn]] void refused_in_backward(F&& set) {
   const PyGILState_STATE gil = PyGILState_Ensure();
   python_error e;
   try {
-    check_status(status, where);
+    set();
   } catch (const Raised&) {
     e.persist();
   }
   PyGILState_Release(gil);
   throw e;
+}
+
+// What the marshalling of a backward call asks of its tensors (backward() below, make_params), of the saved ones as they come back: hooks
+// of the program may have moved, converted or laid out anew some of them.
+void check_saved(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const at::Tensor& d_out) {
+  if (q.dim() != 4 || q.stride(3) != 1)
+    refused_in_backward([] { raise(PyExc_ValueError, "expected a [B,H,N,d] tensor with contiguous last axis"); });
+  if (q.scalar_type() != at::kHalf && q.scalar_type() != at::kBFloat16)
+    refused_in_backward([] { raise(PyExc_TypeError, "Q/K/V must be float16 or bfloat16"); });
+  if (!q.is_cuda()) refused_in_backward([] { raise(PyExc_ValueError, "the saved tensors are not on the GPU"); });
+  if (!alike(q, k) || !alike(q, v) || !alike(q, d_out))
+    refused_in_backward([] { raise(PyExc_ValueError, "all [B,H,N,d] tensors must share shape, strides and device"); });
 }
 
 using torch::autograd::AutogradContext;
@@ -243,6 +257,7 @@ struct FlashAttention : torch::autograd::Function<FlashAttention> {
     at::Tensor d_out = d_outs[0];
     if (d_out.sizes() != q.sizes() || d_out.strides() != q.strides())   // the library addresses dO with the strides of q
       d_out = like(q, q.scalar_type()).copy_(d_out);
+    check_saved(q, k, v, d_out);
     auto& data = ctx->saved_data;
     Attention a = {};
     a.p.B = (int32_t)q.size(0); a.p.H = (int32_t)q.size(1); a.p.N = (int32_t)q.size(2); a.p.d = (int32_t)q.size(3);
@@ -266,7 +281,7 @@ struct FlashAttention : torch::autograd::Function<FlashAttention> {
                                 out.data_ptr(), d_out.data_ptr(), lp, g[0].data_ptr(), g[1].data_ptr(), g[2].data_ptr(), ws.data_ptr(), ws.numel())
                : lib.bwd(&p, q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), d_out.data_ptr(), lp, g[0].data_ptr(), g[1].data_ptr(),
                          g[2].data_ptr(), ws.data_ptr(), ws.numel());
-    if (status != ATTN_OK) refused_in_backward(status, sparse ? "attn_blocksparse_bwd" : "attn_bwd");
+    if (status != ATTN_OK) refused_in_backward([&] { check_status(status, sparse ? "attn_blocksparse_bwd" : "attn_bwd"); });
     return {g[0], g[1], g[2], at::Tensor()};
   }
 };

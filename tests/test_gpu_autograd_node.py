@@ -99,6 +99,27 @@ def test_saved_tensor_hooks_and_checkpoint():
         assert all(torch.equal(a, b) for a, b in zip(_grads(out, ts, do), want))
 
 
+# what comes back from the program's hooks is looked at again: as another layout, another type, or left on the host
+@pytest.mark.parametrize("which", [0, 1, 2])
+@pytest.mark.parametrize("change,error", [(lambda x: x.contiguous(), ValueError), (lambda x: x.transpose(2, 3).contiguous().transpose(2, 3), ValueError),
+                                          (lambda x: x.float(), TypeError), (lambda x: x.cpu(), ValueError)])
+@pytest.mark.parametrize("node", ["native", "python"])
+def test_saved_tensors_that_come_back_changed(which, change, error, node):
+    if error is TypeError and which > 0:
+        pytest.skip("the types of k and v are taken to be that of q")
+    ts, do = _tensors(token_major=True)
+    count = [-1]
+
+    def pack(x):
+        count[0] += 1
+        return count[0], x
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda p: change(p[1]) if p[0] == which else p[1]):
+        out = (flash_attention if node == "native" else _python_node)(*ts)
+    with pytest.raises(error):
+        torch.autograd.grad(out, ts, do)
+
+
 def _grads(out, ts, do):
     for t in ts:
         t.grad = None
