@@ -138,7 +138,7 @@ int fwd_common(const attn_params* p, const uint8_t* mask, int64_t mask_sh, bool 
   c.k.Q = Q; c.k.K = K; c.k.V = V; c.k.O = O; c.k.LSE = LSE;
   c.k.mask = mask; c.k.mask_sh = mask_sh;
   set_items(c.k, c.k.T);
-  const int e = attn::launch_fwd(c.k, c.dtype, c.d, c.causal, c.dropout, sparse, c.stream);
+  const int e = attn::launch_fwd(c.k, c.dtype, c.d, c.causal, c.dropout, sparse, attn::overrides(), c.stream);
   return e == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
@@ -176,7 +176,7 @@ int bwd_common(const attn_params* p, const uint8_t* mask, int64_t mask_sh, bool 
       ev[i] = (hipEvent_t)events[i];
     }
   }
-  const int e = attn::launch_bwd(c.k, c.dtype, c.d, c.causal, c.dropout, sparse, c.stream,
+  const int e = attn::launch_bwd(c.k, c.dtype, c.d, c.causal, c.dropout, sparse, attn::overrides(), c.stream,
                                  events ? ev : nullptr);
   return e == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
@@ -209,9 +209,6 @@ int env_choice(const char* name, char c1, char c2, char c3 = 0) {
   return v[0] == c1 ? 1 : (v[0] == c2 ? 2 : (c3 != 0 && v[0] == c3 ? 3 : 0));
 }
 
-}  // namespace
-
-namespace attn {
 int fwd_variant() {
   int v = g_fwd_variant.load(std::memory_order_relaxed);
   if (v < 0) {
@@ -230,6 +227,11 @@ int dkv_variant() {
   }
   return v;
 }
+
+}  // namespace
+
+namespace attn {
+Overrides overrides() { return {fwd_variant(), dkv_variant()}; }
 }  // namespace attn
 
 extern "C" {
@@ -337,8 +339,9 @@ int attn_debug_kernel_choice(const attn_params* p, int32_t sparse, int32_t* fwd_
   if (st != ATTN_OK) return st;
   if (fwd_kernel == nullptr || dkv_kernel == nullptr) return ATTN_ERR_NULL;
   if (sparse != 0 && p->N % attn::kMaskBlock != 0) return ATTN_ERR_SHAPE;
-  *fwd_kernel = attn::choose_fwd(c.k, c.d, c.causal, c.dropout, sparse != 0);
-  *dkv_kernel = attn::choose_dkv(c.k, c.d, c.causal, c.dropout, sparse != 0);
+  const attn::Overrides v = attn::overrides();
+  *fwd_kernel = attn::choose_fwd(c.k, c.d, c.causal, c.dropout, sparse != 0, v);
+  *dkv_kernel = attn::choose_dkv(c.k, c.d, c.causal, c.dropout, sparse != 0, v);
   return ATTN_OK;
 }
 

@@ -384,8 +384,8 @@ template <> constexpr int kDtype<__bf16> = 1;
 //            16 x 2048 136 -1.5 +18.3; 8 x 4096 253 -5.1 +28.4, causal 213 -6.0 +23.5, dropout 272 -8.3 +30.0; 40 x 1024 93.6 +10.1 +18.4
 //   block-sparse (butterfly mask of T x T blocks, heads x T)  d = 64  4 x 8 48.2 -1.5 -4.2 -4.0; 4 x 32 65.7 -1.8 -4.4 -4.4; 4 x 64 76.0 -2.0 -1.4 +7.0;
 //            8 x 64 112 +5.8 +6.2 +24.1; d = 128  4 x 32 89.9 -0.3 -4.4; 4 x 64 132 +0.3 +17.4
-WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse) {
-  if (!may_divide()) return {4, 1};
+WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
+  if (!divide) return {4, 1};
   const bool pairs = causal && !sparse && d == 64;
   const WorkItems w(a, sparse, pairs);
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return d <= 64 && w.tiles >= (d == 64 ? 24 : 12) && !sparse ? WaveGroups{2, 4} : WaveGroups{2, 2};
@@ -396,8 +396,8 @@ WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse) {
 }
 
 template <typename T, int D>
-int launch_dq_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStream_t s) {
-  const WaveGroups w = dq_groups(a, D, causal, sparse);
+int launch_dq_td(const KArgs& a, bool causal, bool dropout, bool sparse, bool divide, hipStream_t s) {
+  const WaveGroups w = dq_groups(a, D, causal, sparse, divide);
   if constexpr (D <= 64)
     if (w.waves == 2 && w.groups == 4) return launch_dq<T, D, 2, 4>(a, causal, dropout, sparse, s);
   if (w.waves == 2) return launch_dq<T, D, 2, 2>(a, causal, dropout, sparse, s);
@@ -407,34 +407,36 @@ int launch_dq_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStre
 }
 
 template <typename T, int D>
-int launch_bwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStream_t s, hipEvent_t* ev) {
+int launch_bwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, const Overrides& v, hipStream_t s, hipEvent_t* ev) {
+  const int choice = choose_dkv(a, D, causal, dropout, sparse, v);
+  const bool divide = may_divide(v);
   if (ev) (void)hipEventRecord(ev[0], s);
   if (ev) (void)hipEventRecord(ev[1], s);   // (there is no separate preparation launch any more)
   int e;
-  if (choose_dkv(a, D, causal, dropout, sparse) == kBwdShort) {
+  if (choice == kBwdShort) {
     e = launch_bwd_short(a, kDtype<T>, D, causal, dropout, s);
     if (ev) (void)hipEventRecord(ev[2], s);
     if (ev) (void)hipEventRecord(ev[3], s);
     return e;
   }
-  e = launch_dq_td<T, D>(a, causal, dropout, sparse, s);
+  e = launch_dq_td<T, D>(a, causal, dropout, sparse, divide, s);
   if (e != 0) return e;
   if (ev) (void)hipEventRecord(ev[2], s);
-  e = launch_dkv_rs(a, kDtype<T>, D, causal, dropout, sparse, s);
+  e = launch_dkv(a, kDtype<T>, D, causal, dropout, sparse, choice, divide, s);
   if (ev) (void)hipEventRecord(ev[3], s);
   return e;
 }
 
 }  // namespace
 
-int launch_bwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s,
+int launch_bwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, const Overrides& v, hipStream_t s,
                hipEvent_t* ev) {
-  if (dtype == 0 && d == 32) return launch_bwd_td<_Float16, 32>(a, causal, dropout, sparse, s, ev);
-  if (dtype == 1 && d == 32) return launch_bwd_td<__bf16, 32>(a, causal, dropout, sparse, s, ev);
-  if (dtype == 0 && d == 64) return launch_bwd_td<_Float16, 64>(a, causal, dropout, sparse, s, ev);
-  if (dtype == 0 && d == 128) return launch_bwd_td<_Float16, 128>(a, causal, dropout, sparse, s, ev);
-  if (dtype == 1 && d == 64) return launch_bwd_td<__bf16, 64>(a, causal, dropout, sparse, s, ev);
-  if (dtype == 1 && d == 128) return launch_bwd_td<__bf16, 128>(a, causal, dropout, sparse, s, ev);
+  if (dtype == 0 && d == 32) return launch_bwd_td<_Float16, 32>(a, causal, dropout, sparse, v, s, ev);
+  if (dtype == 1 && d == 32) return launch_bwd_td<__bf16, 32>(a, causal, dropout, sparse, v, s, ev);
+  if (dtype == 0 && d == 64) return launch_bwd_td<_Float16, 64>(a, causal, dropout, sparse, v, s, ev);
+  if (dtype == 0 && d == 128) return launch_bwd_td<_Float16, 128>(a, causal, dropout, sparse, v, s, ev);
+  if (dtype == 1 && d == 64) return launch_bwd_td<__bf16, 64>(a, causal, dropout, sparse, v, s, ev);
+  if (dtype == 1 && d == 128) return launch_bwd_td<__bf16, 128>(a, causal, dropout, sparse, v, s, ev);
   return (int)hipErrorInvalidValue;
 }
 

@@ -334,19 +334,11 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
   }  // for round
 }
 
-// dK/dV override 1 keeps the role-split kernel at every head dimension (comparisons and tests)
-bool force_role_split() { return dkv_variant() == 1; }
-
 template <typename T, int D>
-int launch_td(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
-  const int list_groups = sparse && sparse_plan_groups(a) > 0 ? kListGroups : 0;   // walk the segments of heavy columns
+int launch_td(KArgs a, bool causal, bool dropout, bool sparse, int list_groups, hipStream_t s) {
   if (causal && !sparse) {   // items are pairs of key blocks
     a.n_items = a.B * a.H * ((a.T + 1) / 2);
     a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  }
-  if (sparse && choose_dkv(a, D, causal, dropout, sparse) == kDkvOneWave) {
-    // d <= 64: the kernel in which one wavefront does all four products, same work assignment
-    return launch_dkv_fr(a, std::is_same<T, __bf16>::value ? 1 : 0, D, causal, dropout, true, list_groups, s);
   }
   const dim3 grid(kXcds * a.chunk + list_groups), block(NT);
 #define ATTN_DKV_CASE(C, P, S)                                                    \
@@ -368,13 +360,14 @@ int launch_td(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
 
 }  // namespace
 
-int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
+int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse, const Overrides& v) {
+  const bool role_split = v.dkv == 1;   // at every head dimension it has (comparisons and tests)
   // short heads: one workgroup has all of a head's keys, and both launches become one
-  if (!sparse && dkv_variant() == 0 && bwd_short_is_faster(a, d, causal)) return kBwdShort;
+  if (!sparse && v.dkv == 0 && bwd_short_is_faster(a, d, causal)) return kBwdShort;
   // Problems with d <= 64 take the kernel in which one wavefront does all four products
-  // (attn_bwd_dkv_fr.hip; the block-sparse ones from inside launch_td).
+  // (attn_bwd_dkv_fr.hip).
   // (head dimension 16 exists in that kernel only)
-  if (d <= 64 && (!force_role_split() || a.dvalid < d)) return kDkvOneWave;
+  if (d <= 64 && (!role_split || a.dvalid < d)) return kDkvOneWave;
   // d = 128, dense: the one-wavefront kernel with the V block in LDS (attn_bwd_dkv_fr128.hip)
   // (without dropout, with 64 keys per wavefront where a head has at least two blocks of 256 keys
   // and whole 32-query tiles: attn_bwd_dkv_w64.hip)
@@ -385,31 +378,33 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
   // 200 | 163, 4096 714 | 569; B H = 128, N = 1024 126 | 92; B H = 48, N = 1400 137 | 77)
   const int64_t blocks = (int64_t)a.B * a.H * a.T;
   const bool one_round_of_pairs = blocks > kComputeUnits && blocks <= 2 * kComputeUnits && a.N >= 1024;
-  if (!sparse && d == 128 && !force_role_split() && !(dropout && causal && dkv_variant() == 0 && one_round_of_pairs)) {
+  if (!sparse && d == 128 && !role_split && !(dropout && causal && v.dkv == 0 && one_round_of_pairs)) {
     // measured against the 32-key kernel: 1 % faster at N = 2048, 5 % at 4096, 7 % at 16384; slower below,
     // slower under the causal mask at every length (its 256-key work items balance worse), and with no more key blocks than compute
     // units, where the 32-key kernel can split a block's sweep: B H = 8, N = 2048 130 | 86 us of the backward pass, B H = 8, N = 4096 253 | 205
-    const bool w64 = dkv_variant() == 3 || (dkv_variant() == 0 && !causal && a.N >= 2048 && blocks > kComputeUnits);
+    const bool w64 = v.dkv == 3 || (v.dkv == 0 && !causal && a.N >= 2048 && blocks > kComputeUnits);
     return w64 && !dropout && a.N >= 512 && a.N % 32 == 0 ? kDkvOneWave64 : kDkvOneWave128;
   }
   // d = 128, block-sparse: the one-wavefront kernel as well (us of the backward pass, role-split | one wavefront, butterfly mask of heads x T:
   // 2 x 8 51 | 48, 4 x 16 78 | 71, 8 x 64 186 | 160, 8 x 128 351 | 287, causal 251 | 194, 4 x 200 312 | 246).  Above that, where no more than
   // 64 heads of 32 blocks and 8 of 512 were looked at, the role-split kernel stays.
-  if (sparse && d == 128 && !force_role_split() && blocks < 8 * kComputeUnits) return kDkvOneWave128;
+  if (sparse && d == 128 && !role_split && blocks < 8 * kComputeUnits) return kDkvOneWave128;
   return kDkvRoleSplit;
 }
 
-int launch_dkv_rs(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s) {
-  const int choice = choose_dkv(a, d, causal, dropout, sparse);
-  if (!sparse && choice == kDkvOneWave) return launch_dkv_fr(a, dtype, d, causal, dropout, false, 0, s);
+int launch_dkv(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int choice, bool divide, hipStream_t s) {
+  const int list_groups = sparse && sparse_plan_groups(a) > 0 ? kListGroups : 0;   // walk the segments of heavy columns
+  if (choice == kDkvOneWave) return launch_dkv_fr(a, dtype, d, causal, dropout, sparse, list_groups, divide, s);
   if (choice == kDkvOneWave64) return launch_dkv_w64(a, dtype, causal, s);
-  if (choice == kDkvOneWave128) return launch_dkv_fr128(a, dtype, causal, dropout, sparse, sparse && sparse_plan_groups(a) > 0 ? kListGroups : 0, s);
-  if (dtype == 0 && d == 32) return launch_td<_Float16, 32>(a, causal, dropout, sparse, s);
-  if (dtype == 1 && d == 32) return launch_td<__bf16, 32>(a, causal, dropout, sparse, s);
-  if (dtype == 0 && d == 64) return launch_td<_Float16, 64>(a, causal, dropout, sparse, s);
-  if (dtype == 0 && d == 128) return launch_td<_Float16, 128>(a, causal, dropout, sparse, s);
-  if (dtype == 1 && d == 64) return launch_td<__bf16, 64>(a, causal, dropout, sparse, s);
-  if (dtype == 1 && d == 128) return launch_td<__bf16, 128>(a, causal, dropout, sparse, s);
+  if (choice == kDkvOneWave128) return launch_dkv_fr128(a, dtype, causal, dropout, sparse, list_groups, divide, s);
+  // the role-split kernel reads and writes whole rows of d elements (head dimension 16: of 32)
+  if (choice != kDkvRoleSplit || a.dvalid < d) return (int)hipErrorInvalidValue;
+  if (dtype == 0 && d == 32) return launch_td<_Float16, 32>(a, causal, dropout, sparse, list_groups, s);
+  if (dtype == 1 && d == 32) return launch_td<__bf16, 32>(a, causal, dropout, sparse, list_groups, s);
+  if (dtype == 0 && d == 64) return launch_td<_Float16, 64>(a, causal, dropout, sparse, list_groups, s);
+  if (dtype == 0 && d == 128) return launch_td<_Float16, 128>(a, causal, dropout, sparse, list_groups, s);
+  if (dtype == 1 && d == 64) return launch_td<__bf16, 64>(a, causal, dropout, sparse, list_groups, s);
+  if (dtype == 1 && d == 128) return launch_td<__bf16, 128>(a, causal, dropout, sparse, list_groups, s);
   return (int)hipErrorInvalidValue;
 }
 

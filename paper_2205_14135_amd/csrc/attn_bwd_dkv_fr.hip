@@ -408,8 +408,8 @@ int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_gro
 //   d = 32 causal (pairs)  16 x 197 18.9 -2.0 -3.6 -2.9; 8 x 4096 121 -22 -33 -42; 10 x 4096 132 -23 -24 -16; 128 x 512 29.2 -2.9 -3.0 +3.3
 //   block-sparse (butterfly mask of T x T blocks, heads x T), {4, 2} only  d = 64  4 x 8 48.1 +0.2; 8 x 16 69.8 -5.7; 4 x 32 65.8 -4.7; 8 x 32 69.6 +6.9,
 //            causal 68.4 -3.8; 4 x 64 75.5 +9.2 (the workgroups of the segment list take whole compute units then)
-WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse) {
-  if (!may_divide()) return {4, 1};
+WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
+  if (!divide) return {4, 1};
   const bool pairs = causal && !sparse;
   const WorkItems w(a, sparse, pairs);
   if (sparse) return w.of128 <= kComputeUnits / 2 ? WaveGroups{4, 2} : WaveGroups{4, 1};
@@ -421,8 +421,8 @@ WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse) {
 }
 
 template <typename T, int D>
-int launch_td(const KArgs& a, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
-  const WaveGroups w = dkv_fr_groups(a, D, causal, sparse);
+int launch_td(const KArgs& a, bool causal, bool dropout, bool sparse, int extra_groups, bool divide, hipStream_t s) {
+  const WaveGroups w = dkv_fr_groups(a, D, causal, sparse, divide);
   if (w.waves == 2 && w.groups == 4) return launch_groups<T, D, 2, 4>(a, causal, dropout, sparse, extra_groups, s);
   if (w.waves == 2) return launch_groups<T, D, 2, 2>(a, causal, dropout, sparse, extra_groups, s);
   if (w.groups == 2) return launch_groups<T, D, 4, 2>(a, causal, dropout, sparse, extra_groups, s);
@@ -432,12 +432,12 @@ int launch_td(const KArgs& a, bool causal, bool dropout, bool sparse, int extra_
 }  // namespace
 
 // sparse: extra_groups workgroups walk the segments of heavy columns.
-int launch_dkv_fr(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int extra_groups,
+int launch_dkv_fr(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int extra_groups, bool divide,
                   hipStream_t s) {
-  if (dtype == 0 && d == 32) return launch_td<_Float16, 32>(a, causal, dropout, sparse, extra_groups, s);
-  if (dtype == 1 && d == 32) return launch_td<__bf16, 32>(a, causal, dropout, sparse, extra_groups, s);
-  if (dtype == 0 && d == 64) return launch_td<_Float16, 64>(a, causal, dropout, sparse, extra_groups, s);
-  if (dtype == 1 && d == 64) return launch_td<__bf16, 64>(a, causal, dropout, sparse, extra_groups, s);
+  if (dtype == 0 && d == 32) return launch_td<_Float16, 32>(a, causal, dropout, sparse, extra_groups, divide, s);
+  if (dtype == 1 && d == 32) return launch_td<__bf16, 32>(a, causal, dropout, sparse, extra_groups, divide, s);
+  if (dtype == 0 && d == 64) return launch_td<_Float16, 64>(a, causal, dropout, sparse, extra_groups, divide, s);
+  if (dtype == 1 && d == 64) return launch_td<__bf16, 64>(a, causal, dropout, sparse, extra_groups, divide, s);
   return (int)hipErrorInvalidValue;
 }
 

@@ -371,16 +371,16 @@ int launch_groups(const KArgs& a, const WaveGroups& w, bool causal, bool dropout
 //            40 x 1024 93.6 +7.3 +16.3 +21.6
 //   causal   16 x 1024 62.4 -5.5 -9.1 -7.6; 8 x 2048 110 -15 -21 -22; 8 x 4096 213 -23 +6 -9; 40 x 1024 78.3 -2.8 +11.3 +19.4; 10 x 4096 254 +8 +42 +16
 //   dropout  8 x 2048 137 -19 -31 -35; 8 x 4096 272 -30 +16 -5; 60 x 512 48.2 -2.7 +8.2 +16.5; 10 x 4096 372 +23 +46 +5
-static WaveGroups fr128_groups(const KArgs& a, bool sparse) {
-  if (!may_divide()) return {4, 1};
+static WaveGroups fr128_groups(const KArgs& a, bool sparse, bool divide) {
+  if (!divide) return {4, 1};
   const WorkItems w(a, sparse, false);
   if (sparse) return w.of128 <= kComputeUnits / 2 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return w.tiles >= 32 ? WaveGroups{2, 4} : WaveGroups{2, 2};
   return w.of128 <= kComputeUnits && w.tiles >= 5 ? WaveGroups{4, 2} : WaveGroups{4, 1};
 }
 
-int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
-  const WaveGroups w = fr128_groups(a, sparse);
+int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool sparse, int extra_groups, bool divide, hipStream_t s) {
+  const WaveGroups w = fr128_groups(a, sparse, divide);
   return dtype == 0 ? launch_groups<_Float16>(a, w, causal, dropout, sparse, extra_groups, s)
                     : launch_groups<__bf16>(a, w, causal, dropout, sparse, extra_groups, s);
 }

@@ -64,14 +64,15 @@ enum { kLongBlocks = 24, kHeavyBlocks = 14, kSegBlocks = 12, kShortSegBlocks = 8
 // when first needed).  fwd: 0 = by measurement, 1 = free-running kernel, 2 = two-group kernel;
 // dkv: 0 = by measurement, 1 = role-split kernel wherever it exists, 2 = the 64-key kernel is not used,
 // 3 = the 64-key kernel wherever it exists.
-int fwd_variant();
-int dkv_variant();
+// A call reads them once: another thread may set them while it is under way.
+struct Overrides { int fwd, dkv; };
+Overrides overrides();
 
 // Which kernel serves a problem (the launchers use these; attn_debug_kernel_choice reports them).
 enum { kFwdFreeRunning = 0, kFwdTwoGroup = 1 };
 enum { kDkvRoleSplit = 0, kDkvOneWave = 1, kDkvOneWave128 = 2, kDkvOneWave64 = 3, kBwdShort = 4 };
-int choose_fwd(const KArgs& a, int d, bool causal, bool dropout, bool sparse);
-int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse);
+int choose_fwd(const KArgs& a, int d, bool causal, bool dropout, bool sparse, const Overrides& v);
+int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse, const Overrides& v);
 
 // How a tile kernel divides its work: `waves` wavefronts of 32 rows (dK/dV: keys) each share the streamed tiles of a workgroup,
 // and `groups` groups of that many wavefronts work on the same rows, group k on every groups-th tile; what the groups
@@ -80,7 +81,7 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse);
 // sweep a half or a quarter of the tiles each.  With more items than fit at once neither helps, {4, 1} has least overhead.
 // A dK/dV override (comparisons and tests) keeps every kernel at {4, 1}.
 struct WaveGroups { int waves, groups; };
-inline bool may_divide() { return dkv_variant() == 0; }
+inline bool may_divide(const Overrides& v) { return v.dkv == 0; }
 // The problem as these choices see it: work items with 64 and with 128 rows (pairs of row blocks where the kernel takes pairs),
 // 64-wide tiles that a row sweeps (block-sparse: a guess, the masks are on the GPU; a row of the butterfly mask keeps 5 to 10 blocks).
 struct WorkItems {
@@ -103,18 +104,19 @@ inline int sparse_plan_groups(const KArgs& a) {
 }
 
 // Launchers (defined in the .hip files).  dtype: 0 fp16, 1 bf16.  Return hipError_t as int.
-int launch_fwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s);
+int launch_fwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, const Overrides& v, hipStream_t s);
 // ev: nullptr, or four events: two recorded before the first launch, one after the dQ kernel, one after dK/dV.
-int launch_bwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s,
+int launch_bwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, const Overrides& v, hipStream_t s,
                hipEvent_t* ev);
 int launch_dropout_mask(const KArgs& a, uint8_t* keep, hipStream_t s);
-// dK/dV kernel with the S->P->dV and dP->dS->dK halves on two wavefronts of a SIMD (attn_bwd_dkv.hip)
-int launch_dkv_rs(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s);
-// dense dK/dV kernel for d <= 64: one wavefront does all four tile products (attn_bwd_dkv_fr.hip)
-int launch_dkv_fr(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int extra_groups,
+// the dK/dV kernel that `choice` names (kDkv...); divide: its work may be divided over groups of wavefronts.  The kernel with the S->P->dV
+// and dP->dS->dK halves on two wavefronts of a SIMD (attn_bwd_dkv.hip) is launched by this function itself
+int launch_dkv(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int choice, bool divide, hipStream_t s);
+// dK/dV kernel for d <= 64: one wavefront does all four tile products (attn_bwd_dkv_fr.hip)
+int launch_dkv_fr(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, int extra_groups, bool divide,
                   hipStream_t s);
 // the same at d = 128 (attn_bwd_dkv_fr128.hip)
-int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s);
+int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool sparse, int extra_groups, bool divide, hipStream_t s);
 // the same with 64 keys per wavefront and the accumulators in the accumulation registers (attn_bwd_dkv_w64.hip)
 int launch_dkv_w64(const KArgs& a, int dtype, bool causal, hipStream_t s);
 // the whole backward pass of short dense heads at d <= 64, one launch (attn_bwd_short.hip), and which heads take it

@@ -337,8 +337,8 @@ int launch_fwd_groups(KArgs a, bool causal, bool dropout, bool sparse, hipStream
 //            48 x 693 20.1 22.2 -, 24 x 2001 56.4 45.1 66.5, 40 x 1024 32.0 32.1 36.5, 48 x 1400 42.9 44.0 62.3, 64 x 1024 34.0 38.9 56.4
 //   block-sparse (butterfly mask of T x T blocks, heads x T)  d = 64  4 x 16 15.5 13.1 10.8 11.0; 4 x 64 20.0 17.0 17.4 24.3; 8 x 64 27.7 31.0 31.5 46.5;
 //            d = 128  4 x 16 20.4 18.3 17.4; 4 x 64 28.4 26.9 43.1; 8 x 64 43.8 51.7 85.0
-WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
-  if (!may_divide()) return {4, 1};
+WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
+  if (!divide) return {4, 1};
   const WorkItems w(a, sparse, causal && !sparse && d == 64);
   // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise)
   const int64_t fit24 = d == 64 ? kComputeUnits : (causal && w.tiles >= 24 ? 4 * kComputeUnits : 5 * kComputeUnits / 2);
@@ -364,8 +364,8 @@ WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool dropout, bool spa
 }
 
 template <typename T, int D>
-int launch_fwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, hipStream_t s) {
-  const WaveGroups w = fwd_groups(a, D, causal, dropout, sparse);
+int launch_fwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, bool divide, hipStream_t s) {
+  const WaveGroups w = fwd_groups(a, D, causal, sparse, divide);
   if constexpr (D <= 64)
     if (w.waves == 2 && w.groups == 4) return launch_fwd_groups<T, D, 2, 4>(a, causal, dropout, sparse, s);
   if (w.waves == 2) return launch_fwd_groups<T, D, 2, 2>(a, causal, dropout, sparse, s);
@@ -440,26 +440,26 @@ static bool two_group_is_faster(const KArgs& a, bool causal, bool dropout) {
   return pp < base;
 }
 
-int choose_fwd(const KArgs& a, int d, bool causal, bool dropout, bool sparse) {
-  const int variant = fwd_variant();
+int choose_fwd(const KArgs& a, int d, bool causal, bool dropout, bool sparse, const Overrides& v) {
   bool use_pp = d == 128 && two_group_is_faster(a, causal, dropout);
-  if (variant == 1) use_pp = false;
-  if (variant == 2 && d != 32) use_pp = true;
+  if (v.fwd == 1) use_pp = false;
+  if (v.fwd == 2 && d != 32) use_pp = true;
   return !sparse && use_pp ? kFwdTwoGroup : kFwdFreeRunning;
 }
 
-int launch_fwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, hipStream_t s) {
+int launch_fwd(const KArgs& a, int dtype, int d, bool causal, bool dropout, bool sparse, const Overrides& v, hipStream_t s) {
+  const bool divide = may_divide(v);
   // Dense d = 128 problems: see two_group_is_faster above.
   // At d <= 64 the vector ALU work dominates and this file's kernel measured faster at every N;
   // block-sparse problems always take it.  attn_debug_set_variant overrides the choice
   // (comparisons and tests).
-  if (choose_fwd(a, d, causal, dropout, sparse) == kFwdTwoGroup) return launch_fwd_pp(a, dtype, d, causal, dropout, s);
-  if (dtype == 0 && d == 32) return launch_fwd_td<_Float16, 32>(a, causal, dropout, sparse, s);
-  if (dtype == 1 && d == 32) return launch_fwd_td<__bf16, 32>(a, causal, dropout, sparse, s);
-  if (dtype == 0 && d == 64) return launch_fwd_td<_Float16, 64>(a, causal, dropout, sparse, s);
-  if (dtype == 0 && d == 128) return launch_fwd_td<_Float16, 128>(a, causal, dropout, sparse, s);
-  if (dtype == 1 && d == 64) return launch_fwd_td<__bf16, 64>(a, causal, dropout, sparse, s);
-  if (dtype == 1 && d == 128) return launch_fwd_td<__bf16, 128>(a, causal, dropout, sparse, s);
+  if (choose_fwd(a, d, causal, dropout, sparse, v) == kFwdTwoGroup) return launch_fwd_pp(a, dtype, d, causal, dropout, s);
+  if (dtype == 0 && d == 32) return launch_fwd_td<_Float16, 32>(a, causal, dropout, sparse, divide, s);
+  if (dtype == 1 && d == 32) return launch_fwd_td<__bf16, 32>(a, causal, dropout, sparse, divide, s);
+  if (dtype == 0 && d == 64) return launch_fwd_td<_Float16, 64>(a, causal, dropout, sparse, divide, s);
+  if (dtype == 0 && d == 128) return launch_fwd_td<_Float16, 128>(a, causal, dropout, sparse, divide, s);
+  if (dtype == 1 && d == 64) return launch_fwd_td<__bf16, 64>(a, causal, dropout, sparse, divide, s);
+  if (dtype == 1 && d == 128) return launch_fwd_td<__bf16, 128>(a, causal, dropout, sparse, divide, s);
   return (int)hipErrorInvalidValue;
 }
 
