@@ -23,7 +23,56 @@ __device__ __forceinline__ KArgsPtr kernel_args_again() {
   return p;
 }
 
-// Planning workgroup `id` of the dQ launch (all of its threads; lds: at least 64 * wavefronts ints).  Leaves the columns' block counts and
+// Kept blocks of the whole problem, from some rows of the masks: all of them up to 4096 bytes (a shared mask of T = 64), otherwise as many as
+// make 4096 bytes (16 at least), spread over the lengths and the heads' masks in turn, and over the rows by the fractions of the
+// golden ratio.  Every planning workgroup counts for itself and finds the same: a sum over the workgroups would take a launch of its own, and the
+// columns that one workgroup plans say least about the others where a global-token column is among them.  us, backward, butterfly mask of heads x T,
+// d = 64, heavy by a share estimated from the planned columns | from these rows (by the exact sum, in a launch of its own):
+//   16 x 512 2744 | 1577 (1560); 24 x 256 1492 | 1090 (1085); 32 x 128 843 | 664 (668); 48 x 64 540 | 448 (456); 8 x 128 173 | 174 (186)
+struct MaskSample {
+  int lengths, masks, rows;   // different lengths, different masks, rows looked at
+  __host__ __device__ explicit MaskSample(const KArgs& a) {
+    lengths = a.klen ? a.B : 1;
+    masks = a.mask_sh != 0 ? a.H : 1;
+    const int64_t all = (int64_t)lengths * masks * a.T, some = 4096 / a.T > 16 ? 4096 / a.T : 16;
+    rows = (int)(all < some ? all : some);
+  }
+  // this thread's part of the kept blocks in those rows
+  __host__ __device__ int count(const KArgs& a, bool causal, int thread, int n_threads) const {
+    const bool all = rows == (int64_t)lengths * masks * a.T;
+    const int words = (a.T + 3) / 4;   // four mask bytes at a time
+    int n = 0;
+#pragma unroll 4
+    for (int p = thread; p < rows * words; p += n_threads) {
+      const int i = p / words, c = 4 * (p % words);
+      const int lm = all ? i / a.T : (int)((int64_t)i * lengths * masks / rows);
+      const int row = all ? i % a.T : (int)((uint64_t)((uint32_t)i * 2654435769u + 0x80000000u) * (uint32_t)a.T >> 32);
+      int blocks = a.T;
+      if (a.klen) blocks = (min(max(a.klen[lm / masks], 0), a.N) + kMaskBlock - 1) / kMaskBlock;
+      const int end = row < blocks ? min(causal ? row + 1 : a.T, blocks) - c : 0;   // columns from c on that count
+      const uint8_t* const m = a.mask + (int64_t)(lm % masks) * a.mask_sh + (int64_t)row * a.T + c;
+      uint32_t w = 0;
+      if (c + 4 <= a.T) __builtin_memcpy(&w, m, 4);
+      else for (int e = 0; c + e < a.T; ++e) w |= (uint32_t)m[e] << 8 * e;
+      uint32_t kept = (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u;   // a bit per byte that is not 0
+      if (end < 4) kept &= end > 0 ? (1u << 8 * end) - 1 : 0;
+      n += __builtin_popcount(kept);
+    }
+    return n;
+  }
+  __host__ __device__ int64_t total(const KArgs& a, int64_t counted) const { return counted * a.B * a.H * a.T / rows; }
+};
+
+// Segments that a column of cnt kept blocks is cut into (0: it is not heavy), by the rule at kLongBlocks; near: the kept blocks of the n_near columns planned
+// together, total: those of the whole problem.
+__host__ __device__ inline int column_segments(int cnt, int near, int n_near, int64_t total) {
+  const bool stands_out = (int64_t)cnt * n_near > 2 * (int64_t)near;
+  if (cnt <= total / (2 * kComputeUnits) || cnt <= (stands_out ? (int)kHeavyBlocks : (int)kLongBlocks)) return 0;
+  const int seg_blocks = stands_out && cnt <= kShortSegLimit ? (int)kShortSegBlocks : (int)kSegBlocks;
+  return min((int)kMaxSegs, (cnt + seg_blocks - 1) / seg_blocks);
+}
+
+// Planning workgroup `id` of the dQ launch (all of its threads; lds: at least 65 * wavefronts ints).  Leaves the columns' block counts and
 // numbers of segments (0: not heavy), the sum of the latter, zeroed tickets, and zeroed accumulators for the heavy columns.
 template <int D>
 __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal, int* lds) {
@@ -36,6 +85,11 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   const uint8_t* const mask = a.mask + (int64_t)(bh % a.H) * a.mask_sh + col;
   const int first = causal ? col : 0;                                             // same row range as the
   const int limit = col < a.T && col * 128 < len ? min(a.T, (len + 127) / 128) : 0;   // tile iterators of the dK/dV kernels
+  const MaskSample sample(a);
+  int counted = sample.count(a, causal, threadIdx.x, blockDim.x);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) counted += __shfl_xor(counted, off, 64);
+  if (lane == 0) lds[64 * n_waves + wave] = counted;
   int cnt = 0;
 #pragma unroll 8
   for (int row = (64 / kPlanCols) * wave + lane / kPlanCols; row < a.T; row += (64 / kPlanCols) * n_waves)
@@ -45,18 +99,15 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   // every wavefront knows all totals
   cnt = 0;
   for (int i = c; i < 64 * n_waves; i += kPlanCols) cnt += lds[i];
-  int total = cnt;
+  int near = cnt;
 #pragma unroll
-  for (int off = kPlanCols / 2; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
-  // more than half of a compute unit's fair share, were all columns of all heads as full as these
-  const int n_cols = min((int)kPlanCols, a.T - cg * kPlanCols);
-  const int64_t share = (int64_t)total * a.T / n_cols * a.B * a.H / (2 * kComputeUnits);
-  const bool stands_out = (int64_t)cnt * n_cols > 2 * (int64_t)total;
-  const bool heavy = col < a.T && cnt > share && cnt > (stands_out ? (int)kHeavyBlocks : (int)kLongBlocks);
-  const int seg_blocks = stands_out && cnt <= kShortSegLimit ? (int)kShortSegBlocks : (int)kSegBlocks;
-  const uint32_t heavy_cols = (uint32_t)__ballot(heavy) & ((1u << kPlanCols) - 1);
+  for (int off = kPlanCols / 2; off > 0; off >>= 1) near += __shfl_xor(near, off, 64);
+  int64_t all_counted = 0;
+  for (int w = 0; w < n_waves; ++w) all_counted += lds[64 * n_waves + w];
+  int segs = column_segments(cnt, near, min((int)kPlanCols, a.T - cg * kPlanCols), sample.total(a, all_counted));
+  if (col >= a.T) segs = 0;
+  const uint32_t heavy_cols = (uint32_t)__ballot(segs > 0) & ((1u << kPlanCols) - 1);
   if (wave == 0) {
-    int segs = heavy ? min((int)kMaxSegs, (cnt + seg_blocks - 1) / seg_blocks) : 0;
     if (lane < kPlanCols && col < a.T) {
       a.colcnt[item] = cnt;
       a.col_segs[item] = segs;
