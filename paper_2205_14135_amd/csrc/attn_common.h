@@ -52,7 +52,7 @@ struct KArgs {
 
 enum { kXcds = 8, kMaskBlock = 128 };
 // Block-sparse dK/dV: a mask column is "heavy" when it keeps more than kLongBlocks blocks, or more than kHeavyBlocks and twice as
-// many as its neighbours on average, AND more than half of a compute unit's fair share of all kept blocks (so a mask whose columns are
+// many as its neighbours (the columns looked at with it, but itself) on average, AND more than half of a compute unit's fair share of all kept blocks (so a mask whose columns are
 // all long, e.g. a dense one, is not split at all).  Heavy columns are cut into segments (at most kMaxSegs), one workgroup
 // each, summed with fp32 atomics: of about kSegBlocks blocks, or kShortSegBlocks where a single column stands out from its neighbours
 // and is not longer than kShortSegLimit.  us, backward with 24 and segments of 12 for all | this; heads x T, butterfly mask: d = 64

@@ -63,10 +63,14 @@ struct MaskSample {
   __host__ __device__ int64_t total(const KArgs& a, int64_t counted) const { return counted * a.B * a.H * a.T / rows; }
 };
 
-// Segments that a column of cnt kept blocks is cut into (0: it is not heavy), by the rule at kLongBlocks; near: the kept blocks of the n_near columns planned
-// together, total: those of the whole problem.
+// The planning workgroups of a head look at kPlanCols columns each.  Those of the last one start early where T is no multiple, so that a
+// column always has neighbours to stand out from; it leaves alone the ones that the workgroup before it plans.
+__host__ __device__ inline int plan_window(int T, int cg) { return min(cg * kPlanCols, max(T - kPlanCols, 0)); }
+
+// Segments that a column of cnt kept blocks is cut into (0: it is not heavy), by the rule at kLongBlocks; near: the kept blocks of the n_near columns looked at
+// together, this one among them, total: those of the whole problem.
 __host__ __device__ inline int column_segments(int cnt, int near, int n_near, int64_t total) {
-  const bool stands_out = (int64_t)cnt * n_near > 2 * (int64_t)near;
+  const bool stands_out = (int64_t)cnt * (n_near - 1) > 2 * (int64_t)(near - cnt);
   if (cnt <= total / (2 * kComputeUnits) || cnt <= (stands_out ? (int)kHeavyBlocks : (int)kLongBlocks)) return 0;
   const int seg_blocks = stands_out && cnt <= kShortSegLimit ? (int)kShortSegBlocks : (int)kSegBlocks;
   return min((int)kMaxSegs, (cnt + seg_blocks - 1) / seg_blocks);
@@ -81,7 +85,8 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   const int bh = id / n_cg, cg = id % n_cg;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
   const int len = a.klen ? min(max(a.klen[bh / a.H], 0), a.N) : a.N;
-  const int c = lane % kPlanCols, col = cg * kPlanCols + c, item = bh * a.T + col;   // a wavefront reads its columns of four rows at a time
+  const int col0 = plan_window(a.T, cg);
+  const int c = lane % kPlanCols, col = col0 + c, item = bh * a.T + col;   // a wavefront reads its columns of four rows at a time
   const uint8_t* const mask = a.mask + (int64_t)(bh % a.H) * a.mask_sh + col;
   const int first = causal ? col : 0;                                             // same row range as the
   const int limit = col < a.T && col * 128 < len ? min(a.T, (len + 127) / 128) : 0;   // tile iterators of the dK/dV kernels
@@ -104,11 +109,12 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   for (int off = kPlanCols / 2; off > 0; off >>= 1) near += __shfl_xor(near, off, 64);
   int64_t all_counted = 0;
   for (int w = 0; w < n_waves; ++w) all_counted += lds[64 * n_waves + w];
-  int segs = column_segments(cnt, near, min((int)kPlanCols, a.T - cg * kPlanCols), sample.total(a, all_counted));
-  if (col >= a.T) segs = 0;
+  int segs = column_segments(cnt, near, min((int)kPlanCols, a.T), sample.total(a, all_counted));
+  const bool mine = col >= cg * kPlanCols && col < a.T;
+  if (!mine) segs = 0;
   const uint32_t heavy_cols = (uint32_t)__ballot(segs > 0) & ((1u << kPlanCols) - 1);
   if (wave == 0) {
-    if (lane < kPlanCols && col < a.T) {
+    if (lane < kPlanCols && mine) {
       a.colcnt[item] = cnt;
       a.col_segs[item] = segs;
       a.ticket[item] = 0;
@@ -118,7 +124,7 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
     if (lane == 0) a.group_segs[id] = segs;
   }
   for (uint32_t bits = heavy_cols; bits != 0; bits &= bits - 1) {
-    const int64_t off = ((int64_t)bh * a.N + (int64_t)(cg * kPlanCols + __builtin_ctz(bits)) * 128) * D;
+    const int64_t off = ((int64_t)bh * a.N + (int64_t)(col0 + __builtin_ctz(bits)) * 128) * D;
     for (int i = threadIdx.x; i < 128 * D / 4; i += blockDim.x) {
       const f32x4 z = {0.f, 0.f, 0.f, 0.f};
       *(f32x4*)(a.dKacc + off + 4 * i) = z;

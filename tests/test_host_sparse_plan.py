@@ -22,6 +22,7 @@ extern "C" int64_t estimate(const uint8_t* mask, int per_head, const int* length
   for (int t = 0; t < threads; ++t) counted += s.count(a, causal != 0, t, threads);
   return s.total(a, counted);
 }
+extern "C" int window(int T, int cg) { return attn::plan_window(T, cg); }
 extern "C" int segments(int cnt, int near, int n_near, int64_t total) { return attn::column_segments(cnt, near, n_near, total); }
 """
 
@@ -52,10 +53,10 @@ def _kept(mask, B, H, lengths=None, causal=False):
     return total
 
 
-def _planned(mask, col):
-    """Kept blocks of a column, and what is planned together with it."""
+def _planned(shim, mask, col):
+    """Kept blocks of a column, and of the columns that are looked at together with it."""
     T = mask.shape[0]
-    c0 = col // 16 * 16
+    c0 = shim.window(T, col // 16)
     counts = (mask != 0).sum(0)
     near = counts[c0:c0 + 16]
     return int(counts[col]), int(near.sum()), len(near)
@@ -105,7 +106,7 @@ def test_the_global_column_is_split_while_it_exceeds_a_fair_share(shim, heads, T
     """The column that every row keeps, in the mask whose other columns keep about ten blocks: it is cut wherever it is longer than half of what a
     compute unit gets, however many heads there are."""
     m = butterfly_block_mask(T)
-    assert (shim.segments(*_planned(m, 0), _estimate(shim, m, 1, heads)) > 0) == (_length_over_share(heads, T) > 1)
+    assert (shim.segments(*_planned(shim, m, 0), _estimate(shim, m, 1, heads)) > 0) == (_length_over_share(heads, T) > 1)
 
 
 @pytest.mark.parametrize("heads,T", [(16, 512), (24, 256), (32, 128), (48, 64), (8, 128)])
@@ -115,10 +116,26 @@ def test_no_workgroup_outlasts_the_others(shim, heads, T):
     counts, work = (m != 0).sum(0), []
     total = _estimate(shim, m, 1, heads)
     for col in range(T):
-        cnt, near, n_near = _planned(m, col)
+        cnt, near, n_near = _planned(shim, m, col)
         s = shim.segments(cnt, near, n_near, total)
         work += [-(-cnt // s)] * s if s else [cnt]
     places = np.zeros(PLACES)
     for w in sorted(work * heads, reverse=True):
         places[places.argmin()] += w
     assert places.max() <= 1.25 * counts.sum() * heads / PLACES + 12
+
+
+@pytest.mark.parametrize("T", [17, 18, 31, 33, 34, 47, 49])
+def test_the_last_columns_stand_out_too(shim, T):
+    """A full column among thin ones is cut, wherever it stands: also where the columns do not divide by the sixteen of a planning workgroup."""
+    for col in range(T):
+        m = np.eye(T, dtype=np.uint8)
+        m[:, col] = 1
+        cnt, near, n_near = _planned(shim, m, col)
+        assert n_near == 16 and shim.segments(cnt, near, n_near, _estimate(shim, m, 1, 1)) >= 2
+
+
+def test_standing_out_is_by_the_neighbours(shim):
+    """Twice as many blocks as the other columns keep on average, not as all of them do: 15 blocks beside fifteen columns of 7 (106 in all) are more than that."""
+    assert shim.segments(15, 15 + 15 * 7, 16, 1000) > 0
+    assert shim.segments(15, 15 + 15 * 8, 16, 1000) == 0
