@@ -90,11 +90,6 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   const uint8_t* const mask = a.mask + (int64_t)(bh % a.H) * a.mask_sh + col;
   const int first = causal ? col : 0;                                             // same row range as the
   const int limit = col < a.T && col * 128 < len ? min(a.T, (len + 127) / 128) : 0;   // tile iterators of the dK/dV kernels
-  const MaskSample sample(a);
-  int counted = sample.count(a, causal, threadIdx.x, blockDim.x);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) counted += __shfl_xor(counted, off, 64);
-  if (lane == 0) lds[64 * n_waves + wave] = counted;
   int cnt = 0;
 #pragma unroll 8
   for (int row = (64 / kPlanCols) * wave + lane / kPlanCols; row < a.T; row += (64 / kPlanCols) * n_waves)
@@ -107,9 +102,18 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   int near = cnt;
 #pragma unroll
   for (int off = kPlanCols / 2; off > 0; off >>= 1) near += __shfl_xor(near, off, 64);
-  int64_t all_counted = 0;
-  for (int w = 0; w < n_waves; ++w) all_counted += lds[64 * n_waves + w];
-  int segs = column_segments(cnt, near, min((int)kPlanCols, a.T), sample.total(a, all_counted));
+  int segs = 0;
+  if (__ballot(cnt > kHeavyBlocks) != 0) {   // (the same in all wavefronts)
+    const MaskSample sample(a);
+    int counted = sample.count(a, causal, threadIdx.x, blockDim.x);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) counted += __shfl_xor(counted, off, 64);
+    if (lane == 0) lds[64 * n_waves + wave] = counted;
+    __syncthreads();
+    int64_t all_counted = 0;
+    for (int w = 0; w < n_waves; ++w) all_counted += lds[64 * n_waves + w];
+    segs = column_segments(cnt, near, min((int)kPlanCols, a.T), sample.total(a, all_counted));
+  }
   const bool mine = col >= cg * kPlanCols && col < a.T;
   if (!mine) segs = 0;
   const uint32_t heavy_cols = (uint32_t)__ballot(segs > 0) & ((1u << kPlanCols) - 1);
@@ -134,7 +138,9 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
 }
 
 // Segment number idx of all heavy columns, in the order of the planning groups: its column, its first kept block, its length.  Every
-// wavefront finds it by itself.  False past the end.
+// wavefront finds it by itself: each lane adds up a run of the groups' sums, whose loads do not wait for one another, then the run that holds the
+// segment is searched.  Backward of masks of the diagonal alone, heads x T, the sums in turns of 64 (a load and a scan each) | this: d = 32 512 x 64
+// 812 | 799 us, 1024 x 32 814 | 800, 4096 x 16 1595 | 1572; d = 64 64 x 512 1573 | 1562.  False past the end.
 __device__ __forceinline__ bool sparse_segment(int idx, int& item, int& skip_blocks, int& take_blocks) {
   const auto& a = *kernel_args_again();
   const int lane = threadIdx.x & 63;
@@ -146,29 +152,36 @@ __device__ __forceinline__ bool sparse_segment(int idx, int& item, int& skip_blo
     }
     return v;
   };
-  const int n_cg = (a.T + kPlanCols - 1) / kPlanCols, n_groups = a.B * a.H * n_cg;
-  for (int g0 = 0; g0 < n_groups; g0 += 64) {
-    const int sum = inclusive(g0 + lane < n_groups ? a.group_segs[g0 + lane] : 0);
-    const int total = __builtin_amdgcn_readlane(sum, 63);
-    if (idx >= total) {
+  const int n_cg = (a.T + kPlanCols - 1) / kPlanCols, n_groups = a.B * a.H * n_cg, run = (n_groups + 63) / 64;
+  int sum = 0;
+#pragma unroll 8
+  for (int k = 0; k < run; ++k) sum += lane * run + k < n_groups ? a.group_segs[lane * run + k] : 0;
+  sum = inclusive(sum);
+  if (idx >= __builtin_amdgcn_readlane(sum, 63)) return false;
+  int at = __builtin_ctzll(__ballot(sum > idx));
+  if (at > 0) idx -= __builtin_amdgcn_readlane(sum, at - 1);
+  int group = at * run;
+  if (run > 1) {
+    for (const int end = min(group + run, n_groups);; group += 64) {
+      sum = inclusive(group + lane < end ? a.group_segs[group + lane] : 0);
+      const int total = __builtin_amdgcn_readlane(sum, 63);
+      if (idx < total) break;
       idx -= total;
-      continue;
     }
-    const int at = __builtin_ctzll(__ballot(sum > idx));
+    at = __builtin_ctzll(__ballot(sum > idx));
     if (at > 0) idx -= __builtin_amdgcn_readlane(sum, at - 1);
-    const int group = g0 + at, bh = group / n_cg, cg = group % n_cg;
-    const int col = cg * kPlanCols + lane;
-    const int segs = lane < kPlanCols && col < a.T ? a.col_segs[bh * a.T + col] : 0;
-    const int csum = inclusive(segs);
-    const int which = __builtin_ctzll(__ballot(csum > idx));
-    // (the same in all lanes: in scalar registers)
-    item = __builtin_amdgcn_readfirstlane(bh * a.T + cg * kPlanCols + which);
-    const int n = __builtin_amdgcn_readlane(segs, which), seg = idx - (which > 0 ? __builtin_amdgcn_readlane(csum, which - 1) : 0);
-    take_blocks = __builtin_amdgcn_readfirstlane((a.colcnt[item] + n - 1) / n);
-    skip_blocks = __builtin_amdgcn_readfirstlane(seg * take_blocks);
-    return true;
+    group += at;
   }
-  return false;
+  const int bh = group / n_cg, cg = group % n_cg, col = cg * kPlanCols + lane;
+  const int segs = lane < kPlanCols && col < a.T ? a.col_segs[bh * a.T + col] : 0;
+  sum = inclusive(segs);
+  at = __builtin_ctzll(__ballot(sum > idx));
+  // (the same in all lanes: in scalar registers)
+  item = __builtin_amdgcn_readfirstlane(bh * a.T + cg * kPlanCols + at);
+  const int n = __builtin_amdgcn_readlane(segs, at), seg = idx - (at > 0 ? __builtin_amdgcn_readlane(sum, at - 1) : 0);
+  take_blocks = __builtin_amdgcn_readfirstlane((a.colcnt[item] + n - 1) / n);
+  skip_blocks = __builtin_amdgcn_readfirstlane(seg * take_blocks);
+  return true;
 }
 
 // After a segment's atomics, with all threads of its workgroup: the last of the column's segments to get here converts the sums to

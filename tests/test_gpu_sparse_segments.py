@@ -90,6 +90,27 @@ def test_segments_on_dirty_workspaces(B, H, T, d, kind):
         assert float((x.float() - y.float()).norm()) <= 2.0 ** -8 * norm
 
 
+# more planning groups than the lanes that look for a segment, and more than they look through in one turn: a few heads that keep heavy columns among
+# many that keep nothing
+@pytest.mark.parametrize("H,T", [(100, 17), (4200, 15)])
+def test_segments_far_apart(H, T):
+    d, N, at = 32, 128 * T, [0, 31, 32, 33, H // 2 + 1, H - 3, H - 1]
+    _, few = hp.make_case(1, len(at), N, d, "bf16", inputs.BASE_SEED + 6900 + T)
+    masks = torch.from_numpy(_masks("columns", len(at), T)).cuda()
+    kw = dict(softmax_scale=1 / math.sqrt(d))
+    want = _backward(few, masks, **kw)()
+    many = {n: torch.zeros(1, H, N, d, dtype=t.dtype, device="cuda") for n, t in few.items()}
+    for n, t in many.items():
+        t[:, at] = few[n]
+    all_masks = torch.zeros(H, T, T, dtype=torch.uint8, device="cuda")
+    all_masks[at] = masks
+    for x, y in zip(_backward(many, all_masks, **kw)(), want):
+        # sums of float32 parts, in other orders, rounded once
+        assert float((x[:, at].float() - y.float()).norm()) <= 2.0 ** -8 * float(y.float().norm())
+        x[:, at] = 0
+        assert not bool(x.any())
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_segments_replayed(d):
     H, T = 2, 17
