@@ -190,9 +190,9 @@ int attn_blocksparse_fwd(const attn_params* p, const uint8_t* block_mask, int32_
  * Block-sparse backward: Algorithm 4 restricted to the non-zero blocks (the
  * paper states only that the backward skips the same blocks, Section 3.3).
  * Arguments as attn_bwd plus the mask arguments of attn_blocksparse_fwd; the workspace must
- * hold attn_blocksparse_bwd_workspace_bytes(p) bytes.  dK and dV of mask columns that are split
- * over several workgroups are summed with fp32 atomics, so their last bits may differ from run
- * to run; everything else is bit-reproducible.
+ * hold attn_blocksparse_bwd_workspace_bytes(p) bytes.  dK and dV of mask columns that keep more
+ * than 24 blocks may be split over several workgroups and summed with fp32 atomics, so their last bits may
+ * differ from run to run; everything else is bit-reproducible.
  */
 int attn_blocksparse_bwd(const attn_params* p, const uint8_t* block_mask, int32_t mask_block,
                          int64_t mask_stride_h, const void* Q, const void* K, const void* V,

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
   constexpr bool PAIRED = CAUSAL && !SPARSE;
   const int n_pair = (n_kt + 1) / 2;
   for (int round = 0;; ++round) {
-  int item, skip_blocks = 0, take_blocks = 0x7fffffff;
+  int item, slot = 0, skip_blocks = 0, take_blocks = 0x7fffffff;
   bool heavy = false, last_round = true;
   if (!list_mode) {
     item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
       item = (item / n_pair) * n_kt + (round == 0 ? q : n_kt - 1 - q);
     }
   } else {
-    if (!sparse_segment((int)blockIdx.x + round * n_list, item, skip_blocks, take_blocks)) return;
+    if (!sparse_segment((int)blockIdx.x + round * n_list, item, slot, skip_blocks, take_blocks)) return;
     heavy = true;
   }
   const int bh = SPARSE ? item / n_kt : dealt_head(a, item / n_kt);
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(NT) void dkv_rs_kernel(const KArgs a) {
     // Q buffers stage 32 x D floats for each of four wavefronts: role A's dV first, then role B's dK
     __syncthreads();   // role B has finished reading the tiles
     float* stage = (float*)&Qs[0][0] + pair * 32 * D;
-    const int64_t acc_row0 = ((int64_t)bh * a.N + kw0) * D;
+    const int64_t acc_row0 = ((int64_t)slot * 128 + (kw0 - kt * 128)) * D;
     if (!role_b) atomic_add_rows_coalesced<D>(stage, a.dVacc + acc_row0, acc, out_scale, D == 32 ? a.dvalid : D);
     __syncthreads();
     if (role_b) atomic_add_rows_coalesced<D>(stage, a.dKacc + acc_row0, acc, out_scale, D == 32 ? a.dvalid : D);

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
   constexpr bool PAIRED = CAUSAL && !SPARSE;
   const int n_pair = (n_kt + 1) / 2;
   for (int round = 0;; ++round) {
-  int item, skip_blocks = 0, take_blocks = 0x7fffffff;
+  int item, slot = 0, skip_blocks = 0, take_blocks = 0x7fffffff;
   bool heavy = false, last_round = true;
   if (!list_mode) {
     item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
       item = (item / n_pair) * n_kt + (round == 0 ? q : n_kt - 1 - q);
     }
   } else {
-    if (!sparse_segment((int)blockIdx.x + round * n_list, item, skip_blocks, take_blocks)) return;
+    if (!sparse_segment((int)blockIdx.x + round * n_list, item, slot, skip_blocks, take_blocks)) return;
     heavy = true;
   }
   const int bh = SPARSE ? item / n_kt : dealt_head(a, item / n_kt);
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
     // ended on a barrier: the two Q buffers stage the rows of wavefronts 0 and 1, the two dO buffers
     // those of wavefronts 2 and 3 (32 x D floats each), first for dV, then for dK
     float* stage = (float*)(wave < 2 ? Qs0 : Gs0) + (wave & 1) * 32 * D;
-    const int64_t acc_row0 = ((int64_t)bh * a.N + kw0) * D;
+    const int64_t acc_row0 = ((int64_t)slot * 128 + (kw0 - kt * 128)) * D;
     atomic_add_rows_coalesced<D>(stage, a.dVacc + acc_row0, dv, DROPOUT ? a.keep_scale : 1.f, D == 32 ? a.dvalid : D);
     atomic_add_rows_coalesced<D>(stage, a.dKacc + acc_row0, dk, a.tau, D == 32 ? a.dvalid : D);
   } else {

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
   const int n_list = SPARSE ? (int)gridDim.x - kXcds * a.chunk : 0;
   const bool list_mode = SPARSE && (int)blockIdx.x < n_list;
   for (int round = 0;; ++round) {
-  int item, skip_blocks = 0, take_blocks = 0x7fffffff;
+  int item, slot = 0, skip_blocks = 0, take_blocks = 0x7fffffff;
   if (!list_mode) {
     item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
     if (item < 0) return;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
       if (n_list > 0 && a.col_segs[item] > 0) return;   // heavy
     }
   } else {
-    if (!sparse_segment((int)blockIdx.x + round * n_list, item, skip_blocks, take_blocks)) return;
+    if (!sparse_segment((int)blockIdx.x + round * n_list, item, slot, skip_blocks, take_blocks)) return;
   }
   int bh = item / n_kt;
   int kt = item % n_kt;
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
     // one of several segments of this column: sum in fp32; the last of them converts.  32 x 128 floats per wavefront
     static_assert(!SPARSE || (RW == 4 && 4 * 32 * D * 4 <= (int)sizeof(all)), "LDS stages a gradient in fp32");
     float* stage = (float*)all + wave * 32 * D;
-    const int64_t acc_row0 = ((int64_t)bh * a.N + kw0) * D;
+    const int64_t acc_row0 = ((int64_t)slot * 128 + (kw0 - kt * 128)) * D;
     atomic_add_rows_coalesced<D>(stage, a.dVacc + acc_row0, dv, DROPOUT ? a.keep_scale : 1.f);
     atomic_add_rows_coalesced<D>(stage, a.dKacc + acc_row0, dk, a.tau);
   } else {

@@ -25,7 +25,7 @@ struct KArgs {
   float* Dvec;             // bwd scratch: -D_i = -rowsum(dO_i o O_i)   [B,H,Nr], 0 for rows >= N
   float* L2vec;            // bwd scratch: L_i * log2(e), +inf where L_i = -inf and for rows >= N   [B,H,Nr]
   int* colcnt;             // block-sparse bwd scratch: kept blocks per mask column   [B*H, T]
-  int* col_segs;           // block-sparse bwd scratch: segments of a heavy column, 0 for the others   [B*H, T]
+  int* col_segs;           // block-sparse bwd scratch: segments of a heavy column, 0 for the others (column_entry in attn_sparse.h)   [B*H, T]
   int* ticket;             // block-sparse bwd scratch: segments of a heavy column that have ended   [B*H, T]
   int* group_segs;         // block-sparse bwd scratch: segments of the heavy columns among kPlanCols   [B*H, ceil(T / kPlanCols)]
   int plan_groups;         // block-sparse bwd: planning workgroups at the head of the dQ launch (0: no column can be heavy)
@@ -56,8 +56,9 @@ enum { kXcds = 8, kMaskBlock = 128 };
 // all long, e.g. a dense one, is not split at all).  Heavy columns are cut into segments (at most kMaxSegs), one workgroup
 // each, summed with fp32 atomics: of about kSegBlocks blocks, or kShortSegBlocks where a single column stands out from its neighbours
 // and is not longer than kShortSegLimit.  us, backward with 24 and segments of 12 for all | this; heads x T, butterfly mask: d = 64
-// 8 x 24 83.5 | 54.3, 3 x 20 52.9 | 41.7, 4 x 32 50.2 | 45.6, 8 x 64 96.3 | 92.3; d = 128 8 x 24 126 | 87, 4 x 16 71.5 | 74.1, 8 x 64 165 | 156.  A dense mask
-// of 4 x 48: 182 | 207 with 14 and 8 for all columns, 8 x 128 at d = 128 292 | 294 with segments of 8 for the longest.
+// 8 x 24 92 | 53, 3 x 20 80 | 41, 4 x 32 66 | 44, 8 x 64 106 | 91; d = 128 8 x 24 124 | 85, 16 x 16 101 | 85, 8 x 64 186 | 152 (with the planning launches and,
+// at d = 128, the role-split kernel of then).  A dense mask of 4 x 48: 182 | 207 with 14 and 8 for all columns, 8 x 128 at d = 128 292 | 294 with segments of 8
+// for the longest.
 enum { kLongBlocks = 24, kHeavyBlocks = 14, kSegBlocks = 12, kShortSegBlocks = 8, kShortSegLimit = 64, kMaxSegs = 32, kComputeUnits = 256 };
 
 // Kernel-choice overrides (attn_debug_set_variant; initial values from the environment, read once

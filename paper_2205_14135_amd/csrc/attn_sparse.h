@@ -6,6 +6,8 @@
 // of a head; the last segment of a column to end converts its sums.  (Three launches of 5 to 6 us each before, two between dQ and dK/dV and
 // one after: backward pass of 2 heads of T = 8 blocks, d = 64, 40 us, now 31; 8 heads of 64 blocks 107, now 91; 8 x 128 181, now 167.)
 #pragma once
+#include <type_traits>
+
 #include "attn_common.h"
 #include "attn_tiles.h"
 
@@ -76,6 +78,21 @@ __host__ __device__ inline int column_segments(int cnt, int near, int n_near, in
   return min((int)kMaxSegs, (cnt + seg_blocks - 1) / seg_blocks);
 }
 
+// Columns of up to kLongBlocks blocks keep reproducible gradients.  Sums of two addends do not depend on which comes first, so two of a column's
+// three segments add into its own accumulators and the third into those of a light column, which stand idle; the last one to end adds
+// the two.  (Two segments where no light column is left.  Two for all: 8 x 24 at d = 64 53 -> 64 us, at d = 128 85 -> 103.)  A column's entry in col_segs is
+// its number of segments, and from bit 8 on where the third one goes: the other column's number less its own plus kPlanCols, or 0.
+__host__ __device__ inline int segs_of(int entry) { return entry & 255; }
+// The column whose accumulators segment seg of column item adds into.
+__host__ __device__ inline int slot_of(int item, int entry, int seg) { return seg == 2 && entry > 255 ? item + (entry >> 8) - kPlanCols : item; }
+// The entry of column c among those looked at together, from their segments; light, three: of which columns the accumulators are idle, and which have
+// three segments and must not have more than two addends (bits).
+__host__ __device__ inline int column_entry(int c, int segs, uint32_t light, uint32_t three) {
+  if (!(three >> c & 1)) return segs;
+  for (uint32_t before = three & ((1u << c) - 1); before != 0; before &= before - 1) light &= light - 1;   // taken
+  return light == 0 ? 2 : 3 | (__builtin_ctz(light) - c + kPlanCols) << 8;
+}
+
 // Planning workgroup `id` of the dQ launch (all of its threads; lds: at least 65 * wavefronts ints).  Leaves the columns' block counts and
 // numbers of segments (0: not heavy), the sum of the latter, zeroed tickets, and zeroed accumulators for the heavy columns.
 template <int D>
@@ -116,18 +133,25 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   }
   const bool mine = col >= cg * kPlanCols && col < a.T;
   if (!mine) segs = 0;
-  const uint32_t heavy_cols = (uint32_t)__ballot(segs > 0) & ((1u << kPlanCols) - 1);
+  constexpr uint32_t kCols = (1u << kPlanCols) - 1;
+  const uint32_t heavy = (uint32_t)__ballot(segs > 0) & kCols, light = (uint32_t)__ballot(mine && segs == 0) & kCols;
+  const uint32_t three = (uint32_t)__ballot(segs == 3 && cnt <= kLongBlocks) & kCols;
+  const int entry = column_entry(c, segs, light, three);
+  const uint32_t lent = (uint32_t)__ballot(entry > 255) & kCols;
   if (wave == 0) {
     if (lane < kPlanCols && mine) {
       a.colcnt[item] = cnt;
-      a.col_segs[item] = segs;
+      a.col_segs[item] = entry;
       a.ticket[item] = 0;
     }
+    segs = segs_of(entry);
 #pragma unroll
     for (int off = kPlanCols / 2; off > 0; off >>= 1) segs += __shfl_xor(segs, off, 64);
     if (lane == 0) a.group_segs[id] = segs;
   }
-  for (uint32_t bits = heavy_cols; bits != 0; bits &= bits - 1) {
+  uint32_t cleared = heavy;   // and the first light ones, one for each column that adds into one
+  for (uint32_t rest = light, n = __builtin_popcount(lent); n > 0; --n, rest &= rest - 1) cleared |= rest & -rest;
+  for (uint32_t bits = cleared; bits != 0; bits &= bits - 1) {
     const int64_t off = ((int64_t)bh * a.N + (int64_t)(col0 + __builtin_ctz(bits)) * 128) * D;
     for (int i = threadIdx.x; i < 128 * D / 4; i += blockDim.x) {
       const f32x4 z = {0.f, 0.f, 0.f, 0.f};
@@ -137,11 +161,11 @@ __device__ __forceinline__ void sparse_plan(const KArgs& a, int id, bool causal,
   }
 }
 
-// Segment number idx of all heavy columns, in the order of the planning groups: its column, its first kept block, its length.  Every
+// Segment number idx of all heavy columns, in the order of the planning groups: its column, the column whose accumulators it adds into, its first kept block, its length.  Every
 // wavefront finds it by itself: each lane adds up a run of the groups' sums, whose loads do not wait for one another, then the run that holds the
 // segment is searched.  Backward of masks of the diagonal alone, heads x T, the sums in turns of 64 (a load and a scan each) | this: d = 32 512 x 64
 // 812 | 799 us, 1024 x 32 814 | 800, 4096 x 16 1595 | 1572; d = 64 64 x 512 1573 | 1562.  False past the end.
-__device__ __forceinline__ bool sparse_segment(int idx, int& item, int& skip_blocks, int& take_blocks) {
+__device__ __forceinline__ bool sparse_segment(int idx, int& item, int& slot, int& skip_blocks, int& take_blocks) {
   const auto& a = *kernel_args_again();
   const int lane = threadIdx.x & 63;
   auto inclusive = [&](int v) {
@@ -173,14 +197,15 @@ __device__ __forceinline__ bool sparse_segment(int idx, int& item, int& skip_blo
     group += at;
   }
   const int bh = group / n_cg, cg = group % n_cg, col = cg * kPlanCols + lane;
-  const int segs = lane < kPlanCols && col < a.T ? a.col_segs[bh * a.T + col] : 0;
-  sum = inclusive(segs);
+  const int entry = lane < kPlanCols && col < a.T ? a.col_segs[bh * a.T + col] : 0;
+  sum = inclusive(segs_of(entry));
   at = __builtin_ctzll(__ballot(sum > idx));
   // (the same in all lanes: in scalar registers)
   item = __builtin_amdgcn_readfirstlane(bh * a.T + cg * kPlanCols + at);
-  const int n = __builtin_amdgcn_readlane(segs, at), seg = idx - (at > 0 ? __builtin_amdgcn_readlane(sum, at - 1) : 0);
+  const int found = __builtin_amdgcn_readlane(entry, at), n = segs_of(found), seg = idx - (at > 0 ? __builtin_amdgcn_readlane(sum, at - 1) : 0);
   take_blocks = __builtin_amdgcn_readfirstlane((a.colcnt[item] + n - 1) / n);
   skip_blocks = __builtin_amdgcn_readfirstlane(seg * take_blocks);
+  slot = __builtin_amdgcn_readfirstlane(slot_of(item, found, seg));
   return true;
 }
 
@@ -192,32 +217,53 @@ __device__ __forceinline__ bool sparse_segment(int idx, int& item, int& skip_blo
 template <typename T, int D>
 __device__ __forceinline__ void sparse_finish(int item) {
   const auto& a = *kernel_args_again();
-  typedef typename Vec<T>::x4 T4;
   __shared__ int is_last;
   asm volatile("" ::: "memory");
   wait_async_copies();   // vmcnt(0): this wavefront's atomics
   __syncthreads();
-  if (threadIdx.x == 0) is_last = __hip_atomic_fetch_add(a.ticket + item, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.col_segs[item] - 1;
+  if (threadIdx.x == 0) is_last = __hip_atomic_fetch_add(a.ticket + item, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == segs_of(a.col_segs[item]) - 1;
   __syncthreads();
   if (!is_last) return;
   const int bh = item / a.T, kt = item % a.T;
   const int64_t head_off = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int64_t acc_off = ((int64_t)bh * a.N + (int64_t)kt * 128) * D;
+  const int64_t acc_off = (int64_t)item * 128 * D;
+  const int64_t more = (int64_t)(slot_of(item, a.col_segs[item], 2) - item) * 128 * D;   // 0: one accumulator holds the sum
   const int tid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 + lane_id_here();
-#pragma unroll 4
-  for (int i = tid; i < 128 * D / 4; i += blockDim.x) {
-    const int row = (4 * i) / D, colx = (4 * i) % D;
-    T4 ko, vo;
+  // Two floats a lane, so that a line is asked for once, beyond the L2 where it is; all loads of a batch before its first store, which they are
+  // not moved across.  (One load at a time, four floats a lane | this, both with two accumulators: 8 x 24 at d = 64 61 | 53 us, 3 x 20 at d = 128 78 | 67.)
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  constexpr int kBatch = 8;
+  auto part = [](const float* p) {
+    return __builtin_bit_cast(f32x2, __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  };
+  auto convert = [&](auto two) {
+    for (int i0 = tid; i0 < 128 * D / 2; i0 += kBatch * (int)blockDim.x) {
+      f32x2 k[kBatch], v[kBatch];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      ko[e] = (T)__hip_atomic_load(a.dKacc + acc_off + 4 * i + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      vo[e] = (T)__hip_atomic_load(a.dVacc + acc_off + 4 * i + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int n = 0; n < kBatch; ++n) {
+        const int64_t at = acc_off + 2 * min(i0 + n * (int)blockDim.x, 128 * D / 2 - 1);
+        k[n] = part(a.dKacc + at);
+        v[n] = part(a.dVacc + at);
+        if (two) {
+          const f32x2 k2 = part(a.dKacc + at + more), v2 = part(a.dVacc + at + more);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) { k[n][e] += k2[e]; v[n][e] += v2[e]; }
+        }
+      }
+#pragma unroll
+      for (int n = 0; n < kBatch; ++n) {
+        const int i = i0 + n * (int)blockDim.x, row = (2 * i) / D, colx = (2 * i) % D;
+        if (i >= 128 * D / 2 || (D == 32 && colx >= a.dvalid)) continue;   // head dimension 16: the tensors' rows end there
+        const int64_t o = head_off + (int64_t)(kt * 128 + row) * a.sn + colx;
+        const T2 ko = {(T)k[n][0], (T)k[n][1]}, vo = {(T)v[n][0], (T)v[n][1]};
+        *(T2*)((T*)a.dK + o) = ko;
+        *(T2*)((T*)a.dV + o) = vo;
+      }
     }
-    if (D == 32 && colx >= a.dvalid) continue;   // head dimension 16: the tensors' rows end there
-    const int64_t o = head_off + (int64_t)(kt * 128 + row) * a.sn + colx;
-    *(T4*)((T*)a.dK + o) = ko;
-    *(T4*)((T*)a.dV + o) = vo;
-  }
+  };
+  if (more != 0) convert(std::true_type());
+  else convert(std::false_type());
 }
 
 }  // namespace attn

@@ -90,6 +90,18 @@ def test_segments_on_dirty_workspaces(B, H, T, d, kind):
         assert float((x.float() - y.float()).norm()) <= 2.0 ** -8 * norm
 
 
+# heavy columns of up to 24 blocks: at most two addends to a sum, which is the same whichever comes first (T = 17: the last column's planning group
+# has no idle accumulators)
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("T,causal", [(15, False), (17, False), (20, False), (24, False), (24, True)])
+def test_gradients_of_short_columns_repeat(T, causal, d):
+    _, dev = hp.make_case(1, 6, 128 * T, d, "fp16", inputs.BASE_SEED + 6800 + T + d)
+    run = _backward(dev, torch.from_numpy(_masks("columns", 6, T)).cuda(), softmax_scale=1 / math.sqrt(d), causal=causal)
+    first = [g.clone() for g in run()]
+    for _ in range(20):
+        assert all(torch.equal(x, y) for x, y in zip(first, run()))
+
+
 # more planning groups than the lanes that look for a segment, and more than they look through in one turn: a few heads that keep heavy columns among
 # many that keep nothing
 @pytest.mark.parametrize("H,T", [(100, 17), (4200, 15)])

@@ -23,6 +23,9 @@ extern "C" int64_t estimate(const uint8_t* mask, int per_head, const int* length
   return s.total(a, counted);
 }
 extern "C" int window(int T, int cg) { return attn::plan_window(T, cg); }
+extern "C" int entry(int c, int segs, unsigned light, unsigned three) { return attn::column_entry(c, segs, light, three); }
+extern "C" int segs_of(int entry) { return attn::segs_of(entry); }
+extern "C" int slot(int item, int entry, int seg) { return attn::slot_of(item, entry, seg); }
 extern "C" int segments(int cnt, int near, int n_near, int64_t total) { return attn::column_segments(cnt, near, n_near, total); }
 """
 
@@ -139,3 +142,32 @@ def test_standing_out_is_by_the_neighbours(shim):
     """Twice as many blocks as the other columns keep on average, not as all of them do: 15 blocks beside fifteen columns of 7 (106 in all) are more than that."""
     assert shim.segments(15, 15 + 15 * 7, 16, 1000) > 0
     assert shim.segments(15, 15 + 15 * 8, 16, 1000) == 0
+
+
+def test_short_columns_add_no_more_than_two_parts_into_one_place(shim):
+    """Their gradients stay reproducible: float32 sums of two addends do not depend on which comes first.  Columns of up to 24 blocks have three
+    segments at most, the third of which goes to the accumulators of a column that does not use its own."""
+    assert [shim.segments(cnt, cnt, 16, 100) for cnt in (14, 15, 16, 17, 24, 25)] == [0, 2, 2, 3, 3, 4]
+    rng = np.random.default_rng(5)
+    for _ in range(2000):
+        n_cols = int(rng.integers(1, 17))
+        cnt = rng.choice([3, 15, 17, 24, 30, 64], size=n_cols)
+        segs = [shim.segments(int(c), int(c), 16, 100) for c in cnt]   # (every column stands out)
+        light = sum(1 << c for c in range(n_cols) if segs[c] == 0)
+        three = sum(1 << c for c in range(n_cols) if segs[c] == 3 and cnt[c] <= 24)
+        item0 = 16 * int(rng.integers(0, 1 << 20))
+        added = {}
+        for c in range(n_cols):
+            entry = shim.entry(c, segs[c], light, three)
+            n = shim.segs_of(entry)
+            assert n == segs[c] or (n, segs[c]) == (2, 3)
+            for seg in range(n):
+                slot = shim.slot(item0 + c, entry, seg)
+                assert slot == item0 + c or (seg == 2 and light >> (slot - item0) & 1)
+                added.setdefault(slot, []).append(c)
+        for slot, cs in added.items():
+            assert len(set(cs)) == 1
+            if cnt[cs[0]] <= 24:
+                assert len(cs) <= 2
+        given = sum(1 for c in range(n_cols) if three >> c & 1 and shim.segs_of(shim.entry(c, segs[c], light, three)) == 3)
+        assert given == min(bin(three).count("1"), bin(light).count("1"))   # as many as there are idle ones
