@@ -371,13 +371,15 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse, co
   // d = 128, dense: the one-wavefront kernel with the V block in LDS (attn_bwd_dkv_fr128.hip)
   // (without dropout, with 64 keys per wavefront where a head has at least two blocks of 256 keys
   // and whole 32-query tiles: attn_bwd_dkv_w64.hip)
-  // (dropout under the causal mask: the role-split kernel pairs a long and a short key block in one workgroup of eight wavefronts and
-  // is ahead where those make one full round over the compute units.  us, role-split | one wavefront: B H = 10, N = 4096 289 | 311,
-  // B H = 32, N = 2048 185 | 193, B H = 8, N = 8192 322 | 382, 40 heads of 1024 99 | 96, 64 102 | 95, 128 of 512 77 | 71.  With fewer blocks the one-wavefront kernel
-  // splits their sweep (B H = 8, N = 4096 265 | 236; B H = 16, N = 1024 86 | 63), with more its workgroups even out by themselves: B H = 64, N = 2048
-  // 200 | 163, 4096 714 | 569; B H = 128, N = 1024 126 | 92; B H = 48, N = 1400 137 | 77)
-  const int64_t blocks = (int64_t)a.B * a.H * a.T;
-  const bool one_round_of_pairs = blocks > kComputeUnits && blocks <= 2 * kComputeUnits && a.N >= 1024;
+  // (dropout under the causal mask: the role-split kernel pairs a long and a short key block in one workgroup of eight wavefronts, and is
+  // ahead for long heads whose pairs are one round over the compute units.  us, role-split | one wavefront, heads x N: 8 x 8192 599 | 659, 10 x 4096 296 | 319,
+  // 16 x 3000 227 | 244, 20 x 2048 165 | 170, 32 x 2048 177 | 185, 25 x 1920 158 | 161, 32 x 1792 153 | 155, 22 x 1792 147 | 148.  Shorter heads: 24 x 1664 139 | 137,
+  // 32 x 1536 130 | 129, 29 x 1400 120 | 117, 42 x 1152 104 | 99, 40 x 1024 99 | 95, 64 x 1024 104 | 98.  A few pairs in a second round (an odd
+  // number of blocks makes a pair of the last one alone): 34 x 1920 242 | 172, 39 x 1664 189 | 155, 46 x 1400 193 | 135, 56 x 1152 145 | 116.  With no more blocks
+  // than compute units the one-wavefront kernel splits their sweep (8 x 4096 265 | 236; 16 x 1024 86 | 63), with many its
+  // workgroups even out by themselves: 64 x 2048 200 | 163, 4096 714 | 569; 128 x 1024 126 | 92)
+  const int64_t heads = (int64_t)a.B * a.H, blocks = heads * a.T;
+  const bool one_round_of_pairs = blocks > kComputeUnits && heads * ((a.T + 1) / 2) <= kComputeUnits && a.T >= 14;
   if (!sparse && d == 128 && !role_split && !(dropout && causal && v.dkv == 0 && one_round_of_pairs)) {
     // measured against the 32-key kernel: 1 % faster at N = 2048, 5 % at 4096, 7 % at 16384; slower below,
     // slower under the causal mask at every length (its 256-key work items balance worse), and with no more key blocks than compute
