@@ -308,19 +308,31 @@ int launch_td(const KArgs& a, bool causal, bool dropout, hipStream_t s) {
 
 }  // namespace
 
-// us of the backward pass, two launches (divided over wavefront groups where there are few heads) | this kernel; heads x N, d = 64:
-//   N <= 128  1 x 128 12.1 | 7.9, 96 x 128 13.2 | 8.6, 2048 x 128 83.9 | 66.6, causal with dropout 91.7 | 70.5; 4032 x 65 116 | 85; 96 x 1 10.4 | 6.0
-//   three tiles  16 x 150 15.3 | 14.1, causal 23.1 | 13.2; 256 x 150 22.9 | 17.2; 1024 x 150 75.4 | 67.3, causal with dropout 80.2 | 80.7; 1600 x 129 110 | 102
-//   four tiles  16 x 197 14.3 | 17.6, causal 23.0 | 16.5; 96 x 197 18.9 | 18.7, dropout 21.7 | 22.9; 96 x 256 19.0 | 20.7, causal 25.0 | 19.5;
-//     200 x 256 26.8 | 26.0, causal 32.7 | 23.9; 256 x 197 27.0 | 22.3; 400 x 197 47.3 | 41.3, causal with dropout 49.0 | 47.7; 1024 x 197 92.5 | 88.1,
-//     causal with dropout 95.9 | 99.9; 400 x 256 50.2 | 52.2; 1024 x 256 102 | 107
-//   d = 32  16 x 150 12.9 | 11.6; 96 x 197 13.8 | 15.2, causal 15.3 | 13.2; 200 x 197 18.3 | 15.7; 200 x 256 18.8 | 18.2; 400 x 197 31.2 | 29.5; 400 x 256 33.6 | 37.8
-bool bwd_short_is_faster(const KArgs& a, int d, bool causal) {
+// Which heads take this kernel.  us of the backward pass, two launches (divided over wavefront groups where there are few heads) | this kernel; heads x N:
+//   one or two tiles, d = 64  1 x 128 12.1 | 7.9, 96 x 128 13.2 | 8.6, 2048 x 128 83.9 | 66.6, causal with dropout 91.7 | 70.5; 4032 x 65 116 | 85; 96 x 1 10.4 | 6.0
+// From three tiles on, the time of this kernel over that of the two launches, by heads; three tiles (N = 129, 150, 176, 192), then four (N = 193, 208, 224, 256):
+//   d = 64  64 0.92-0.97, 1.22 1.23 1.25 1.32; 96 0.91-0.98, 1.02 1.03 1.03 1.11; 128 1.01 1.02 1.03 1.09; 160 0.72-0.78, 0.82 0.82 0.83 0.90; 256 0.73-0.82, 0.82 0.70
+//     0.65 0.83; 257 0.99 0.99 1.00 1.08; 320 0.87-0.97, 0.99 0.99 0.99 1.06; 400 0.80-0.86, 0.87 0.88 0.89 0.96; 512 0.81-0.87, 0.87 0.88 0.87 0.96; 1024 0.86-0.92, 0.93 0.95 0.96 1.05
+//   d = 64, dropout  64 0.94-1.02, 1.33 1.33 1.34 1.39; 96 0.93-1.02, 1.05 1.05 1.05 1.12; 128 1.04 1.04 1.04 1.11; 160 0.71-0.78, 0.78 0.78 0.80 0.86; 256 0.73-0.84, 0.84 0.85
+//     0.86 0.91; 257 1.01 1.02 1.04 1.11; 320 0.91-1.02, 1.03 1.04 1.05 1.10; 400 0.81-0.90, 0.89 0.91 0.92 0.99; 512 0.84-0.89, 0.90 0.90 0.92 0.99; 1024 0.90-1.00, 1.00 0.97 1.01 1.07
+//   d = 64, causal  64 0.58-0.62, 0.74 0.75 0.76 0.79; 256 0.61-0.67, 0.66 0.67 0.67 0.70; 257 0.95 0.96 0.98 1.01; 400 0.87-0.96, 0.97 0.98 1.00 1.02; 1024 0.90-0.99, 1.00 1.02 1.03 1.01;
+//     dropout  64 0.58-0.62, 0.75 0.75 0.77 0.79; 256 0.61-0.69, 0.67 0.67 0.68 0.71; 257 0.92 0.93 0.96 0.99; 400 0.88-0.98, 0.96 0.98 1.00 1.05; 1024 0.95-1.05, 1.02 1.03 1.03 1.05
+//   d = 32  64 0.86-0.94, 1.23 1.26 1.28 1.38; 96 0.86-0.94, 1.08 1.07 1.10 1.21; 128 1.07 1.07 1.09 1.19; 160 0.72-0.80, 0.88 0.87 0.90 0.99; 256 0.72-0.79, 0.86 0.86 0.88 0.96;
+//     257 1.14 1.15 1.17 1.33; 320 0.97-1.04, 1.11 1.12 1.14 1.29; 400 0.80-0.89, 0.93 0.94 0.97 1.06; 512 0.78-0.93, 0.96 0.96 1.00 1.09; 1024 0.86-0.97, 1.03 1.03 1.06 1.18;
+//     dropout  128 1.05 1.04 1.06 1.15; 160 0.67-0.72, 0.81 0.81 0.83 0.90; 320 0.90-0.97, 1.03 1.03 1.06 1.16; 400 0.73-0.79, 0.84 0.85 0.88 0.97; 1024 0.78-0.89, 0.92 0.93 0.96 1.06
+//   d = 32, causal  64 0.64-0.67, 0.90 0.91 0.91 0.93; 256 0.61-0.64, 0.71 0.71 0.72 0.74; 257 1.00 1.01 1.02 1.04; 400 0.83-0.85, 0.91 0.92 0.95 0.99; 1024 0.88-0.94, 0.99 1.00 1.02 1.07
+// Three tiles: always, the few losses are below 5 %.  Four tiles: up to 64 heads the two launches' divided blocks fill more of the chip, up to 128 both of them
+// take one round over the compute units (even to 3 % with d = 64 and no dropout, where the launch saved decides), from 129 on two, and this kernel one up to
+// 256 (N = 197, d = 32: 129 heads 17.0 | 15.1 us).  Beyond, its second round of whole heads has to be more than half full, where the two launches' blocks begin a
+// fourth one (384 heads 26.5 | 29.0, 390 31.0 | 29.0), and only up to 224 tokens; beyond 512 heads neither is ahead throughout.  The causal
+// mask halves this kernel's work, and the two launches pair blocks there, few as they are.
+bool bwd_short_is_faster(const KArgs& a, int d, bool causal, bool dropout) {
   if (d > 64 || a.N > 256) return false;
   if (a.N <= 3 * TILE) return true;
   const int64_t heads = (int64_t)a.B * a.H;
-  if (heads > kComputeUnits) return a.N <= 208 && heads <= 2 * kComputeUnits;
-  return causal || heads >= (d == 64 && a.N <= 208 ? 80 : 160);   // fewer: the two launches' divided blocks fill more of the chip
+  if (heads > 2 * kComputeUnits) return false;
+  if (heads > kComputeUnits) return a.N <= 224 && (causal || 2 * heads > 3 * kComputeUnits);
+  return causal || heads > kComputeUnits / 2 || (heads > kComputeUnits / 4 && d == 64 && a.N <= 208 && !dropout);
 }
 
 int launch_bwd_short(const KArgs& a_in, int dtype, int d, bool causal, bool dropout, hipStream_t s) {

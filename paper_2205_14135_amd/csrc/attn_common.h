@@ -121,7 +121,7 @@ int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool 
 // the same with 64 keys per wavefront and the accumulators in the accumulation registers (attn_bwd_dkv_w64.hip)
 int launch_dkv_w64(const KArgs& a, int dtype, bool causal, hipStream_t s);
 // the whole backward pass of short dense heads at d <= 64, one launch (attn_bwd_short.hip), and which heads take it
-bool bwd_short_is_faster(const KArgs& a, int d, bool causal);
+bool bwd_short_is_faster(const KArgs& a, int d, bool causal, bool dropout);
 int launch_bwd_short(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);
 // dense forward with two wavefront groups in ping-pong (attn_fwd_pp.hip); sets its own work items
 int launch_fwd_pp(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);

@@ -11,6 +11,7 @@ extern "C" int choice(int heads, int N, int d, int causal, int dropout) {
   a.B = 1; a.H = heads; a.N = N; a.T = (N + 127) / 128; a.Nr = 128 * a.T; a.dvalid = d;
   return attn::choose_dkv(a, d, causal, dropout, false, attn::Overrides{0, 0});
 }
+extern "C" int short_heads() { return attn::kBwdShort; }
 extern "C" int role_split() { return attn::kDkvRoleSplit; }
 extern "C" int one_wave128() { return attn::kDkvOneWave128; }
 """
@@ -28,3 +29,20 @@ def shim(tmp_path_factory):
 def test_role_split_where_its_pairs_are_one_round(shim, heads, N, expect):
     assert shim.choice(heads, N, 128, 1, 1) == (shim.role_split() if expect else shim.one_wave128())
     assert shim.choice(heads, N, 128, 1, 0) == shim.one_wave128()
+
+
+# the one-launch backward: always up to three tiles of 64 tokens; with four, where the two launches have two rounds over 256 compute units and it has one, or
+# a second one more than half full; under the causal mask from the first head on
+@pytest.mark.parametrize("N", [1, 128, 129, 192])
+@pytest.mark.parametrize("heads", [1, 64, 600, 5000])
+def test_short_heads_up_to_three_tiles(shim, heads, N):
+    for d in (32, 64):
+        assert all(shim.choice(heads, N, d, c, p) == shim.short_heads() for c in (0, 1) for p in (0, 1))
+
+
+@pytest.mark.parametrize("heads,N,d,causal,dropout,expect", [
+    (64, 197, 64, 0, 0, 0), (65, 197, 64, 0, 0, 1), (65, 197, 64, 0, 1, 0), (96, 209, 64, 0, 0, 0), (96, 197, 32, 0, 0, 0), (128, 256, 64, 0, 1, 0), (129, 256, 64, 0, 1, 1),
+    (129, 256, 32, 0, 0, 1), (256, 256, 32, 0, 0, 1), (257, 197, 32, 0, 0, 0), (384, 197, 64, 0, 1, 0), (385, 197, 64, 0, 1, 1), (385, 224, 32, 0, 0, 1), (385, 225, 32, 0, 0, 0),
+    (512, 224, 64, 0, 0, 1), (513, 197, 64, 0, 0, 0), (1, 256, 64, 1, 0, 1), (256, 256, 64, 1, 1, 1), (257, 224, 64, 1, 1, 1), (257, 225, 64, 1, 1, 0), (513, 197, 64, 1, 1, 0)])
+def test_short_heads_of_four_tiles(shim, heads, N, d, causal, dropout, expect):
+    assert (shim.choice(heads, N, d, causal, dropout) == shim.short_heads()) == bool(expect)
