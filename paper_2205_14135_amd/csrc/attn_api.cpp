@@ -84,6 +84,7 @@ int check_params(const attn_params* p, Checked* out) {
   k.offset_lo = (uint32_t)(p->offset & 0xFFFFFFFFu);
   k.o_fp32 = p->o_fp32 != 0;
   k.klen = p->key_lengths;
+  k.deal = k.klen != nullptr && T > 1;
   out->dtype = p->dtype;
   out->d = p->d == 16 ? 32 : p->d;   // head dimension 16 runs on the d = 32 kernels (zero upper half on chip)
   out->causal = p->causal != 0;

@@ -1,6 +1,7 @@
 // Internal declarations shared by the gfx950 attention kernels and the C-ABI front end.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace attn {
@@ -15,28 +16,19 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Problem description handed to every kernel (plain data, passed by value).
+// Problem description handed to every kernel (plain data, passed by value).  What every dense kernel reads first stands in the first two cache
+// lines (args_at_once).
 struct KArgs {
+  int n_items;             // work items (B*H*tiles)
+  int chunk;               // items per XCD = ceil(n_items / 8)
+  int group;               // causal dQ: heads whose row blocks are dealt out together, heaviest first
+  int deal;                // heads are dealt round the XCDs (dealt_head)
+  int B, H, N, T;          // T = ceil(N / 128)
+  const int* klen;         // key-padding lengths [B] or nullptr
+  int64_t sb, sh, sn;      // element strides of the [B,H,N,d] tensors
   const void* Q; const void* K; const void* V;
   void* O;                 // fwd: out; bwd: in
   float* LSE;              // fwd: out; bwd: in        [B,H,N]
-  const void* dO;          // bwd in
-  void* dQ; void* dK; void* dV;   // bwd out
-  float* Dvec;             // bwd scratch: -D_i = -rowsum(dO_i o O_i)   [B,H,Nr], 0 for rows >= N
-  float* L2vec;            // bwd scratch: L_i * log2(e), +inf where L_i = -inf and for rows >= N   [B,H,Nr]
-  int* colcnt;             // block-sparse bwd scratch: kept blocks per mask column   [B*H, T]
-  int* col_segs;           // block-sparse bwd scratch: segments of a heavy column, 0 for the others (column_entry in attn_sparse.h)   [B*H, T]
-  int* ticket;             // block-sparse bwd scratch: segments of a heavy column that have ended   [B*H, T]
-  int* group_segs;         // block-sparse bwd scratch: segments of the heavy columns among kPlanCols   [B*H, ceil(T / kPlanCols)]
-  int plan_groups;         // block-sparse bwd: planning workgroups at the head of the dQ launch (0: no column can be heavy)
-  float* dKacc;            // block-sparse bwd scratch: fp32 dK / dV of the columns that are
-  float* dVacc;            //   split over several workgroups                         [B,H,N,d]
-  int causal;              // causal flag for the kernels that are not specialised on it
-  const uint8_t* mask;     // block mask [T,T] (per head if mask_sh != 0) or nullptr
-  int64_t mask_sh;
-  const int* klen;         // key-padding lengths [B] or nullptr
-  int64_t sb, sh, sn;      // element strides of the [B,H,N,d] tensors
-  int B, H, N, T;          // T = ceil(N / 128)
   int Nr;                  // 128 T: rows per head of the backward scratch vectors
   int dvalid;              // head dimension of the tensors: 16 with the D = 32 kernels (columns 16..31 are zeros on chip), else D
   float tau;               // softmax scale
@@ -45,10 +37,22 @@ struct KArgs {
   uint32_t drop_thr;       // T: keep iff 8-bit philox field >= T (1..255 when dropout is on)
   uint32_t seed_lo, seed_hi, offset_lo;
   int o_fp32;
-  int n_items;             // work items (B*H*tiles)
-  int chunk;               // items per XCD = ceil(n_items / 8)
-  int group;               // causal dQ: heads whose row blocks are dealt out together, heaviest first
+  const uint8_t* mask;     // block mask [T,T] (per head if mask_sh != 0) or nullptr
+  int64_t mask_sh;
+  const void* dO;          // bwd in
+  void* dQ; void* dK; void* dV;   // bwd out
+  float* Dvec;             // bwd scratch: -D_i = -rowsum(dO_i o O_i)   [B,H,Nr], 0 for rows >= N
+  float* L2vec;            // bwd scratch: L_i * log2(e), +inf where L_i = -inf and for rows >= N   [B,H,Nr]
+  int* colcnt;             // block-sparse bwd scratch: kept blocks per mask column   [B*H, T]
+  int* col_segs;           // block-sparse bwd scratch: segments of a heavy column, 0 for the others (column_entry in attn_sparse.h)   [B*H, T]
+  int* ticket;             // block-sparse bwd scratch: segments of a heavy column that have ended   [B*H, T]
+  int* group_segs;         // block-sparse bwd scratch: segments of the heavy columns among kPlanCols   [B*H, ceil(T / kPlanCols)]
+  float* dKacc;            // block-sparse bwd scratch: fp32 dK / dV of the columns that are
+  float* dVacc;            //   split over several workgroups                         [B,H,N,d]
+  int plan_groups;         // block-sparse bwd: planning workgroups at the head of the dQ launch (0: no column can be heavy)
 };
+
+static_assert(offsetof(KArgs, LSE) + sizeof(float*) <= 128, "the dense kernels' first arguments in two cache lines");
 
 enum { kXcds = 8, kMaskBlock = 128 };
 // Block-sparse dK/dV: a mask column is "heavy" when it keeps more than kLongBlocks blocks, or more than kHeavyBlocks and twice as
@@ -501,6 +505,15 @@ __device__ __forceinline__ int xcd_item(int n_items, int chunk, int id = (int)bl
   const int item = (id % kXcds) * chunk + id / kXcds;
   return item < n_items && (id / kXcds) < chunk ? item : -1;
 }
+// Asks for the arguments that a dense forward reads before its first tile in one go: left to itself, the compiler loads what stands behind each branch of the
+// prologue behind it, and a problem of few tiles waits for the scalar cache two to four times in a row, about 0.08 us each (one head of 128 tokens, d = 64:
+// 4.71 us with three such waits, 4.79 with four, 4.44 so).
+__device__ __forceinline__ void args_at_once(const KArgs& a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" ::"s"(a.n_items), "s"(a.chunk), "s"(a.deal), "s"(a.H), "s"(a.N), "s"(a.T), "s"(a.klen), "s"(a.sb), "s"(a.sh), "s"(a.sn), "s"(a.Q), "s"(a.K),
+               "s"(a.V));
+#endif
+}
 // The head that the dealt-out position `pos` of a dense problem stands for.  xcd_item gives each XCD a run of consecutive positions.  With a
 // key-padding mask the heads of a batch entry cost what its length says, and entries of like length tend to stand together
 // (batches sorted by length), so that one XCD would get the long ones: there the j-th head of XCD x is 8 j + (x + j) % 8.  (Not
@@ -510,7 +523,7 @@ __device__ __forceinline__ int xcd_item(int n_items, int chunk, int id = (int)bl
 // heads | dealt round: 16 x 8 of 700, d = 32 68.3 | 57.7, d = 64 101 | 86, d = 128 166 | 145; 16 x 16 of 512, dropout 127 | 109, causal 82 | 78; 5 x 12 of
 // 1000 88 | 72; 16 x 16 of 1024 316 | 246; 4 x 16 of 4096, d = 128 1958 | 1338; 8 x 16 of 1024 causal with dropout, d = 128 216 | 181; 32 x 12 of 197 46.4 | 44.9.
 __device__ __forceinline__ int dealt_head(const KArgs& a, int pos) {
-  if (!a.klen || a.T == 1) return pos;
+  if (__builtin_expect(!a.deal, 1)) return pos;   // (the rest out of the way, so that no jump stands before the first loads)
   const int n = a.B * a.H, whole = n / kXcds, rest = n % kXcds;   // XCDs below `rest` have one head more
   const int in_long = rest * (whole + 1);
   const int x = pos < in_long ? pos / (whole + 1) : rest + (pos - in_long) / (whole > 0 ? whole : 1);

@@ -61,6 +61,7 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 ? (D <= 64 ? 3 : 2) : (RW * K
     Vs = bufs + 2 * KG;
   }
 
+  args_at_once(a);
   const int item = xcd_item(a.n_items, a.chunk);
   if (item < 0) return;
   const int n_qt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last block may be ragged
