@@ -115,7 +115,8 @@ WsLayout ws_layout(const attn_params* p) {
   const size_t T = ((size_t)p->N + attn::kMaskBlock - 1) / attn::kMaskBlock;
   // two floats per row, rows padded to whole 128-blocks per head
   w.d_bytes = align_up(2 * (size_t)p->B * p->H * T * attn::kMaskBlock * sizeof(float), 256);
-  // column counts, tickets and segment counts (a third of this would do; the size is part of what callers see)
+  // column counts, segments and tickets, and the segments of each planning group: at most 4 ints per column (an eighth of this; the size is part of
+  // what callers see)
   w.cnt_bytes = align_up(((size_t)p->B * p->H * T * (1 + attn::kMaxSegs) + 64) * sizeof(int), 256);
   const size_t d_kernel = p->d == 16 ? 32 : p->d;   // the fp32 accumulators have the kernels' row length
   w.acc_bytes = align_up((size_t)p->B * p->H * p->N * d_kernel * sizeof(float), 256);

@@ -100,6 +100,9 @@ struct WorkItems {
   }
 };
 
+// The forward's division (attn_fwd.hip).
+WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide);
+
 // Planning workgroups of a block-sparse backward: one for kPlanCols mask columns of a head (what each clears takes no longer than the
 // launch it is part of), padded to whole rounds over the XCDs; none where the columns are too short for any to be heavy.
 constexpr int kPlanCols = 16;

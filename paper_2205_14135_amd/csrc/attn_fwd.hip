@@ -40,7 +40,7 @@ constexpr int BC = 64;   // keys per K/V tile
 // RW wavefronts of 32 query rows each share the K/V tiles of a workgroup.  KG groups of RW wavefronts work on the same rows: group
 // k takes every KG-th tile, into buffers of its own, and the groups' (m, l, O) are merged through LDS at the end.
 template <typename T, int D, bool CAUSAL, bool DROPOUT, bool SPARSE, int RW, int KG>
-__global__ __launch_bounds__(64 * RW * KG, KG == 1 ? (D <= 64 ? 3 : 2) : (RW * KG > 8 ? RW * KG / 4 : 2)) void fwd_kernel(const KArgs a) {
+__global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_kernel(const KArgs a) {
   typedef typename Vec<T>::x8 T8;
   typedef typename Vec<T>::x4 T4;
   constexpr int KK = D / 16;        // MFMA k-steps over the head dimension
@@ -325,45 +325,6 @@ int launch_fwd_groups(KArgs a, bool causal, bool dropout, bool sparse, hipStream
   return (int)hipErrorInvalidValue;
 }
 
-// us, forward alone, {4, 1} | {4, 2} | {2, 2} | {2, 4} (wavefronts of rows, groups; heads x N):
-//   d = 64   4 x 117 5.5 5.7 5.3 6.3; 16 x 256 6.9 7.1 6.2 6.8; 16 x 640 11.1 10.3 8.5 9.1; 16 x 1024 16.0 13.7 12.9 11.0;
-//            8 x 2048 27.5 22.5 21.9 16.5; 1 x 8192 99.2 76.2 73.2 46.5; 24 x 1024 16.0 13.7 16.7 19.7; 16 x 2048 28.4 24.2 29.7 30.6;
-//            8 x 4096 52.4 43.0 54.4 51.2; 60 x 512 9.9 9.6 10.7 14.7; 20 x 2048 38.5 44.2 44.9 43.9; 128 x 512 14.1 17.1 19.6 27.6
-//   d = 64 causal (pairs of row blocks)  60 x 400 14.1 13.7 11.1 12.3; 16 x 1024 20.3 18.3 16.8 15.2; 8 x 4096 57.1 45.4 43.4 31.8;
-//            20 x 2048 32.7 27.7 33.2 38.8; 10 x 4096 57.3 45.6 56.7 59.0; 64 x 1024 21.1 19.2 - 28.7; 48 x 1400 33.0 41.7 - 47.0
-//   d = 32   4 x 117 4.7 5.0 5.1 5.0; 16 x 640 9.7 8.9 7.1 7.1; 16 x 1024 13.5 11.6 10.3 8.4; 60 x 512 8.5 7.9 8.6 8.5; 8 x 4096 45.1 35.5 39.8 32.8;
-//            10 x 4096 60.7 55.3 52.9 47.6; 32 x 2048 32.9 31.3 38.5 35.1, causal 34.0 30.0 29.2 26.9; 128 x 512 11.1 11.4 13.9 14.7
-//   d = 128  4 x 117 6.6 7.8 7.2; 64 x 189 8.5 - 9.7; 40 x 359 11.7 - 11.0; 16 x 1024 22.1 19.9 18.8; 1 x 8192 140 107 107; 60 x 512 14.4 14.5 23.1; 24 x 1024 22.4 20.5 35.3;
-//            8 x 4096 78.3 69.9 112, causal 75.9 58.4 62.8; 40 x 1024 32.8 39.8 51.8; causal 10 x 4096 104 71.5 116, 8 x 8192 170 141 230,
-//            48 x 693 20.1 22.2 -, 24 x 2001 56.4 45.1 66.5, 40 x 1024 32.0 32.1 36.5, 48 x 1400 42.9 44.0 62.3, 64 x 1024 34.0 38.9 56.4
-//   block-sparse (butterfly mask of T x T blocks, heads x T)  d = 64  4 x 16 15.5 13.1 10.8 11.0; 4 x 64 20.0 17.0 17.4 24.3; 8 x 64 27.7 31.0 31.5 46.5;
-//            d = 128  4 x 16 20.4 18.3 17.4; 4 x 64 28.4 26.9 43.1; 8 x 64 43.8 51.7 85.0
-WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
-  if (!divide) return {4, 1};
-  const WorkItems w(a, sparse, causal && !sparse && d == 64);
-  // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise)
-  const int64_t fit24 = d == 64 ? kComputeUnits : (causal && w.tiles >= 24 ? 4 * kComputeUnits : 5 * kComputeUnits / 2);
-  if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
-  if (w.of64 <= kComputeUnits && w.tiles >= (d == 128 ? 6 : 3)) return {2, 2};
-  if (d <= 64) return w.of128 <= (d == 32 ? 2 : 1) * kComputeUnits && w.tiles >= 10 ? WaveGroups{4, 2} : WaveGroups{4, 1};
-  // d = 128: {4, 2} has one workgroup on a compute unit, {4, 1} two, which together get through a tile hardly faster than one
-  // of them alone.  Estimates in us: the tiles of all items over the compute units, and under the causal mask the longest sweep.
-  // (From 512 items on {4, 2} would gain for few heads of long causal sequences only, 8 x 8192 above, where the results are held to the
-  // last bit to those of the two-group kernel, whose references a row's undivided sweep shares; the line stays below.)
-  if (w.of128 > 3 * kComputeUnits / 2 || (w.of128 > kComputeUnits && w.tiles < 16)) return {4, 1};
-  const double heads = (double)a.B * a.H, per_unit = 1.0 / kComputeUnits;
-  double one, two;
-  if (causal && !sparse) {
-    const double tiles = heads * std::min<double>((double)a.T * (a.T + 1), (double)a.T * w.tiles);
-    one = std::max(1.12 * tiles * per_unit, 1.25 * w.tiles) + 3.0;
-    two = std::max(1.08 * tiles * per_unit + 4.5 * (double)w.of128 * per_unit, 0.9 * w.tiles + 4.5);
-  } else {
-    one = std::max(1.12 * (double)w.of128 * per_unit, 1.25) * w.tiles + 3.0;
-    two = std::ceil((double)w.of128 * per_unit) * (1.08 * w.tiles + 4.5);
-  }
-  return two < one ? WaveGroups{4, 2} : WaveGroups{4, 1};
-}
-
 template <typename T, int D>
 int launch_fwd_td(const KArgs& a, bool causal, bool dropout, bool sparse, bool divide, hipStream_t s) {
   const WaveGroups w = fwd_groups(a, D, causal, sparse, divide);
@@ -404,6 +365,49 @@ __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
 }
 
 }  // namespace
+
+// us, forward alone, {4, 1} | {4, 2} | {2, 2} | {2, 4} (wavefronts of rows, groups; heads x N):
+//   d = 64   4 x 117 5.5 5.7 5.3 6.3; 16 x 256 6.9 7.1 6.2 6.8; 16 x 640 11.1 10.3 8.5 9.1; 16 x 1024 16.0 13.7 12.9 11.0;
+//            8 x 2048 27.5 22.5 21.9 16.5; 1 x 8192 99.2 76.2 73.2 46.5; 24 x 1024 16.0 13.7 16.7 19.7; 16 x 2048 28.4 24.2 29.7 30.6;
+//            8 x 4096 52.4 43.0 54.4 51.2; 60 x 512 9.9 9.6 10.7 14.7; 20 x 2048 38.5 44.2 44.9 43.9; 128 x 512 14.1 17.1 19.6 27.6
+//   two tiles, {4, 1} | {2, 2}  d = 64 1 x 128 4.5 4.3, 16 x 100 5.0 4.7, 128 x 128 5.1 4.9, dropout 6.0 5.6; causal 1 x 128 5.1 7.5; d = 32 1 x 128 3.9 3.7,
+//            16 x 100 4.6 4.1, 128 x 65 with dropout 5.6 4.7, causal 128 x 128 4.8 4.3; one tile d = 64 16 x 64 4.1 4.6; d = 32 16 x 64 3.7 3.9
+//   d = 64 causal (pairs of row blocks)  64 x 129 9.3 - 8.4; 64 x 192 9.4 - 8.8, dropout 11.7 - 10.0; 60 x 400 14.1 13.7 11.1 12.3; 16 x 1024 20.3 18.3 16.8 15.2; 8 x 4096 57.1 45.4 43.4 31.8;
+//            20 x 2048 32.7 27.7 33.2 38.8; 10 x 4096 57.3 45.6 56.7 59.0; 64 x 1024 21.1 19.2 - 28.7; 48 x 1400 33.0 41.7 - 47.0
+//   d = 32   4 x 117 4.7 5.0 5.1 5.0; 16 x 640 9.7 8.9 7.1 7.1; 16 x 1024 13.5 11.6 10.3 8.4; 60 x 512 8.5 7.9 8.6 8.5; 8 x 4096 45.1 35.5 39.8 32.8;
+//            10 x 4096 60.7 55.3 52.9 47.6; 32 x 2048 32.9 31.3 38.5 35.1, causal 34.0 30.0 29.2 26.9; 128 x 512 11.1 11.4 13.9 14.7
+//   d = 128  4 x 117 6.6 7.8 7.2; 64 x 189 8.5 - 9.7; 40 x 359 11.7 - 11.0; 16 x 1024 22.1 19.9 18.8; 1 x 8192 140 107 107; 60 x 512 14.4 14.5 23.1; 24 x 1024 22.4 20.5 35.3;
+//            8 x 4096 78.3 69.9 112, causal 75.9 58.4 62.8; 40 x 1024 32.8 39.8 51.8; causal 10 x 4096 104 71.5 116, 8 x 8192 170 141 230,
+//            48 x 693 20.1 22.2 -, 24 x 2001 56.4 45.1 66.5, 40 x 1024 32.0 32.1 36.5, 48 x 1400 42.9 44.0 62.3, 64 x 1024 34.0 38.9 56.4
+//   block-sparse (butterfly mask of T x T blocks, heads x T)  d = 64  4 x 16 15.5 13.1 10.8 11.0; 4 x 64 20.0 17.0 17.4 24.3; 8 x 64 27.7 31.0 31.5 46.5;
+//            d = 128  4 x 16 20.4 18.3 17.4; 4 x 64 28.4 26.9 43.1; 8 x 64 43.8 51.7 85.0
+WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
+  if (!divide) return {4, 1};
+  const WorkItems w(a, sparse, causal && !sparse && d == 64);
+  // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise)
+  const int64_t fit24 = d == 64 ? kComputeUnits : (causal && w.tiles >= 24 ? 4 * kComputeUnits : 5 * kComputeUnits / 2);
+  if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
+  // (two tiles would gain 0.2 to 0.8 us, less than the host spends on a call, but not in pairs; a head of up to 128 tokens keeps one form instead, and with it
+  // the same last bits in whatever batch it stands)
+  if (w.of64 <= kComputeUnits && w.tiles >= (d == 128 ? 6 : 3)) return {2, 2};
+  if (d <= 64) return w.of128 <= (d == 32 ? 2 : 1) * kComputeUnits && w.tiles >= 10 ? WaveGroups{4, 2} : WaveGroups{4, 1};
+  // d = 128: {4, 2} has one workgroup on a compute unit, {4, 1} two, which together get through a tile hardly faster than one
+  // of them alone.  Estimates in us: the tiles of all items over the compute units, and under the causal mask the longest sweep.
+  // (From 512 items on {4, 2} would gain for few heads of long causal sequences only, 8 x 8192 above, where the results are held to the
+  // last bit to those of the two-group kernel, whose references a row's undivided sweep shares; the line stays below.)
+  if (w.of128 > 3 * kComputeUnits / 2 || (w.of128 > kComputeUnits && w.tiles < 16)) return {4, 1};
+  const double heads = (double)a.B * a.H, per_unit = 1.0 / kComputeUnits;
+  double one, two;
+  if (causal && !sparse) {
+    const double tiles = heads * std::min<double>((double)a.T * (a.T + 1), (double)a.T * w.tiles);
+    one = std::max(1.12 * tiles * per_unit, 1.25 * w.tiles) + 3.0;
+    two = std::max(1.08 * tiles * per_unit + 4.5 * (double)w.of128 * per_unit, 0.9 * w.tiles + 4.5);
+  } else {
+    one = std::max(1.12 * (double)w.of128 * per_unit, 1.25) * w.tiles + 3.0;
+    two = std::ceil((double)w.of128 * per_unit) * (1.08 * w.tiles + 4.5);
+  }
+  return two < one ? WaveGroups{4, 2} : WaveGroups{4, 1};
+}
 
 // Which dense d = 128 problems take the two-group kernel (attn_fwd_pp.hip): an estimate of either kernel's time,
 // in units of one 64-key tile of the two-group kernel (256 rows on a whole compute unit, 1.78 us without

@@ -1,15 +1,22 @@
-"""Which backward kernel a problem takes, at the lines of the rules (no GPU needed)."""
+"""Which kernel, or which division of one, a problem takes, at the lines of the rules (no GPU needed)."""
 import pytest
 
 from tests.host_library import compile_shim
 
 SOURCE = r"""
 #include <cstring>
-extern "C" int choice(int heads, int N, int d, int causal, int dropout) {
+static attn::KArgs problem(int heads, int N, int d) {
   attn::KArgs a;
   std::memset(&a, 0, sizeof(a));
   a.B = 1; a.H = heads; a.N = N; a.T = (N + 127) / 128; a.Nr = 128 * a.T; a.dvalid = d;
-  return attn::choose_dkv(a, d, causal, dropout, false, attn::Overrides{0, 0});
+  return a;
+}
+extern "C" int choice(int heads, int N, int d, int causal, int dropout) {
+  return attn::choose_dkv(problem(heads, N, d), d, causal, dropout, false, attn::Overrides{0, 0});
+}
+extern "C" int fwd_form(int heads, int N, int d, int causal) {   // wavefronts of rows, groups
+  const attn::WaveGroups w = attn::fwd_groups(problem(heads, N, d), d, causal, false, true);
+  return 10 * w.waves + w.groups;
 }
 extern "C" int short_heads() { return attn::kBwdShort; }
 extern "C" int role_split() { return attn::kDkvRoleSplit; }
@@ -46,3 +53,10 @@ def test_short_heads_up_to_three_tiles(shim, heads, N):
     (512, 224, 64, 0, 0, 1), (513, 197, 64, 0, 0, 0), (1, 256, 64, 1, 0, 1), (256, 256, 64, 1, 1, 1), (257, 224, 64, 1, 1, 1), (257, 225, 64, 1, 1, 0), (513, 197, 64, 1, 1, 0)])
 def test_short_heads_of_four_tiles(shim, heads, N, d, causal, dropout, expect):
     assert (shim.choice(heads, N, d, causal, dropout) == shim.short_heads()) == bool(expect)
+
+
+# heads of up to two tiles have one form, however many there are; three are divided between two groups of wavefronts where there are few
+@pytest.mark.parametrize("heads,N,d,causal,form", [(1, 64, 64, 0, 41), (1, 128, 64, 0, 41), (500, 128, 64, 0, 41), (1, 128, 64, 1, 41), (1, 129, 64, 1, 22), (85, 192, 64, 0, 22),
+                                                   (86, 192, 64, 0, 41), (1, 128, 32, 1, 41), (1, 129, 32, 1, 22), (1, 320, 128, 0, 41), (1, 321, 128, 0, 22)])
+def test_forward_of_few_tiles(shim, heads, N, d, causal, form):
+    assert shim.fwd_form(heads, N, d, causal) == form
