@@ -104,6 +104,26 @@ def io_bytes(cfg):
     return 4 * elem + 4 * rows, 8 * elem + 4 * rows
 
 
+# Tile products per launch, counted and executed (Algorithm 4 has five in the backward pass; one tile product over the
+# whole problem is 2 B H N^2 d FLOPs).  Counted: forward S, PV; dK/dV kernel S, dP, dV, dK; dQ kernel dQ.  Executed: the
+# dQ kernel recomputes S and dP as well.  The backward of short heads is one launch, which forms all five once.
+ONE_LAUNCH_BACKWARD = "bwd_short_kernel"
+
+
+def backward_launches(n_fwd, n_dkv):
+    """Kernel names of a step, and between which of its five events each of them runs."""
+    if n_dkv == ONE_LAUNCH_BACKWARD:
+        return [n_fwd, n_dkv], [(0, 1), (1, 4)]
+    return [n_fwd, "dq_kernel", n_dkv], [(0, 1), (1, 3), (3, 4)]
+
+
+def tile_products(names):
+    """{kernel: (counted, executed)}"""
+    if len(names) == 2:
+        return {names[0]: (2, 2), names[1]: (5, 5)}
+    return dict(zip(names, [(2, 2), (1, 3), (4, 4)]))
+
+
 def run_gpu(cfg, steps, warmup, seed, mask_override=None, nsets=1):
     """Times `steps` forward+backward passes.  nsets > 1 rotates over that many separate copies of
     all inputs and outputs, so that no step finds its tensors in the 256 MB last-level cache."""
@@ -184,7 +204,7 @@ def run_gpu(cfg, steps, warmup, seed, mask_override=None, nsets=1):
     # launches of the backward pass); the kernels are named by the library's own choice
     pk = binding.make_params(g0["Q"], tau, cfg["causal"], cfg["p"], inputs.BASE_DROPOUT_SEED, 0)
     n_fwd, n_dkv = binding.attn_debug_kernel_choice(pk, cfg["sparse"])
-    names = [n_fwd, "dq_kernel", n_dkv]
+    names, spans = backward_launches(n_fwd, n_dkv)
     kevs = [[hev.new() for _ in range(5)] for _ in range(steps)]   # f0, f1=b0, b1, b2, b3
     for s in range(steps):
         e = kevs[s]
@@ -194,7 +214,6 @@ def run_gpu(cfg, steps, warmup, seed, mask_override=None, nsets=1):
         bwd_timed(z, e[1:5])
     torch.cuda.synchronize()
     # events: e[0] before the forward, e[1] = e[2] before the backward, e[3] after dQ, e[4] after dK/dV
-    spans = [(0, 1), (1, 3), (3, 4)]
     dur = {n: sum(hev.elapsed_ms(e[i0], e[i1]) for e in kevs) / steps for (i0, i1), n in zip(spans, names)}
     hev.close()
     peak_bytes = torch.cuda.max_memory_allocated(dev)
@@ -414,12 +433,15 @@ def load_traffic(workload, kernel):
         return None
 
 
-def kernel_bytes(cfg):
-    """Minimum HBM bytes per launch of the three kernels: forward reads Q, K, V and writes O and the
+def kernel_bytes(cfg, launches=3):
+    """Minimum HBM bytes per launch of the kernels: forward reads Q, K, V and writes O and the
     row statistic; the dQ kernel reads Q, K, V, O, dO and the statistic and writes dQ and the two row
-    vectors; the dK/dV kernel reads Q, K, V, dO and the row vectors and writes dK, dV."""
+    vectors; the dK/dV kernel reads Q, K, V, dO and the row vectors and writes dK, dV.
+    Where one launch does the whole backward pass it reads Q, K, V, O, dO and the statistic and writes the three gradients."""
     rows = cfg["B"] * cfg["H"] * cfg["N"]
     elem = rows * cfg["d"] * 2
+    if launches == 2:
+        return [4 * elem + 4 * rows, 8 * elem + 4 * rows]
     return [4 * elem + 4 * rows, 6 * elem + 12 * rows, 6 * elem + 8 * rows]
 
 
@@ -534,14 +556,10 @@ def main():
     kms = run["kernel_ms"]
     st = run["stats"]
     peak = PEAK_TFLOPS[cfg["dtype"]]
-    # Tile products per launch (Algorithm 4 has five in the backward pass; one tile product over the
-    # whole problem is 2 B H N^2 d FLOPs = f_fwd / 2).  Algorithmic: forward S, PV; dK/dV kernel
-    # S, dP, dV, dK; dQ kernel dQ.  Executed: the dQ kernel recomputes S and dP as well.
-    n_fwd, n_dq, n_dkv = run["names"]
-    products = {n_fwd: (2, 2), n_dq: (1, 3), n_dkv: (4, 4)}
+    products = tile_products(run["names"])
     algo = {n: products[n][0] * 0.5 * f_fwd for n in run["names"]}
     executed = {n: products[n][1] * 0.5 * f_fwd for n in run["names"]}
-    kbytes = dict(zip(run["names"], kernel_bytes(cfg)))
+    kbytes = dict(zip(run["names"], kernel_bytes(cfg, len(run["names"]))))
     dominant = max(kms, key=lambda n: kms[n])
     # which roofline bounds the dominant kernel: the longer of its algorithmic FLOPs at the matrix
     # peak and its minimum bytes at the HBM peak
@@ -604,7 +622,8 @@ def main():
                         "executed_frac_of_peak": round(executed[n] / v * 1e-9 / peak, 4)}
                     for n, v in kms.items()},
         "kernels_note": "per-kernel durations from a second pass of the same steps through attn_bwd_timed "
-                        "(events between the launches); backward: 5 tile products counted, 7 executed",
+                        "(events between the launches); backward: 5 tile products counted, "
+                        f"{sum(products[n][1] for n in run['names'][1:])} executed",
     }
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(cfg, run)
