@@ -213,8 +213,8 @@ template <typename F> [[noreturn]] void refused_in_backward(F&& set) {
 }
 
 // What the marshalling of a backward call asks of its tensors (backward() below, make_params), of the saved ones as they come back: hooks
-// of the program may have moved, converted or laid out anew some of them.
-void check_saved(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const at::Tensor& d_out) {
+// of the program may have moved, converted or laid out anew some of them, or have given them another batch than the lengths and the masks are for.
+void check_saved(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const at::Tensor& d_out, const Attention& a) {
   if (q.dim() != 4 || q.stride(3) != 1)
     refused_in_backward([] { raise(PyExc_ValueError, "expected a [B,H,N,d] tensor with contiguous last axis"); });
   if (q.scalar_type() != at::kHalf && q.scalar_type() != at::kBFloat16)
@@ -222,6 +222,10 @@ void check_saved(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, 
   if (!q.is_cuda()) refused_in_backward([] { raise(PyExc_ValueError, "the saved tensors are not on the GPU"); });
   if (!alike(q, k) || !alike(q, v) || !alike(q, d_out))
     refused_in_backward([] { raise(PyExc_ValueError, "all [B,H,N,d] tensors must share shape, strides and device"); });
+  if (a.key_lengths.defined() && a.key_lengths.size(0) != q.size(0))
+    refused_in_backward([] { raise(PyExc_TypeError, "key_lengths must be a contiguous int32 tensor of shape [B]"); });
+  if (a.block_mask.defined() && a.block_mask.dim() == 3 && a.block_mask.size(0) != q.size(1))
+    refused_in_backward([] { raise(PyExc_ValueError, "block_mask must be [T,T] or [H,T,T]"); });
 }
 
 using torch::autograd::AutogradContext;
@@ -257,9 +261,11 @@ struct FlashAttention : torch::autograd::Function<FlashAttention> {
     at::Tensor d_out = d_outs[0];
     if (d_out.sizes() != q.sizes() || d_out.strides() != q.strides())   // the library addresses dO with the strides of q
       d_out = like(q, q.scalar_type()).copy_(d_out);
-    check_saved(q, k, v, d_out);
     auto& data = ctx->saved_data;
     Attention a = {};
+    if (data.count("key_lengths")) a.key_lengths = data["key_lengths"].toTensor();
+    if (data.count("block_mask")) a.block_mask = data["block_mask"].toTensor();
+    check_saved(q, k, v, d_out, a);
     a.p.B = (int32_t)q.size(0); a.p.H = (int32_t)q.size(1); a.p.N = (int32_t)q.size(2); a.p.d = (int32_t)q.size(3);
     a.p.dtype = q.scalar_type() == at::kHalf ? ATTN_FP16 : ATTN_BF16;
     a.p.softmax_scale = (float)data["softmax_scale"].toDouble();
@@ -267,8 +273,6 @@ struct FlashAttention : torch::autograd::Function<FlashAttention> {
     a.p.dropout_p = (float)data["dropout_p"].toDouble();
     a.p.seed = (uint64_t)data["seed"].toInt();
     a.p.offset = (uint64_t)data["offset"].toInt();
-    if (data.count("key_lengths")) a.key_lengths = data["key_lengths"].toTensor();
-    if (data.count("block_mask")) a.block_mask = data["block_mask"].toTensor();
     const bool sparse = a.block_mask.defined();
     const attn_params p = on_current_stream(a, q);
     at::Tensor g[3];

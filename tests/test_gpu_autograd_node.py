@@ -120,6 +120,20 @@ def test_saved_tensors_that_come_back_changed(which, change, error, node):
         torch.autograd.grad(out, ts, do)
 
 
+# and of more batch entries than there are lengths, or other heads than the mask is for (dO is broadcast to them)
+@pytest.mark.parametrize("node", ["native", "python"])
+@pytest.mark.parametrize("axis,kw,error", [(0, "key_lengths", TypeError), (1, "block_mask", ValueError)])
+def test_saved_tensors_of_another_batch(axis, kw, error, node):
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    ts = [torch.randn(1, 1, 256, 64, generator=gen, device="cuda").bfloat16().requires_grad_(True) for _ in range(3)]
+    do = torch.ones_like(ts[0])
+    opts = {kw: torch.full((1,), 200, dtype=torch.int32, device="cuda") if kw == "key_lengths" else torch.ones(1, 2, 2, dtype=torch.uint8, device="cuda")}
+    with torch.autograd.graph.saved_tensors_hooks(lambda x: x, lambda x: torch.cat([x, x], axis)):
+        out = (flash_attention if node == "native" else _python_node)(*ts, **opts)
+    with pytest.raises(error, match=kw):
+        torch.autograd.grad(out, ts, do)
+
+
 def _grads(out, ts, do):
     for t in ts:
         t.grad = None
