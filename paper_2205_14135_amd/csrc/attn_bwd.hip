@@ -64,6 +64,7 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
     all = Ks;
   }
 
+  if constexpr (!SPARSE) args_at_once(a);
   if constexpr (SPARSE) {
     // the first workgroups plan the dK/dV launch (a multiple of the XCD count of them)
     if ((int)blockIdx.x < a.plan_groups) {

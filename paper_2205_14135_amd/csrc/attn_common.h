@@ -508,9 +508,10 @@ __device__ __forceinline__ int xcd_item(int n_items, int chunk, int id = (int)bl
   const int item = (id % kXcds) * chunk + id / kXcds;
   return item < n_items && (id / kXcds) < chunk ? item : -1;
 }
-// Asks for the arguments that a dense forward reads before its first tile in one go: left to itself, the compiler loads what stands behind each branch of the
+// Asks for the arguments that a dense kernel reads before its first tile in one go: left to itself, the compiler loads what stands behind each branch of the
 // prologue behind it, and a problem of few tiles waits for the scalar cache two to four times in a row, about 0.08 us each (one head of 128 tokens, d = 64:
-// 4.71 us with three such waits, 4.79 with four, 4.44 so).
+// 4.71 us with three such waits, 4.79 with four, 4.44 so; dQ of 64 causal heads of 4096, d = 128, with the head as one value below, 374 -> 369 us).  In the forward and in dQ; no
+// gain in the two-group forward (487 | 488), nor from the dropout arguments (16 heads of 8 x 1024, causal, forward 39.4 | 39.5).
 __device__ __forceinline__ void args_at_once(const KArgs& a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("" ::"s"(a.n_items), "s"(a.chunk), "s"(a.deal), "s"(a.H), "s"(a.N), "s"(a.T), "s"(a.klen), "s"(a.sb), "s"(a.sh), "s"(a.sn), "s"(a.Q), "s"(a.K),
@@ -526,12 +527,18 @@ __device__ __forceinline__ void args_at_once(const KArgs& a) {
 // heads | dealt round: 16 x 8 of 700, d = 32 68.3 | 57.7, d = 64 101 | 86, d = 128 166 | 145; 16 x 16 of 512, dropout 127 | 109, causal 82 | 78; 5 x 12 of
 // 1000 88 | 72; 16 x 16 of 1024 316 | 246; 4 x 16 of 4096, d = 128 1958 | 1338; 8 x 16 of 1024 causal with dropout, d = 128 216 | 181; 32 x 12 of 197 46.4 | 44.9.
 __device__ __forceinline__ int dealt_head(const KArgs& a, int pos) {
-  if (__builtin_expect(!a.deal, 1)) return pos;   // (the rest out of the way, so that no jump stands before the first loads)
-  const int n = a.B * a.H, whole = n / kXcds, rest = n % kXcds;   // XCDs below `rest` have one head more
-  const int in_long = rest * (whole + 1);
-  const int x = pos < in_long ? pos / (whole + 1) : rest + (pos - in_long) / (whole > 0 ? whole : 1);
-  const int j = pos - x * whole - (x < rest ? x : rest);
-  return j * kXcds + (j < whole ? (x + j) % kXcds : x);
+  int head = pos;
+  if (__builtin_expect(a.deal, 0)) {   // (out of the way, so that no jump stands before the first loads)
+    const int n = a.B * a.H, whole = n / kXcds, rest = n % kXcds;   // XCDs below `rest` have one head more
+    const int in_long = rest * (whole + 1);
+    const int x = pos < in_long ? pos / (whole + 1) : rest + (pos - in_long) / (whole > 0 ? whole : 1);
+    const int j = pos - x * whole - (x < rest ? x : rest);
+    head = j * kXcds + (j < whole ? (x + j) % kXcds : x);
+  }
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+s"(head));   // one value from here on
+#endif
+  return head;
 }
 // XOR swizzle of the 16-byte chunk index inside an unpadded [rows][D] LDS tile.  It makes both
 // access patterns used on the tiles conflict-free on a 64-bank LDS: 16 consecutive rows at one
