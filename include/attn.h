@@ -47,7 +47,11 @@
  *
  * Which kernel a call takes depends on head dimension, length, masks and the
  * number of heads; every choice computes the same operation to the same
- * tolerance.  attn_debug_set_variant overrides the choice for comparisons and
+ * tolerance.  The last bits of a head's results may therefore depend on how many
+ * heads share its call (few heads are divided over groups of wavefronts, which
+ * sum in an order of their own); for given sizes and options they are the same in
+ * every call, but for the block-sparse columns named at attn_blocksparse_bwd.
+ * attn_debug_set_variant overrides the choice for comparisons and
  * tests; its initial values come from two environment variables read once, when
  * the first call needs them: ATTN_FWD_VARIANT=base|pp and ATTN_DKV_VARIANT=rs|fr|w64.
  * Unset, the library picks by measurement.

@@ -383,6 +383,7 @@ template <> constexpr int kDtype<__bf16> = 1;
 //            10 x 4096 138 +8.1 -12.7 -2.7; 24 x 2001 81.7 +5.3 -5.1 +1.9; 64 x 1024 43.1 +3.1 +0.9 +8.8
 //   d = 128  1 x 128 17.4 +2.5 +0.2; 16 x 640 42.5 +0.9 -2.4; 8 x 2048 130 -3.5 -9.1; 1 x 8192 474 -26 -45; 60 x 512 41.5 +2.5 +9.7;
 //            16 x 2048 136 -1.5 +18.3; 8 x 4096 253 -5.1 +28.4, causal 213 -6.0 +23.5, dropout 272 -8.3 +30.0; 40 x 1024 93.6 +10.1 +18.4
+//   (d = 128 without the causal mask spills one vector register in every form of 4 wavefronts of rows)
 //   block-sparse (butterfly mask of T x T blocks, heads x T)  d = 64  4 x 8 48.2 -1.5 -4.2 -4.0; 4 x 32 65.7 -1.8 -4.4 -4.4; 4 x 64 76.0 -2.0 -1.4 +7.0;
 //            8 x 64 112 +5.8 +6.2 +24.1; d = 128  4 x 32 89.9 -0.3 -4.4; 4 x 64 132 +0.3 +17.4
 WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {

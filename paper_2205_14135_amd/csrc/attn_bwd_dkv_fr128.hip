@@ -371,6 +371,8 @@ int launch_groups(const KArgs& a, const WaveGroups& w, bool causal, bool dropout
 //            40 x 1024 93.6 +7.3 +16.3 +21.6
 //   causal   16 x 1024 62.4 -5.5 -9.1 -7.6; 8 x 2048 110 -15 -21 -22; 8 x 4096 213 -23 +6 -9; 40 x 1024 78.3 -2.8 +11.3 +19.4; 10 x 4096 254 +8 +42 +16
 //   dropout  8 x 2048 137 -19 -31 -35; 8 x 4096 272 -30 +16 -5; 60 x 512 48.2 -2.7 +8.2 +16.5; 10 x 4096 372 +23 +46 +5
+// Vector registers spilled (bytes of scratch per lane): {2, 4} 56 (228), with dropout 69 (280), whose wavefronts hold the copy offsets of twice as many
+// rows each; block-sparse {4, 1} 9 to 13 (40 to 56), {4, 2} 18 (76), with dropout 27 (112); the others none.  The figures above include them.
 static WaveGroups fr128_groups(const KArgs& a, bool sparse, bool divide) {
   if (!divide) return {4, 1};
   const WorkItems w(a, sparse, false);

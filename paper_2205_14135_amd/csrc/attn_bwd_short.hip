@@ -10,9 +10,10 @@
 // A wavefront owns 32 keys (layout "lane = key", as in attn_bwd_dkv_fr.hip) for dK and dV, and then 32 queries for dQ: dS
 // changes owner through LDS, [key][query] rows written four queries at a time and read with the transposing read, so
 // that dQ^T = K^T dS^T takes both operands from LDS in the layout the other kernels read V^T and K^T in.
-// What bounds it: at N = 128 memory (2048 heads, d = 64: 268 MB in 66.6 us, 4.0 TB/s; the two launches moved 402 MB in 83.9);
+// What bounds it: at N = 128 memory (2048 heads, d = 64: 268 MB in 67 to 72 us, 3.7 to 4.0 TB/s; the two launches move 403 MB in 83);
 // with few heads the latency of one head (96 heads of 128: 13.2 -> 8.6 us); at N > 128 a compute unit holds one workgroup, and
 // nothing covers its loads and stores from the second head on (256 heads of 197 27.0 -> 22.3 us, 1024 of 256 102 -> 107, not taken).
+// Vector registers spilled: 5 with dropout at d = 64 and N > 128, none elsewhere.
 #include "attn_common.h"
 #include "attn_tiles.h"
 
