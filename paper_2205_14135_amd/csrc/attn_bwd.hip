@@ -72,7 +72,8 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
       return;
     }
   }
-  const int item = xcd_item(a.n_items, a.chunk, SPARSE ? (int)blockIdx.x - a.plan_groups : (int)blockIdx.x);
+  constexpr bool BLOCKS = CAUSAL && !SPARSE && D != 64;   // (at d = 128 the loop over a pair costs registers the kernel does not have)
+  const int item = BLOCKS ? causal_item(a) : xcd_item(a.n_items, a.chunk, SPARSE ? (int)blockIdx.x - a.plan_groups : (int)blockIdx.x);
   if (item < 0) return;
   const int n_qt = a.T * (4 / RW);   // blocks of BR rows, to the end of the last 128-row block: the scratch vectors are written whole
   // Work item = (head, row block).  Under the causal mask row block q sweeps 2 (q + 1) key tiles;
@@ -83,19 +84,8 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
   const int n_per_head = PAIRED ? (n_qt + 1) / 2 : n_qt;
   int bh = item / n_per_head;
   int q_item = item % n_per_head;
-  if constexpr (CAUSAL && !PAIRED) {
-    // unpaired causal items: the row blocks of a.group consecutive heads are dealt out together,
-    // heaviest first, so that the items a compute unit receives last are light ones.  The host
-    // sizes the group so that the K and V of its heads (the L2 working set of an XCD) stay within
-    // 8 MiB: larger groups balance better but thrash L2 on long sequences.
-    const int n_heads = a.B * a.H;
-    const int grp0 = (bh / a.group) * a.group;             // first head of this group
-    const int gsz = min(a.group, n_heads - grp0);          // heads in it (the last group may be short)
-    const int within = (bh - grp0) * n_qt + q_item;        // position inside the group's items
-    bh = grp0 + within % gsz;
-    q_item = within / gsz;                                 // q_item-th heaviest block (see qt below)
-  }
-  if constexpr (!SPARSE) bh = dealt_head(a, bh);
+  if constexpr (CAUSAL && !PAIRED) causal_block(a, item, n_qt, bh, q_item);
+  if (!SPARSE && !(BLOCKS && a.group == 0)) bh = dealt_head(a, bh);
   const int n_pass = PAIRED && q_item != n_qt - 1 - q_item ? 2 : 1;
 #pragma clang loop unroll(disable)
   for (int pass = 0; pass < n_pass; ++pass) {
@@ -345,11 +335,7 @@ int launch_dq(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
   const int blocks = a.T * (4 / RW);
   a.n_items = a.B * a.H * (causal && !sparse && D == 64 ? (blocks + 1) / 2 : blocks);   // (pairs of row blocks)
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  {
-    const int64_t kv_bytes = 2 * (int64_t)a.N * D * (int64_t)sizeof(T);
-    const int64_t fit = ((int64_t)8 << 20) / kv_bytes;
-    a.group = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
-  }
+  a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
   if (sparse) a.plan_groups = sparse_plan_groups(a);
   const dim3 grid(kXcds * a.chunk + (sparse ? a.plan_groups : 0)), block(64 * RW * KG);
 #define ATTN_DQ_CASE(C, P, S)                                                          \
@@ -393,6 +379,9 @@ WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse, bool divid
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return d <= 64 && w.tiles >= (d == 64 ? 24 : 12) && !sparse ? WaveGroups{2, 4} : WaveGroups{2, 2};
   if (d == 32) return w.of64 <= 3 * kComputeUnits && w.tiles >= 4 ? WaveGroups{2, 2} : WaveGroups{4, 1};   // (three workgroups fit)
   if (w.of128 <= kComputeUnits && w.tiles >= (d == 64 ? 16 : 24)) return {4, 2};
+  // (causal, two blocks in turn on a compute unit, heaviest first; {4, 1} | {4, 2}, us: 8 x 8192 511 | 485, 10 x 4096 226 | 214, 20 x 2000 with dropout 151 | 140;
+  // 30 x 2048 151 | 152, 48 x 900 67.6 | 73.2)
+  if (d == 128 && causal && !sparse && w.of128 <= (w.tiles >= 64 ? 2 : 3 / 2.) * kComputeUnits && w.tiles >= 24) return {4, 2};
   if (d == 64 && !pairs && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
   return {4, 1};
 }

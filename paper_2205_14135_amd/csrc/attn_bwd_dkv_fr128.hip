@@ -59,7 +59,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
   for (int round = 0;; ++round) {
   int item, slot = 0, skip_blocks = 0, take_blocks = 0x7fffffff;
   if (!list_mode) {
-    item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
+    item = CAUSAL && !SPARSE ? causal_item(a) : xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
     if (item < 0) return;
     if constexpr (SPARSE) {
       if (n_list > 0 && a.col_segs[item] > 0) return;   // heavy
@@ -69,19 +69,8 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
   }
   int bh = item / n_kt;
   int kt = item % n_kt;
-  if constexpr (CAUSAL && !SPARSE) {
-    // Key block k is visited by the query tiles from the diagonal on, so its work falls with k.
-    // The key blocks of a.group consecutive heads are dealt out together, heaviest first, so that
-    // the items a compute unit receives last are light ones (the host sizes the group so that the
-    // Q and dO of its heads, the L2 working set of an XCD, stay within 8 MiB).
-    const int n_heads = a.B * a.H;
-    const int grp0 = (bh / a.group) * a.group;             // first head of this group
-    const int gsz = min(a.group, n_heads - grp0);          // heads in it (the last group may be short)
-    const int within = (bh - grp0) * n_kt + kt;            // position inside the group's items
-    bh = grp0 + within % gsz;
-    kt = within / gsz;
-  }
-  if constexpr (!SPARSE) bh = dealt_head(a, bh);
+  if constexpr (CAUSAL && !SPARSE) causal_block(a, item, n_kt, bh, kt);   // (key block k is visited by the query tiles from the diagonal on)
+  if (!SPARSE && !(CAUSAL && a.group == 0)) bh = dealt_head(a, bh);
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;
@@ -327,14 +316,10 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
 template <typename T, int RW, int KG>
 int launch_t(const KArgs& a_in, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
   KArgs a = a_in;
-  {
-    const int64_t tile_bytes = 2 * (int64_t)a.N * D * (int64_t)sizeof(T);   // Q and dO of one head
-    const int64_t fit = ((int64_t)8 << 20) / tile_bytes;
-    a.group = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
-  }
   const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));   // Q and dO
   const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(64 * RW * KG);
 #define ATTN_DKV_FR128_CASE(C, P, S)                                                            \
   if constexpr (!S || RW == 4)                                                                  \
@@ -373,16 +358,19 @@ int launch_groups(const KArgs& a, const WaveGroups& w, bool causal, bool dropout
 //   dropout  8 x 2048 137 -19 -31 -35; 8 x 4096 272 -30 +16 -5; 60 x 512 48.2 -2.7 +8.2 +16.5; 10 x 4096 372 +23 +46 +5
 // Vector registers spilled (bytes of scratch per lane): {2, 4} 56 (228), with dropout 69 (280), whose wavefronts hold the copy offsets of twice as many
 // rows each; block-sparse {4, 1} 9 to 13 (40 to 56), {4, 2} 18 (76), with dropout 27 (112); the others none.  The figures above include them.
-static WaveGroups fr128_groups(const KArgs& a, bool sparse, bool divide) {
+static WaveGroups fr128_groups(const KArgs& a, bool causal, bool sparse, bool divide) {
   if (!divide) return {4, 1};
   const WorkItems w(a, sparse, false);
   if (sparse) return w.of128 <= kComputeUnits / 2 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return w.tiles >= 32 ? WaveGroups{2, 4} : WaveGroups{2, 2};
+  // (causal: one workgroup on a compute unit at a time takes the blocks heaviest first, and a heavy one takes half as long; {4, 1} | {4, 2}, us: 8 x 8192 510 | 463,
+  // 10 x 4096 226 | 203, 30 x 2048 153 | 145, 36 x 1300 88.5 | 84.7, 48 x 900 67.9 | 65.5, 64 x 1024 with dropout 101 | 99; 128 x 512 62 | 67)
+  if (causal && w.of128 <= 2 * kComputeUnits && w.tiles >= 14) return {4, 2};
   return w.of128 <= kComputeUnits && w.tiles >= 5 ? WaveGroups{4, 2} : WaveGroups{4, 1};
 }
 
 int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool sparse, int extra_groups, bool divide, hipStream_t s) {
-  const WaveGroups w = fr128_groups(a, sparse, divide);
+  const WaveGroups w = fr128_groups(a, causal, sparse, divide);
   return dtype == 0 ? launch_groups<_Float16>(a, w, causal, dropout, sparse, extra_groups, s)
                     : launch_groups<__bf16>(a, w, causal, dropout, sparse, extra_groups, s);
 }

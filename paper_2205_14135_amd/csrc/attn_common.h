@@ -21,7 +21,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct KArgs {
   int n_items;             // work items (B*H*tiles)
   int chunk;               // items per XCD = ceil(n_items / 8)
-  int group;               // causal dQ: heads whose row blocks are dealt out together, heaviest first
+  int group;               // causal kernels with a block of rows per item: heads whose blocks are dealt out together, 0: all (causal_block)
   int deal;                // heads are dealt round the XCDs (dealt_head)
   int B, H, N, T;          // T = ceil(N / 128)
   const int* klen;         // key-padding lengths [B] or nullptr
@@ -134,6 +134,22 @@ int launch_bwd_short(const KArgs& a, int dtype, int d, bool causal, bool dropout
 int launch_fwd_pp(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);
 // MFMA-only kernel for measuring the sustained matrix rate (attn_probe.hip); *flops = FLOPs launched
 int launch_mfma_rate(int dtype, int iters, int operand_sets, float* sink, hipStream_t s, double* flops);
+
+// a.group: how many heads the causal kernels deal out together (causal_block); head_bytes: what a head's items stream.  All of them (0), unless
+// many heads of 128 columns fill every XCD evenly or nearly so: then what an XCD streams at a time stays within 8 MiB, the L2 working set (a level of all heads
+// streams them all).  A run of whole groups per XCD leaves some XCDs the heavy blocks of a group and others the light ones where the heads do not divide
+// evenly, and one head at a time (the forward before) puts blocks of the same weight on a compute unit.  us, runs | all heads, heads x N:
+//   d = 128, forward  64 x 1024 37.1 | 30.0, dropout 44.2 | 34.0; 48 x 900 29.7 | 24.0; 36 x 2048 63.9 | 50.8; 20 x 4096 124 | 97.5; 12 x 8192 265 | 214;
+//            96 x 1024 43.8 | 37.4; 300 x 300 25.5 | 31.2, 250 x 512 36.9 | 39.3, 256 x 512 33.7 | 36.8
+//   d = 128, backward  64 x 1024 87 | 88; 60 x 700 58.0 | 54.5; 36 x 2048 185 | 158; 10 x 8192 699 | 582; 72 x 1024 110 | 90; 136 x 1024 191 | 164; 192 x 1024
+//            233 | 225 (taken as runs all the same: 64 x 1500 145 | 151, 64 x 4096 847 | 862);   128 x 1024 150 | 158, 250 x 512 110 | 119, 256 x 512 105 | 114, 1000 x 300 234 | 239
+//   d = 32, forward  96 x 2048 68.3 | 45.1; 100 x 1024 24.9 | 17.3; 60 x 1000, dropout 26.1 | 19.9; 1024 x 512 48.6 | 45.2; backward 96 x 2048 156 | 143; 1024 x 512 136 | 135
+inline int causal_group(const KArgs& a, int d, bool sparse, int64_t head_bytes) {
+  const int64_t heads = (int64_t)a.B * a.H;
+  if (!sparse && (d < 128 || a.n_items <= 2 * kComputeUnits || (heads % (8 * kXcds) != 0 && heads < 224))) return 0;
+  const int64_t fit = ((int64_t)8 << 20) / head_bytes;
+  return (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
+}
 
 #if defined(__HIPCC__)
 // ---------------------------------------------------------------- device helpers
@@ -539,6 +555,29 @@ __device__ __forceinline__ int dealt_head(const KArgs& a, int pos) {
   asm volatile("" : "+s"(head));   // one value from here on
 #endif
   return head;
+}
+// The causal kernels that take one block of rows (or keys) per work item (d = 32 and 128; at d = 64 pairs of blocks): this workgroup's item
+// (-1: none), and the item's head and block, counted from the head's heaviest, level 0.  The blocks of all heads (a.group == 0) or of a.group consecutive heads
+// (each XCD a run of items) are dealt out together, heaviest first, so that a compute unit gets blocks of different weights at the start and light ones
+// last.  All heads: see causal_group.  (The order of the heads: see dealt_head.)
+__device__ __forceinline__ int causal_item(const KArgs& a) {
+  if (a.group > 0) return xcd_item(a.n_items, a.chunk);
+  return (int)blockIdx.x < a.n_items ? (int)blockIdx.x : -1;
+}
+__device__ __forceinline__ void causal_block(const KArgs& a, int item, int n_levels, int& head, int& level) {
+  const int n_heads = a.B * a.H;
+  if (a.group == 0) {
+    head = item % n_heads;
+    level = item / n_heads;
+    const int j = head / kXcds;
+    if (j < n_heads / kXcds) head = j * kXcds + (head + j) % kXcds;
+  } else {
+    const int grp0 = item / n_levels / a.group * a.group;  // first head of this group
+    const int gsz = min(a.group, n_heads - grp0);          // heads in it (the last group may be short)
+    const int within = item - grp0 * n_levels;             // position inside the group's items
+    head = grp0 + within % gsz;
+    level = within / gsz;
+  }
 }
 // XOR swizzle of the 16-byte chunk index inside an unpadded [rows][D] LDS tile.  It makes both
 // access patterns used on the tiles conflict-free on a 64-bank LDS: 16 consecutive rows at one

@@ -62,7 +62,8 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
   }
 
   args_at_once(a);
-  const int item = xcd_item(a.n_items, a.chunk);
+  constexpr bool BLOCKS = CAUSAL && !SPARSE && D != 64;   // one block of rows per item
+  const int item = BLOCKS ? causal_item(a) : xcd_item(a.n_items, a.chunk);
   if (item < 0) return;
   const int n_qt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last block may be ragged
   // Work item = (head, row block), heavy (late) blocks first under a causal mask.  For dense
@@ -70,8 +71,9 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
   // every workgroup does the same amount of work.
   constexpr bool PAIRED = CAUSAL && !SPARSE && D == 64;
   const int n_per_head = PAIRED ? (n_qt + 1) / 2 : n_qt;
-  const int bh = SPARSE ? item / n_per_head : dealt_head(a, item / n_per_head);
-  const int q_item = item % n_per_head;
+  int bh = item / n_per_head, q_item = item % n_per_head;
+  if constexpr (BLOCKS) causal_block(a, item, n_qt, bh, q_item);
+  if (!SPARSE && !(BLOCKS && a.group == 0)) bh = dealt_head(a, bh);
   const int n_pass = PAIRED && q_item != n_qt - 1 - q_item ? 2 : 1;
 #pragma clang loop unroll(disable)
   for (int pass = 0; pass < n_pass; ++pass) {
@@ -307,6 +309,7 @@ int launch_fwd_groups(KArgs a, bool causal, bool dropout, bool sparse, hipStream
   const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
   a.n_items = a.B * a.H * (causal && !sparse && D == 64 ? (blocks + 1) / 2 : blocks);   // (pairs of row blocks)
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
   const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
 #define ATTN_FWD_CASE(C, P, S)                                                              \
   if (causal == C && dropout == P && sparse == S) {                                         \
@@ -417,12 +420,12 @@ WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divi
 // therefore less evenly under the causal mask).  us, two-group | this file's (16384 tokens, 16 heads):
 //   causal     N = 512 76 | 74, 640 111 | 70, 768 111 | 81, 1024 97 | 107, 1400 138 | 116, 2048 151 | 174, 4096 268 | 309
 //   no mask    N = 512 89 | 83, 640 110 | 97, 768 115 | 111, 1024 142 | 143, 1400 205 | 184, 2048 253 | 267, 4096 485 | 517
-//   causal with dropout  N = 512 85 | 84, 1024 114 | 125, 2048 182 | 206, 4096 326 | 369; 64 heads of 1024: 51 | 40
+//   causal with dropout  N = 512 85 | 84, 1024 114 | 125, 2048 182 | 206, 4096 326 | 369; 64 heads of 1024: 51 | 34
 //   few heads  12 of 4096 102 | 118, 24 of 2001 55 | 62; causal with dropout, 8 of 8192 267 | 209
 // The estimate is the faster kernel in all of these but for less than 1 % (no mask, 1024; causal with dropout, 512).  It is
 // no better than that: for the two-group kernel it is within 4 % of the time from N = 1024 on where the rounds are full, 6-13 % short
 // with dropout, and up to 36 % long where the last round is part-filled or the odd block of a head stands alone, charged
-// as a pair (causal 640: 151; no mask 1400: 231); for this file's kernel within 10 %, but for 64 heads of 1024 (32).
+// as a pair (causal 640: 151; no mask 1400: 231); for this file's kernel within 10 %.
 // Dropout without a mask is plain vector ALU work, which evens the two out in favour of this file's: N = 512
 // 112 | 94, 1024 180 | 165, 2048 322 | 313, 4096 626 | 610, 8192 1215 | 1203.
 static bool two_group_is_faster(const KArgs& a, bool causal, bool dropout) {
