@@ -178,10 +178,8 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
 
   // LDS operand reads run PF fragments ahead of the MFMA that consumes them
   constexpr int PF = 4;
-  // out[qb] = Tile[32 qb .. +31][:] . frags, starting from zero or (with_init: a literal at every
-  // call, a test of the pointer would be evaluated at run time) from the 64 per-row values at cinit
-  auto row_product = [&](const T* tile, const T8 (&bfrag)[KK], const bool with_init, const float* cinit,
-                         f32x16 (&out)[2]) {
+  // out[qb] = Tile[32 qb .. +31][:] . frags; between(f) comes after MFMA f of 2 KK
+  auto row_product = [&](const T* tile, const T8 (&bfrag)[KK], f32x16 (&out)[2], auto between) __attribute__((always_inline)) {
     auto frag = [&](int f) { return *(const T8*)(tile + lds_off<D>(32 * (f & 1) + r, 2 * (f >> 1) + g)); };  // f = 2 kk + qb
     T8 ring[PF];
 #pragma unroll
@@ -190,29 +188,14 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
 #pragma unroll
     for (int f = 0; f < 2 * KK; ++f) {
       const T8 cur = ring[f % PF];
-      if (f < 2) {
-        f32x16 z;
-        if (with_init) {
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            const f32x4 c4 = *(const f32x4*)(cinit + 32 * f + 8 * i4 + 4 * g);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) z[4 * i4 + e] = c4[e];
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) z[i] = 0.f;
-        }
-        out[f & 1] = mfma32(cur, bfrag[f >> 1], z);
-      } else {
-        out[f & 1] = mfma32(cur, bfrag[f >> 1], out[f & 1]);
-      }
+      out[f & 1] = mfma32(cur, bfrag[f >> 1], out[f & 1]);
       if (f + PF < 2 * KK) ring[f % PF] = frag(f + PF);
+      between(f);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // acc^T += Tile^T . frag   (contraction over the 64 queries of the tile)
-  auto col_product = [&](const T* tile, const T8 (&bfrag)[4], f32x16 (&acc)[DB]) {
+  // acc^T += Tile^T . frag   (contraction over the 64 queries of the tile); between(f) comes after MFMA f of 4 DB
+  auto col_product = [&](const T* tile, const T8 (&bfrag)[4], f32x16 (&acc)[DB], auto between) __attribute__((always_inline)) {
     auto frag = [&](int f) {   // f = DB cc + db: consecutive MFMAs hit different accumulators
       const T* base = tile + 16 * (f / DB) * D;
       return tr_frag<T8>(base + tro.off[f % DB][0], base + tro.off[f % DB][1]);
@@ -226,9 +209,16 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
       const T8 cur = ring[f % PF];
       acc[f % DB] = mfma32(cur, bfrag[f / DB], acc[f % DB]);
       if (f + PF < 4 * DB) ring[f % PF] = frag(f + PF);
+      between(f);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  auto nothing = [](int) {};
+  // The vector work of P and dS in between the MFMAs of the products that do not wait for it (below).  us of this kernel, before | after: d = 32, where a product is
+  // four MFMAs and latency binds, B H = 128, N = 700 34.7 | 28.9, 64 x 1500 72.7 | 57.1; d = 64 causal 128 x 1024 49.3 | 47.6, 64 x 2000 82.9 | 80.3, block-sparse N =
+  // 16384 1 %; without a mask nothing (128 x 2048 294 | 290, 60 x 900 38.0 | 38.9), nor d = 32 causal (60 x 1000 21.6 | 22.1); with dropout it spills or is slower (d = 64, 256 x 512 56.4 | 61.3, d = 32, 96 x 1000
+  // 63.4 | 70.9).
+  constexpr bool BETWEEN = !DROPOUT && (D == 32 ? !CAUSAL : CAUSAL || SPARSE);
   // ---- pipeline over the query tiles of this key block: tile t + 1 streams in while t is used
   int buf_rt = 0;
   // t: this group's tile, -1 if there is none; more: some group (then the first) has one
@@ -247,7 +237,11 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
     const int i0 = t * TILE;
     if ((KG == 1 || t >= 0) && (!CAUSAL || i0 + TILE - 1 >= kw0)) {
       f32x16 s[2], dp[2];
-      row_product(Qs0 + buf * TILE * D, kf, false, nullptr, s);                // S = Q K^T
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[qb][i] = 0.f;
+      row_product(Qs0 + buf * TILE * D, kf, s, nothing);                       // S = Q K^T
       uint32_t kept = 0;   // the keep flags of this lane's key for the tile's 64 queries it holds
       if constexpr (DROPOUT) kept = keep.draw<2>(i0, kw0, bh, a.offset_lo, a.seed_lo, a.seed_hi);
       // hidden entries get the logit -inf, hence P = 0: above the causal diagonal (tiles that cross it
@@ -261,53 +255,70 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
           for (int i = 0; i < 16; ++i)
             if (i0 + 32 * qb + 8 * (i >> 2) + 4 * g + (i & 3) < first_query) s[qb][i] = -INFINITY;
       }
-      // P = exp(S - L), kept in fp32 in s[] for dS; the 16-bit (dropped) copy feeds dV
-      T8 pf[4];
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
+      // P = exp(S - L), kept in fp32 in s[] for dS; the 16-bit (dropped) copy feeds dV.  Four elements: j = 2 i4 + qb
+      T8 pf[4], dsf[4];
+      auto p_group = [&](int j) __attribute__((always_inline)) {
+        const int i4 = j >> 1, qb = j & 1;
         // (keeps the bit extracts where they are used: hoisted, they make the forms short of registers spill; the
         // plain form is faster without)
-        if constexpr (DROPOUT && (CAUSAL || SPARSE)) asm volatile("" : "+v"(kept));
+        if constexpr (DROPOUT && (CAUSAL || SPARSE))
+          if (qb == 0) asm volatile("" : "+v"(kept));
+        const f32x4 l4 = *(const f32x4*)(Ls0 + buf * TILE + 32 * qb + 8 * i4 + 4 * g);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          const f32x4 l4 = *(const f32x4*)(Ls0 + buf * TILE + 32 * qb + 8 * i4 + 4 * g);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int i = 4 * i4 + e;
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qb][i], c, -l4[e]));
-            s[qb][i] = p;
-            const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
-            if constexpr (DROPOUT) {
-              pf[cc][tt] = (T)keep_or_zero(p, KeepLK::mask(kept, qb, i4, e));
-            } else {
-              pf[cc][tt] = (T)p;
-            }
-          }
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * i4 + e;
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qb][i], c, -l4[e]));
+          s[qb][i] = p;
+          const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
+          pf[cc][tt] = DROPOUT ? (T)keep_or_zero(p, KeepLK::mask(kept, qb, i4, e)) : (T)p;
         }
-      }
-      col_product(Gs0 + buf * TILE * D, pf, dv);                          // dV^T += dO^T P_dropped
-      // dP = dO V^T; without dropout it starts from -D, so the result is dP - D
-      row_product(Gs0 + buf * TILE * D, vf, !DROPOUT, Ds0 + buf * TILE, dp);
-      T8 dsf[4];
+      };
+      auto start_dp = [&]() __attribute__((always_inline)) {   // without dropout dP starts from -D, so that the result is dP - D
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
+        for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
-          if constexpr (DROPOUT) d4 = *(const f32x4*)(Ds0 + buf * TILE + 32 * qb + 8 * i4 + 4 * g);   // -D_i
+          for (int i4 = 0; i4 < 4; ++i4) {
+            f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (!DROPOUT) d4 = *(const f32x4*)(Ds0 + buf * TILE + 32 * qb + 8 * i4 + 4 * g);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int i = 4 * i4 + e;
-            const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
-            float dpv = dp[qb][i];
-            if constexpr (DROPOUT) {
-              dpv = dropped_dp_minus_d(dpv, a.keep_scale, KeepLK::mask(kept, qb, i4, e), d4[e]);
-            }
-            dsf[cc][tt] = (T)(s[qb][i] * dpv);
+            for (int e = 0; e < 4; ++e) dp[qb][4 * i4 + e] = d4[e];
           }
+      };
+      auto ds_group = [&](int j) __attribute__((always_inline)) {
+        const int i4 = j >> 1, qb = j & 1;
+        f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (DROPOUT) d4 = *(const f32x4*)(Ds0 + buf * TILE + 32 * qb + 8 * i4 + 4 * g);   // -D_i
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int i = 4 * i4 + e;
+          const int cc = 2 * qb + (i4 >> 1), tt = 4 * (i4 & 1) + e;
+          float dpv = dp[qb][i];
+          if constexpr (DROPOUT) dpv = dropped_dp_minus_d(dpv, a.keep_scale, KeepLK::mask(kept, qb, i4, e), d4[e]);
+          dsf[cc][tt] = (T)(s[qb][i] * dpv);
         }
+      };
+      if constexpr (!BETWEEN) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p_group(j);
+        col_product(Gs0 + buf * TILE * D, pf, dv, nothing);               // dV^T += dO^T P_dropped
+        start_dp();
+        row_product(Gs0 + buf * TILE * D, vf, dp, nothing);               // dP = dO V^T
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ds_group(j);
+      } else {
+        // P comes between the MFMAs of dP and dS between those of dV: the matrix pipe and the vector ALU work at once within a wavefront, not only
+        // where two wavefronts happen to be in different parts of a tile
+        start_dp();
+        row_product(Gs0 + buf * TILE * D, vf, dp, [&](int f) __attribute__((always_inline)) {
+#pragma unroll
+          for (int j = 8 * f / (2 * KK); j < 8 * (f + 1) / (2 * KK); ++j) p_group(j);
+        });
+        col_product(Gs0 + buf * TILE * D, pf, dv, [&](int f) __attribute__((always_inline)) {
+#pragma unroll
+          for (int j = 8 * f / (4 * DB); j < 8 * (f + 1) / (4 * DB); ++j) ds_group(j);
+        });
       }
-      col_product(Qs0 + buf * TILE * D, dsf, dk);                         // dK^T += Q^T dS
+      col_product(Qs0 + buf * TILE * D, dsf, dk, nothing);                // dK^T += Q^T dS
     }
     wait_async_copies();
     __syncthreads();   // the next tile has landed, and everyone is done with this buffer
