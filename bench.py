@@ -151,7 +151,7 @@ def run_gpu(cfg, steps, warmup, seed, mask_override=None, nsets=1):
         sets.append(dict(g=g, O=torch.empty_like(g["Q"]),
                          L=torch.empty((B, H, N), dtype=torch.float32, device=dev),
                          grads=tuple(torch.empty_like(g["Q"]) for _ in range(3))))
-    pp = binding.make_params(g0["Q"], tau)
+    pp = binding.make_params(g0["Q"], tau, cfg["causal"], cfg["p"])
     ws_bytes = binding.attn_blocksparse_bwd_workspace_bytes(pp) if cfg["sparse"] else binding.attn_bwd_workspace_bytes(pp)
     ws = torch.empty(max(256, ws_bytes), dtype=torch.uint8, device=dev)
     stream = torch.cuda.current_stream(dev).cuda_stream
@@ -204,6 +204,9 @@ def run_gpu(cfg, steps, warmup, seed, mask_override=None, nsets=1):
     # launches of the backward pass); the kernels are named by the library's own choice
     pk = binding.make_params(g0["Q"], tau, cfg["causal"], cfg["p"], inputs.BASE_DROPOUT_SEED, 0)
     n_fwd, n_dkv = binding.attn_debug_kernel_choice(pk, cfg["sparse"])
+    vectors = 2 * 4 * B * H * 128 * ((N + 127) // 128)
+    if not cfg["sparse"] and binding.attn_bwd_workspace_bytes(pk) > vectors:   # room for dQ between key blocks: one launch
+        n_dkv = ONE_LAUNCH_BACKWARD
     names, spans = backward_launches(n_fwd, n_dkv)
     kevs = [[hev.new() for _ in range(5)] for _ in range(steps)]   # f0, f1=b0, b1, b2, b3
     for s in range(steps):

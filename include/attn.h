@@ -130,9 +130,12 @@ int attn_fwd(const attn_params* p, const void* Q, const void* K, const void* V,
              void* O, float* LSE);
 
 /*
- * Bytes of scratch that attn_bwd needs for these params: two floats per query
+ * Bytes of scratch for attn_bwd with these params: two floats per query
  * row (D_i of Eq. (4), Appendix B.2, and the row statistic in base 2), i.e. the
- * O(N) additional memory of Theorem 1; never quadratic in N.  Returns 0 if the
+ * O(N) additional memory of Theorem 1; never quadratic in N.  Where the one-launch
+ * kernel takes heads of 257 to 512 tokens (d <= 64), a row of dQ in float32 more;
+ * attn_bwd takes such problems in two launches if it is given the two floats per
+ * row only (the same gradients but for the last bits).  Returns 0 if the
  * params are invalid.
  */
 size_t attn_bwd_workspace_bytes(const attn_params* p);
@@ -151,7 +154,8 @@ size_t attn_blocksparse_bwd_workspace_bytes(const attn_params* p);
  *   Q, K, V, O, dO : in,  [B,H,N,d] (O as written by attn_fwd with the same params)
  *   LSE            : in,  [B,H,N] float32 from attn_fwd
  *   dQ, dK, dV     : out, [B,H,N,d] dtype
- *   workspace      : device scratch, 256-byte aligned, >= attn_bwd_workspace_bytes(p);
+ *   workspace      : device scratch, 256-byte aligned, of attn_bwd_workspace_bytes(p) (at least
+ *                    two floats per row, rows counted in whole blocks of 128 per head);
  *                    contents on entry are ignored and on exit unspecified
  */
 int attn_bwd(const attn_params* p, const void* Q, const void* K, const void* V,
@@ -161,10 +165,10 @@ int attn_bwd(const attn_params* p, const void* Q, const void* K, const void* V,
 /*
  * attn_bwd for callers that can neither allocate device memory nor pass a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments and results as attn_bwd (bit-identical), except that the two row vectors live in a
- * fixed array inside the library, ATTN_STATIC_SCRATCH_BYTES per GPU, held from the first
+ * arguments and results as attn_bwd with a workspace of ATTN_STATIC_SCRATCH_BYTES (bit-identical), a
+ * fixed array inside the library, per GPU, held from the first
  * use on that GPU until the process ends.  The call allocates and frees nothing.  Problems whose
- * attn_bwd_workspace_bytes(p) exceeds ATTN_STATIC_SCRATCH_BYTES (more than 2^20 query rows
+ * two row vectors exceed ATTN_STATIC_SCRATCH_BYTES (more than 2^20 query rows
  * over all heads, counted in whole blocks of 128 per head) return ATTN_ERR_WORKSPACE.  All calls
  * on one GPU share that GPU's array: calls that overlap in time on one GPU (different streams or
  * threads) race and give wrong gradients; calls on one stream, or otherwise ordered, are safe,
@@ -248,7 +252,8 @@ int attn_debug_mfma_rate(int32_t dtype, int32_t iters, int32_t operand_sets, flo
  * *dkv_kernel: 0 = role-split dK/dV kernel, 1 = one-wavefront kernel (d <= 64),
  * 2 = one-wavefront kernel for d = 128 (32 keys per wavefront), 3 = the same with 64 keys
  * per wavefront, 4 = short heads at d <= 64, dQ included (one launch).  (The dQ kernel is the same
- * for every other problem.)
+ * for every other problem.)  The answer is for a workspace of the two row vectors: heads of more than
+ * 256 tokens whose attn_bwd_workspace_bytes holds more than these take 4 with that much.
  */
 int attn_debug_kernel_choice(const attn_params* p, int32_t sparse, int32_t* fwd_kernel, int32_t* dkv_kernel);
 

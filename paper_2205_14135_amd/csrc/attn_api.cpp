@@ -109,7 +109,7 @@ void set_items(attn::KArgs& k, int tiles_per_head) {
 
 // Backward scratch layout: D vector, base-2 row statistic | (block-sparse only) column counts |
 // fp32 dK | fp32 dV.
-struct WsLayout { size_t d_bytes, cnt_bytes, acc_bytes; };
+struct WsLayout { size_t d_bytes, cnt_bytes, acc_bytes, part_bytes; };
 WsLayout ws_layout(const attn_params* p) {
   WsLayout w;
   const size_t T = ((size_t)p->N + attn::kMaskBlock - 1) / attn::kMaskBlock;
@@ -120,6 +120,8 @@ WsLayout ws_layout(const attn_params* p) {
   w.cnt_bytes = align_up(((size_t)p->B * p->H * T * (1 + attn::kMaxSegs) + 64) * sizeof(int), 256);
   const size_t d_kernel = p->d == 16 ? 32 : p->d;   // the fp32 accumulators have the kernels' row length
   w.acc_bytes = align_up((size_t)p->B * p->H * p->N * d_kernel * sizeof(float), 256);
+  // dense, short heads in several key blocks: dQ in fp32 between them, by tiles of 64 rows
+  w.part_bytes = (size_t)p->B * p->H * (((size_t)p->N + 63) / 64 * 64) * d_kernel * sizeof(float);
   return w;
 }
 
@@ -153,14 +155,16 @@ int bwd_common(const attn_params* p, const uint8_t* mask, int64_t mask_sh, bool 
   if (st != ATTN_OK) return st;
   if (!Q || !K || !V || !O || !dO || !LSE || !dQ || !dK || !dV) return ATTN_ERR_NULL;
   if (!aligned16({Q, K, V, O, dO, dQ, dK, dV}) || ((uintptr_t)LSE & 3u) != 0) return ATTN_ERR_SHAPE;
-  const size_t need = sparse ? attn_blocksparse_bwd_workspace_bytes(p) : attn_bwd_workspace_bytes(p);
+  // (without room for dQ between key blocks the two launches take every problem)
+  const WsLayout w = ws_layout(p);
+  const size_t need = sparse ? attn_blocksparse_bwd_workspace_bytes(p) : w.d_bytes;
   if (ws == nullptr || ((uintptr_t)ws & 255u) != 0 || ws_bytes < need) return ATTN_ERR_WORKSPACE;
   c.k.Q = Q; c.k.K = K; c.k.V = V; c.k.O = const_cast<void*>(O); c.k.LSE = const_cast<float*>(LSE);
   c.k.dO = dO; c.k.dQ = dQ; c.k.dK = dK; c.k.dV = dV;
   c.k.Dvec = (float*)ws;
   c.k.L2vec = c.k.Dvec + (size_t)p->B * p->H * c.k.Nr;
+  if (!sparse && ws_bytes >= w.d_bytes + w.part_bytes) c.k.dQpart = (float*)((char*)ws + w.d_bytes);
   if (sparse) {
-    const WsLayout w = ws_layout(p);
     const size_t cols = (size_t)p->B * p->H * (p->N / attn::kMaskBlock);
     c.k.colcnt = (int*)((char*)ws + w.d_bytes);
     c.k.col_segs = c.k.colcnt + cols;
@@ -245,8 +249,9 @@ int attn_fwd(const attn_params* p, const void* Q, const void* K, const void* V, 
 size_t attn_bwd_workspace_bytes(const attn_params* p) {
   Checked c;
   if (check_params(p, &c) != ATTN_OK) return 0;
-  // D_i = rowsum(dO_i o O_i) and the base-2 row statistic: two floats per row
-  return ws_layout(p).d_bytes;
+  // D_i = rowsum(dO_i o O_i) and the base-2 row statistic: two floats per row; a row of dQ in fp32 where the one-launch backward takes several key blocks
+  const WsLayout w = ws_layout(p);
+  return w.d_bytes + (attn::bwd_blocks_is_faster(c.k, c.d, c.causal, c.dropout) ? w.part_bytes : 0);
 }
 
 size_t attn_blocksparse_bwd_workspace_bytes(const attn_params* p) {

@@ -49,6 +49,7 @@ struct KArgs {
   int* group_segs;         // block-sparse bwd scratch: segments of the heavy columns among kPlanCols   [B*H, ceil(T / kPlanCols)]
   float* dKacc;            // block-sparse bwd scratch: fp32 dK / dV of the columns that are
   float* dVacc;            //   split over several workgroups                         [B,H,N,d]
+  float* dQpart;           // one-launch backward of heads of more than 256 tokens: fp32 dQ between the key blocks (nullptr: no room for it)
   int plan_groups;         // block-sparse bwd: planning workgroups at the head of the dQ launch (0: no column can be heavy)
 };
 
@@ -128,7 +129,8 @@ int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool 
 // the same with 64 keys per wavefront and the accumulators in the accumulation registers (attn_bwd_dkv_w64.hip)
 int launch_dkv_w64(const KArgs& a, int dtype, bool causal, hipStream_t s);
 // the whole backward pass of short dense heads at d <= 64, one launch (attn_bwd_short.hip), and which heads take it
-bool bwd_short_is_faster(const KArgs& a, int d, bool causal, bool dropout);
+bool bwd_short_is_faster(const KArgs& a, int d, bool causal, bool dropout);    // up to 256 tokens
+bool bwd_blocks_is_faster(const KArgs& a, int d, bool causal, bool dropout);   // more, given a.dQpart
 int launch_bwd_short(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);
 // dense forward with two wavefront groups in ping-pong (attn_fwd_pp.hip); sets its own work items
 int launch_fwd_pp(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);

@@ -1,0 +1,58 @@
+"""The one-launch backward of heads of 257 to 512 tokens (d <= 64, two key blocks) against the oracle, and against the two launches that a workspace without
+room for its float32 dQ brings back: the same products, summed in another order in dQ."""
+import math
+
+import pytest
+import torch
+
+from tests import helpers as hp
+from paper_2205_14135_amd import binding, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+# lengths at the edges of the key blocks (256, 512), wavefronts (32), tiles (64) and the rule (384)
+@pytest.mark.parametrize("N", [257, 288, 320, 321, 383, 384, 385, 449, 511, 512])
+@pytest.mark.parametrize("d", [16, 32, 64])
+@pytest.mark.parametrize("causal,p", [(False, 0.0), (True, 0.0), (False, 0.1), (True, 0.37)])
+def test_two_key_blocks(N, d, causal, p):
+    B, H = 14, 16   # enough heads that the one launch is taken
+    dtype, tau = ("fp16", "bf16")[N % 2], 1 / math.sqrt(d)
+    t, dev = hp.make_case(B, H, N, d, dtype, inputs.BASE_SEED + 8000 + N + d)
+    q, k, v, do = (dev[n] for n in ("Q", "K", "V", "dO"))
+    opts = dict(causal=causal, seed=inputs.BASE_DROPOUT_SEED + 23, offset=1)
+    rows = 128 * ((N + 127) // 128)
+    small = torch.empty(2 * 4 * B * H * rows, dtype=torch.uint8, device="cuda")
+    one_launch = binding.attn_bwd_workspace_bytes(binding.make_params(q, softmax_scale=tau, dropout_p=p, **opts)) > small.numel()
+    assert one_launch or (d < 64 and N <= 384 and not causal)   # (that is where the two launches stay)
+    if not one_launch:
+        return
+    hp.assert_backward_ok(hp.check_backward(t, dev, dtype, tau, p=p, heads=[(0, 0), (B - 1, H - 1)], **opts))
+    lengths = torch.tensor([max(0, N - 41 * b) for b in range(B)], dtype=torch.int32, device="cuda")
+    for kl in (None, lengths):
+        kw = dict(softmax_scale=tau, dropout_p=p, key_lengths=kl, **opts)
+        size = binding.attn_bwd_workspace_bytes(binding.make_params(q, **kw))
+        assert size >= small.numel() + 4 * B * H * N * max(d, 32)
+        large = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")   # (NaN throughout)
+        o, lse = binding.attn_fwd(q, k, v, **kw)
+        got, again, want = (binding.attn_bwd(q, k, v, o, do, lse, grads=tuple(torch.full_like(q, 7.0) for _ in range(3)), workspace=ws, **kw)
+                            for ws in (large, large, small))
+        for a, a2, b in zip(got, again, want):
+            assert bool(torch.isfinite(a).all()) and torch.equal(a, a2)
+            # float32 sums of the same terms, rounded once: half a unit of the 16-bit type each, where they differ at all
+            assert float((a.float() - b.float()).norm()) <= 2.0 ** -8 * float(b.float().norm())
+
+
+def test_strides_and_float32_output():
+    """Heads interleaved in memory, and O in float32."""
+    B, H, N, d = 14, 16, 330, 64
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, do = (torch.randn(B, N, H, d, generator=gen, device="cuda").bfloat16().transpose(1, 2) for _ in range(4))
+    kw = dict(softmax_scale=0.125, causal=True, o_fp32=True)
+    o, lse = binding.attn_fwd(q, k, v, **kw)
+    assert o.dtype == torch.float32
+    got = binding.attn_bwd(q, k, v, o, do, lse, **kw)
+    packed = [x.contiguous() for x in (q, k, v, o, do)]
+    want = binding.attn_bwd(*packed, lse, **kw)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
