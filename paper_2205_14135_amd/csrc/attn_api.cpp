@@ -251,7 +251,7 @@ size_t attn_bwd_workspace_bytes(const attn_params* p) {
   if (check_params(p, &c) != ATTN_OK) return 0;
   // D_i = rowsum(dO_i o O_i) and the base-2 row statistic: two floats per row; a row of dQ in fp32 where the one-launch backward takes several key blocks
   const WsLayout w = ws_layout(p);
-  return w.d_bytes + (attn::bwd_blocks_is_faster(c.k, c.d, c.causal, c.dropout) ? w.part_bytes : 0);
+  return w.d_bytes + (attn::bwd_blocks_is_faster(c.k, c.d, c.causal) ? w.part_bytes : 0);
 }
 
 size_t attn_blocksparse_bwd_workspace_bytes(const attn_params* p) {

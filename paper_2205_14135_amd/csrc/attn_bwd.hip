@@ -72,25 +72,15 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
       return;
     }
   }
-  constexpr bool BLOCKS = CAUSAL && !SPARSE && D != 64;   // (at d = 128 the loop over a pair costs registers the kernel does not have)
-  const int item = BLOCKS ? causal_item(a) : xcd_item(a.n_items, a.chunk, SPARSE ? (int)blockIdx.x - a.plan_groups : (int)blockIdx.x);
+  constexpr bool DEALT = CAUSAL && !SPARSE;   // see causal_block
+  const int item = DEALT ? causal_item(a) : xcd_item(a.n_items, a.chunk, SPARSE ? (int)blockIdx.x - a.plan_groups : (int)blockIdx.x);
   if (item < 0) return;
   const int n_qt = a.T * (4 / RW);   // blocks of BR rows, to the end of the last 128-row block: the scratch vectors are written whole
-  // Work item = (head, row block).  Under the causal mask row block q sweeps 2 (q + 1) key tiles;
-  // for dense d = 64 problems an item is the pair (n_qt - 1 - q, q), one per pass, so that every
-  // workgroup does the same amount of work (at d = 128 the loop costs registers the kernel does
-  // not have).
-  constexpr bool PAIRED = CAUSAL && !SPARSE && D == 64;
-  const int n_per_head = PAIRED ? (n_qt + 1) / 2 : n_qt;
-  int bh = item / n_per_head;
-  int q_item = item % n_per_head;
-  if constexpr (CAUSAL && !PAIRED) causal_block(a, item, n_qt, bh, q_item);
-  if (!SPARSE && !(BLOCKS && a.group == 0)) bh = dealt_head(a, bh);
-  const int n_pass = PAIRED && q_item != n_qt - 1 - q_item ? 2 : 1;
-#pragma clang loop unroll(disable)
-  for (int pass = 0; pass < n_pass; ++pass) {
-  if (pass) __syncthreads();   // the tile buffers staged the first block's output rows
-  const int qt = PAIRED ? (pass ? q_item : n_qt - 1 - q_item) : (CAUSAL ? n_qt - 1 - q_item : q_item);
+  // Work item = (head, row block); under the causal mask row block q sweeps 2 (q + 1) key tiles, and the late blocks come first
+  int bh = item / n_qt, q_item = item % n_qt;
+  if constexpr (CAUSAL) causal_block(a, item, n_qt, bh, q_item);
+  if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
+  const int qt = CAUSAL ? n_qt - 1 - q_item : q_item;
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Kg = (const T*)a.K + head_off;
@@ -321,19 +311,18 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
           }
     }
     __syncthreads();   // the buffers stage the output rows
-    if (group > 0) continue;
+    if (group > 0) return;
   }
   // the loop ends on a barrier (or never touched LDS): the tile buffers stage the output rows
   T* stage = (wave < 2 ? Ks0 + wave * 32 * D : Vs0 + (wave - 2) * 32 * D);
   store_rows_coalesced<T, D>(stage, (T*)a.dQ + head_off + (int64_t)q0 * a.sn, a.sn, dq, a.tau, a.N - q0,
                              D == 32 ? a.dvalid : D);
-  }  // for pass
 }
 
 template <typename T, int D, int RW, int KG>
 int launch_dq(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
   const int blocks = a.T * (4 / RW);
-  a.n_items = a.B * a.H * (causal && !sparse && D == 64 ? (blocks + 1) / 2 : blocks);   // (pairs of row blocks)
+  a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
   a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
   if (sparse) a.plan_groups = sparse_plan_groups(a);
@@ -363,7 +352,7 @@ template <> constexpr int kDtype<__bf16> = 1;
 //   d = 64   1 x 128 12.3 +1.2 -0.3 +1.3; 16 x 197 17.7 +0.6 -1.3 +0.1; 4 x 512 25.0 -0.3 -2.8 -1.9; 16 x 1024 41.0 -2.0 -5.2 -5.1; 8 x 2048 72.2 -5.3 -10.2 -11.6;
 //            1 x 8192 263 -28 -48 -61; 60 x 512 26.5 -0.1 +0.5 +6.2; 24 x 1024 42.0 -2.0 -1.2 +4.5; 8 x 4096 140 -8.7 -5.5 -0.8;
 //            10 x 4096 186 +10.1 -1.3 +2.6, dropout 271 +9.5 -15.9 -7.3; 24 x 2001 110 +6.1 -2.1 +4.9; 40 x 1024 57.1 +5.8 +0.9 +8.1; 32 x 2048 116 +3.6 +4.8 +16.8
-//   d = 64 causal (pairs of row blocks)  1 x 128 13.1 +1.0 +2.8 +6.2; 16 x 197 26.9 +1.0 -1.9 +1.2; 16 x 1024 51.6 -0.6 -5.9 -4.4;
+//   d = 64 causal (measured with pairs of row blocks)  1 x 128 13.1 +1.0 +2.8 +6.2; 16 x 197 26.9 +1.0 -1.9 +1.2; 16 x 1024 51.6 -0.6 -5.9 -4.4;
 //            8 x 4096 146 -8.2 -20.5 -24.4; 40 x 1024 53.2 -0.5 -1.3 +11.4; 10 x 4096 148 -8.8 -8.8 +5.8; 32 x 2048 85.8 -2.6 -2.3 +9.6; 128 x 512 39.5 +0.8 -0.4 +12.2
 //   d = 32   1 x 128 10.0 -0.4 -0.4 +0.1; 16 x 640 22.6 -1.0 -2.6 -2.6; 8 x 2048 56.2 -3.8 -8.0 -10.0; 60 x 512 20.1 -0.7 -0.7 +2.1; 8 x 4096 107 -8.3 -8.1 -4.9;
 //            10 x 4096 138 +8.1 -12.7 -2.7; 24 x 2001 81.7 +5.3 -5.1 +1.9; 64 x 1024 43.1 +3.1 +0.9 +8.8
@@ -374,15 +363,19 @@ template <> constexpr int kDtype<__bf16> = 1;
 //            8 x 64 112 +5.8 +6.2 +24.1; d = 128  4 x 32 89.9 -0.3 -4.4; 4 x 64 132 +0.3 +17.4
 WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
   if (!divide) return {4, 1};
-  const bool pairs = causal && !sparse && d == 64;
-  const WorkItems w(a, sparse, pairs);
+  const bool halves = causal && !sparse && d == 64;
+  const WorkItems w(a, sparse, halves);
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return d <= 64 && w.tiles >= (d == 64 ? 24 : 12) && !sparse ? WaveGroups{2, 4} : WaveGroups{2, 2};
-  if (d == 32) return w.of64 <= 3 * kComputeUnits && w.tiles >= 4 ? WaveGroups{2, 2} : WaveGroups{4, 1};   // (three workgroups fit)
+  // (causal, now | {2, 2}: d = 64 24 x 1500 49.0 47.0, 20 x 2048 62.9 60.6, 10 x 4096 110 106, 40 x 1024 40.5 40.9, 32 x 2048 79.7 83.8; d = 32 32 x 2048 58.5 54.7, 60 x 1000 with dropout
+  // 50.8 48.8, 128 x 700 33.7 35.9; 8 x 4096 {2, 2} 64.8, {2, 4} 58.7, 10 x 4096 69.7, 74.9)
+  if (halves && w.of64 <= 5 * kComputeUnits / 4 && w.tiles >= 24) return {2, 2};
+  if (d == 32 && causal && !sparse && w.of64 <= 2 * kComputeUnits && w.tiles >= 32) return {2, 4};
+  if (d == 32) return w.of64 <= (causal && !sparse ? 4 : 3) * kComputeUnits && w.tiles >= 4 ? WaveGroups{2, 2} : WaveGroups{4, 1};   // (three workgroups fit)
   if (w.of128 <= kComputeUnits && w.tiles >= (d == 64 ? 16 : 24)) return {4, 2};
   // (causal, two blocks in turn on a compute unit, heaviest first; {4, 1} | {4, 2}, us: 8 x 8192 511 | 485, 10 x 4096 226 | 214, 20 x 2000 with dropout 151 | 140;
   // 30 x 2048 151 | 152, 48 x 900 67.6 | 73.2)
   if (d == 128 && causal && !sparse && w.of128 <= (w.tiles >= 64 ? 2 : 3 / 2.) * kComputeUnits && w.tiles >= 24) return {4, 2};
-  if (d == 64 && !pairs && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
+  if (d == 64 && !halves && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
   return {4, 1};
 }
 

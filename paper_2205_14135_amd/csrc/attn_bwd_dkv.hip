@@ -363,7 +363,7 @@ int launch_td(KArgs a, bool causal, bool dropout, bool sparse, int list_groups, 
 int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse, const Overrides& v) {
   const bool role_split = v.dkv == 1;   // at every head dimension it has (comparisons and tests)
   // short heads: one workgroup has all of a head's keys, and both launches become one
-  if (!sparse && v.dkv == 0 && (bwd_short_is_faster(a, d, causal, dropout) || (a.dQpart != nullptr && bwd_blocks_is_faster(a, d, causal, dropout)))) return kBwdShort;
+  if (!sparse && v.dkv == 0 && (bwd_short_is_faster(a, d, causal, dropout) || (a.dQpart != nullptr && bwd_blocks_is_faster(a, d, causal)))) return kBwdShort;
   // Problems with d <= 64 take the kernel in which one wavefront does all four products
   // (attn_bwd_dkv_fr.hip).
   // (head dimension 16 exists in that kernel only)

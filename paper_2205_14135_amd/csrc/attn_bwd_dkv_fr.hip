@@ -64,9 +64,8 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
 
   constexpr int BR = 32 * RW;
   const int n_kt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last key block may be ragged
-  // Work assignment.  Dense: one key block per workgroup; under the causal mask key block k is
-  // visited by N/64 - 2k query tiles, so a workgroup takes the pair (k, n_kt - 1 - k), one per
-  // round.  Block-sparse (as in attn_bwd_dkv.hip): the first 8 * chunk workgroups take one mask
+  // Work assignment.  Dense: one key block per workgroup (under the causal mask key block k is
+  // visited by N/64 - 2k query tiles, and the early ones come first: causal_block).  Block-sparse (as in attn_bwd_dkv.hip): the first 8 * chunk workgroups take one mask
   // column each and leave the heavy ones alone; those are cut into segments (attn_sparse.h),
   // which the remaining workgroups walk.
   const int n_col_groups = kXcds * a.chunk;
@@ -74,28 +73,23 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
   // long segments start with the launch instead of queueing behind every column)
   const int n_list = SPARSE ? (int)gridDim.x - n_col_groups : 0;
   const bool list_mode = SPARSE && (int)blockIdx.x < n_list;
-  constexpr bool PAIRED = CAUSAL && !SPARSE;
-  const int n_pair = (n_kt + 1) / 2;
+  constexpr bool DEALT = CAUSAL && !SPARSE;
   for (int round = 0;; ++round) {
   int item, slot = 0, skip_blocks = 0, take_blocks = 0x7fffffff;
-  bool heavy = false, last_round = true;
+  bool heavy = false;
   if (!list_mode) {
-    item = xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
+    item = DEALT ? causal_item(a) : xcd_item(a.n_items, a.chunk, (int)blockIdx.x - n_list);
     if (item < 0) return;
     if constexpr (SPARSE) {
       if (n_list > 0 && a.col_segs[item] > 0) return;   // heavy
-    }
-    if constexpr (PAIRED) {
-      const int q = item % n_pair;
-      last_round = round == 1 || q == n_kt - 1 - q;
-      item = (item / n_pair) * n_kt + (round == 0 ? q : n_kt - 1 - q);
     }
   } else {
     if (!sparse_segment((int)blockIdx.x + round * n_list, item, slot, skip_blocks, take_blocks)) return;
     heavy = true;
   }
-  const int bh = SPARSE ? item / n_kt : dealt_head(a, item / n_kt);
-  const int kt = item % n_kt;
+  int bh = item / n_kt, kt = item % n_kt;
+  if constexpr (DEALT) causal_block(a, item, n_kt, bh, kt);
+  if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;
@@ -371,7 +365,7 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
     // the loop ends on a barrier (or never touched LDS): the tile buffers stage the output rows
     T* stage_v = Qs0 + wave * 32 * D;   // 4 wavefronts x 32 rows = the two Q buffers
     T* stage_k = Gs0 + wave * 32 * D;
-    const int out_lane = SPARSE || PAIRED ? lane_id_here() : lane;
+    const int out_lane = SPARSE ? lane_id_here() : lane;
     store_rows_coalesced<T, D>(stage_v, (T*)a.dV + head_off + (int64_t)kw0 * a.sn, a.sn, dv,
                                DROPOUT ? a.keep_scale : 1.f, a.N - kw0, D == 32 ? a.dvalid : D, out_lane);
     store_rows_coalesced<T, D>(stage_k, (T*)a.dK + head_off + (int64_t)kw0 * a.sn, a.sn, dk, a.tau, a.N - kw0,
@@ -379,16 +373,17 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
   }
   if constexpr (SPARSE)
     if (heavy) sparse_finish<T, D>(item);
-  if (!list_mode && last_round) return;
-  __syncthreads();   // LDS is reused by the next key block
+  if (!list_mode) return;
+  __syncthreads();   // LDS is reused by the next segment
   }  // for round
 }
 
 template <typename T, int D, int RW, int KG>
 int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_groups, hipStream_t s) {
   const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
-  a.n_items = a.B * a.H * (causal && !sparse ? (blocks + 1) / 2 : blocks);   // (pairs of key blocks)
+  a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
+  a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));   // Q and dO
   const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(64 * RW * KG);
 #define ATTN_DKV_FR_CASE(C, P, S)                                                           \
   if constexpr (!S || RW == 4)                                                              \
@@ -413,7 +408,7 @@ int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_gro
 //   d = 64   1 x 128 12.3 +1.0 -0.3 +1.4; 16 x 197 17.7 -0.4 -2.1 -0.9; 4 x 512 25.0 -1.3 -3.8 -3.4; 16 x 1024 41.0 -4.2 -7.5 -8.1; 8 x 2048 72.2 -10.2 -15.6 -18.5;
 //            1 x 8192 263 -47 -68 -89; 60 x 300 20.6 -0.2 +0.1 +7.0; 24 x 1024 42.0 -4.2 -3.2 +3.2; 8 x 4096 140 -16.6 -10.8 -5.6;
 //            10 x 4096 186 +9.3 -4.4 -0.2, dropout 271 +14.7 -19.0 -9.5; 24 x 2001 110 +2.6 -4.2 +3.1; 40 x 1024 57.1 +5.4 +0.4 +8.2; 32 x 2048 116 +2.3 +6.0 +19.2
-//   d = 64 causal (pairs of key blocks)  1 x 128 13.1 +0.8 +2.9 +6.6; 16 x 197 26.9 -0.1 -2.9 +0.3; 16 x 1024 51.6 -3.6 -9.4 -7.8;
+//   d = 64 causal (measured with pairs of key blocks)  1 x 128 13.1 +0.8 +2.9 +6.6; 16 x 197 26.9 -0.1 -2.9 +0.3; 16 x 1024 51.6 -3.6 -9.4 -7.8;
 //            8 x 4096 146 -20 -34 -39; 40 x 1024 53.2 -3.7 -3.3 +10.4; 32 x 2048 85.8 -6.3 -4.5 +7.4; 128 x 512 39.5 -0.7 -1.5 +12.2
 //   d = 32   1 x 128 10.0 -0.3 -0.4 -0.1; 16 x 640 22.6 -2.2 -3.7 -4.5; 8 x 2048 56.2 -8.9 -12.2 -16.4; 60 x 512 20.1 -1.6 -1.5 +1.6;
 //            8 x 4096 107 -18.5 -16.4 -11.7; 10 x 4096 138 +6.0 -5.7 -4.1; 64 x 1024 43.1 +2.9 +3.1 +10.6
@@ -422,13 +417,15 @@ int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_gro
 //            causal 68.4 -3.8; 4 x 64 75.5 +9.2 (the workgroups of the segment list take whole compute units then)
 WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
   if (!divide) return {4, 1};
-  const bool pairs = causal && !sparse;
-  const WorkItems w(a, sparse, pairs);
+  const bool halves = causal && !sparse;
+  const WorkItems w(a, sparse, halves);
   if (sparse) return w.of128 <= kComputeUnits / 2 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return w.tiles >= (d == 64 ? 24 : 12) ? WaveGroups{2, 4} : WaveGroups{2, 2};
+  // (causal, {4, 2} | {2, 2}: 24 x 1500 48.7 45.3, 20 x 2048 63.0 59.6, 10 x 4096 110 103; 40 x 1024 40.0 40.2, 32 x 2048 80.3 82.8)
+  if (d == 64 && halves && w.of64 <= 5 * kComputeUnits / 4 && w.tiles >= 24) return {2, 2};
   if (d == 64 && w.of128 <= kComputeUnits && w.tiles >= 4) return {4, 2};
   if (d == 32 && w.of64 <= 2 * kComputeUnits && w.tiles >= 4) return {2, 2};
-  if (!pairs && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
+  if (!halves && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
   return {4, 1};
 }
 

@@ -681,24 +681,19 @@ bool bwd_short_is_faster(const KArgs& a, int d, bool causal, bool dropout) {
   return causal || heads > kComputeUnits / 2 || (heads > kComputeUnits / 4 && d == 64 && a.N <= 208 && !dropout);
 }
 
-// Which heads of more than 256 tokens do: time of this kernel over that of the two launches, by heads; N = 257 to 384, then 385 to 512 (448 and 512 measured).
-//   d = 64  128 1.28-1.36, 1.4; 160 1.27-1.31, 0.99 1.04; 192 0.91-0.93, 0.99 1.03; 256 0.92-0.94, 0.86 0.89; 257 1.48, 1.3; 512 1.06, 0.97 1.02; 1024 1.2, 1.0
+// Which heads of more than 256 tokens do: time of this kernel over that of the two launches, by heads; N = 257 to 384, then 385 to 512.
+//   d = 64  128 1.28-1.36, 1.4; 160 1.27-1.31, 0.99 1.04; 192 0.91-0.93, 0.99 1.03; 224 0.92-0.94, 0.86 0.89; 256 0.92-0.94, 0.86 0.89; 257 1.48, 1.3; 512 1.06, 0.97 1.02; 1024 1.2, 1.0
 //   d = 64, dropout  160 1.3, 1.06; 192 0.94-0.95, 1.05 1.08; 224 0.95-0.98, 0.89 0.92; 256 0.95-0.97, 0.89 0.91; 257 1.5, 1.4; 512 1.1, 1.0
-//   d = 64, causal  64 1.04-1.22, 1.4; 96 0.90-0.96, 1.07 1.19; 160 0.75-0.77, 0.88 0.93; 256 0.78, 0.9; 257 0.92-0.96, 1.06 1.13; 384 0.89-0.91, 1.03 1.12; 512 0.80, 0.95 1.04; 640
-//           0.88-0.94, 1.06 1.12; 1024 0.88-0.93, 0.98 1.00;  dropout  96 0.86-0.95; 160 0.70, 0.83 0.86; 256 0.73, 0.85 0.90; 257 0.88-0.90, 1.03 1.09; 512 0.74; 1024 0.81-0.86
+//   d = 64, causal, with and without dropout  96 1.2, 1.2-1.4; 128 1.07-1.12, 1.13-1.21; 160 1.03-1.10, 0.96-1.10; 192 0.87-0.91, 0.89-1.00; 224 0.80-0.87, 0.84-0.92; 256 0.80-0.84,
+//           0.85-0.88; 257 1.22-1.30, 1.3; 512 0.92-1.02, 0.92-1.01; 1024 1.02-1.09, 0.95-1.00
 //   d = 32  192 0.98-1.10, 1.14 1.24; 224 1.0-1.1, 0.88 0.98; 256 1.03-1.09, 0.89 0.98; 257 1.5;  dropout 256 0.95-1.02, 0.90 0.97
-//   d = 32, causal  128 0.93-1.10, 1.03 1.20; 160 0.82-0.97, 0.84-0.90; 256 0.70-0.78, 0.82-0.85; 257 0.92-1.00, 1.12-1.19; 512 0.80-0.86, 0.88-0.95; 1024 0.86-0.91, 0.94-1.07
-// A compute unit holds one workgroup, a head: without the causal mask one round that is nearly full pays, where the two launches' blocks begin another one
-// (three or four blocks of 128 rows a head, two workgroups per compute unit).  The causal mask leaves this kernel three quarters of the tiles
-// of two blocks up to 384 tokens and the two launches' pairs a block alone.
-bool bwd_blocks_is_faster(const KArgs& a, int d, bool causal, bool dropout) {
-  (void)dropout;   // (the same lines)
+//   d = 32, causal  160 0.87-1.05, 1.04-1.18; 192 0.88-1.00, 0.95-1.04; 224 0.85-0.92, 0.79-0.91; 256 0.81-0.93, 0.82-0.93; 257 1.15-1.37, 1.3-1.5; 512 0.97-1.02, 0.91-1.00
+// A compute unit holds one workgroup, a head: one round that is nearly full pays.
+bool bwd_blocks_is_faster(const KArgs& a, int d, bool causal) {
   if (d > 64 || a.N <= 256 || a.N > 512) return false;
   const int64_t heads = (int64_t)a.B * a.H;
-  const bool three_blocks = a.N <= 384;
-  if (causal) return three_blocks ? heads >= (d == 64 ? 96 : 160) : heads >= 160 && heads <= kComputeUnits;
   if (heads > kComputeUnits) return false;
-  return d == 64 && three_blocks ? heads >= 192 : !three_blocks && heads >= 224;
+  return a.N > 384 ? heads >= 224 : heads >= 192 && (d == 64 || causal);
 }
 
 int launch_bwd_short(const KArgs& a_in, int dtype, int d, bool causal, bool dropout, hipStream_t s) {

@@ -88,15 +88,15 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse, co
 // A dK/dV override (comparisons and tests) keeps every kernel at {4, 1}.
 struct WaveGroups { int waves, groups; };
 inline bool may_divide(const Overrides& v) { return v.dkv == 0; }
-// The problem as these choices see it: work items with 64 and with 128 rows (pairs of row blocks where the kernel takes pairs),
+// The problem as these choices see it: work items with 64 and with 128 rows (halves: two blocks under a causal mask count as one, they see half the tiles),
 // 64-wide tiles that a row sweeps (block-sparse: a guess, the masks are on the GPU; a row of the butterfly mask keeps 5 to 10 blocks).
 struct WorkItems {
   int64_t of64, of128;
   int tiles;
-  WorkItems(const KArgs& a, bool sparse, bool pairs) {
+  WorkItems(const KArgs& a, bool sparse, bool halves) {
     const int64_t heads = (int64_t)a.B * a.H, blocks64 = ((int64_t)a.N + 63) / 64, blocks128 = a.T;
-    of64 = heads * (pairs ? (blocks64 + 1) / 2 : blocks64);
-    of128 = heads * (pairs ? (blocks128 + 1) / 2 : blocks128);
+    of64 = heads * (halves ? (blocks64 + 1) / 2 : blocks64);
+    of128 = heads * (halves ? (blocks128 + 1) / 2 : blocks128);
     tiles = sparse ? 16 : (int)blocks64;
   }
 };
@@ -130,7 +130,7 @@ int launch_dkv_fr128(const KArgs& a, int dtype, bool causal, bool dropout, bool 
 int launch_dkv_w64(const KArgs& a, int dtype, bool causal, hipStream_t s);
 // the whole backward pass of short dense heads at d <= 64, one launch (attn_bwd_short.hip), and which heads take it
 bool bwd_short_is_faster(const KArgs& a, int d, bool causal, bool dropout);    // up to 256 tokens
-bool bwd_blocks_is_faster(const KArgs& a, int d, bool causal, bool dropout);   // more, given a.dQpart
+bool bwd_blocks_is_faster(const KArgs& a, int d, bool causal);   // more, given a.dQpart
 int launch_bwd_short(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);
 // dense forward with two wavefront groups in ping-pong (attn_fwd_pp.hip); sets its own work items
 int launch_fwd_pp(const KArgs& a, int dtype, int d, bool causal, bool dropout, hipStream_t s);
@@ -558,10 +558,13 @@ __device__ __forceinline__ int dealt_head(const KArgs& a, int pos) {
 #endif
   return head;
 }
-// The causal kernels that take one block of rows (or keys) per work item (d = 32 and 128; at d = 64 pairs of blocks): this workgroup's item
+// The dense causal kernels of one block of rows (or keys) per work item: this workgroup's item
 // (-1: none), and the item's head and block, counted from the head's heaviest, level 0.  The blocks of all heads (a.group == 0) or of a.group consecutive heads
 // (each XCD a run of items) are dealt out together, heaviest first, so that a compute unit gets blocks of different weights at the start and light ones
-// last.  All heads: see causal_group.  (The order of the heads: see dealt_head.)
+// last.  All heads: see causal_group.  (The order of the heads: see dealt_head.)  At d <= 64 an item was a pair of a light and a heavy block before: half as many
+// workgroups, a loop over the two that cost registers, and an odd block that counted as a pair.  us, pairs | blocks: d = 64, forward 16 x 16384 611 | 579, 128 x 1024 with dropout
+// 40.8 | 34.5, 128 x 2048 98 | 91, 100 x 700 with dropout 31.3 | 22.2, 16 x 700 12.1 | 9.1; backward 16 x 16384 1840 | 1740, 128 x 1024 94 | 95, with dropout 111 | 109, 100 x 700 with dropout 79.5 |
+// 59.7, 40 x 1024 48.6 | 40.3, 16 x 700 30.9 | 22.9; d = 32, backward 128 x 700 40.7 | 33.9.
 __device__ __forceinline__ int causal_item(const KArgs& a) {
   if (a.group > 0) return xcd_item(a.n_items, a.chunk);
   return (int)blockIdx.x < a.n_items ? (int)blockIdx.x : -1;

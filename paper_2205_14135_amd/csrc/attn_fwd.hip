@@ -62,23 +62,15 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
   }
 
   args_at_once(a);
-  constexpr bool BLOCKS = CAUSAL && !SPARSE && D != 64;   // one block of rows per item
-  const int item = BLOCKS ? causal_item(a) : xcd_item(a.n_items, a.chunk);
+  constexpr bool DEALT = CAUSAL && !SPARSE;   // see causal_block
+  const int item = DEALT ? causal_item(a) : xcd_item(a.n_items, a.chunk);
   if (item < 0) return;
   const int n_qt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last block may be ragged
-  // Work item = (head, row block), heavy (late) blocks first under a causal mask.  For dense
-  // causal d = 64 problems an item is the pair (n_qt - 1 - q, q), one block per pass, so that
-  // every workgroup does the same amount of work.
-  constexpr bool PAIRED = CAUSAL && !SPARSE && D == 64;
-  const int n_per_head = PAIRED ? (n_qt + 1) / 2 : n_qt;
-  int bh = item / n_per_head, q_item = item % n_per_head;
-  if constexpr (BLOCKS) causal_block(a, item, n_qt, bh, q_item);
-  if (!SPARSE && !(BLOCKS && a.group == 0)) bh = dealt_head(a, bh);
-  const int n_pass = PAIRED && q_item != n_qt - 1 - q_item ? 2 : 1;
-#pragma clang loop unroll(disable)
-  for (int pass = 0; pass < n_pass; ++pass) {
-  if (pass) __syncthreads();   // the tile buffers staged the first block's output rows
-  const int qt = PAIRED ? (pass ? q_item : n_qt - 1 - q_item) : (CAUSAL ? n_qt - 1 - q_item : q_item);
+  // Work item = (head, row block); under a causal mask the late blocks, which see most keys, first
+  int bh = item / n_qt, q_item = item % n_qt;
+  if constexpr (DEALT) causal_block(a, item, n_qt, bh, q_item);
+  if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
+  const int qt = CAUSAL ? n_qt - 1 - q_item : q_item;
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;
@@ -250,7 +242,7 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
       s_part[2 * kLanes] = lr_run[0];
     }
     __syncthreads();
-    if (group > 0) continue;
+    if (group > 0) return;
 #pragma unroll
     for (int k = 1; k < KG; ++k) {
       const float* const sp = s_part + k * 3 * kLanes;
@@ -301,13 +293,12 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
     store_rows_coalesced<T, D>(stage, (T*)a.O + head_off + (int64_t)q0 * a.sn, a.sn, o, inv, a.N - q0,
                                D == 32 ? a.dvalid : D);
   }
-  }  // for pass
 }
 
 template <typename T, int D, int RW, int KG>
 int launch_fwd_groups(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
   const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
-  a.n_items = a.B * a.H * (causal && !sparse && D == 64 ? (blocks + 1) / 2 : blocks);   // (pairs of row blocks)
+  a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
   a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
   const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
@@ -375,7 +366,7 @@ __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
 //            8 x 4096 52.4 43.0 54.4 51.2; 60 x 512 9.9 9.6 10.7 14.7; 20 x 2048 38.5 44.2 44.9 43.9; 128 x 512 14.1 17.1 19.6 27.6
 //   two tiles, {4, 1} | {2, 2}  d = 64 1 x 128 4.5 4.3, 16 x 100 5.0 4.7, 128 x 128 5.1 4.9, dropout 6.0 5.6; causal 1 x 128 5.1 7.5; d = 32 1 x 128 3.9 3.7,
 //            16 x 100 4.6 4.1, 128 x 65 with dropout 5.6 4.7, causal 128 x 128 4.8 4.3; one tile d = 64 16 x 64 4.1 4.6; d = 32 16 x 64 3.7 3.9
-//   d = 64 causal (pairs of row blocks)  64 x 129 9.3 - 8.4; 64 x 192 9.4 - 8.8, dropout 11.7 - 10.0; 60 x 400 14.1 13.7 11.1 12.3; 16 x 1024 20.3 18.3 16.8 15.2; 8 x 4096 57.1 45.4 43.4 31.8;
+//   d = 64 causal (measured with pairs of row blocks)  64 x 129 9.3 - 8.4; 64 x 192 9.4 - 8.8, dropout 11.7 - 10.0; 60 x 400 14.1 13.7 11.1 12.3; 16 x 1024 20.3 18.3 16.8 15.2; 8 x 4096 57.1 45.4 43.4 31.8;
 //            20 x 2048 32.7 27.7 33.2 38.8; 10 x 4096 57.3 45.6 56.7 59.0; 64 x 1024 21.1 19.2 - 28.7; 48 x 1400 33.0 41.7 - 47.0
 //   d = 32   4 x 117 4.7 5.0 5.1 5.0; 16 x 640 9.7 8.9 7.1 7.1; 16 x 1024 13.5 11.6 10.3 8.4; 60 x 512 8.5 7.9 8.6 8.5; 8 x 4096 45.1 35.5 39.8 32.8;
 //            10 x 4096 60.7 55.3 52.9 47.6; 32 x 2048 32.9 31.3 38.5 35.1, causal 34.0 30.0 29.2 26.9; 128 x 512 11.1 11.4 13.9 14.7
@@ -388,11 +379,15 @@ WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divi
   if (!divide) return {4, 1};
   const WorkItems w(a, sparse, causal && !sparse && d == 64);
   // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise)
-  const int64_t fit24 = d == 64 ? kComputeUnits : (causal && w.tiles >= 24 ? 4 * kComputeUnits : 5 * kComputeUnits / 2);
+  const int64_t fit24 = d == 64 ? kComputeUnits : !causal || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
   if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
   // (two tiles would gain 0.2 to 0.8 us, less than the host spends on a call, but not in pairs; a head of up to 128 tokens keeps one form instead, and with it
   // the same last bits in whatever batch it stands)
-  if (w.of64 <= kComputeUnits && w.tiles >= (d == 128 ? 6 : 3)) return {2, 2};
+  // (causal blocks are dealt out heaviest first: two more rounds of light ones do no harm.  {2, 2} against {4, 2} or {4, 1}: d = 64 24 x 1500 16.2 18.7, 20 x 2048 20.4 23.6,
+  // 10 x 4096 36.0 41.6, 60 x 700 13.4 13.8, 12 x 5000 60.1 56.4, 32 x 2048 30.9 28.5; d = 32 40 x 1024 10.2 11.8, 60 x 700 8.6 9.8, 32 x 2048 20.7 22.2, 60 x 1000 with
+  // dropout 18.0 19.8, 128 x 700 13.0 12.9; {2, 4} there 12.0, 11.1, 23.0, 20.1, 18.6, and 10 x 4096 27.4 29.9)
+  const int64_t fit22 = !causal || sparse || d == 128 ? kComputeUnits : d == 64 ? 11 * kComputeUnits / 8 : 9 * kComputeUnits / 2;
+  if (w.of64 <= fit22 && w.tiles >= (d == 128 ? 6 : 3)) return {2, 2};
   if (d <= 64) return w.of128 <= (d == 32 ? 2 : 1) * kComputeUnits && w.tiles >= 10 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   // d = 128: {4, 2} has one workgroup on a compute unit, {4, 1} two, which together get through a tile hardly faster than one
   // of them alone.  Estimates in us: the tiles of all items over the compute units, and under the causal mask the longest sweep.

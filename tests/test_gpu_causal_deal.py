@@ -1,4 +1,4 @@
-"""Causal kernels with one block of rows per work item (d = 32 and 128): whichever heads are dealt out together and in whatever order, each block of
+"""Dense causal kernels, one block of rows or keys per work item: whichever heads are dealt out together and in whatever order, each block of
 each head is worked on once.  A head's results do not depend on that order: with nothing divided over groups of wavefronts they are, bit for bit, those
 of the head alone."""
 import math
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 # blocks of 128 rows: all heads together (few items; heads that divide over the XCDs, or not; a head alone in its last group of eight), and runs of
 # grouped heads (128 heads or a multiple, 224 or more; the last group short), each with a ragged last block
-@pytest.mark.parametrize("heads,N,d", [(1, 300, 128), (9, 700, 128), (16, 1000, 128), (130, 600, 128), (128, 600, 128), (229, 390, 128), (256, 300, 128),
+@pytest.mark.parametrize("heads,N,d", [(1, 700, 64), (12, 1000, 64), (130, 600, 64), (1, 300, 128), (9, 700, 128), (16, 1000, 128), (130, 600, 128), (128, 600, 128), (229, 390, 128), (256, 300, 128),
                                        (13, 900, 32), (136, 500, 32)])
 def test_every_block_of_every_head_once(heads, N, d):
     from paper_2205_14135_amd import binding
