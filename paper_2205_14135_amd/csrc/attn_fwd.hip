@@ -71,6 +71,10 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
   if constexpr (DEALT) causal_block(a, item, n_qt, bh, q_item);
   if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
   const int qt = CAUSAL ? n_qt - 1 - q_item : q_item;
+  // (one pass of a loop: the form in which the compiler lays the code out with no jump between the last tile and the epilogue; one head of 128
+  // tokens 4.51 -> 4.44 us)
+#pragma clang loop unroll(disable)
+  for (int pass = 0; pass < 1; ++pass) {
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;
@@ -292,6 +296,7 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
     T* stage = KG > 1 ? &Vs[2 * KG - 2][0] + wave * 32 * D : (wave < 2 ? &Ks[0][0] + wave * 32 * D : &Vs[0][0] + (wave - 2) * 32 * D);
     store_rows_coalesced<T, D>(stage, (T*)a.O + head_off + (int64_t)q0 * a.sn, a.sn, o, inv, a.N - q0,
                                D == 32 ? a.dvalid : D);
+  }
   }
 }
 
