@@ -611,6 +611,10 @@ __global__ __launch_bounds__(512, 2) void bwd_blocks_kernel(const KArgs a) {
     store_rows_coalesced<T, D>(stage, (T*)a.dK + out_row0, a.sn, dk, a.tau, a.N - kw0, dvalid);
     if (!last_block) {
       __syncthreads();   // everyone's rows are out of the tile buffers
+      if (D == 32 && a.dvalid < D) {   // those rows lie across the columns >= 16 that the copies leave untouched
+        zero_tiles(Q0, 4 * kQ);
+        __syncthreads();
+      }
       const int next = CAUSAL ? (k0 + KEYS) / TILE : 0;
       if (next < n_tiles) fetch_tile(next, Q0);
     }
