@@ -384,7 +384,7 @@ WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divi
   if (!divide) return {4, 1};
   const WorkItems w(a, sparse, causal && !sparse && d == 64);
   // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise)
-  const int64_t fit24 = d == 64 ? kComputeUnits : !causal || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
+  const int64_t fit24 = d == 64 ? kComputeUnits : !causal || sparse || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
   if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
   // (two tiles would gain 0.2 to 0.8 us, less than the host spends on a call, but not in pairs; a head of up to 128 tokens keeps one form instead, and with it
   // the same last bits in whatever batch it stands)

@@ -18,6 +18,10 @@ extern "C" int fwd_form(int heads, int N, int d, int causal) {   // wavefronts o
   const attn::WaveGroups w = attn::fwd_groups(problem(heads, N, d), d, causal, false, true);
   return 10 * w.waves + w.groups;
 }
+extern "C" int sparse_fwd_form(int heads, int N, int d, int causal) {
+  const attn::WaveGroups w = attn::fwd_groups(problem(heads, N, d), d, causal, true, true);
+  return 10 * w.waves + w.groups;
+}
 extern "C" int short_heads() { return attn::kBwdShort; }
 extern "C" int role_split() { return attn::kDkvRoleSplit; }
 extern "C" int one_wave128() { return attn::kDkvOneWave128; }
@@ -60,3 +64,11 @@ def test_short_heads_of_four_tiles(shim, heads, N, d, causal, dropout, expect):
                                                    (86, 192, 64, 0, 41), (1, 128, 32, 1, 41), (1, 129, 32, 1, 22), (1, 320, 128, 0, 41), (1, 321, 128, 0, 22)])
 def test_forward_of_few_tiles(shim, heads, N, d, causal, form):
     assert shim.fwd_form(heads, N, d, causal) == form
+
+
+# block masks: how many tiles a row keeps is not known on the host, and the causal mask changes nothing in the division
+@pytest.mark.parametrize("heads,N,d,form", [(8, 4096, 32, 24), (9, 4096, 32, 24), (10, 4096, 32, 24), (5, 8192, 32, 24), (11, 4096, 32, 42), (16, 4096, 32, 42), (17, 4096, 32, 41),
+                                            (4, 4096, 64, 24), (8, 4096, 64, 42), (9, 4096, 64, 41), (4, 4096, 128, 22)])
+def test_forward_under_a_block_mask(shim, heads, N, d, form):
+    assert shim.sparse_fwd_form(heads, N, d, 0) == form
+    assert shim.sparse_fwd_form(heads, N, d, 1) == form
