@@ -81,6 +81,11 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
   if constexpr (CAUSAL) causal_block(a, item, n_qt, bh, q_item);
   if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
   const int qt = CAUSAL ? n_qt - 1 - q_item : q_item;
+  // (one pass of a loop: the form in which the {2, 2} kernels of d = 32 stay within the 168 registers of three wavefronts per SIMD without being held to them;
+  // straight on they take 182, with dropout 174, and held to 168 they spill.  dQ in us, straight | so: 100 heads of 300 13.9 | 11.3, 80 of 400 15.3 | 12.7, 8 of 5000 72.9 | 59.1,
+  // with dropout 100 of 300 15.8 | 13.9)
+#pragma clang loop unroll(disable)
+  for (int pass = 0; pass < 1; ++pass) {
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Kg = (const T*)a.K + head_off;
@@ -317,6 +322,7 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
   T* stage = (wave < 2 ? Ks0 + wave * 32 * D : Vs0 + (wave - 2) * 32 * D);
   store_rows_coalesced<T, D>(stage, (T*)a.dQ + head_off + (int64_t)q0 * a.sn, a.sn, dq, a.tau, a.N - q0,
                              D == 32 ? a.dvalid : D);
+  }  // for pass
 }
 
 template <typename T, int D, int RW, int KG>
