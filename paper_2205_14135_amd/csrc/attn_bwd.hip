@@ -330,7 +330,7 @@ int launch_dq(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
   const int blocks = a.T * (4 / RW);
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
+  a.group = causal_group(a, D, sparse, false, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
   if (sparse) a.plan_groups = sparse_plan_groups(a);
   const dim3 grid(kXcds * a.chunk + (sparse ? a.plan_groups : 0)), block(64 * RW * KG);
 #define ATTN_DQ_CASE(C, P, S)                                                          \

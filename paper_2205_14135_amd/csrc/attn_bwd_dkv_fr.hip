@@ -383,7 +383,7 @@ int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_gro
   const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));   // Q and dO
+  a.group = causal_group(a, D, sparse, false, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));   // Q and dO
   const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(64 * RW * KG);
 #define ATTN_DKV_FR_CASE(C, P, S)                                                           \
   if constexpr (!S || RW == 4)                                                              \

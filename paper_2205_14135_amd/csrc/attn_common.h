@@ -137,20 +137,35 @@ int launch_fwd_pp(const KArgs& a, int dtype, int d, bool causal, bool dropout, h
 // MFMA-only kernel for measuring the sustained matrix rate (attn_probe.hip); *flops = FLOPs launched
 int launch_mfma_rate(int dtype, int iters, int operand_sets, float* sink, hipStream_t s, double* flops);
 
-// a.group: how many heads the causal kernels deal out together (causal_block); head_bytes: what a head's items stream.  All of them (0), unless
-// many heads of 128 columns fill every XCD evenly or nearly so: then what an XCD streams at a time stays within 8 MiB, the L2 working set (a level of all heads
-// streams them all).  A run of whole groups per XCD leaves some XCDs the heavy blocks of a group and others the light ones where the heads do not divide
-// evenly, and one head at a time (the forward before) puts blocks of the same weight on a compute unit.  us, runs | all heads, heads x N:
+// a.group: how many heads the causal kernels deal out together (causal_block); head_bytes: what a head's items stream; fwd: the forward kernel asks, not a
+// backward one.  All of them (0), unless many heads of 128 columns fill every XCD evenly or nearly so: then what an XCD streams at a time stays within 8 MiB, the L2
+// working set (a level of all heads streams them all).  A run of whole groups per XCD leaves some XCDs the heavy blocks of a group and others the light ones where the
+// heads do not divide evenly, and one head at a time puts blocks of the same weight on a compute unit.  us, runs | all heads, heads x N:
 //   d = 128, forward  64 x 1024 37.1 | 30.0, dropout 44.2 | 34.0; 48 x 900 29.7 | 24.0; 36 x 2048 63.9 | 50.8; 20 x 4096 124 | 97.5; 12 x 8192 265 | 214;
-//            96 x 1024 43.8 | 37.4; 300 x 300 25.5 | 31.2, 250 x 512 36.9 | 39.3, 256 x 512 33.7 | 36.8
+//            96 x 1024 43.8 | 37.4; 64 x 2352 125 | 102; 300 x 300 25.5 | 31.2, 250 x 512 36.9 | 39.3, 256 x 512 33.7 | 36.8
 //   d = 128, backward  64 x 1024 87 | 88; 60 x 700 58.0 | 54.5; 36 x 2048 185 | 158; 10 x 8192 699 | 582; 72 x 1024 110 | 90; 136 x 1024 191 | 164; 192 x 1024
 //            233 | 225 (taken as runs all the same: 64 x 1500 145 | 151, 64 x 4096 847 | 862);   128 x 1024 150 | 158, 250 x 512 110 | 119, 256 x 512 105 | 114, 1000 x 300 234 | 239
 //   d = 32, forward  96 x 2048 68.3 | 45.1; 100 x 1024 24.9 | 17.3; 60 x 1000, dropout 26.1 | 19.9; 1024 x 512 48.6 | 45.2; backward 96 x 2048 156 | 143; 1024 x 512 136 | 135
-inline int causal_group(const KArgs& a, int d, bool sparse, int64_t head_bytes) {
-  const int64_t heads = (int64_t)a.B * a.H;
-  if (!sparse && (d < 128 || a.n_items <= 2 * kComputeUnits || (heads % (8 * kXcds) != 0 && heads < 224))) return 0;
+// d = 128, no more items than compute units: nothing is left to even out, and one head after the other (1) keeps its items on one XCD, whose L2 then
+// loads K and V (or Q and dO) once.  us, all heads | one: forward 13 x 993 19.2 | 18.2, 23 x 1030 21.6 | 19.6, 35 x 677 16.6 | 15.3, 63 x 474 15.0 | 13.3, 11 x 2033 34.1 | 31.4, 5 x 4273
+// 61.4 | 58.5; backward 61 x 194 23.7 | 22.4, 62 x 206 with dropout 26.5 | 24.6, 31 x 444 31.5 | 29.4, 25 x 703 with dropout 52.2 | 51.5 (but 50 x 274 28.2 | 31.9).
+// Heads of one block: nothing to deal out, and the backward reads consecutive heads faster on one XCD: 1414 x 111 backward 106 | 102, forward 481 x 103 11.6 | 12.2.
+// Two or three blocks of which the last is short, up to two rounds (three blocks in the forward: up to three halves) over the compute units: forward, all heads | runs of 8 |
+// one head 236 x 142 12.0 | - | 10.4, 238 x 151 12.4 | - | 11.2, 164 x 308 with dropout 18.7 | 17.6 | 17.7, 245 x 342 27.0 | 26.4 | 24.3, 213 x 320 22.8 | 24.0 | 21.7, 256 x 272 21.5 |
+// 24.1 | 23.4; fewer heads 230 x 195 15.4 | 16.4 | 16.3, 199 x 327 22.3 | 22.8 | 23.4; backward 250 x 206 42.2 | 40.5 | 40.1, 146 x 328 with dropout 50.0 | 47.8 | 50.9, 164 x 302
+// 42.6 | 40.9 | 43.0; 224 x 197 34.4 | 36.8 | 36.9.
+inline int causal_group(const KArgs& a, int d, bool sparse, bool fwd, int64_t head_bytes) {
+  const int64_t heads = (int64_t)a.B * a.H, levels = a.n_items / heads;
   const int64_t fit = ((int64_t)8 << 20) / head_bytes;
-  return (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
+  const int run = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
+  if (sparse) return run;
+  if (d < 128) return 0;
+  if (levels == 1) return fwd ? 0 : 1;
+  if (a.n_items <= kComputeUnits) return 1;
+  if (levels <= 3 && a.n_items > (levels == 2 ? 7 : 6) * kComputeUnits / 4 && a.n_items <= 2 * kComputeUnits) return fwd ? 1 : run;
+  if (levels == 3 && fwd && 2 * a.n_items >= 5 * kComputeUnits && a.n_items <= 3 * kComputeUnits) return 1;
+  if (a.n_items <= 2 * kComputeUnits) return 0;
+  return heads >= 224 || (heads % (8 * kXcds) == 0 && (heads >= 128 || !fwd)) ? run : 0;
 }
 
 #if defined(__HIPCC__)
@@ -576,12 +591,15 @@ __device__ __forceinline__ void causal_block(const KArgs& a, int item, int n_lev
     level = item / n_heads;
     const int j = head / kXcds;
     if (j < n_heads / kXcds) head = j * kXcds + (head + j) % kXcds;
-  } else {
-    const int grp0 = item / n_levels / a.group * a.group;  // first head of this group
-    const int gsz = min(a.group, n_heads - grp0);          // heads in it (the last group may be short)
-    const int within = item - grp0 * n_levels;             // position inside the group's items
-    head = grp0 + within % gsz;
-    level = within / gsz;
+  } else {   // (one division for a.group == 1, and few in front of the first loads: 653 heads of 42 tokens, d = 128, pay 0.3 us of 10.4 for three)
+    const uint32_t per = (uint32_t)(a.group * n_levels), grp = (uint32_t)item / per, within = (uint32_t)item - grp * per;
+    head = (int)grp * a.group;   // first head of this group
+    level = (int)within;
+    if (a.group > 1) {
+      const uint32_t gsz = (uint32_t)min(a.group, n_heads - head);   // heads in it (the last group may be short)
+      level = (int)(within / gsz);
+      head += (int)(within - (uint32_t)level * gsz);
+    }
   }
 }
 // XOR swizzle of the 16-byte chunk index inside an unpadded [rows][D] LDS tile.  It makes both

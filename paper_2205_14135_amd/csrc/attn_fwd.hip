@@ -305,7 +305,7 @@ int launch_fwd_groups(KArgs a, bool causal, bool dropout, bool sparse, hipStream
   const int blocks = RW == 4 ? a.T : (a.N + 32 * RW - 1) / (32 * RW);
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
-  a.group = causal_group(a, D, sparse, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
+  a.group = causal_group(a, D, sparse, true, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
   const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
 #define ATTN_FWD_CASE(C, P, S)                                                              \
   if (causal == C && dropout == P && sparse == S) {                                         \

@@ -22,6 +22,11 @@ extern "C" int sparse_fwd_form(int heads, int N, int d, int causal) {
   const attn::WaveGroups w = attn::fwd_groups(problem(heads, N, d), d, causal, true, true);
   return 10 * w.waves + w.groups;
 }
+extern "C" int dealt_together(int heads, int N, int d, int rows, int fwd) {
+  attn::KArgs a = problem(heads, N, d);
+  a.n_items = heads * ((N + rows - 1) / rows);
+  return attn::causal_group(a, d, false, fwd != 0, (int64_t)4 * N * d);
+}
 extern "C" int short_heads() { return attn::kBwdShort; }
 extern "C" int role_split() { return attn::kDkvRoleSplit; }
 extern "C" int one_wave128() { return attn::kDkvOneWave128; }
@@ -72,3 +77,14 @@ def test_forward_of_few_tiles(shim, heads, N, d, causal, form):
 def test_forward_under_a_block_mask(shim, heads, N, d, form):
     assert shim.sparse_fwd_form(heads, N, d, 0) == form
     assert shim.sparse_fwd_form(heads, N, d, 1) == form
+
+
+# causal heads: how many of them are dealt out together (0: all), with the rows of a work item
+@pytest.mark.parametrize("heads,N,d,rows,fwd,bwd", [
+    (35, 677, 128, 128, 1, 1), (13, 993, 128, 64, 1, 1), (64, 512, 128, 128, 1, 1), (61, 194, 128, 64, 1, 1), (65, 512, 128, 128, 0, 0), (12, 8192, 128, 128, 0, 0),   # one round
+    (1414, 111, 128, 128, 0, 1), (7, 64, 128, 64, 0, 1),                                                                       # one block
+    (224, 142, 128, 128, 0, 0), (225, 142, 128, 128, 1, 8), (256, 250, 128, 128, 1, 8), (257, 250, 128, 128, 8, 8),            # two
+    (128, 300, 128, 128, 0, 0), (129, 300, 128, 128, 1, 8), (170, 300, 128, 128, 1, 8), (171, 300, 128, 128, 0, 0), (214, 300, 128, 128, 1, 0), (256, 300, 128, 128, 1, 8),
+    (257, 300, 128, 128, 8, 8), (64, 2352, 128, 128, 0, 6), (128, 1110, 128, 128, 8, 8), (136, 1110, 128, 128, 0, 0), (96, 2048, 32, 128, 0, 0), (2, 200, 64, 64, 0, 0)])
+def test_causal_heads_dealt_together(shim, heads, N, d, rows, fwd, bwd):
+    assert (shim.dealt_together(heads, N, d, rows, 1), shim.dealt_together(heads, N, d, rows, 0)) == (fwd, bwd)
