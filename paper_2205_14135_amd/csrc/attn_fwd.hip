@@ -383,8 +383,9 @@ __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
 WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
   if (!divide) return {4, 1};
   const WorkItems w(a, sparse, causal && !sparse && d == 64);
-  // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise)
-  const int64_t fit24 = d == 64 ? kComputeUnits : !causal || sparse || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
+  // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise.  Causal, long sweeps, {2, 2} | {2, 4}: 8 x 7975 with dropout 97.4 | 89.9, 9 x 5741 with dropout 63.2 | 57.0,
+  // 4 x 10405 63.0 | 59.4, 9 x 6324 47.9 | 46.9; 15 x 4219 36.0 | 37.4, 16 x 4019 34.3 | 35.4)
+  const int64_t fit24 = d == 64 ? kComputeUnits : causal && !sparse && w.tiles >= 86 ? 4 * kComputeUnits : !causal || sparse || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
   if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
   // (two tiles would gain 0.2 to 0.8 us, less than the host spends on a call, but not in pairs; a head of up to 128 tokens keeps one form instead, and with it
   // the same last bits in whatever batch it stands)

@@ -88,3 +88,9 @@ def test_forward_under_a_block_mask(shim, heads, N, d, form):
     (257, 300, 128, 128, 8, 8), (64, 2352, 128, 128, 0, 6), (128, 1110, 128, 128, 8, 8), (136, 1110, 128, 128, 0, 0), (96, 2048, 32, 128, 0, 0), (2, 200, 64, 64, 0, 0)])
 def test_causal_heads_dealt_together(shim, heads, N, d, rows, fwd, bwd):
     assert (shim.dealt_together(heads, N, d, rows, 1), shim.dealt_together(heads, N, d, rows, 0)) == (fwd, bwd)
+
+
+# long causal sweeps of narrow heads over four groups of wavefronts: 86 tiles and up to four blocks of 64 rows per compute unit
+@pytest.mark.parametrize("heads,N,causal,form", [(8, 7975, 1, 24), (11, 5441, 1, 24), (11, 5440, 1, 22), (12, 5441, 1, 22), (8, 7975, 0, 42), (7, 5440, 1, 24)])
+def test_forward_of_long_narrow_heads(shim, heads, N, causal, form):
+    assert shim.fwd_form(heads, N, 32, causal) == form
