@@ -371,8 +371,10 @@ __global__ void dropout_mask_kernel(const KArgs a, uint8_t* keep) {
 //            8 x 4096 52.4 43.0 54.4 51.2; 60 x 512 9.9 9.6 10.7 14.7; 20 x 2048 38.5 44.2 44.9 43.9; 128 x 512 14.1 17.1 19.6 27.6
 //   two tiles, {4, 1} | {2, 2}  d = 64 1 x 128 4.5 4.3, 16 x 100 5.0 4.7, 128 x 128 5.1 4.9, dropout 6.0 5.6; causal 1 x 128 5.1 7.5; d = 32 1 x 128 3.9 3.7,
 //            16 x 100 4.6 4.1, 128 x 65 with dropout 5.6 4.7, causal 128 x 128 4.8 4.3; one tile d = 64 16 x 64 4.1 4.6; d = 32 16 x 64 3.7 3.9
-//   d = 64 causal (measured with pairs of row blocks)  64 x 129 9.3 - 8.4; 64 x 192 9.4 - 8.8, dropout 11.7 - 10.0; 60 x 400 14.1 13.7 11.1 12.3; 16 x 1024 20.3 18.3 16.8 15.2; 8 x 4096 57.1 45.4 43.4 31.8;
-//            20 x 2048 32.7 27.7 33.2 38.8; 10 x 4096 57.3 45.6 56.7 59.0; 64 x 1024 21.1 19.2 - 28.7; 48 x 1400 33.0 41.7 - 47.0
+//   d = 64 causal  64 x 129 6.0 6.2 5.7 -; 64 x 192 6.1 6.7 5.9 -, dropout 7.1 7.3 6.5 -; 60 x 400 9.4 8.8 8.1 12.0; 16 x 1024 17.2 13.8 11.2 10.6; 8 x 4096 57.0 41.7 35.3 32.4;
+//            20 x 2048 30.8 23.7 20.3 28.7; 10 x 4096 57.1 42.3 36.7 44.5; 64 x 1024 18.6 18.6 19.4 29.4; 48 x 1400 24.0 25.7 24.4 38.0; 160 x 225 7.7 10.0 10.2 -; 75 x 506 11.2 11.4 13.5 -;
+//            52 x 520 11.0 9.8 8.8 -; 60 x 579 12.6 11.2 12.1 -; 67 x 654 14.6 16.0 16.9 -; 82 x 648 15.1 17.9 17.7 -; 63 x 715 with dropout 19.2 17.5 19.6 25.7; 57 x 794 15.9 16.7 16.6 -;
+//            85 x 705 16.7 18.8 21.7 -; 60 x 900 16.9 18.3 18.0 -; 50 x 1000 18.4 17.4 17.9 -; 51 x 985 19.6 18.8 20.4 30.7
 //   d = 32   4 x 117 4.7 5.0 5.1 5.0; 16 x 640 9.7 8.9 7.1 7.1; 16 x 1024 13.5 11.6 10.3 8.4; 60 x 512 8.5 7.9 8.6 8.5; 8 x 4096 45.1 35.5 39.8 32.8;
 //            10 x 4096 60.7 55.3 52.9 47.6; 32 x 2048 32.9 31.3 38.5 35.1, causal 34.0 30.0 29.2 26.9; 128 x 512 11.1 11.4 13.9 14.7
 //   d = 128  4 x 117 6.6 7.8 7.2; 64 x 189 8.5 - 9.7; 40 x 359 11.7 - 11.0; 16 x 1024 22.1 19.9 18.8; 1 x 8192 140 107 107; 60 x 512 14.4 14.5 23.1; 24 x 1024 22.4 20.5 35.3;
@@ -387,13 +389,15 @@ WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divi
   // 4 x 10405 63.0 | 59.4, 9 x 6324 47.9 | 46.9; 15 x 4219 36.0 | 37.4, 16 x 4019 34.3 | 35.4)
   const int64_t fit24 = d == 64 ? kComputeUnits : causal && !sparse && w.tiles >= 86 ? 4 * kComputeUnits : !causal || sparse || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
   if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
-  // (two tiles would gain 0.2 to 0.8 us, less than the host spends on a call, but not in pairs; a head of up to 128 tokens keeps one form instead, and with it
-  // the same last bits in whatever batch it stands)
+  // (two tiles would gain 0.2 to 0.8 us, less than the host spends on a call; a head of up to 128 tokens keeps one form instead, and with it the same last bits in whatever
+  // batch it stands)
   // (causal blocks are dealt out heaviest first: two more rounds of light ones do no harm.  {2, 2} against {4, 2} or {4, 1}: d = 64 24 x 1500 16.2 18.7, 20 x 2048 20.4 23.6,
   // 10 x 4096 36.0 41.6, 60 x 700 13.4 13.8, 12 x 5000 60.1 56.4, 32 x 2048 30.9 28.5; d = 32 40 x 1024 10.2 11.8, 60 x 700 8.6 9.8, 32 x 2048 20.7 22.2, 60 x 1000 with
   // dropout 18.0 19.8, 128 x 700 13.0 12.9; {2, 4} there 12.0, 11.1, 23.0, 20.1, 18.6, and 10 x 4096 27.4 29.9)
-  const int64_t fit22 = !causal || sparse || d == 128 ? kComputeUnits : d == 64 ? 11 * kComputeUnits / 8 : 9 * kComputeUnits / 2;
-  if (w.of64 <= fit22 && w.tiles >= (d == 128 ? 6 : 3)) return {2, 2};
+  const int64_t fit22 = !causal || sparse || d == 128 ? kComputeUnits : d == 64 ? (w.tiles >= 9 ? 11 : 8) * kComputeUnits / 8 : 9 * kComputeUnits / 2;
+  const bool one_round = d == 64 && causal && !sparse && (int64_t)a.B * a.H * w.tiles <= 2 * kComputeUnits;   // (an odd block counts as a whole half in of64)
+  if ((w.of64 <= fit22 || one_round) && w.tiles >= (d == 128 ? 6 : 3)) return {2, 2};
+  if (d == 64 && causal && !sparse) return w.of128 <= (w.tiles >= 16 ? 4 : 3) * kComputeUnits / 4 && w.tiles >= 12 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (d <= 64) return w.of128 <= (d == 32 ? 2 : 1) * kComputeUnits && w.tiles >= 10 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   // d = 128: {4, 2} has one workgroup on a compute unit, {4, 1} two, which together get through a tile hardly faster than one
   // of them alone.  Estimates in us: the tiles of all items over the compute units, and under the causal mask the longest sweep.

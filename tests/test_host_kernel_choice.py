@@ -71,6 +71,14 @@ def test_forward_of_few_tiles(shim, heads, N, d, causal, form):
     assert shim.fwd_form(heads, N, d, causal) == form
 
 
+# causal heads of 64 columns: {2, 2} up to 11/8 half blocks per compute unit from nine tiles on, {4, 2} from twelve tiles on (sixteen
+# for more than three halves of 128 rows on four compute units)
+@pytest.mark.parametrize("heads,N,form", [(160, 225, 41), (128, 225, 22), (75, 506, 41), (64, 506, 22), (52, 520, 22), (56, 520, 22), (70, 520, 22), (71, 520, 41), (67, 654, 41), (85, 700, 41),
+                                          (85, 705, 41), (64, 705, 42), (65, 705, 41), (57, 960, 41), (57, 961, 42), (50, 705, 22), (51, 985, 42), (64, 1024, 42), (65, 1024, 41)])
+def test_forward_of_causal_heads_of_64_columns(shim, heads, N, form):
+    assert shim.fwd_form(heads, N, 64, 1) == form
+
+
 # block masks: how many tiles a row keeps is not known on the host, and the causal mask changes nothing in the division
 @pytest.mark.parametrize("heads,N,d,form", [(8, 4096, 32, 24), (9, 4096, 32, 24), (10, 4096, 32, 24), (5, 8192, 32, 24), (11, 4096, 32, 42), (16, 4096, 32, 42), (17, 4096, 32, 41),
                                             (4, 4096, 64, 24), (8, 4096, 64, 42), (9, 4096, 64, 41), (4, 4096, 128, 22)])
