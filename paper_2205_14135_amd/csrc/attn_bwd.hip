@@ -353,13 +353,16 @@ int launch_dq(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
 template <typename T> constexpr int kDtype = 0;
 template <> constexpr int kDtype<__bf16> = 1;
 
+}  // namespace
+
 // us of the backward pass with {4, 1}, and the difference with {4, 2} | {2, 2} | {2, 4} (wavefronts of rows, groups) in this kernel
 // alone; heads x N:
 //   d = 64   1 x 128 12.3 +1.2 -0.3 +1.3; 16 x 197 17.7 +0.6 -1.3 +0.1; 4 x 512 25.0 -0.3 -2.8 -1.9; 16 x 1024 41.0 -2.0 -5.2 -5.1; 8 x 2048 72.2 -5.3 -10.2 -11.6;
 //            1 x 8192 263 -28 -48 -61; 60 x 512 26.5 -0.1 +0.5 +6.2; 24 x 1024 42.0 -2.0 -1.2 +4.5; 8 x 4096 140 -8.7 -5.5 -0.8;
 //            10 x 4096 186 +10.1 -1.3 +2.6, dropout 271 +9.5 -15.9 -7.3; 24 x 2001 110 +6.1 -2.1 +4.9; 40 x 1024 57.1 +5.8 +0.9 +8.1; 32 x 2048 116 +3.6 +4.8 +16.8
-//   d = 64 causal (measured with pairs of row blocks)  1 x 128 13.1 +1.0 +2.8 +6.2; 16 x 197 26.9 +1.0 -1.9 +1.2; 16 x 1024 51.6 -0.6 -5.9 -4.4;
-//            8 x 4096 146 -8.2 -20.5 -24.4; 40 x 1024 53.2 -0.5 -1.3 +11.4; 10 x 4096 148 -8.8 -8.8 +5.8; 32 x 2048 85.8 -2.6 -2.3 +9.6; 128 x 512 39.5 +0.8 -0.4 +12.2
+//   d = 64 causal (the other kernel as its rule has it)  16 x 1024 33.7 -2.1 -5.8 -5.8; 8 x 4096 105 -12.1 -17.6 -20.5; 13 x 2382 73.9 -8.0 -10.9 -8.3; 40 x 1024 42.0 -1.9 -1.1 +6.2;
+//            10 x 4096 119 -13.8 -19.0 -9.0; 32 x 2048 82.2 -3.1 0 +11.3; 128 x 512 38.1 +3.1 +3.0 +15.4; 46 x 661 32.8 +0.6 -1.8 +4.2; 52 x 694 with dropout 43.5 +0.4 -2.1 +7.4; 61 x 575 30.7 +3.0
+//            +1.8 +10.8; 25 x 1470 with dropout 74.7 -5.6 -8.9 +3.0; 15 x 2832 with dropout 132 -11.1 -17.8 -4.6; 60 x 1000 49.9 +1.9 +2.2 -; 51 x 1200 58.0 +2.5 +4.5 -; 50 x 1000 47.4 +1.4 +1.4 -
 //   d = 32   1 x 128 10.0 -0.4 -0.4 +0.1; 16 x 640 22.6 -1.0 -2.6 -2.6; 8 x 2048 56.2 -3.8 -8.0 -10.0; 60 x 512 20.1 -0.7 -0.7 +2.1; 8 x 4096 107 -8.3 -8.1 -4.9;
 //            10 x 4096 138 +8.1 -12.7 -2.7; 24 x 2001 81.7 +5.3 -5.1 +1.9; 64 x 1024 43.1 +3.1 +0.9 +8.8
 //   d = 128  1 x 128 17.4 +2.5 +0.2; 16 x 640 42.5 +0.9 -2.4; 8 x 2048 130 -3.5 -9.1; 1 x 8192 474 -26 -45; 60 x 512 41.5 +2.5 +9.7;
@@ -372,18 +375,20 @@ WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse, bool divid
   const bool halves = causal && !sparse && d == 64;
   const WorkItems w(a, sparse, halves);
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return d <= 64 && w.tiles >= (d == 64 ? 24 : 12) && !sparse ? WaveGroups{2, 4} : WaveGroups{2, 2};
-  // (causal, now | {2, 2}: d = 64 24 x 1500 49.0 47.0, 20 x 2048 62.9 60.6, 10 x 4096 110 106, 40 x 1024 40.5 40.9, 32 x 2048 79.7 83.8; d = 32 32 x 2048 58.5 54.7, 60 x 1000 with dropout
+  // (causal, now | {2, 2}: d = 32 32 x 2048 58.5 54.7, 60 x 1000 with dropout
   // 50.8 48.8, 128 x 700 33.7 35.9; 8 x 4096 {2, 2} 64.8, {2, 4} 58.7, 10 x 4096 69.7, 74.9)
-  if (halves && w.of64 <= 5 * kComputeUnits / 4 && w.tiles >= 24) return {2, 2};
+  if (halves && w.of64 <= 11 * kComputeUnits / 8 && w.tiles >= 11) return {2, 2};
   if (d == 32 && causal && !sparse && w.of64 <= 2 * kComputeUnits && w.tiles >= 32) return {2, 4};
   if (d == 32) return w.of64 <= (causal && !sparse ? 4 : 3) * kComputeUnits && w.tiles >= 4 ? WaveGroups{2, 2} : WaveGroups{4, 1};   // (three workgroups fit)
-  if (w.of128 <= kComputeUnits && w.tiles >= (d == 64 ? 16 : 24)) return {4, 2};
+  if (w.of128 <= (halves && w.tiles < 24 ? 3 : 4) * kComputeUnits / 4 && w.tiles >= (d == 64 ? 16 : 24)) return {4, 2};
   // (causal, two blocks in turn on a compute unit, heaviest first; {4, 1} | {4, 2}, us: 8 x 8192 511 | 485, 10 x 4096 226 | 214, 20 x 2000 with dropout 151 | 140;
   // 30 x 2048 151 | 152, 48 x 900 67.6 | 73.2)
   if (d == 128 && causal && !sparse && w.of128 <= (w.tiles >= 64 ? 2 : 3 / 2.) * kComputeUnits && w.tiles >= 24) return {4, 2};
   if (d == 64 && !halves && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
   return {4, 1};
 }
+
+namespace {
 
 template <typename T, int D>
 int launch_dq_td(const KArgs& a, bool causal, bool dropout, bool sparse, bool divide, hipStream_t s) {

@@ -403,16 +403,21 @@ int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_gro
   return (int)hipErrorInvalidValue;
 }
 
+}  // namespace
+
 // us of the backward pass with {4, 1}, and the difference with {4, 2} | {2, 2} | {2, 4} (wavefronts of keys, groups) in this kernel
 // alone; heads x N:
 //   d = 64   1 x 128 12.3 +1.0 -0.3 +1.4; 16 x 197 17.7 -0.4 -2.1 -0.9; 4 x 512 25.0 -1.3 -3.8 -3.4; 16 x 1024 41.0 -4.2 -7.5 -8.1; 8 x 2048 72.2 -10.2 -15.6 -18.5;
 //            1 x 8192 263 -47 -68 -89; 60 x 300 20.6 -0.2 +0.1 +7.0; 24 x 1024 42.0 -4.2 -3.2 +3.2; 8 x 4096 140 -16.6 -10.8 -5.6;
 //            10 x 4096 186 +9.3 -4.4 -0.2, dropout 271 +14.7 -19.0 -9.5; 24 x 2001 110 +2.6 -4.2 +3.1; 40 x 1024 57.1 +5.4 +0.4 +8.2; 32 x 2048 116 +2.3 +6.0 +19.2
-//   d = 64 causal (measured with pairs of key blocks)  1 x 128 13.1 +0.8 +2.9 +6.6; 16 x 197 26.9 -0.1 -2.9 +0.3; 16 x 1024 51.6 -3.6 -9.4 -7.8;
-//            8 x 4096 146 -20 -34 -39; 40 x 1024 53.2 -3.7 -3.3 +10.4; 32 x 2048 85.8 -6.3 -4.5 +7.4; 128 x 512 39.5 -0.7 -1.5 +12.2
+//   d = 64 causal (the other kernel as its rule has it)  16 x 1024 36.0 -3.5 -8.1 -8.8; 8 x 4096 116 -17.5 -27.3 -34.0; 13 x 2382 79.7 -9.7 -14.8 -14.4; 40 x 1024 44.1 -3.6 -4.7 +3.9;
+//            10 x 4096 126 -17.9 -25.8 -15.8; 32 x 2048 84.4 -4.6 -2.2 +9.6; 128 x 512 33.6 +4.4 +3.7 +16.6; 90 x 408 29.0 +2.9 +1.6 +9.7; 46 x 661 34.5 -1.6 -3.2 +1.9; 74 x 656 38.8 +3.1 +2.7 +14.9;
+//            61 x 575 32.2 -1.2 -0.9 +9.9; 25 x 1470 with dropout 78.5 -9.9 -15.2 -5.0; 15 x 2832 with dropout 141 -20.9 -34.1 -18.5; 85 x 705 42.8 +4.5 +4.5 -, dropout 55.1 +4.4 +1.8 -;
+//            63 x 715 39.3 +0.1 +1.3 -, dropout 52.6 -3.0 -0.9 -; 60 x 900 46.2 +1.4 +1.1 -, dropout 62.5 0 -1.1 -; 64 x 800 with dropout 54.5 -2.1 -1.6 -
 //   d = 32   1 x 128 10.0 -0.3 -0.4 -0.1; 16 x 640 22.6 -2.2 -3.7 -4.5; 8 x 2048 56.2 -8.9 -12.2 -16.4; 60 x 512 20.1 -1.6 -1.5 +1.6;
 //            8 x 4096 107 -18.5 -16.4 -11.7; 10 x 4096 138 +6.0 -5.7 -4.1; 64 x 1024 43.1 +2.9 +3.1 +10.6
-//   d = 32 causal (pairs)  16 x 197 18.9 -2.0 -3.6 -2.9; 8 x 4096 121 -22 -33 -42; 10 x 4096 132 -23 -24 -16; 128 x 512 29.2 -2.9 -3.0 +3.3
+//   d = 32 causal (the other kernel as its rule has it)  16 x 197 13.1 -0.9 -2.2 -2.2; 8 x 4096 97.4 -24.5 -33.8 -39.7; 10 x 4096 101 -23.1 -31.2 -25.2; 128 x 512 24.9 +1.3 +0.7 +7.9;
+//            32 x 2048 62.6 -8.1 -7.8 +0.3; 60 x 1000 38.5 -1.5 -1.5 +5.6
 //   block-sparse (butterfly mask of T x T blocks, heads x T), {4, 2} only  d = 64  4 x 8 48.1 +0.2; 8 x 16 69.8 -5.7; 4 x 32 65.8 -4.7; 8 x 32 69.6 +6.9,
 //            causal 68.4 -3.8; 4 x 64 75.5 +9.2 (the workgroups of the segment list take whole compute units then)
 WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide) {
@@ -421,13 +426,15 @@ WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse, bool d
   const WorkItems w(a, sparse, halves);
   if (sparse) return w.of128 <= kComputeUnits / 2 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (w.of64 <= kComputeUnits && w.tiles >= 4) return w.tiles >= (d == 64 ? 24 : 12) ? WaveGroups{2, 4} : WaveGroups{2, 2};
-  // (causal, {4, 2} | {2, 2}: 24 x 1500 48.7 45.3, 20 x 2048 63.0 59.6, 10 x 4096 110 103; 40 x 1024 40.0 40.2, 32 x 2048 80.3 82.8)
-  if (d == 64 && halves && w.of64 <= 5 * kComputeUnits / 4 && w.tiles >= 24) return {2, 2};
+  if (d == 64 && halves && w.of64 <= 11 * kComputeUnits / 8 && w.tiles >= 11) return {2, 2};
+  if (d == 64 && halves) return w.of128 <= (w.tiles >= 13 ? 4 : 3) * kComputeUnits / 4 && w.tiles >= 9 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (d == 64 && w.of128 <= kComputeUnits && w.tiles >= 4) return {4, 2};
   if (d == 32 && w.of64 <= 2 * kComputeUnits && w.tiles >= 4) return {2, 2};
   if (!halves && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
   return {4, 1};
 }
+
+namespace {
 
 template <typename T, int D>
 int launch_td(const KArgs& a, bool causal, bool dropout, bool sparse, int extra_groups, bool divide, hipStream_t s) {

@@ -101,8 +101,10 @@ struct WorkItems {
   }
 };
 
-// The forward's division (attn_fwd.hip).
+// The division of the forward (attn_fwd.hip), of dQ (attn_bwd.hip), and of dK and dV at d <= 64 (attn_bwd_dkv_fr.hip).
 WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide);
+WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide);
+WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse, bool divide);
 
 // Planning workgroups of a block-sparse backward: one for kPlanCols mask columns of a head (what each clears takes no longer than the
 // launch it is part of), padded to whole rounds over the XCDs; none where the columns are too short for any to be heavy.

@@ -22,6 +22,14 @@ extern "C" int sparse_fwd_form(int heads, int N, int d, int causal) {
   const attn::WaveGroups w = attn::fwd_groups(problem(heads, N, d), d, causal, true, true);
   return 10 * w.waves + w.groups;
 }
+extern "C" int dq_form(int heads, int N, int d, int causal) {
+  const attn::WaveGroups w = attn::dq_groups(problem(heads, N, d), d, causal, false, true);
+  return 10 * w.waves + w.groups;
+}
+extern "C" int dkv_form(int heads, int N, int d, int causal) {
+  const attn::WaveGroups w = attn::dkv_fr_groups(problem(heads, N, d), d, causal, false, true);
+  return 10 * w.waves + w.groups;
+}
 extern "C" int dealt_together(int heads, int N, int d, int rows, int fwd) {
   attn::KArgs a = problem(heads, N, d);
   a.n_items = heads * ((N + rows - 1) / rows);
@@ -102,3 +110,12 @@ def test_causal_heads_dealt_together(shim, heads, N, d, rows, fwd, bwd):
 @pytest.mark.parametrize("heads,N,causal,form", [(8, 7975, 1, 24), (11, 5441, 1, 24), (11, 5440, 1, 22), (12, 5441, 1, 22), (8, 7975, 0, 42), (7, 5440, 1, 24)])
 def test_forward_of_long_narrow_heads(shim, heads, N, causal, form):
     assert shim.fwd_form(heads, N, 32, causal) == form
+
+
+# gradients of causal heads of 64 columns: {2, 2} up to 11/8 half blocks per compute unit from 11 tiles on, {4, 2} for longer sweeps in up to one half of 128 rows (three on four compute
+# units where they are short)
+@pytest.mark.parametrize("heads,N,dq,dkv", [(50, 600, 22, 22), (60, 592, 41, 42), (52, 694, 22, 22), (58, 700, 22, 22), (59, 700, 41, 42), (64, 700, 41, 42), (65, 700, 41, 41), (64, 800, 41, 42), (65, 800, 41, 41),
+                                            (90, 408, 41, 41), (128, 512, 41, 41), (44, 1024, 22, 22), (45, 1024, 42, 42), (48, 1024, 42, 42), (49, 1024, 41, 42), (64, 1024, 41, 42), (65, 1024, 41, 41),
+                                            (37, 1500, 42, 42), (40, 1500, 42, 42), (43, 1500, 41, 41)])
+def test_gradients_of_causal_heads_of_64_columns(shim, heads, N, dq, dkv):
+    assert (shim.dq_form(heads, N, 64, 1), shim.dkv_form(heads, N, 64, 1)) == (dq, dkv)
