@@ -371,16 +371,12 @@ int choose_dkv(const KArgs& a, int d, bool causal, bool dropout, bool sparse, co
   // d = 128, dense: the one-wavefront kernel with the V block in LDS (attn_bwd_dkv_fr128.hip)
   // (without dropout, with 64 keys per wavefront where a head has at least two blocks of 256 keys
   // and whole 32-query tiles: attn_bwd_dkv_w64.hip)
-  // (dropout under the causal mask: the role-split kernel pairs a long and a short key block in one workgroup of eight wavefronts, and is
-  // ahead for long heads whose pairs are one round over the compute units.  us, role-split | one wavefront, heads x N: 8 x 8192 599 | 659, 10 x 4096 296 | 319,
-  // 16 x 3000 227 | 244, 20 x 2048 165 | 170, 32 x 2048 177 | 185, 25 x 1920 158 | 161, 32 x 1792 153 | 155, 22 x 1792 147 | 148.  Shorter heads: 24 x 1664 139 | 137,
-  // 32 x 1536 130 | 129, 29 x 1400 120 | 117, 42 x 1152 104 | 99, 40 x 1024 99 | 95, 64 x 1024 104 | 98.  A few pairs in a second round (an odd
-  // number of blocks makes a pair of the last one alone): 34 x 1920 242 | 172, 39 x 1664 189 | 155, 46 x 1400 193 | 135, 56 x 1152 145 | 116.  With no more blocks
-  // than compute units the one-wavefront kernel splits their sweep (8 x 4096 265 | 236; 16 x 1024 86 | 63), with many its
-  // workgroups even out by themselves: 64 x 2048 200 | 163, 4096 714 | 569; 128 x 1024 126 | 92)
+  // (dropout under the causal mask: the role-split kernel, which pairs a long and a short key block in one workgroup of eight wavefronts, was ahead for long
+  // heads whose pairs are one round over the compute units until the one-wavefront kernel's blocks were dealt out together and its sweeps divided.  us of the backward
+  // pass, role-split | one wavefront, heads x N: 8 x 8192 569 | 531, 10 x 4096 257 | 227, 16 x 3000 197 | 176, 20 x 2048 142 | 122, 32 x 2048 173 | 163, 25 x 1920 143 | 125,
+  // 32 x 1792 150 | 133, 36 x 1792 157 | 150, 16 x 4096 292 | 276, 14 x 4600 328 | 312, 40 x 1024 93 | 76, 1 x 65536 4150 | 3960)
   const int64_t heads = (int64_t)a.B * a.H, blocks = heads * a.T;
-  const bool one_round_of_pairs = blocks > kComputeUnits && heads * ((a.T + 1) / 2) <= kComputeUnits && a.T >= 14;
-  if (!sparse && d == 128 && !role_split && !(dropout && causal && v.dkv == 0 && one_round_of_pairs)) {
+  if (!sparse && d == 128 && !role_split) {
     // measured against the 32-key kernel: 1 % faster at N = 2048, 5 % at 4096, 7 % at 16384; slower below,
     // slower under the causal mask at every length (its 256-key work items balance worse), and with no more key blocks than compute
     // units, where the 32-key kernel can split a block's sweep: B H = 8, N = 2048 130 | 86 us of the backward pass, B H = 8, N = 4096 253 | 205

@@ -48,8 +48,7 @@ def fwd_variant(request):
 @pytest.fixture
 def dkv_variant(request):
     from paper_2205_14135_amd import binding
-    # ("fr" keeps the 64-keys-per-wavefront kernel of d = 128 out and takes the 32-key one also with
-    # the causal mask and dropout together, which "auto" leaves to the role-split kernel; "w64" brings
+    # ("fr" keeps the 64-keys-per-wavefront kernel of d = 128 out; "w64" brings
     # the 64-key kernel in wherever it exists, so that both one-wavefront kernels are reached at every
     # length and under the causal mask)
     binding.attn_debug_set_variant(dkv={"role_split": "rs", "one_wave_32_keys": "fr", "one_wave_64_keys": "w64"}.get(request.param, "auto"))

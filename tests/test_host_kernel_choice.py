@@ -36,7 +36,6 @@ extern "C" int dealt_together(int heads, int N, int d, int rows, int fwd) {
   return attn::causal_group(a, d, false, fwd != 0, (int64_t)4 * N * d);
 }
 extern "C" int short_heads() { return attn::kBwdShort; }
-extern "C" int role_split() { return attn::kDkvRoleSplit; }
 extern "C" int one_wave128() { return attn::kDkvOneWave128; }
 """
 
@@ -46,12 +45,10 @@ def shim(tmp_path_factory):
     return compile_shim(SOURCE, tmp_path_factory.mktemp("choice"))
 
 
-# the role-split kernel's pairs of key blocks: long heads, in one round over 256 compute units, and more blocks than compute units
-@pytest.mark.parametrize("heads,N,expect", [(64, 1024, 0), (42, 1152, 0), (34, 1400, 0), (32, 1536, 0), (29, 1664, 0), (32, 1792, 1), (36, 1792, 1), (37, 1792, 0),
-                                            (32, 1920, 1), (33, 1920, 0), (32, 2048, 1), (33, 2048, 0), (16, 2048, 0), (17, 2048, 1), (10, 4096, 1), (8, 8192, 1),
-                                            (4, 8192, 0), (9, 8192, 0), (1, 65536, 1)])
-def test_role_split_where_its_pairs_are_one_round(shim, heads, N, expect):
-    assert shim.choice(heads, N, 128, 1, 1) == (shim.role_split() if expect else shim.one_wave128())
+# causal mask and dropout at d = 128: the one-wavefront kernel, also where the role-split kernel's pairs of key blocks would be one round over 256 compute units
+@pytest.mark.parametrize("heads,N", [(64, 1024), (32, 1792), (36, 1792), (37, 1792), (33, 1920), (16, 2048), (17, 2048), (32, 2048), (10, 4096), (8, 8192), (1, 65536)])
+def test_causal_mask_and_dropout_at_128_columns(shim, heads, N):
+    assert shim.choice(heads, N, 128, 1, 1) == shim.one_wave128()
     assert shim.choice(heads, N, 128, 1, 0) == shim.one_wave128()
 
 
