@@ -660,38 +660,53 @@ int launch_td(const KArgs& a, bool causal, bool dropout, hipStream_t s) {
 
 // Which heads take this kernel.  us of the backward pass, two launches (divided over wavefront groups where there are few heads) | this kernel; heads x N:
 //   one or two tiles, d = 64  1 x 128 12.1 | 7.9, 96 x 128 13.2 | 8.6, 2048 x 128 83.9 | 66.6, causal with dropout 91.7 | 70.5; 4032 x 65 116 | 85; 96 x 1 10.4 | 6.0
-// From three tiles on, the time of this kernel over that of the two launches, by heads; three tiles (N = 129, 150, 176, 192), then four (N = 193, 208, 224, 256):
-//   d = 64  64 0.92-0.97, 1.22 1.23 1.25 1.32; 96 0.91-0.98, 1.02 1.03 1.03 1.11; 128 1.01 1.02 1.03 1.09; 160 0.72-0.78, 0.82 0.82 0.83 0.90; 256 0.73-0.82, 0.82 0.70
-//     0.65 0.83; 257 0.99 0.99 1.00 1.08; 320 0.87-0.97, 0.99 0.99 0.99 1.06; 400 0.80-0.86, 0.87 0.88 0.89 0.96; 512 0.81-0.87, 0.87 0.88 0.87 0.96; 1024 0.86-0.92, 0.93 0.95 0.96 1.05
-//   d = 64, dropout  64 0.94-1.02, 1.33 1.33 1.34 1.39; 96 0.93-1.02, 1.05 1.05 1.05 1.12; 128 1.04 1.04 1.04 1.11; 160 0.71-0.78, 0.78 0.78 0.80 0.86; 256 0.73-0.84, 0.84 0.85
-//     0.86 0.91; 257 1.01 1.02 1.04 1.11; 320 0.91-1.02, 1.03 1.04 1.05 1.10; 400 0.81-0.90, 0.89 0.91 0.92 0.99; 512 0.84-0.89, 0.90 0.90 0.92 0.99; 1024 0.90-1.00, 1.00 0.97 1.01 1.07
-//   d = 64, causal  64 0.58-0.62, 0.74 0.75 0.76 0.79; 256 0.61-0.67, 0.66 0.67 0.67 0.70; 257 0.95 0.96 0.98 1.01; 400 0.87-0.96, 0.97 0.98 1.00 1.02; 1024 0.90-0.99, 1.00 1.02 1.03 1.01;
-//     dropout  64 0.58-0.62, 0.75 0.75 0.77 0.79; 256 0.61-0.69, 0.67 0.67 0.68 0.71; 257 0.92 0.93 0.96 0.99; 400 0.88-0.98, 0.96 0.98 1.00 1.05; 1024 0.95-1.05, 1.02 1.03 1.03 1.05
-//   d = 32  64 0.86-0.94, 1.23 1.26 1.28 1.38; 96 0.86-0.94, 1.08 1.07 1.10 1.21; 128 1.07 1.07 1.09 1.19; 160 0.72-0.80, 0.88 0.87 0.90 0.99; 256 0.72-0.79, 0.86 0.86 0.88 0.96;
-//     257 1.14 1.15 1.17 1.33; 320 0.97-1.04, 1.11 1.12 1.14 1.29; 400 0.80-0.89, 0.93 0.94 0.97 1.06; 512 0.78-0.93, 0.96 0.96 1.00 1.09; 1024 0.86-0.97, 1.03 1.03 1.06 1.18;
-//     dropout  128 1.05 1.04 1.06 1.15; 160 0.67-0.72, 0.81 0.81 0.83 0.90; 320 0.90-0.97, 1.03 1.03 1.06 1.16; 400 0.73-0.79, 0.84 0.85 0.88 0.97; 1024 0.78-0.89, 0.92 0.93 0.96 1.06
-//   d = 32, causal  64 0.64-0.67, 0.90 0.91 0.91 0.93; 256 0.61-0.64, 0.71 0.71 0.72 0.74; 257 1.00 1.01 1.02 1.04; 400 0.83-0.85, 0.91 0.92 0.95 0.99; 1024 0.88-0.94, 0.99 1.00 1.02 1.07
-// Three tiles: always, the few losses are below 5 %.  Four tiles: up to 64 heads the two launches' divided blocks fill more of the chip, up to 128 both of them
-// take one round over the compute units (even to 3 % with d = 64 and no dropout, where the launch saved decides), from 129 on two, and this kernel one up to
-// 256 (N = 197, d = 32: 129 heads 17.0 | 15.1 us).  Beyond, its second round of whole heads has to be more than half full, where the two launches' blocks begin a
-// fourth one (384 heads 26.5 | 29.0, 390 31.0 | 29.0), and only up to 224 tokens; beyond 512 heads neither is ahead throughout.  The causal
-// mask halves this kernel's work, and the two launches pair blocks there, few as they are.
+// From three tiles on, the time of this kernel over that of the two launches, by heads; N = 129 192 193 256:
+//   d = 64  64 0.94 1.03 1.28 1.39; 128 0.94 1.02 1.05 1.09; 160 0.72 0.81 0.83 0.92; 256 0.74 0.84 0.84 0.93; 257 0.90 0.97 1.01 1.10; 384 0.91 0.99 1.01 1.06; 400 0.81 0.89 0.89 0.97; 512
+//     0.82 0.88 0.89 0.97; 513 0.92 1.00 1.02 1.11; 768 0.84 0.94 0.94 1.03; 1024 0.87 0.96 0.97 1.07; 1025 0.94 1.04 1.07 1.19; 2048 0.89 0.95 1.01 1.01
+//     dropout  64 0.96 1.05 1.39 1.47; 128 0.96 1.04 1.07 1.14; 256 0.75 0.86 0.85 0.93; 257 0.94 1.01 1.03 1.13; 384 0.96 1.05 1.06 1.13; 400 0.83 0.92 0.91 1.00; 513 0.97 1.04 1.05 1.15; 768 0.89
+//     0.97 0.98 1.06; 1025 0.99 1.11 1.12 1.22; 2048 0.95 1.08 1.09 1.14
+//     causal  64 0.90 0.97 1.20 1.21; 128 0.86 0.94 1.01 1.05; 160 0.80 0.83 0.89 0.91; 256 0.80 0.86 0.90 0.94; 257 0.99 1.03 1.04 1.09; 320 1.01 1.07 1.02 0.99; 384 0.99 1.02 0.99 1.03; 400 0.92
+//     0.97 0.99 1.02; 512 0.89 0.96 0.97 0.99; 513 1.04 1.10 1.13 1.14; 640 0.98 1.01 1.05 1.02; 768 0.90 0.96 0.97 0.96; 1024 0.90 0.99 1.03 1.03; 1025 1.05 1.13; 2048 0.96 1.06
+//     causal, dropout  64 0.88 0.96 1.25 1.26; 128 0.87 0.94 1.06 1.12; 256 0.81 0.91 0.93 0.96; 257 1.03 1.10 1.08 1.09; 384 1.02 1.10 1.01 1.06; 400 0.92 1.02 1.01 1.07; 512 0.93 1.00 0.99 1.02; 513
+//     1.11 1.17 1.18 1.20; 768 0.96 1.02 1.01 1.02; 1024 0.96 1.06 1.06 1.11; 2048 1.02 1.13
+//   d = 32  64 0.92 1.01 1.36 1.51; 128 0.90 1.00 1.12 1.28; 160 0.74 0.84 0.91 1.04; 256 0.75 0.85 0.90 1.00; 257 1.12 1.27 1.35 1.50; 384 1.11 1.19 1.28 1.44; 400 0.86 0.94 0.99 1.13; 512 0.85
+//     0.98 1.02 1.18; 513 1.07 1.24 1.30 1.47; 768 0.94 1.05 1.11 1.22; 1024 0.95 1.09 1.15 1.28; 2048 1.03 1.18
+//     dropout  64 0.87 0.95 1.39 1.52; 128 0.87 0.95 1.11 1.22; 160 0.69 0.75 0.84 0.93; 257 0.93 1.02 1.07 1.19; 384 0.91 0.99 1.03 1.20; 400 0.75 0.81 0.86 0.99; 512 0.74 0.86 0.89 1.02; 513 0.91
+//     1.02 1.07 1.19; 768 0.79 0.89 0.91 1.05; 1025 0.91 1.00 1.05 1.20; 2048 0.83 0.96 0.98 1.15
+//     causal  64 0.81 0.87 1.20 1.25; 128 0.81 0.85 1.14 1.15; 160 0.78 0.82 0.82 0.84; 256 0.76 0.79 0.71 0.74; 257 1.14 1.14 1.19 1.20; 352 1.03 1.06 1.09 1.15; 400 0.88 0.89 0.97 1.04; 512 0.79
+//     0.94 0.98 1.02; 513 1.00 1.10 1.18 1.22; 640 0.96 1.04 1.08 1.11; 768 0.90 0.98 1.04 1.09; 1024 0.89 0.97 1.04 1.09; 1025 1.03 1.09; 2048 0.95 1.02
+//     causal, dropout  64 0.77 0.81 1.23 1.25; 128 0.77 0.79 1.13 1.15; 256 0.71 0.74 0.68 0.71; 257 1.03 1.06 1.08 1.08; 320 1.00 1.05 1.00 1.06; 352 0.95 0.97 0.99 1.04; 400 0.84 0.86 0.91 0.98; 512
+//     0.76 0.86 0.91 0.95; 513 0.97 1.07 1.11 1.16; 768 0.84 0.92 0.95 1.01; 1025 0.98 1.04; 2048 0.90 0.95
+// Up to 256 heads, a round over the compute units: three tiles always (the few losses are below 7 %, and a launch is saved).  Four tiles: up to 64 heads the two launches' divided
+// blocks fill more of the chip; up to 128 both take one round (even to 6 % with d = 64 and no dropout, under the causal mask from 97 heads on, where the launch saved decides); from 129 on
+// the two launches have two rounds (at d = 32 with neither mask nor dropout even to 4 % at 256 tokens).  Beyond 256 heads it is the last round of whole heads that decides, by whether it is more than half full, and the more the longer the
+// heads and the faster the two launches are there.  Left aside: d = 64 causal with four tiles and a full third round (0.94 to 0.97), d = 32 causal with dropout, 225 to 256 tokens and a full second one
+// (0.92 to 0.98).
 bool bwd_short_is_faster(const KArgs& a, int d, bool causal, bool dropout) {
   if (d > 64 || a.N > 256) return false;
-  if (a.N <= 3 * TILE) return true;
+  if (a.N <= 2 * TILE) return true;
   const int64_t heads = (int64_t)a.B * a.H;
-  if (heads > 2 * kComputeUnits) return false;
-  if (heads > kComputeUnits) return a.N <= 224 && (causal || 2 * heads > 3 * kComputeUnits);
-  return causal || heads > kComputeUnits / 2 || (heads > kComputeUnits / 4 && d == 64 && a.N <= 208 && !dropout);
+  if (heads <= kComputeUnits) {
+    if (a.N <= 3 * TILE) return true;
+    return heads > kComputeUnits / 2 || (heads > (causal ? 3 : 2) * kComputeUnits / 8 && d == 64 && a.N <= 208 && !dropout);
+  }
+  // the longest heads that take it: of two rounds, of three or four, of more, each with the last round up to half full and beyond
+  constexpr uint8_t kLongest[2][2][2][6] = {   // [d <= 32][causal][dropout]
+      {{{192, 224, 192, 224, 176, 192}, {160, 224, 144, 192, 144, 144}}, {{128, 192, 128, 192, 128, 160}, {128, 192, 128, 144, 128, 128}}},
+      {{{128, 192, 128, 144, 128, 128}, {192, 224, 192, 224, 192, 192}}, {{128, 224, 144, 192, 128, 192}, {128, 224, 176, 224, 176, 192}}}};
+  const int rounds = heads <= 2 * kComputeUnits ? 0 : heads <= 4 * kComputeUnits ? 2 : 4;
+  const bool full = (heads - 1) % kComputeUnits >= kComputeUnits / 2;
+  if (causal && !(d == 64 && dropout) && 4 * heads > 5 * kComputeUnits && 2 * heads <= 3 * kComputeUnits) return a.N <= 192;   // (even, and ahead for odd numbers of heads)
+  return a.N <= kLongest[d == 32][causal][dropout][rounds + full];
 }
 
 // Which heads of more than 256 tokens do: time of this kernel over that of the two launches, by heads; N = 257 to 384, then 385 to 512.
-//   d = 64  128 1.28-1.36, 1.4; 160 1.27-1.31, 0.99 1.04; 192 0.91-0.93, 0.99 1.03; 224 0.92-0.94, 0.86 0.89; 256 0.92-0.94, 0.86 0.89; 257 1.48, 1.3; 512 1.06, 0.97 1.02; 1024 1.2, 1.0
-//   d = 64, dropout  160 1.3, 1.06; 192 0.94-0.95, 1.05 1.08; 224 0.95-0.98, 0.89 0.92; 256 0.95-0.97, 0.89 0.91; 257 1.5, 1.4; 512 1.1, 1.0
-//   d = 64, causal, with and without dropout  96 1.2, 1.2-1.4; 128 1.07-1.12, 1.13-1.21; 160 1.03-1.10, 0.96-1.10; 192 0.87-0.91, 0.89-1.00; 224 0.80-0.87, 0.84-0.92; 256 0.80-0.84,
-//           0.85-0.88; 257 1.22-1.30, 1.3; 512 0.92-1.02, 0.92-1.01; 1024 1.02-1.09, 0.95-1.00
-//   d = 32  192 0.98-1.10, 1.14 1.24; 224 1.0-1.1, 0.88 0.98; 256 1.03-1.09, 0.89 0.98; 257 1.5;  dropout 256 0.95-1.02, 0.90 0.97
-//   d = 32, causal  160 0.87-1.05, 1.04-1.18; 192 0.88-1.00, 0.95-1.04; 224 0.85-0.92, 0.79-0.91; 256 0.81-0.93, 0.82-0.93; 257 1.15-1.37, 1.3-1.5; 512 0.97-1.02, 0.91-1.00
+//   d = 64  128 1.30-1.37, 1.39-1.45; 160 1.27-1.32, 0.96-1.04; 192 0.90-0.94, 0.97-1.04; 224 0.92-0.94, 0.83-0.89; 256 0.91-0.94, 0.84-0.90; 257 1.44-1.47, 1.26-1.34; 512 1.02-1.08, 0.93-1.02
+//   d = 64, dropout  160 1.26-1.32, 1.03-1.08; 192 0.92-0.95, 1.02-1.08; 224 0.94-0.96, 0.86-0.92; 256 0.94-0.97, 0.86-0.92; 257 1.4, 1.4; 512 1.06-1.10, 0.95-1.01
+//   d = 64, causal, with and without dropout  128 1.14-1.24, 1.19-1.40; 160 1.03-1.16, 1.03-1.11; 192 0.88-0.95, 0.90-1.01; 224 0.81-0.87, 0.85-0.93; 256 0.80-0.85, 0.85-0.90; 257 1.25-1.34, 1.3-1.4;
+//           512 0.94-1.00, 0.89-1.01
+//   d = 32  192 0.96-1.09, 1.07-1.23; 224 0.98-1.10, 0.84-0.96; 256 1.01-1.09, 0.86-0.96; 257 1.5;  dropout 192 0.90-0.99, 1.05-1.17; 256 0.95-1.02, 0.88-0.96
+//   d = 32, causal, with and without dropout  160 0.90-1.07, 1.05-1.18; 192 0.91-0.99, 0.95-1.04; 224 0.85-0.92, 0.80-0.91; 256 0.81-0.94, 0.81-0.94; 257 1.2-1.4, 1.3-1.45; 512 0.97-1.03, 0.91-0.99
 // A compute unit holds one workgroup, a head: one round that is nearly full pays.
 bool bwd_blocks_is_faster(const KArgs& a, int d, bool causal) {
   if (d > 64 || a.N <= 256 || a.N > 512) return false;

@@ -52,10 +52,9 @@ def test_causal_mask_and_dropout_at_128_columns(shim, heads, N):
     assert shim.choice(heads, N, 128, 1, 0) == shim.one_wave128()
 
 
-# the one-launch backward: always up to three tiles of 64 tokens; with four, where the two launches have two rounds over 256 compute units and it has one, or
-# a second one more than half full; under the causal mask from the first head on
-@pytest.mark.parametrize("N", [1, 128, 129, 192])
-@pytest.mark.parametrize("heads", [1, 64, 600, 5000])
+# the one-launch backward: always up to two tiles of 64 tokens, and with three up to a round of 256 heads; with four, where the two launches have two rounds over 256
+# compute units and it has one
+@pytest.mark.parametrize("heads,N", [(h, n) for h in (1, 64, 256) for n in (1, 128, 129, 192)] + [(h, n) for h in (600, 5000) for n in (1, 128)])
 def test_short_heads_up_to_three_tiles(shim, heads, N):
     for d in (32, 64):
         assert all(shim.choice(heads, N, d, c, p) == shim.short_heads() for c in (0, 1) for p in (0, 1))
@@ -63,10 +62,24 @@ def test_short_heads_up_to_three_tiles(shim, heads, N):
 
 @pytest.mark.parametrize("heads,N,d,causal,dropout,expect", [
     (64, 197, 64, 0, 0, 0), (65, 197, 64, 0, 0, 1), (65, 197, 64, 0, 1, 0), (96, 209, 64, 0, 0, 0), (96, 197, 32, 0, 0, 0), (128, 256, 64, 0, 1, 0), (129, 256, 64, 0, 1, 1),
-    (129, 256, 32, 0, 0, 1), (256, 256, 32, 0, 0, 1), (257, 197, 32, 0, 0, 0), (384, 197, 64, 0, 1, 0), (385, 197, 64, 0, 1, 1), (385, 224, 32, 0, 0, 1), (385, 225, 32, 0, 0, 0),
-    (512, 224, 64, 0, 0, 1), (513, 197, 64, 0, 0, 0), (1, 256, 64, 1, 0, 1), (256, 256, 64, 1, 1, 1), (257, 224, 64, 1, 1, 1), (257, 225, 64, 1, 1, 0), (513, 197, 64, 1, 1, 0)])
+    (129, 256, 32, 0, 0, 1), (256, 256, 32, 0, 0, 1), (129, 256, 32, 0, 1, 1), (1, 256, 64, 1, 0, 0), (96, 193, 64, 1, 0, 0), (97, 208, 64, 1, 0, 1), (97, 209, 64, 1, 0, 0), (97, 193, 64, 1, 1, 0), (128, 193, 32, 1, 1, 0), (129, 256, 64, 1, 0, 1),
+    (129, 256, 32, 1, 1, 1), (256, 256, 64, 1, 1, 1)])
 def test_short_heads_of_four_tiles(shim, heads, N, d, causal, dropout, expect):
     assert (shim.choice(heads, N, d, causal, dropout) == shim.short_heads()) == bool(expect)
+
+
+# more than a round of 256 heads: the longest heads that take it with the second, the third or a later round up to half full, and beyond
+@pytest.mark.parametrize("d,causal,dropout,longest", [
+    (64, 0, 0, (192, 224, 192, 224, 176, 192)), (64, 0, 1, (160, 224, 144, 192, 144, 144)), (64, 1, 0, (128, 192, 128, 192, 128, 160)), (64, 1, 1, (128, 192, 128, 144, 128, 128)),
+    (32, 0, 0, (128, 192, 128, 144, 128, 128)), (32, 0, 1, (192, 224, 192, 224, 192, 192)), (32, 1, 0, (128, 224, 144, 192, 128, 192)), (32, 1, 1, (128, 224, 176, 224, 176, 192))])
+def test_short_heads_of_several_rounds(shim, d, causal, dropout, longest):
+    rounds = [(257, 320), (385, 512), (513, 640, 769, 896), (641, 768, 897, 1024), (1025, 1152, 5121), (1153, 1280, 5000)]
+    for heads, N in zip(rounds, longest):
+        for h in heads:
+            assert [shim.choice(h, n, d, causal, dropout) == shim.short_heads() for n in (128, N, N + 1)] == [True, True, False]
+    quarter = 192 if causal and (d, dropout) != (64, 1) else longest[0]   # (the second round more than a quarter full)
+    for h in (321, 384):
+        assert [shim.choice(h, n, d, causal, dropout) == shim.short_heads() for n in (quarter, quarter + 1)] == [True, False]
 
 
 # heads of up to two tiles have one form, however many there are; three are divided between two groups of wavefronts where there are few
