@@ -379,7 +379,9 @@ WaveGroups dq_groups(const KArgs& a, int d, bool causal, bool sparse, bool divid
   // 50.8 48.8, 128 x 700 33.7 35.9; 8 x 4096 {2, 2} 64.8, {2, 4} 58.7, 10 x 4096 69.7, 74.9)
   if (halves && w.of64 <= 11 * kComputeUnits / 8 && w.tiles >= 11) return {2, 2};
   if (d == 32 && causal && !sparse && w.of64 <= 2 * kComputeUnits && w.tiles >= 32) return {2, 4};
-  if (d == 32) return w.of64 <= (causal && !sparse ? 4 : 3) * kComputeUnits && w.tiles >= 4 ? WaveGroups{2, 2} : WaveGroups{4, 1};   // (three workgroups fit)
+  // (three workgroups fit; causal, a fourth round of light blocks, {4, 1} | {2, 2}: 9 tiles and more 100 x 576 with dropout 36.0 34.9, 53 x 1000 35.6 33.7, 27 x 2048 55.4 47.6, 32 x 2048 57.5 52.8; fewer
+  // 152 x 310 20.0 19.4, 158 x 310 21.9 22.8, 204 x 310 20.9 23.1, 150 x 380 23.6 25.7, 160 x 324 with dropout 28.3 28.3, 170 x 380 with dropout 31.3 32.5, 120 x 512 23.8 25.4)
+  if (d == 32) return w.of64 <= (causal && !sparse && w.tiles >= 9 ? 4 : 3) * kComputeUnits && w.tiles >= 4 ? WaveGroups{2, 2} : WaveGroups{4, 1};
   if (w.of128 <= (halves && w.tiles < 24 ? 3 : 4) * kComputeUnits / 4 && w.tiles >= (d == 64 ? 16 : 24)) return {4, 2};
   // (causal, two blocks in turn on a compute unit, heaviest first; {4, 1} | {4, 2}, us: 8 x 8192 511 | 485, 10 x 4096 226 | 214, 20 x 2000 with dropout 151 | 140;
   // 30 x 2048 151 | 152, 48 x 900 67.6 | 73.2)

@@ -429,7 +429,10 @@ WaveGroups dkv_fr_groups(const KArgs& a, int d, bool causal, bool sparse, bool d
   if (d == 64 && halves && w.of64 <= 11 * kComputeUnits / 8 && w.tiles >= 11) return {2, 2};
   if (d == 64 && halves) return w.of128 <= (w.tiles >= 13 ? 4 : 3) * kComputeUnits / 4 && w.tiles >= 9 ? WaveGroups{4, 2} : WaveGroups{4, 1};
   if (d == 64 && w.of128 <= kComputeUnits && w.tiles >= 4) return {4, 2};
-  if (d == 32 && w.of64 <= 2 * kComputeUnits && w.tiles >= 4) return {2, 2};
+  // (causal, few tiles, {4, 1} | {2, 2}: 100 x 324 17.7 17.2, 117 x 324 19.2 20.7, 120 x 310 16.2 17.0, 152 x 310 17.9 19.4, with dropout 23.6 23.8, 150 x 205 15.6 17.7; 88 x 450 20.7 19.8, 95 x 450 23.5 24.5,
+  // 112 x 512 24.5 24.8; 84 x 576 23.0 22.3, 100 x 576 26.5 26.5)
+  const int eighths = !halves || w.tiles >= 9 ? 16 : w.tiles >= 7 ? 11 : 10;
+  if (d == 32 && w.of64 <= eighths * kComputeUnits / 8 && w.tiles >= 4) return {2, 2};
   if (!halves && w.of64 > 2 * kComputeUnits && w.of64 <= 3 * kComputeUnits && w.tiles >= 24) return {2, 2};
   return {4, 1};
 }

@@ -129,3 +129,10 @@ def test_forward_of_long_narrow_heads(shim, heads, N, causal, form):
                                             (37, 1500, 42, 42), (40, 1500, 42, 42), (43, 1500, 41, 41)])
 def test_gradients_of_causal_heads_of_64_columns(shim, heads, N, dq, dkv):
     assert (shim.dq_form(heads, N, 64, 1), shim.dkv_form(heads, N, 64, 1)) == (dq, dkv)
+
+
+# gradients of causal heads of 32 columns: {2, 2} in dQ up to three blocks of 64 rows per compute unit, four from nine tiles on; in dK/dV up to two halves, fewer where there are few tiles
+@pytest.mark.parametrize("heads,N,dq,dkv", [(153, 310, 22, 41), (154, 310, 41, 41), (106, 324, 22, 22), (107, 324, 22, 41), (88, 450, 22, 22), (89, 450, 22, 41), (96, 512, 22, 41), (97, 512, 41, 41),
+                                            (102, 576, 22, 22), (103, 576, 22, 41), (113, 576, 22, 41), (114, 576, 41, 41), (128, 256, 22, 22), (160, 205, 22, 22), (161, 205, 22, 41)])
+def test_gradients_of_causal_heads_of_32_columns(shim, heads, N, dq, dkv):
+    assert (shim.dq_form(heads, N, 32, 1), shim.dkv_form(heads, N, 32, 1)) == (dq, dkv)
