@@ -386,8 +386,10 @@ WaveGroups fwd_groups(const KArgs& a, int d, bool causal, bool sparse, bool divi
   if (!divide) return {4, 1};
   const WorkItems w(a, sparse, causal && !sparse && d == 64);
   // (a compute unit holds two workgroups of {2, 4} at d = 32, one otherwise.  Causal, long sweeps, {2, 2} | {2, 4}: 8 x 7975 with dropout 97.4 | 89.9, 9 x 5741 with dropout 63.2 | 57.0,
-  // 4 x 10405 63.0 | 59.4, 9 x 6324 47.9 | 46.9; 15 x 4219 36.0 | 37.4, 16 x 4019 34.3 | 35.4)
-  const int64_t fit24 = d == 64 ? kComputeUnits : causal && !sparse && w.tiles >= 86 ? 4 * kComputeUnits : !causal || sparse || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
+  // 4 x 10405 63.0 | 59.4, 9 x 6324 47.9 | 46.9; 15 x 4219 36.0 | 37.4, 16 x 4019 34.3 | 35.4.
+  // d = 64 causal, nearly a round of half blocks, {2, 2} | {2, 4}: 21 x 1149 13.5 | 16.0, 18 x 1405 14.9 | 16.7, 20 x 1533 15.7 | 18.2, with dropout 20.1 | 22.0, 18 x 1789 17.8 | 20.7, 16 x 1917 18.5 | 19.6,
+  // 13 x 2429 22.1 | 24.0, with dropout 28.6 | 29.8; fewer or longer 16 x 1149 11 % behind, 14 x 1277 14 %, with dropout 16 x 1324 13 %, 15 x 1458 11 %, 12 x 2366 6 %, 16 x 1533 even, 11 x 2301 4 %, with dropout 11 %, 10 x 3069 1 %, 9 x 3453 2 %, 5 x 6397 13 %)
+  const int64_t fit24 = d == 64 ? (!causal || sparse || w.tiles >= 40 ? 32 : w.tiles >= 32 ? 29 : w.tiles >= 24 ? 26 : 23) * kComputeUnits / 32 : causal && !sparse && w.tiles >= 86 ? 4 * kComputeUnits : !causal || sparse || w.tiles >= 32 ? 5 * kComputeUnits / 2 : 2 * kComputeUnits;
   if (d <= 64 && w.of64 <= fit24 && w.tiles >= 12) return {2, 4};
   // (two tiles would gain 0.2 to 0.8 us, less than the host spends on a call; a head of up to 128 tokens keeps one form instead, and with it the same last bits in whatever
   // batch it stands)

@@ -136,3 +136,11 @@ def test_gradients_of_causal_heads_of_64_columns(shim, heads, N, dq, dkv):
                                             (102, 576, 22, 22), (103, 576, 22, 41), (113, 576, 22, 41), (114, 576, 41, 41), (128, 256, 22, 22), (160, 205, 22, 22), (161, 205, 22, 41)])
 def test_gradients_of_causal_heads_of_32_columns(shim, heads, N, dq, dkv):
     assert (shim.dq_form(heads, N, 32, 1), shim.dkv_form(heads, N, 32, 1)) == (dq, dkv)
+
+
+# causal heads of 64 columns in nearly a round of half blocks: {2, 2} instead of {2, 4} where the sweeps are short
+@pytest.mark.parametrize("heads,N,form", [(20, 1149, 24), (21, 1149, 22), (18, 1280, 24), (19, 1280, 22), (17, 1472, 22), (17, 1473, 24), (14, 1728, 24), (15, 1728, 22), (12, 2240, 24), (13, 2240, 22), (12, 2496, 22), (12, 2497, 24),
+                                           (8, 4096, 24)])
+def test_forward_of_nearly_a_round_of_causal_heads(shim, heads, N, form):
+    assert shim.fwd_form(heads, N, 64, 1) == form
+    assert shim.sparse_fwd_form(heads, 1024, 64, 1) == shim.sparse_fwd_form(heads, 1024, 64, 0)
