@@ -148,6 +148,11 @@ int launch_mfma_rate(int dtype, int iters, int operand_sets, float* sink, hipStr
 //   d = 128, backward  64 x 1024 87 | 88; 60 x 700 58.0 | 54.5; 36 x 2048 185 | 158; 10 x 8192 699 | 582; 72 x 1024 110 | 90; 136 x 1024 191 | 164; 192 x 1024
 //            233 | 225 (taken as runs all the same: 64 x 1500 145 | 151, 64 x 4096 847 | 862);   128 x 1024 150 | 158, 250 x 512 110 | 119, 256 x 512 105 | 114, 1000 x 300 234 | 239
 //   d = 32, forward  96 x 2048 68.3 | 45.1; 100 x 1024 24.9 | 17.3; 60 x 1000, dropout 26.1 | 19.9; 1024 x 512 48.6 | 45.2; backward 96 x 2048 156 | 143; 1024 x 512 136 | 135
+// More than the 256 MB of the last-level cache: a level of all heads comes from HBM again and again.  One head at a time (pairs at d = 64) | all | runs: d = 64, forward 380 x 4106 1010 | 1090 | 1070, 638 x 3671
+// 1330 | 1640 | 1370, 3175 x 738 400 | 540 | 401, 2304 x 1695 1220 | 1720 | 1240, backward 289 x 5395 3930 | 4180 | 3970, 459 x 5100 5420 | 6120 | 5470, 1817 x 2149 4370 | 5020 | 4320; d = 32, forward 992 x 4725
+// 2340 | 2640 | 2420, 1502 x 5199 4200 | 4950 | 4280, backward 437 x 10720 14600 | 15800 | 14000; d = 128 55 x 14029 2720 | 3020 | 2770, backward 84 x 13932 11900 | 13300 | 12400.  At 320 MB the
+// two are even at d <= 64 (d = 64 forward 751 x 1664 365 | 379 | 397, 1412 x 885 263 | 252 | 242), at 400 MB and more at d = 128 (132 x 5886 1408 | 1436 | 1535)
+// and in the forward with dropout, which does more work on what it reads (837 x 1862 754 | 730 | 808, 2027 x 1214 798 | 852 | 867, 282 x 11633, 840 MB, ahead in runs by 14 %).
 // d = 128, no more items than compute units: nothing is left to even out, and one head after the other (1) keeps its items on one XCD, whose L2 then
 // loads K and V (or Q and dO) once.  us, all heads | one: forward 13 x 993 19.2 | 18.2, 23 x 1030 21.6 | 19.6, 35 x 677 16.6 | 15.3, 63 x 474 15.0 | 13.3, 11 x 2033 34.1 | 31.4, 5 x 4273
 // 61.4 | 58.5; backward 61 x 194 23.7 | 22.4, 62 x 206 with dropout 26.5 | 24.6, 31 x 444 31.5 | 29.4, 25 x 703 with dropout 52.2 | 51.5 (but 50 x 274 28.2 | 31.9).
@@ -161,13 +166,14 @@ inline int causal_group(const KArgs& a, int d, bool sparse, bool fwd, int64_t he
   const int64_t fit = ((int64_t)8 << 20) / head_bytes;
   const int run = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
   if (sparse) return run;
-  if (d < 128) return 0;
+  const bool beyond_cache = heads * head_bytes > (int64_t)(d < 128 && !(fwd && a.drop_thr > 0) ? 320 : 512) << 20;
+  if (d < 128) return beyond_cache ? (int)(fit < 1 ? 1 : (fit > 32 ? 32 : fit)) : 0;
   if (levels == 1) return fwd ? 0 : 1;
   if (a.n_items <= kComputeUnits) return 1;
   if (levels <= 3 && a.n_items > (levels == 2 ? 7 : 6) * kComputeUnits / 4 && a.n_items <= 2 * kComputeUnits) return fwd ? 1 : run;
   if (levels == 3 && fwd && 2 * a.n_items >= 5 * kComputeUnits && a.n_items <= 3 * kComputeUnits) return 1;
   if (a.n_items <= 2 * kComputeUnits) return 0;
-  return heads >= 224 || (heads % (8 * kXcds) == 0 && (heads >= 128 || !fwd)) ? run : 0;
+  return beyond_cache || heads >= 224 || (heads % (8 * kXcds) == 0 && (heads >= 128 || !fwd)) ? run : 0;
 }
 
 #if defined(__HIPCC__)

@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("heads,N,d", [(1, 700, 64), (12, 1000, 64), (130, 600, 64), (1, 300, 128), (9, 700, 128), (16, 1000, 128), (130, 600, 128), (128, 600, 128), (229, 390, 128), (256, 300, 128),
                                        (13, 900, 32), (136, 500, 32),
                                        # one head at a time: one round, one block, two short ones, three (the forward; the backward in runs)
-                                       (21, 1400, 128), (300, 100, 128), (240, 142, 128), (150, 300, 128)])
+                                       (21, 1400, 128), (300, 100, 128), (240, 142, 128), (150, 300, 128),
+                                       # K and V beyond the last-level cache: runs, the last one short
+                                       (2900, 460, 64), (167, 8000, 64), (340, 8000, 32)])
 def test_every_block_of_every_head_once(heads, N, d):
     from paper_2205_14135_amd import binding
     binding.load()
