@@ -148,6 +148,9 @@ int launch_mfma_rate(int dtype, int iters, int operand_sets, float* sink, hipStr
 //   d = 128, backward  64 x 1024 87 | 88; 60 x 700 58.0 | 54.5; 36 x 2048 185 | 158; 10 x 8192 699 | 582; 72 x 1024 110 | 90; 136 x 1024 191 | 164; 192 x 1024
 //            233 | 225 (taken as runs all the same: 64 x 1500 145 | 151, 64 x 4096 847 | 862);   128 x 1024 150 | 158, 250 x 512 110 | 119, 256 x 512 105 | 114, 1000 x 300 234 | 239
 //   d = 32, forward  96 x 2048 68.3 | 45.1; 100 x 1024 24.9 | 17.3; 60 x 1000, dropout 26.1 | 19.9; 1024 x 512 48.6 | 45.2; backward 96 x 2048 156 | 143; 1024 x 512 136 | 135
+// d = 64, forward without dropout, heads that are whole runs of 32 on every XCD, pairs (causal_block) | all | runs: 1024 x 450 61.6 | 65.5 | 61.6, 1024 x 512 65.2 | 69.4 | 66.6, 512 x 512 35.9 | 36.6 | 34.4, 512 x 600
+// 51.4 | 48.5 | 45.6, 768 x 512 49.6 | 52.2 | 50.1, 768 x 1536 321 | 335 | 321, 512 x 1024 102.5 | 103.5 | 102.5; with dropout even (1024 x 600 128 | 112 | 114), three blocks 512 x 300 26.2 | 21.3 | 22.4; heads
+// that are not whole runs: 600 x 900 124 | 118 | 124.
 // More than the 256 MB of the last-level cache: a level of all heads comes from HBM again and again.  One head at a time (pairs at d = 64) | all | runs: d = 64, forward 380 x 4106 1010 | 1090 | 1070, 638 x 3671
 // 1330 | 1640 | 1370, 3175 x 738 400 | 540 | 401, 2304 x 1695 1220 | 1720 | 1240, backward 289 x 5395 3930 | 4180 | 3970, 459 x 5100 5420 | 6120 | 5470, 1817 x 2149 4370 | 5020 | 4320; d = 32, forward 992 x 4725
 // 2340 | 2640 | 2420, 1502 x 5199 4200 | 4950 | 4280, backward 437 x 10720 14600 | 15800 | 14000; d = 128 55 x 14029 2720 | 3020 | 2770, backward 84 x 13932 11900 | 13300 | 12400.  At 320 MB the
@@ -167,7 +170,10 @@ inline int causal_group(const KArgs& a, int d, bool sparse, bool fwd, int64_t he
   const int run = (int)(fit < 1 ? 1 : (fit > 8 ? 8 : fit));
   if (sparse) return run;
   const bool beyond_cache = heads * head_bytes > (int64_t)(d < 128 && !(fwd && a.drop_thr > 0) ? 320 : 512) << 20;
-  if (d < 128) return beyond_cache ? (int)(fit < 1 ? 1 : (fit > 32 ? 32 : fit)) : 0;
+  if (d < 128) {
+    if (beyond_cache) return (int)(fit < 1 ? 1 : (fit > 32 ? 32 : fit));
+    return fwd && d == 64 && a.drop_thr == 0 && levels >= 4 && heads % (32 * kXcds) == 0 && heads >= 512 && heads <= 1024 ? 32 : 0;
+  }
   if (levels == 1) return fwd ? 0 : 1;
   if (a.n_items <= kComputeUnits) return 1;
   if (levels <= 3 && a.n_items > (levels == 2 ? 7 : 6) * kComputeUnits / 4 && a.n_items <= 2 * kComputeUnits) return fwd ? 1 : run;

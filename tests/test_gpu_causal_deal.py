@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
                                        (13, 900, 32), (136, 500, 32),
                                        # one head at a time: one round, one block, two short ones, three (the forward; the backward in runs)
                                        (21, 1400, 128), (300, 100, 128), (240, 142, 128), (150, 300, 128),
+                                       # the forward in whole runs of 32
+                                       (512, 450, 64),
                                        # K and V beyond the last-level cache: runs, the last one short
                                        (2900, 460, 64), (167, 8000, 64), (340, 8000, 32)])
 def test_every_block_of_every_head_once(heads, N, d):

@@ -112,8 +112,9 @@ def test_forward_under_a_block_mask(shim, heads, N, d, form):
     (224, 142, 128, 128, 0, 0), (225, 142, 128, 128, 1, 8), (256, 250, 128, 128, 1, 8), (257, 250, 128, 128, 8, 8),            # two
     (128, 300, 128, 128, 0, 0), (129, 300, 128, 128, 1, 8), (170, 300, 128, 128, 1, 8), (171, 300, 128, 128, 0, 0), (214, 300, 128, 128, 1, 0), (256, 300, 128, 128, 1, 8),
     (257, 300, 128, 128, 8, 8), (64, 2352, 128, 128, 0, 6), (128, 1110, 128, 128, 8, 8), (136, 1110, 128, 128, 0, 0), (96, 2048, 32, 128, 0, 0), (2, 200, 64, 64, 0, 0),
-    (512, 2560, 64, 128, 0, 0), (512, 2561, 64, 128, 12, 12), (1300, 1024, 64, 128, 32, 32), (40, 40000, 64, 128, 1, 1), (80, 32768, 32, 128, 0, 0), (81, 32768, 32, 128, 2, 2),   # beyond the cache
-    (100, 10485, 128, 128, 0, 0), (100, 10500, 128, 128, 1, 1)])
+    (512, 2560, 64, 128, 32, 0), (512, 2561, 64, 128, 12, 12), (1300, 1024, 64, 128, 32, 32), (40, 40000, 64, 128, 1, 1), (80, 32768, 32, 128, 0, 0), (81, 32768, 32, 128, 2, 2),   # beyond the cache
+    (100, 10485, 128, 128, 0, 0), (100, 10500, 128, 128, 1, 1),
+    (512, 385, 64, 128, 32, 0), (512, 384, 64, 128, 0, 0), (1024, 1024, 64, 128, 32, 0), (1280, 512, 64, 128, 0, 0), (640, 512, 64, 128, 0, 0), (512, 512, 32, 128, 0, 0)])
 def test_causal_heads_dealt_together(shim, heads, N, d, rows, fwd, bwd):
     assert (shim.dealt_together(heads, N, d, rows, 1), shim.dealt_together(heads, N, d, rows, 0)) == (fwd, bwd)
 
