@@ -107,12 +107,12 @@ def io_bytes(cfg):
 # Tile products per launch, counted and executed (Algorithm 4 has five in the backward pass; one tile product over the
 # whole problem is 2 B H N^2 d FLOPs).  Counted: forward S, PV; dK/dV kernel S, dP, dV, dK; dQ kernel dQ.  Executed: the
 # dQ kernel recomputes S and dP as well.  The backward of short heads is one launch, which forms all five once.
-ONE_LAUNCH_BACKWARD = "bwd_short_kernel"
+ONE_LAUNCH_BACKWARD = ("bwd_short_kernel", "bwd_blocks_kernel")
 
 
 def backward_launches(n_fwd, n_dkv):
     """Kernel names of a step, and between which of its five events each of them runs."""
-    if n_dkv == ONE_LAUNCH_BACKWARD:
+    if n_dkv in ONE_LAUNCH_BACKWARD:
         return [n_fwd, n_dkv], [(0, 1), (1, 4)]
     return [n_fwd, "dq_kernel", n_dkv], [(0, 1), (1, 3), (3, 4)]
 
@@ -204,9 +204,8 @@ def run_gpu(cfg, steps, warmup, seed, mask_override=None, nsets=1):
     # launches of the backward pass); the kernels are named by the library's own choice
     pk = binding.make_params(g0["Q"], tau, cfg["causal"], cfg["p"], inputs.BASE_DROPOUT_SEED, 0)
     n_fwd, n_dkv = binding.attn_debug_kernel_choice(pk, cfg["sparse"])
-    vectors = 2 * 4 * B * H * 128 * ((N + 127) // 128)
-    if not cfg["sparse"] and binding.attn_bwd_workspace_bytes(pk) > vectors:   # room for dQ between key blocks: one launch
-        n_dkv = ONE_LAUNCH_BACKWARD
+    if not cfg["sparse"]:
+        n_dkv = binding.attn_debug_bwd_kernel(pk, ws.numel())
     names, spans = backward_launches(n_fwd, n_dkv)
     kevs = [[hev.new() for _ in range(5)] for _ in range(steps)]   # f0, f1=b0, b1, b2, b3
     for s in range(steps):

@@ -252,10 +252,18 @@ int attn_debug_mfma_rate(int32_t dtype, int32_t iters, int32_t operand_sets, flo
  * *dkv_kernel: 0 = role-split dK/dV kernel, 1 = one-wavefront kernel (d <= 64),
  * 2 = one-wavefront kernel for d = 128 (32 keys per wavefront), 3 = the same with 64 keys
  * per wavefront, 4 = short heads at d <= 64, dQ included (one launch).  (The dQ kernel is the same
- * for every other problem.)  The answer is for a workspace of the two row vectors: heads of more than
- * 256 tokens whose attn_bwd_workspace_bytes holds more than these take 4 with that much.
+ * for every other problem.)  The backward's answer is for a workspace of the two row vectors:
+ * attn_debug_bwd_kernel says what a call with more runs.
  */
 int attn_debug_kernel_choice(const attn_params* p, int32_t sparse, int32_t* fwd_kernel, int32_t* dkv_kernel);
+
+/*
+ * Measurement aid: which dK/dV kernel attn_bwd would launch for these params with a workspace of
+ * workspace_bytes, without launching anything.  *kernel as *dkv_kernel above, or 5 = heads of 257 to
+ * 512 tokens at d <= 64 in two key blocks, dQ included (one launch).  A workspace that attn_bwd would
+ * refuse is refused (ATTN_ERR_WORKSPACE).
+ */
+int attn_debug_bwd_kernel(const attn_params* p, size_t workspace_bytes, int32_t* kernel);
 
 /*
  * Test and comparison hook, outside the paper's operation: which kernel serves the calls that

@@ -22,7 +22,7 @@ ATTN_FP16, ATTN_BF16 = 0, 1
 
 SYMBOLS = (
     "attn_fwd", "attn_bwd_workspace_bytes", "attn_blocksparse_bwd_workspace_bytes", "attn_bwd", "attn_bwd_static", "attn_blocksparse_fwd",
-    "attn_blocksparse_bwd", "attn_bwd_timed", "attn_debug_dropout_mask", "attn_debug_mfma_rate", "attn_debug_kernel_choice", "attn_debug_set_variant", "attn_strerror",
+    "attn_blocksparse_bwd", "attn_bwd_timed", "attn_debug_dropout_mask", "attn_debug_mfma_rate", "attn_debug_kernel_choice", "attn_debug_bwd_kernel", "attn_debug_set_variant", "attn_strerror",
     "attn_version",
 )
 
@@ -100,6 +100,8 @@ def load() -> ctypes.CDLL:
     lib.attn_debug_mfma_rate.argtypes = [i32, i32, i32, vp, vp, ctypes.POINTER(ctypes.c_double)]
     lib.attn_debug_kernel_choice.argtypes = [P, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.attn_debug_kernel_choice.restype = ctypes.c_int
+    lib.attn_debug_bwd_kernel.argtypes = [P, sz, ctypes.POINTER(i32)]
+    lib.attn_debug_bwd_kernel.restype = ctypes.c_int
     lib.attn_debug_mfma_rate.restype = ctypes.c_int
     lib.attn_debug_set_variant.argtypes = [i32, i32]
     lib.attn_debug_set_variant.restype = ctypes.c_int
@@ -277,7 +279,7 @@ def attn_debug_dropout_mask(B, H, N, dropout_p, seed, offset, device="cuda") -> 
 
 
 FWD_KERNELS = ("fwd_kernel", "fwd_pp_kernel")
-DKV_KERNELS = ("dkv_rs_kernel", "dkv_fr_kernel", "dkv_fr128_kernel", "dkv_w64_kernel", "bwd_short_kernel")
+DKV_KERNELS = ("dkv_rs_kernel", "dkv_fr_kernel", "dkv_fr128_kernel", "dkv_w64_kernel", "bwd_short_kernel", "bwd_blocks_kernel")
 
 
 def attn_debug_kernel_choice(p: AttnParams, sparse: bool = False) -> Tuple[str, str]:
@@ -286,6 +288,13 @@ def attn_debug_kernel_choice(p: AttnParams, sparse: bool = False) -> Tuple[str, 
     _check(load().attn_debug_kernel_choice(ctypes.byref(p), int(bool(sparse)), ctypes.byref(f), ctypes.byref(k)),
            "attn_debug_kernel_choice")
     return FWD_KERNELS[f.value], DKV_KERNELS[k.value]
+
+
+def attn_debug_bwd_kernel(p: AttnParams, workspace_bytes: int) -> str:
+    """Name of the dK/dV kernel attn_bwd would launch with a workspace of that size."""
+    k = ctypes.c_int32()
+    _check(load().attn_debug_bwd_kernel(ctypes.byref(p), int(workspace_bytes), ctypes.byref(k)), "attn_debug_bwd_kernel")
+    return DKV_KERNELS[k.value]
 
 
 def attn_debug_mfma_rate(dtype: str, iters: int, sink: torch.Tensor, operand_sets: int = 1) -> float:

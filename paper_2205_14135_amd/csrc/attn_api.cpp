@@ -109,7 +109,10 @@ void set_items(attn::KArgs& k, int tiles_per_head) {
 
 // Backward scratch layout: D vector, base-2 row statistic | (block-sparse only) column counts |
 // fp32 dK | fp32 dV.
-struct WsLayout { size_t d_bytes, cnt_bytes, acc_bytes, part_bytes; };
+struct WsLayout {
+  size_t d_bytes, cnt_bytes, acc_bytes, part_bytes;
+  bool has_part(size_t ws_bytes) const { return ws_bytes >= d_bytes + part_bytes; }
+};
 WsLayout ws_layout(const attn_params* p) {
   WsLayout w;
   const size_t T = ((size_t)p->N + attn::kMaskBlock - 1) / attn::kMaskBlock;
@@ -163,7 +166,7 @@ int bwd_common(const attn_params* p, const uint8_t* mask, int64_t mask_sh, bool 
   c.k.dO = dO; c.k.dQ = dQ; c.k.dK = dK; c.k.dV = dV;
   c.k.Dvec = (float*)ws;
   c.k.L2vec = c.k.Dvec + (size_t)p->B * p->H * c.k.Nr;
-  if (!sparse && ws_bytes >= w.d_bytes + w.part_bytes) c.k.dQpart = (float*)((char*)ws + w.d_bytes);
+  if (!sparse && w.has_part(ws_bytes)) c.k.dQpart = (float*)((char*)ws + w.d_bytes);
   if (sparse) {
     const size_t cols = (size_t)p->B * p->H * (p->N / attn::kMaskBlock);
     c.k.colcnt = (int*)((char*)ws + w.d_bytes);
@@ -349,6 +352,20 @@ int attn_debug_kernel_choice(const attn_params* p, int32_t sparse, int32_t* fwd_
   const attn::Overrides v = attn::overrides();
   *fwd_kernel = attn::choose_fwd(c.k, c.d, c.causal, c.dropout, sparse != 0, v);
   *dkv_kernel = attn::choose_dkv(c.k, c.d, c.causal, c.dropout, sparse != 0, v);
+  return ATTN_OK;
+}
+
+int attn_debug_bwd_kernel(const attn_params* p, size_t workspace_bytes, int32_t* kernel) {
+  Checked c;
+  const int st = check_params(p, &c);
+  if (st != ATTN_OK) return st;
+  if (kernel == nullptr) return ATTN_ERR_NULL;
+  const WsLayout w = ws_layout(p);
+  if (workspace_bytes < w.d_bytes) return ATTN_ERR_WORKSPACE;
+  float part;   // (any address: nothing is launched)
+  if (w.has_part(workspace_bytes)) c.k.dQpart = &part;
+  const int choice = attn::choose_dkv(c.k, c.d, c.causal, c.dropout, false, attn::overrides());
+  *kernel = choice == attn::kBwdShort && p->N > 256 ? 5 : choice;
   return ATTN_OK;
 }
 

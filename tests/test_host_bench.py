@@ -3,10 +3,11 @@ import bench
 
 
 def test_backward_of_one_launch_is_timed_whole():
-    names, spans = bench.backward_launches("fwd_kernel", "bwd_short_kernel")
-    assert names == ["fwd_kernel", "bwd_short_kernel"]
-    assert spans == [(0, 1), (1, 4)]   # events 3 and 4 coincide: nothing lies between them
-    assert bench.tile_products(names) == {"fwd_kernel": (2, 2), "bwd_short_kernel": (5, 5)}
+    for kernel in ("bwd_short_kernel", "bwd_blocks_kernel"):
+        names, spans = bench.backward_launches("fwd_kernel", kernel)
+        assert names == ["fwd_kernel", kernel]
+        assert spans == [(0, 1), (1, 4)]   # events 3 and 4 coincide: nothing lies between them
+        assert bench.tile_products(names) == {"fwd_kernel": (2, 2), kernel: (5, 5)}
 
 
 def test_backward_of_two_launches():

@@ -3,6 +3,7 @@ import ctypes
 
 import pytest
 
+from paper_2205_14135_amd import binding
 from tests.host_library import compile_shim
 from tests.test_host_abi import _params, lib   # noqa: F401  (fixture)
 
@@ -40,6 +41,21 @@ def test_workspace(lib):   # noqa: F811
     assert size(B=16, H=16, N=512, d=64) == vectors + 256 * 512 * 64 * 4
     assert size(B=16, H=16, N=500, d=64) == vectors + 256 * 512 * 64 * 4
     assert size(B=16, H=17, N=512, d=64) == 2 * 4 * 272 * 512
+    # which kernel runs depends on the room, and on the override, which keeps the two launches
+    p = _params(B=16, H=16, N=512, d=64)
+    room = vectors + 256 * 512 * 64 * 4
+    try:
+        assert [binding.attn_debug_bwd_kernel(p, n) for n in (vectors, room - 1, room)] == ["dkv_fr_kernel", "dkv_fr_kernel", "bwd_blocks_kernel"]
+        assert binding.attn_debug_bwd_kernel(_params(B=1, H=1, N=128, d=64), 1 << 20) == "bwd_short_kernel"
+        assert binding.attn_debug_bwd_kernel(_params(B=4, H=16, N=4096, d=128), 1 << 30) == "dkv_w64_kernel"
+        binding.attn_debug_set_variant(dkv="fr")
+        assert binding.attn_debug_bwd_kernel(p, room) == "dkv_fr_kernel"
+    finally:
+        binding.attn_debug_set_variant(dkv="auto")
+    k = ctypes.c_int32()
+    assert lib.attn_debug_bwd_kernel(ctypes.byref(p), vectors - 1, ctypes.byref(k)) == -7
+    assert lib.attn_debug_bwd_kernel(ctypes.byref(p), vectors, None) == -1
+    assert lib.attn_debug_bwd_kernel(ctypes.byref(_params(d=7)), vectors, ctypes.byref(k)) == -4
     # with the vectors alone the call is not refused for its workspace (the NULL tensor is what is refused)
     v, z = ctypes.c_void_p(0x1000), ctypes.c_void_p(0)
     p = _params(B=16, H=16, N=512, d=64)
