@@ -11,7 +11,7 @@
 // ALU work per tile is the same at every head dimension while the matrix work shrinks with it;
 // at d <= 64 that free-running arrangement is faster than the role split (at d = 128 the one-wavefront
 // arrangement is attn_bwd_dkv_fr128.hip, and the role split is left large block masks: choose_dkv).
-// Vector registers spilled: 2 in the divided causal forms with dropout at d = 64, none elsewhere.
+// Vector registers spilled: none.
 // Register layout "lane = key" (S = Q K^T: accumulator rows = queries of the tile, column = the
 // lane's key), as in attn_bwd_dkv.hip.
 #include "attn_common.h"

@@ -300,7 +300,7 @@ __global__ __launch_bounds__(64 * KW, 2) void bwd_short_kernel(const KArgs a) {
 // 64 x 256 keep busy for three quarters of a tile (dQ 2.0 k a tile, dV, dP and the vector work between their MFMAs 2.1 k, S and dK 0.9 k, barrier
 // 0.75 k); with dropout the vector ALU (93 | 85 us).  D of a tile when the tile comes instead of all rows first: 79 -> 81 us (18 registers spilled, and a
 // wait for O waits for the copies in flight); the row vectors spread over the accumulators by a product with ones, instead of 16 LDS reads: no gain.
-// Vector registers spilled at d = 64: 6 to 9.
+// Vector registers spilled at d = 64: 10, causal 9, with dropout 7 and 6.
 template <typename T, int D, bool CAUSAL, bool DROPOUT>
 __global__ __launch_bounds__(512, 2) void bwd_blocks_kernel(const KArgs a) {
   typedef typename Vec<T>::x8 T8;

@@ -140,7 +140,7 @@ int launch_fwd_pp(const KArgs& a, int dtype, int d, bool causal, bool dropout, h
 int launch_mfma_rate(int dtype, int iters, int operand_sets, float* sink, hipStream_t s, double* flops);
 
 // a.group: how many heads the causal kernels deal out together (causal_block); head_bytes: what a head's items stream; fwd: the forward kernel asks, not a
-// backward one.  All of them (0), unless many heads of 128 columns fill every XCD evenly or nearly so: then what an XCD streams at a time stays within 8 MiB, the L2
+// backward one.  All of them (0), unless their K and V exceed the last-level cache, or whole runs pay (both below), or many heads of 128 columns fill every XCD evenly or nearly so: then what an XCD streams at a time stays within 8 MiB, the L2
 // working set (a level of all heads streams them all).  A run of whole groups per XCD leaves some XCDs the heavy blocks of a group and others the light ones where the
 // heads do not divide evenly, and one head at a time puts blocks of the same weight on a compute unit.  us, runs | all heads, heads x N:
 //   d = 128, forward  64 x 1024 37.1 | 30.0, dropout 44.2 | 34.0; 48 x 900 29.7 | 24.0; 36 x 2048 63.9 | 50.8; 20 x 4096 124 | 97.5; 12 x 8192 265 | 214;
@@ -591,8 +591,8 @@ __device__ __forceinline__ int dealt_head(const KArgs& a, int pos) {
 // (-1: none), and the item's head and block, counted from the head's heaviest, level 0.  The blocks of all heads (a.group == 0) or of a.group consecutive heads
 // (each XCD a run of items) are dealt out together, heaviest first, so that a compute unit gets blocks of different weights at the start and light ones
 // last.  All heads: see causal_group.  (The order of the heads: see dealt_head.)  At d <= 64 an item was a pair of a light and a heavy block before: half as many
-// workgroups, a loop over the two that cost registers, and an odd block that counted as a pair.  us, pairs | blocks: d = 64, forward 16 x 16384 611 | 579, 128 x 1024 with dropout
-// 40.8 | 34.5, 128 x 2048 98 | 91, 100 x 700 with dropout 31.3 | 22.2, 16 x 700 12.1 | 9.1; backward 16 x 16384 1840 | 1740, 128 x 1024 94 | 95, with dropout 111 | 109, 100 x 700 with dropout 79.5 |
+// workgroups, a loop over the two that cost registers, and an odd block that counted as a pair.  us, pairs | blocks: d = 64, forward 16 x 16384 619 | 600, 128 x 1024 with dropout
+// 40.8 | 34.5, 128 x 2048 98 | 91, 100 x 700 with dropout 31.3 | 22.2, 16 x 700 12.1 | 9.1; backward 16 x 16384 1950 | 1860, 16 x 8192 502 | 516, with dropout 712 | 703, 16 x 4096 136 | 141, 24 x 8192 771 | 728, 128 x 1024 94 | 95, with dropout 111 | 109, 100 x 700 with dropout 79.5 |
 // 59.7, 40 x 1024 48.6 | 40.3, 16 x 700 30.9 | 22.9; d = 32, backward 128 x 700 40.7 | 33.9.
 __device__ __forceinline__ int causal_item(const KArgs& a) {
   if (a.group > 0) return xcd_item(a.n_items, a.chunk);
