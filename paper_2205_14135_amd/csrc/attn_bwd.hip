@@ -78,8 +78,9 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && three_waves(D, CAUSAL, DRO
   const int n_qt = a.T * (4 / RW);   // blocks of BR rows, to the end of the last 128-row block: the scratch vectors are written whole
   // Work item = (head, row block); under the causal mask row block q sweeps 2 (q + 1) key tiles, and the late blocks come first
   int bh = item / n_qt, q_item = item % n_qt;
-  if constexpr (CAUSAL) causal_block(a, item, n_qt, bh, q_item);
-  if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
+  if constexpr (CAUSAL)
+    if (!causal_block(a, item, n_qt, bh, q_item)) return;
+  if (!SPARSE && !(DEALT && a.group <= 0)) bh = dealt_head(a, bh);
   const int qt = CAUSAL ? n_qt - 1 - q_item : q_item;
   // (one pass of a loop: the form in which the {2, 2} kernels of d = 32 stay within the 168 registers of three wavefronts per SIMD without being held to them;
   // straight on they take 182, with dropout 174, and held to 168 they spill.  dQ in us, straight | so: 100 heads of 300 13.9 | 11.3, 80 of 400 15.3 | 12.7, 8 of 5000 72.9 | 59.1,
@@ -331,6 +332,7 @@ int launch_dq(KArgs a, bool causal, bool dropout, bool sparse, hipStream_t s) {
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
   a.group = causal_group(a, D, sparse, false, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
+  if (causal && !sparse) whole_levels(a, D, false, blocks);
   if (sparse) a.plan_groups = sparse_plan_groups(a);
   const dim3 grid(kXcds * a.chunk + (sparse ? a.plan_groups : 0)), block(64 * RW * KG);
 #define ATTN_DQ_CASE(C, P, S)                                                          \

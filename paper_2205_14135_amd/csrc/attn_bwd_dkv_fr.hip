@@ -88,8 +88,9 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr_kernel(const KArgs a) 
     heavy = true;
   }
   int bh = item / n_kt, kt = item % n_kt;
-  if constexpr (DEALT) causal_block(a, item, n_kt, bh, kt);
-  if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
+  if constexpr (DEALT)
+    if (!causal_block(a, item, n_kt, bh, kt)) return;
+  if (!SPARSE && !(DEALT && a.group <= 0)) bh = dealt_head(a, bh);
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;
@@ -384,6 +385,7 @@ int launch_groups(KArgs a, bool causal, bool dropout, bool sparse, int extra_gro
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
   a.group = causal_group(a, D, sparse, false, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));   // Q and dO
+  if (causal && !sparse) whole_levels(a, D, false, blocks);
   const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(64 * RW * KG);
 #define ATTN_DKV_FR_CASE(C, P, S)                                                           \
   if constexpr (!S || RW == 4)                                                              \

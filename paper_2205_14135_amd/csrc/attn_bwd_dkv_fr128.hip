@@ -69,8 +69,9 @@ __global__ __launch_bounds__(64 * RW * KG, 2) void dkv_fr128_kernel(const KArgs 
   }
   int bh = item / n_kt;
   int kt = item % n_kt;
-  if constexpr (CAUSAL && !SPARSE) causal_block(a, item, n_kt, bh, kt);   // (key block k is visited by the query tiles from the diagonal on)
-  if (!SPARSE && !(CAUSAL && a.group == 0)) bh = dealt_head(a, bh);
+  if constexpr (CAUSAL && !SPARSE)
+    if (!causal_block(a, item, n_kt, bh, kt)) return;   // (key block k is visited by the query tiles from the diagonal on)
+  if (!SPARSE && !(CAUSAL && a.group <= 0)) bh = dealt_head(a, bh);
   const int b = bh / a.H, h = bh % a.H;
   const int64_t head_off = (int64_t)b * a.sb + (int64_t)h * a.sh;
   const T* __restrict__ Qg = (const T*)a.Q + head_off;
@@ -320,6 +321,7 @@ int launch_t(const KArgs& a_in, bool causal, bool dropout, bool sparse, int extr
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
   a.group = causal_group(a, D, sparse, false, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));   // Q and dO
+  if (causal && !sparse) whole_levels(a, D, false, blocks);
   const dim3 grid(kXcds * a.chunk + (sparse ? extra_groups : 0)), block(64 * RW * KG);
 #define ATTN_DKV_FR128_CASE(C, P, S)                                                            \
   if constexpr (!S || RW == 4)                                                                  \

@@ -68,8 +68,9 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
   const int n_qt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last block may be ragged
   // Work item = (head, row block); under a causal mask the late blocks, which see most keys, first
   int bh = item / n_qt, q_item = item % n_qt;
-  if constexpr (DEALT) causal_block(a, item, n_qt, bh, q_item);
-  if (!SPARSE && !(DEALT && a.group == 0)) bh = dealt_head(a, bh);
+  if constexpr (DEALT)
+    if (!causal_block(a, item, n_qt, bh, q_item)) return;
+  if (!SPARSE && !(DEALT && a.group <= 0)) bh = dealt_head(a, bh);
   const int qt = CAUSAL ? n_qt - 1 - q_item : q_item;
   // (one pass of a loop: the form in which the compiler lays the code out with no jump between the last tile and the epilogue; one head of 128
   // tokens 4.51 -> 4.46 to 4.48 us)
@@ -306,6 +307,7 @@ int launch_fwd_groups(KArgs a, bool causal, bool dropout, bool sparse, hipStream
   a.n_items = a.B * a.H * blocks;
   a.chunk = (a.n_items + kXcds - 1) / kXcds;
   a.group = causal_group(a, D, sparse, true, 2 * (int64_t)a.N * D * (int64_t)sizeof(T));
+  if (causal && !sparse) whole_levels(a, D, true, blocks);
   const dim3 grid(kXcds * a.chunk), block(64 * RW * KG);
 #define ATTN_FWD_CASE(C, P, S)                                                              \
   if (causal == C && dropout == P && sparse == S) {                                         \

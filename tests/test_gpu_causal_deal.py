@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
                                        (13, 900, 32), (136, 500, 32),
                                        # one head at a time: one round, one block, two short ones, three (the forward; the backward in runs)
                                        (21, 1400, 128), (300, 100, 128), (240, 142, 128), (150, 300, 128),
+                                       # levels padded to the XCDs
+                                       (133, 600, 64), (103, 700, 128), (39, 500, 32), (462, 192, 64),
                                        # the forward in whole runs of 32
                                        (512, 450, 64),
                                        # K and V beyond the last-level cache: runs, the last one short

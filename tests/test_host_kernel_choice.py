@@ -35,6 +35,13 @@ extern "C" int dealt_together(int heads, int N, int d, int rows, int fwd) {
   a.n_items = heads * ((N + rows - 1) / rows);
   return attn::causal_group(a, d, false, fwd != 0, (int64_t)4 * N * d);
 }
+extern "C" int places_of_a_level(int heads, int N, int d, int fwd) {   // of all heads dealt out together (blocks of 128 rows); 0: not padded
+  attn::KArgs a = problem(heads, N, d);
+  a.n_items = heads * a.T;
+  attn::whole_levels(a, d, fwd != 0, a.T);
+  if (a.group == 0) return a.n_items == heads * a.T ? 0 : -1;
+  return a.n_items == -a.group * a.T && a.chunk * attn::kXcds == a.n_items ? -a.group : -1;
+}
 extern "C" int short_heads() { return attn::kBwdShort; }
 extern "C" int one_wave128() { return attn::kDkvOneWave128; }
 """
@@ -117,6 +124,13 @@ def test_forward_under_a_block_mask(shim, heads, N, d, form):
     (512, 385, 64, 128, 32, 0), (512, 384, 64, 128, 0, 0), (1024, 1024, 64, 128, 32, 0), (1280, 512, 64, 128, 0, 0), (640, 512, 64, 128, 0, 0), (512, 512, 32, 128, 0, 0)])
 def test_causal_heads_dealt_together(shim, heads, N, d, rows, fwd, bwd):
     assert (shim.dealt_together(heads, N, d, rows, 1), shim.dealt_together(heads, N, d, rows, 0)) == (fwd, bwd)
+
+
+# a level of all heads is padded to whole rounds over the XCDs where that is up to 3 %
+@pytest.mark.parametrize("heads,N,d,fwd,bwd", [(462, 192, 64, 464, 464), (464, 192, 64, 0, 0), (1, 700, 64, 0, 0), (12, 700, 64, 0, 0), (31, 700, 64, 0, 0), (39, 700, 64, 40, 40), (233, 700, 128, 0, 0), (234, 700, 64, 240, 240),
+                                               (232, 700, 64, 0, 0), (201, 700, 64, 0, 0), (203, 700, 32, 0, 208)])
+def test_levels_padded_to_the_xcds(shim, heads, N, d, fwd, bwd):
+    assert (shim.places_of_a_level(heads, N, d, 1), shim.places_of_a_level(heads, N, d, 0)) == (fwd, bwd)
 
 
 # long causal sweeps of narrow heads over four groups of wavefronts: 86 tiles and up to four blocks of 64 rows per compute unit
