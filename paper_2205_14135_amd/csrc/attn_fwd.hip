@@ -68,9 +68,10 @@ __global__ __launch_bounds__(64 * RW * KG, KG == 1 && D <= 64 ? 3 : 2) void fwd_
   const int n_qt = RW == 4 ? a.T : (a.N + BR - 1) / BR;   // the last block may be ragged
   // Work item = (head, row block); under a causal mask the late blocks, which see most keys, first
   int bh = item / n_qt, q_item = item % n_qt;
-  if constexpr (DEALT)
+  if constexpr (DEALT && D == 32) causal_block<false>(a, item, n_qt, bh, q_item);
+  if constexpr (DEALT && D != 32)
     if (!causal_block(a, item, n_qt, bh, q_item)) return;
-  if (!SPARSE && !(DEALT && a.group <= 0)) bh = dealt_head(a, bh);
+  if (!SPARSE && !(DEALT && (D == 32 ? a.group == 0 : a.group <= 0))) bh = dealt_head(a, bh);
   const int qt = CAUSAL ? n_qt - 1 - q_item : q_item;
   // (one pass of a loop: the form in which the compiler lays the code out with no jump between the last tile and the epilogue; one head of 128
   // tokens 4.51 -> 4.46 to 4.48 us)
